@@ -90,10 +90,10 @@ dq_status dq_destroy(dq_ctx* ctx);
 
 /* Bytes of device workspace that any call with these sizes needs (a host computation).
  * x_dtype is the storage type of X.  *out receives the size.  Problems of a batch run one after
- * another and share the workspace, except for n == 128 (per-head rotations): there all b problems
- * run in the same kernel launches and the size grows with b (7 matrices of 64 KiB and
- * ceil(T/2048) partial gradients per problem).  A batch gives the same bits as its problems
- * run one by one. */
+ * another and share the workspace, except for n <= 128 (per-head rotations): there all b problems
+ * run in the same kernel launches and the size grows with b (7 matrices of 64 KiB and up to
+ * max(8, ceil(T/2048)) partial gradients per problem); with a smaller workspace such a batch runs in
+ * groups.  A batch gives the same bits as its problems run one by one. */
 dq_status dq_workspace_bytes(int b, int n, int T, dq_dtype x_dtype, size_t* out);
 
 /* Hand the context a caller-owned device buffer (256-byte aligned).  Enqueues one small kernel
@@ -113,7 +113,7 @@ typedef enum {
                                        (CholeskyQR2 + Householder reconstruction); 0: never, default 64 */
     DQ_OPT_SINGLE_STREAM = 2,       /* non-zero: every piece of the QR on the context's stream, no overlap (default 0) */
     DQ_OPT_FUSED_WHIP = 3,          /* zero: Eq. 4 always as a pass of its own, never in the epilogue of X @ R (default 1) */
-    DQ_OPT_HEADS_BATCHED = 4,       /* zero: 128 x 128 problems take the general route one by one (default 1) */
+    DQ_OPT_HEADS_BATCHED = 4,       /* zero: problems of n <= 128 take the general route one by one (default 1) */
     DQ_OPT_DEVICE_SYNC = 5,         /* how the pieces of the QR on the library's streams wait for each other.  0: HIP
                                        events.  1 (default): through a word in device memory that the producing stream
                                        sets and the consuming stream polls (a cross-stream wait on an event that is still
@@ -226,7 +226,7 @@ dq_status dq_objective_loss_grad(dq_ctx* ctx, dq_objective objective, int quant_
 
 /* Selects the objective that dq_rotate_loss_grad, dq_calib_step and dq_calib_step_adam evaluate from now on
  * (default DQ_OBJ_WHIP; Sec. 5, objective ablation).  With another objective Y and dY always pass through the
- * workspace (no fused epilogue, no batched 128-wide route).  DQ_ERR_DTYPE for an unknown objective, DQ_ERR_SHAPE for
+ * workspace (no fused epilogue, no fused kernel for n <= 128).  DQ_ERR_DTYPE for an unknown objective, DQ_ERR_SHAPE for
  * quant_bits outside 1..16; the setting is unchanged on error. */
 dq_status dq_set_objective(dq_ctx* ctx, dq_objective objective, int quant_bits);
 

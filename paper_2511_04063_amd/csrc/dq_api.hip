@@ -1223,9 +1223,9 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
     return DQ_OK;
 }
 
-// ---------------------------------------------------------------- batched 128 x 128 rotations
-// Every problem of the batch runs in the same launches.  The path's buffers (b matrices each, row stride 128) sit
-// behind the general layout in the workspace.
+// ---------------------------------------------------------------- batched small rotations (n <= kHeadDim)
+// Every problem of the batch runs in the same launches.  The path's buffers (b matrices each, n rows of stride
+// kHeadDim) sit behind the general layout in the workspace.
 struct HeadsLayout {
     size_t R = 0, U = 0, G = 0, B = 0, P = 0, M = 0, uinv = 0, gpart = 0, lpart = 0, total = 0;
 };
@@ -1248,31 +1248,37 @@ HeadsLayout make_heads_layout(size_t base, int b, int T) {
     return H;
 }
 
-bool heads_route(const dq_ctx* c, int n) { return c->heads_batched && n == kHeadDim; }
-// the fused rotate + loss + gradient kernel of the batched route evaluates Eq. 4 only
-bool heads_fused_route(const dq_ctx* c, int n) { return heads_route(c, n) && c->objective == DQ_OBJ_WHIP; }
-
-dq_status check_heads_ws(dq_ctx* c, const HeadsLayout& H) {
-    if (c->ws == nullptr || c->ws_bytes < H.total) return DQ_ERR_WORKSPACE;
-    return DQ_OK;
+// n <= 128 fits one workgroup's registers.  32 rotations of order 80 on 3000 tokens: 9.37 ms through the general route,
+// 0.172 ms here; a single rotation of order 64 .. 128 needs one launch instead of some twenty.
+bool heads_route(const dq_ctx* c, int n) { return c->heads_batched && n <= kHeadDim; }
+// the fused rotate + loss + gradient kernel of the batched route evaluates Eq. 4 on bf16 activations only
+bool heads_fused_route(const dq_ctx* c, int n, dq_dtype xdt) {
+    return heads_route(c, n) && c->objective == DQ_OBJ_WHIP && xdt == DQ_BF16;
 }
 
-dq_status heads_qr(dq_ctx* c, int b, const float* Z, long ldz, float* R, long ldr, float* U, long ldu) {
-    const int n = kHeadDim;
+// Problems of a batch that the workspace holds at a time (a workspace sized for fewer problems than the call has still
+// serves it, group by group, with the same bits); 0: not even one.
+int heads_group(const dq_ctx* c, size_t base, int b, int T) {
+    if (c->ws == nullptr) return 0;
+    int g = b > 0 ? b : 1;
+    while (g > 0 && c->ws_bytes < make_heads_layout(base, g, T).total) --g;
+    return g;
+}
+
+dq_status heads_qr(dq_ctx* c, int b, int n, const float* Z, long ldz, float* R, long ldr, float* U, long ldu) {
     if (b < 1) return DQ_OK;
     LaunchScope sc(&c->prof, c->stream, DQ_K_PANEL, b * (10.0 / 3.0) * n * (double)n * n, 0.0);
-    DQ_HIP(launch_heads_qr(b, Z, ldz, (long)n * ldz, R, ldr, (long)n * ldr, U, ldu, (long)n * ldu,
+    DQ_HIP(launch_heads_qr(b, n, Z, ldz, (long)n * ldz, R, ldr, (long)n * ldr, U, ldu, (long)n * ldu,
                            at<unsigned>(c, 0), c->stream));
     return DQ_OK;
 }
 
-dq_status heads_rotate_loss_grad(dq_ctx* c, const HeadsLayout& H, int b, int T, const void* X, long ldx, const float* R,
-                                 long ldr, dq_reduce red, float* loss_dev, float* G, long ldg) {
-    const int n = kHeadDim;
+dq_status heads_rotate_loss_grad(dq_ctx* c, const HeadsLayout& H, int b, int n, int T, const void* X, long ldx,
+                                 const float* R, long ldr, dq_reduce red, float* loss_dev, float* G, long ldg) {
     if (b < 1) return DQ_OK;
     const float scale = (red == DQ_REDUCE_TOKEN_MEAN) ? 1.f / (float)T : 1.f;
     LaunchScope sc(&c->prof, c->stream, DQ_K_GEMM_BF16, b * 4.0 * T * (double)n * n, b * 2.0 * T * (double)n);
-    DQ_HIP(launch_heads_rlg(b, T, static_cast<const bf16_t*>(X), ldx, (long)T * ldx, R, ldr, (long)n * ldr, scale,
+    DQ_HIP(launch_heads_rlg(b, n, T, static_cast<const bf16_t*>(X), ldx, (long)T * ldx, R, ldr, (long)n * ldr, scale,
                             at<float>(c, H.gpart), at<double>(c, H.lpart), G, ldg, (long)n * ldg, loss_dev,
                             at<unsigned>(c, 0), c->stream));
     return DQ_OK;
@@ -1281,26 +1287,26 @@ dq_status heads_rotate_loss_grad(dq_ctx* c, const HeadsLayout& H, int b, int T, 
 // inv(U_i) for every problem on the second stream, beside whatever the caller's stream does next: it depends on the
 // factorisation only, and the 64 workgroups that form it (a quarter of the device, 30 us) need not sit between the
 // gradient and the derivative through the QR.  The caller's stream must wait for sync_ev[1] before inv(U) is used.
-dq_status heads_uinv_early(dq_ctx* c, const HeadsLayout& H, int b, const float* U, long ldu) {
-    const int n = kHeadDim;
+dq_status heads_uinv_early(dq_ctx* c, const HeadsLayout& H, int b, int n, const float* U, long ldu) {
     DQ_HIP(hipEventRecord(c->sync_ev[0], c->stream));
     DQ_HIP(hipStreamWaitEvent(c->stream2, c->sync_ev[0], 0));
     {
         LaunchScope sc(&c->prof, c->stream2, DQ_K_SMALL, 0.0, 8.0 * b * (double)n * n);
         DQ_HIP(launch_trinv_blocks(U, ldu, n, at<float>(c, H.uinv), at<unsigned>(c, 0), c->stream2, b, (long)n * ldu,
-                                   (long)n * n));
+                                   (long)kTrsmBlock * kTrsmBlock));
     }
     DQ_HIP(hipEventRecord(c->sync_ev[1], c->stream2));
     return DQ_OK;
 }
 
 // dZ_i = R_i P_i U_i^{-T} for every problem (or Z_i -= lr dZ_i when Zupd != null): the steps of qr_backward_one with
-// one 128-wide block, as batched launches.  have_uinv: inv(U_i) is already in the workspace (heads_uinv_early).
-dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, const float* R, long ldr, const float* U, long ldu,
+// one block, as batched launches.  have_uinv: inv(U_i) is already in the workspace (heads_uinv_early).
+static_assert(kTrsmBlock >= kHeadDim, "one diagonal block of the triangular solve holds a whole small rotation");
+dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, int n, const float* R, long ldr, const float* U, long ldu,
                          const float* G, long ldg, float* dZ, long lddz, float* Zupd, long ldz, float lr,
                          bool have_uinv = false) {
-    const int n = kHeadDim;
-    const long nn = (long)n * n;
+    const long ld = kHeadDim, nn = (long)n * ld;
+    const long sinv = (long)kTrsmBlock * kTrsmBlock;
     if (b < 1) return DQ_OK;
     hipStream_t s = c->stream;
     unsigned* flags = at<unsigned>(c, 0);
@@ -1313,21 +1319,21 @@ dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, const float* R,
         GemmF32 g;   // B = R^T G
         g.A = R; g.lda = ldr; g.ta = 1; g.batch_a = (long)n * ldr;
         g.B = G; g.ldb = ldg; g.tb = 0; g.batch_b = (long)n * ldg;
-        g.C = Bb; g.ldc = n; g.batch_c = nn;
+        g.C = Bb; g.ldc = ld; g.batch_c = nn;
         g.M = n; g.N = n; g.K = n; g.batch = b;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
         DQ_HIP(launch_gemm_f32(g, s));
     }
     {
-        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 16.0 * b * (double)nn);
-        DQ_HIP(launch_skew_lower(Bb, n, n, Pb, n, nullptr, 0, s, b, nn, nn, 0));
-        if (!have_uinv) DQ_HIP(launch_trinv_blocks(U, ldu, n, uinv, flags, s, b, (long)n * ldu, nn));
+        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 16.0 * b * (double)n * n);
+        DQ_HIP(launch_skew_lower(Bb, ld, n, Pb, ld, nullptr, 0, s, b, nn, nn, 0));
+        if (!have_uinv) DQ_HIP(launch_trinv_blocks(U, ldu, n, uinv, flags, s, b, (long)n * ldu, sinv));
     }
     {
         GemmF32 g;   // M = P inv(U)^T
-        g.A = Pb; g.lda = n; g.ta = 0; g.batch_a = nn;
-        g.B = uinv; g.ldb = kTrsmBlock; g.tb = 1; g.batch_b = nn;
-        g.C = Mb; g.ldc = n; g.batch_c = nn;
+        g.A = Pb; g.lda = ld; g.ta = 0; g.batch_a = nn;
+        g.B = uinv; g.ldb = kTrsmBlock; g.tb = 1; g.batch_b = sinv;
+        g.C = Mb; g.ldc = ld; g.batch_c = nn;
         g.M = n; g.N = n; g.K = n; g.batch = b;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
         DQ_HIP(launch_gemm_f32(g, s));
@@ -1335,7 +1341,7 @@ dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, const float* R,
     {
         GemmF32 g;   // dZ = R M  (or Z <- Z - lr R M)
         g.A = R; g.lda = ldr; g.ta = 0; g.batch_a = (long)n * ldr;
-        g.B = Mb; g.ldb = n; g.tb = 0; g.b_strict_lower = 1; g.batch_b = nn;
+        g.B = Mb; g.ldb = ld; g.tb = 0; g.b_strict_lower = 1; g.batch_b = nn;
         g.M = n; g.N = n; g.K = n; g.batch = b;
         if (Zupd != nullptr) { g.C = Zupd; g.ldc = ldz; g.batch_c = (long)n * ldz; g.alpha = -lr; g.beta = 1.f; }
         else { g.C = dZ; g.ldc = lddz; g.batch_c = (long)n * lddz; }
@@ -1343,6 +1349,32 @@ dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, const float* R,
         DQ_HIP(launch_gemm_f32(g, s));
     }
     return DQ_OK;
+}
+
+// S1 .. S6 of every problem of a batch of small rotations; dZ (or the updated latents) as in heads_backward.  bf16
+// activations under Eq. 4 go through the fused kernel, anything else through S3 .. S5 problem by problem.
+dq_status heads_step(dq_ctx* c, const Layout& L, int b, int T, int n, const void* X, dq_dtype xdt, long ldx, const float* Z,
+                     long ldz, dq_reduce red, float* loss_dev, float* R, long ldr, float* dZ, long lddz, float* Zupd,
+                     float lr) {
+    const HeadsLayout H = make_heads_layout(L.total, b, T);
+    float* Rh = R ? R : at<float>(c, H.R);
+    const long ldrh = R ? ldr : kHeadDim;
+    float* Uh = at<float>(c, H.U);
+    float* Gh = at<float>(c, H.G);
+    DQ_TRY(heads_qr(c, b, n, Z, ldz, Rh, ldrh, Uh, kHeadDim));
+    const bool early = !c->single_stream && b >= 1;
+    if (early) DQ_TRY(heads_uinv_early(c, H, b, n, Uh, kHeadDim));
+    if (heads_fused_route(c, n, xdt)) {
+        DQ_TRY(heads_rotate_loss_grad(c, H, b, n, T, X, ldx, Rh, ldrh, red, loss_dev, Gh, kHeadDim));
+    } else {
+        const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
+        for (int i = 0; i < b; ++i)
+            DQ_TRY(rotate_loss_grad_one(c, L, T, n, static_cast<const char*>(X) + (size_t)i * T * ldx * esz, xdt, ldx,
+                                        Rh + (long)i * n * ldrh, ldrh, red, loss_dev + i, Gh + (long)i * n * kHeadDim,
+                                        kHeadDim, at<float>(c, L.Y), L.ld, at<char>(c, L.dY), L.ld, false));
+    }
+    if (early) DQ_HIP(hipStreamWaitEvent(c->stream, c->sync_ev[1], 0));
+    return heads_backward(c, H, b, n, Rh, ldrh, Uh, kHeadDim, Gh, kHeadDim, dZ, lddz, Zupd, ldz, lr, early);
 }
 
 }  // namespace
@@ -1417,7 +1449,7 @@ dq_status dq_workspace_bytes(int b, int n, int T, dq_dtype x_dtype, size_t* out)
     DQ_TRY(check_n(n));
     if (x_dtype != DQ_F32 && x_dtype != DQ_BF16) return DQ_ERR_DTYPE;
     const Layout L = make_layout(n, T);
-    *out = n == kHeadDim ? make_heads_layout(L.total, b, T).total : L.total;
+    *out = n <= kHeadDim ? make_heads_layout(L.total, b, T).total : L.total;
     return DQ_OK;
 }
 
@@ -1453,7 +1485,7 @@ dq_status dq_qr_orth(dq_ctx* c, int b, int n, const float* Z, long ldz, float* R
     if (U != nullptr) DQ_TRY(check_f32(U, ldu, n));
     const Layout L = make_layout(n, 1);
     DQ_TRY(check_ws(c, L));
-    if (heads_route(c, n)) return heads_qr(c, b, Z, ldz, R, ldr, U, ldu);
+    if (heads_route(c, n)) return heads_qr(c, b, n, Z, ldz, R, ldr, U, ldu);
     for (int i = 0; i < b; ++i)
         DQ_TRY(qr_orth_one(c, L, n, Z + (long)i * n * ldz, ldz, R + (long)i * n * ldr, ldr,
                            U ? U + (long)i * n * ldu : nullptr, ldu));
@@ -1474,10 +1506,14 @@ dq_status dq_rotate_loss_grad(dq_ctx* c, int b, int T, int n, const void* X, dq_
     if (dY != nullptr) DQ_TRY(check_x(dY, xdt, lddy, n));
     const Layout L = make_layout(n, T);
     DQ_TRY(check_ws(c, L));
-    if (heads_fused_route(c, n) && xdt == DQ_BF16 && Y == nullptr && dY == nullptr) {
-        const HeadsLayout H = make_heads_layout(L.total, b, T);
-        DQ_TRY(check_heads_ws(c, H));
-        return heads_rotate_loss_grad(c, H, b, T, X, ldx, R, ldr, red, loss_dev, G, ldg);
+    if (heads_fused_route(c, n, xdt) && Y == nullptr && dY == nullptr) {
+        const int gb = heads_group(c, L.total, b, T);
+        if (gb < 1) return DQ_ERR_WORKSPACE;
+        const HeadsLayout H = make_heads_layout(L.total, gb, T);
+        for (int i = 0; i < b; i += gb)
+            DQ_TRY(heads_rotate_loss_grad(c, H, b - i < gb ? b - i : gb, n, T, static_cast<const bf16_t*>(X) + (long)i * T * ldx,
+                                          ldx, R + (long)i * n * ldr, ldr, red, loss_dev + i, G + (long)i * n * ldg, ldg));
+        return DQ_OK;
     }
     const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
     for (int i = 0; i < b; ++i) {
@@ -1504,21 +1540,17 @@ dq_status dq_calib_step(dq_ctx* c, int b, int T, int n, const void* X, dq_dtype 
     if (R != nullptr) DQ_TRY(check_f32(R, ldr, n));
     const Layout L = make_layout(n, T);
     DQ_TRY(check_ws(c, L));
-    if (heads_fused_route(c, n) && xdt == DQ_BF16) {
-        const HeadsLayout H = make_heads_layout(L.total, b, T);
-        DQ_TRY(check_heads_ws(c, H));
-        float* Rh = R ? R : at<float>(c, H.R);
-        const long ldrh = R ? ldr : kHeadDim;
-        float* Uh = at<float>(c, H.U);
-        float* Gh = at<float>(c, H.G);
-        DQ_TRY(heads_qr(c, b, Z, ldz, Rh, ldrh, Uh, kHeadDim));
-        const bool early = !c->single_stream && b >= 1;
-        if (early) DQ_TRY(heads_uinv_early(c, H, b, Uh, kHeadDim));
-        DQ_TRY(heads_rotate_loss_grad(c, H, b, T, X, ldx, Rh, ldrh, red, loss_dev, Gh, kHeadDim));
-        if (early) DQ_HIP(hipStreamWaitEvent(c->stream, c->sync_ev[1], 0));
-        return heads_backward(c, H, b, Rh, ldrh, Uh, kHeadDim, Gh, kHeadDim, nullptr, 0, Z, ldz, lr, early);
-    }
     const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
+    if (heads_route(c, n)) {
+        const int gb = heads_group(c, L.total, b, T);
+        if (gb < 1) return DQ_ERR_WORKSPACE;
+        for (int i = 0; i < b; i += gb) {
+            float* Zi = Z + (long)i * n * ldz;
+            DQ_TRY(heads_step(c, L, b - i < gb ? b - i : gb, T, n, static_cast<const char*>(X) + (size_t)i * T * ldx * esz, xdt,
+                              ldx, Zi, ldz, red, loss_dev + i, R ? R + (long)i * n * ldr : nullptr, ldr, nullptr, 0, Zi, lr));
+        }
+        return DQ_OK;
+    }
     for (int i = 0; i < b; ++i) {
         float* Zi = Z + (long)i * n * ldz;
         float* Ri = R ? R + (long)i * n * ldr : at<float>(c, L.R);
@@ -1732,9 +1764,15 @@ dq_status dq_qr_backward(dq_ctx* c, int b, int n, const float* R, long ldr, cons
     const Layout L = make_layout(n, 1);
     DQ_TRY(check_ws(c, L));
     if (heads_route(c, n)) {
-        const HeadsLayout H = make_heads_layout(L.total, b, 1);
-        DQ_TRY(check_heads_ws(c, H));
-        return heads_backward(c, H, b, R, ldr, U, ldu, G, ldg, dZ, lddz, nullptr, 0, 0.f);
+        const int gb = heads_group(c, L.total, b, 1);
+        if (gb < 1) return DQ_ERR_WORKSPACE;
+        const HeadsLayout H = make_heads_layout(L.total, gb, 1);
+        for (int i = 0; i < b; i += gb) {
+            const long r0 = (long)i * n;
+            DQ_TRY(heads_backward(c, H, b - i < gb ? b - i : gb, n, R + r0 * ldr, ldr, U + r0 * ldu, ldu, G + r0 * ldg, ldg,
+                                  dZ + r0 * lddz, lddz, nullptr, 0, 0.f));
+        }
+        return DQ_OK;
     }
     for (int i = 0; i < b; ++i)
         DQ_TRY(qr_backward_one(c, L, n, R + (long)i * n * ldr, ldr, U + (long)i * n * ldu, ldu, G + (long)i * n * ldg,
@@ -1851,23 +1889,21 @@ dq_status dq_calib_step_adam(dq_ctx* c, int b, int T, int n, const void* X, dq_d
     const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
     const float c1 = (float)(1.0 / (1.0 - pow((double)beta1, (double)step)));
     const float c2 = (float)(1.0 / (1.0 - pow((double)beta2, (double)step)));
-    if (heads_fused_route(c, n) && xdt == DQ_BF16 && ldz == n && ldm == n && ldv == n) {
-        const HeadsLayout H = make_heads_layout(L.total, b, T);
-        DQ_TRY(check_heads_ws(c, H));
-        float* Rh = R ? R : at<float>(c, H.R);
-        const long ldrh = R ? ldr : kHeadDim;
-        float* Uh = at<float>(c, H.U);
-        float* Gh = at<float>(c, H.G);
-        float* dZh = at<float>(c, H.B);   // B = R^T G is consumed before the last product writes dZ there
-        DQ_TRY(heads_qr(c, b, Z, ldz, Rh, ldrh, Uh, kHeadDim));
-        const bool early = !c->single_stream && b >= 1;
-        if (early) DQ_TRY(heads_uinv_early(c, H, b, Uh, kHeadDim));
-        DQ_TRY(heads_rotate_loss_grad(c, H, b, T, X, ldx, Rh, ldrh, red, loss_dev, Gh, kHeadDim));
-        if (early) DQ_HIP(hipStreamWaitEvent(c->stream, c->sync_ev[1], 0));
-        DQ_TRY(heads_backward(c, H, b, Rh, ldrh, Uh, kHeadDim, Gh, kHeadDim, dZh, kHeadDim, nullptr, 0, 0.f, early));
-        // the b problems are stacked row-wise with a common row stride: one elementwise pass over b*n rows
-        LaunchScope sc(&c->prof, c->stream, DQ_K_SMALL, 12.0 * b * n * (double)n, 28.0 * b * n * (double)n);
-        DQ_HIP(launch_adam2d(Z, ldz, dZh, kHeadDim, m, ldm, v, ldv, n, lr, beta1, beta2, eps, c1, c2, c->stream, b * n));
+    if (heads_route(c, n)) {
+        const int gb = heads_group(c, L.total, b, T);
+        if (gb < 1) return DQ_ERR_WORKSPACE;
+        // B = R^T G is consumed before the last product writes dZ there
+        float* dZh = at<float>(c, make_heads_layout(L.total, gb, T).B);
+        for (int i = 0; i < b; i += gb) {
+            const int g = b - i < gb ? b - i : gb;
+            const long r0 = (long)i * n;
+            DQ_TRY(heads_step(c, L, g, T, n, static_cast<const char*>(X) + (size_t)i * T * ldx * esz, xdt, ldx, Z + r0 * ldz, ldz,
+                              red, loss_dev + i, R ? R + r0 * ldr : nullptr, ldr, dZh, kHeadDim, nullptr, 0.f));
+            // the problems are stacked row-wise with a common row stride: one elementwise pass over g * n rows
+            LaunchScope sc(&c->prof, c->stream, DQ_K_SMALL, 12.0 * g * n * (double)n, 28.0 * g * n * (double)n);
+            DQ_HIP(launch_adam2d(Z + r0 * ldz, ldz, dZh, kHeadDim, m + r0 * ldm, ldm, v + r0 * ldv, ldv, n, lr, beta1, beta2, eps,
+                                 c1, c2, c->stream, g * n));
+        }
         return DQ_OK;
     }
     for (int i = 0; i < b; ++i) {

@@ -13,8 +13,8 @@ constexpr int kPanel = 64;           // QR panel width nb (columns aggregated in
 constexpr int kTrsmBlock = 128;      // diagonal block size of the blocked triangular solve
 constexpr int kTrsmOuter = 512;      // its outer block: columns solved before the rest of the matrix is updated once
 constexpr int kMaxSplit = 64;        // upper bound on split-K partials
-constexpr int kHeadDim = 128;         // matrix size served by the batched small-rotation path
-constexpr int kHeadsChunk = 2048;     // tokens per workgroup of its fused rotate / loss / gradient kernel
+constexpr int kHeadDim = 128;         // largest matrix size served by the batched small-rotation path
+constexpr int kHeadsChunk = 2048;     // most tokens per workgroup of its fused rotate / loss / gradient kernel
 constexpr int kLossPartials = 65536; // upper bound on workgroups of the Whip pass (one partial each)
 constexpr int kAccumPanels = 4;      // panels whose reflectors are merged before they are applied to the accumulated R
 constexpr int kCholMaxParts = 64;    // upper bound on the Gram partials of the tall-panel path
@@ -200,14 +200,14 @@ hipError_t launch_fill_u32(unsigned* p, long count, unsigned v, hipStream_t s);
 hipError_t launch_sign_normalise(const float* Afac, long lda, int n, float* R, long ldr, float* U, long ldu,
                                  unsigned* flags, hipStream_t s);
 
-// ---- batched 128 x 128 rotations (all problems of a batch in one launch) -------------
+// ---- batched small rotations, n <= kHeadDim (all problems of a batch in one launch) -------------
 // R (orthogonal, diag(U) >= 0) and U (optional) of b latents; problem i at Z + i*sz etc. (element strides).
-hipError_t launch_heads_qr(int b, const float* Z, long ldz, long sz, float* R, long ldr, long sr, float* U, long ldu,
+hipError_t launch_heads_qr(int b, int n, const float* Z, long ldz, long sz, float* R, long ldr, long sr, float* U, long ldu,
                            long su, unsigned* flags, hipStream_t s);
-// loss[i] = scale * sum exp(-|X_i R_i|) and G_i = X_i^T dY_i for bf16 X_i (T x 128), fused.  Gpart needs
+// loss[i] = scale * sum exp(-|X_i R_i|) and G_i = X_i^T dY_i for bf16 X_i (T x n), fused.  Gpart needs
 // b * heads_splits(T) * 128 * 128 floats, lpart b * heads_splits(T) doubles.
 int heads_splits(int T);
-hipError_t launch_heads_rlg(int b, int T, const bf16_t* X, long ldx, long sx, const float* R, long ldr, long sr,
+hipError_t launch_heads_rlg(int b, int n, int T, const bf16_t* X, long ldx, long sx, const float* R, long ldr, long sr,
                             float scale, float* Gpart, double* lpart, float* G, long ldg, long sg, float* loss,
                             unsigned* flags, hipStream_t s);
 

@@ -1,6 +1,6 @@
-// Batched path for many small rotations of size 128 (per-head rotations; the "heads" workload): every problem of a
-// batch runs in the same launch.
-//   * heads_qr_kernel: R, U = qr(Z) for one 128 x 128 latent per workgroup, entirely in LDS.  Alg. 2 as printed:
+// Batched path for small rotations, n <= 128 (per-head rotations; the "heads" workload has 64 of size 128): every problem
+// of a batch runs in the same launch.
+//   * heads_qr_kernel: R, U = qr(Z) for one latent per workgroup, entirely on chip.  Alg. 2 as printed:
 //     column by column, the reflector is applied to the trailing columns of the matrix and accumulated into the
 //     orthogonal factor in the same step (A <- H A, Q <- Q H); the signs are then fixed so that diag(U) >= 0.
 //   * heads_rlg_kernel: Alg. 1, rotation and loss steps, fused for bf16 activations.  A workgroup streams 64-token tiles of X once;
@@ -21,7 +21,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-constexpr int HN = kHeadDim;     // matrix size of this path
+constexpr int HN = kHeadDim;     // largest matrix size of this path
 
 __device__ __forceinline__ float wave_total(float v) {
 #pragma unroll
@@ -120,10 +120,13 @@ __device__ __forceinline__ void reflect_from(const float* cb, float (&xc)[4 * NG
         default: CALL(7); break;                                                                   \
     }
 
+// FULL: n == 128, nothing to guard.
+template <bool FULL>
 __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restrict__ Z, long ldz, long sz,
                                                            float* __restrict__ R, long ldr, long sr,
-                                                           float* __restrict__ U, long ldu, long su,
+                                                           float* __restrict__ U, long ldu, long su, int n_,
                                                            unsigned* flags) {
+    const int n = FULL ? HN : n_;
     __shared__ __attribute__((aligned(16))) float cbuf[2][HN];
     __shared__ __attribute__((aligned(16))) float sgn[HN];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -136,13 +139,13 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int i = 4 * (k * QS + h) + e;
-            xc[4 * k + e] = Zp[(long)i * ldz + col];
+            xc[4 * k + e] = (i < n && col < n) ? Zp[(long)i * ldz + col] : 0.f;
             xq[4 * k + e] = (i == item) ? 1.f : 0.f;
         }
     float mydiag = 0.f;
     if (col == 0) publish_from<0>(cbuf[0], xc, h, 0);
     __syncthreads();
-    for (int j = 0; j < HN; ++j) {
+    for (int j = 0; j < n; ++j) {           // (rows and columns from n on are zero and stay zero)
         const float* cb = cbuf[j & 1];
         // column norm below the pivot: DPP inside the rows of 16 lanes, then the four row sums through scalar registers
         const float a0 = cb[lane], a1 = cb[lane + 64];
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
         }
         __syncthreads();
     }
-    if (h == 0) {
+    if (h == 0 && col < n) {
         if (!(fabsf(mydiag) <= 3.0e38f)) atomicOr(flags, DQ_FLAG_NONFINITE);
         else if (mydiag == 0.f) atomicOr(flags, DQ_FLAG_SINGULAR);
     }
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int i = 4 * (k * QS + h) + e;
-                Up[(long)i * ldu + col] = i < col ? sgn[i] * xc[4 * k + e] : (i == col ? fabsf(mydiag) : 0.f);
+                if (i < n && col < n) Up[(long)i * ldu + col] = i < col ? sgn[i] * xc[4 * k + e] : (i == col ? fabsf(mydiag) : 0.f);
             }
     }
     {                     // R[r][c] = s_c Q[r][c]
@@ -195,34 +198,57 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
         for (int k = 0; k < NG; ++k) {
             const int c = 4 * (k * QS + h);
             const float4 sg = *reinterpret_cast<const float4*>(sgn + c);
-            *reinterpret_cast<float4*>(Rp + c) =
-                make_float4(xq[4 * k] * sg.x, xq[4 * k + 1] * sg.y, xq[4 * k + 2] * sg.z, xq[4 * k + 3] * sg.w);
+            const float4 v = make_float4(xq[4 * k] * sg.x, xq[4 * k + 1] * sg.y, xq[4 * k + 2] * sg.z, xq[4 * k + 3] * sg.w);
+            if (item < n && c + 3 < n) {
+                *reinterpret_cast<float4*>(Rp + c) = v;
+            } else if (item < n) {
+                if (c < n) Rp[c] = v.x;
+                if (c + 1 < n) Rp[c + 1] = v.y;
+                if (c + 2 < n) Rp[c + 2] = v.z;
+            }
         }
     }
 }
 #undef DQ_BLOCK_SWITCH
 
 // ------------------------------------------------------------------------------------------------ S3 + S4 + S5
+// JB = number of 32-column blocks of the rotation (n <= 32 JB): a workgroup has JB wavefronts, wavefront w forms the columns
+// [32 w, 32 w + 32) of Y and the same rows of G.  A narrower rotation thus costs its own share of the matrix-core work and
+// of the registers instead of the 128-wide one's.
 constexpr int TT = 64;            // tokens per tile
-constexpr int XLD = HN + 8;       // halfwords per LDS row of an X tile (272 bytes: 16-byte rows, 4-bank skew)
 constexpr int DLD = TT + 8;       // halfwords per LDS row of the transposed dY tile (144 bytes)
+template <int JB> constexpr int xld() { return 32 * JB + 8; }   // halfwords per LDS row of an X tile (16-byte rows, 4-bank skew)
 
 struct XRegs { uint4 q0, q1, q2, q3; };
 
-// tile rows [t0, t0 + 64) of X (tokens >= tend read as zero): 16 threads per row, 16 bytes each
-__device__ __forceinline__ XRegs fetch_x(const bf16_t* __restrict__ Xp, long ldx, int t0, int tend, int tid) {
-    const int col = (tid & 15) * 8, row = t0 + (tid >> 4);
+// columns [col, col + 8) of one row; columns from n on read as zero (EXACT: there are none, n == 32 JB)
+template <bool EXACT>
+__device__ __forceinline__ uint4 load8(const bf16_t* p, int col, int n) {
+    if (EXACT || col + 8 <= n) return *reinterpret_cast<const uint4*>(p);
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (col + e < n) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// tile rows [t0, t0 + 64) of X (tokens >= tend and columns >= n read as zero): 4 JB threads per row, 16 bytes each
+template <int JB, bool EXACT>
+__device__ __forceinline__ XRegs fetch_x(const bf16_t* __restrict__ Xp, long ldx, int t0, int tend, int n, int tid) {
+    const int col = (tid % (4 * JB)) * 8, row = t0 + tid / (4 * JB);
     const bf16_t* p = Xp + (long)row * ldx + col;
     XRegs r;
     r.q0 = r.q1 = r.q2 = r.q3 = make_uint4(0u, 0u, 0u, 0u);
-    if (row < tend) r.q0 = *reinterpret_cast<const uint4*>(p);
-    if (row + 16 < tend) r.q1 = *reinterpret_cast<const uint4*>(p + 16 * ldx);
-    if (row + 32 < tend) r.q2 = *reinterpret_cast<const uint4*>(p + 32 * ldx);
-    if (row + 48 < tend) r.q3 = *reinterpret_cast<const uint4*>(p + 48 * ldx);
+    if (row < tend) r.q0 = load8<EXACT>(p, col, n);
+    if (row + 16 < tend) r.q1 = load8<EXACT>(p + 16 * ldx, col, n);
+    if (row + 32 < tend) r.q2 = load8<EXACT>(p + 32 * ldx, col, n);
+    if (row + 48 < tend) r.q3 = load8<EXACT>(p + 48 * ldx, col, n);
     return r;
 }
+template <int JB>
 __device__ __forceinline__ void stash_x(bf16_t* Xs, int tid, const XRegs r) {
-    bf16_t* p = Xs + (tid >> 4) * XLD + (tid & 15) * 8;
+    constexpr int XLD = xld<JB>();
+    bf16_t* p = Xs + (tid / (4 * JB)) * XLD + (tid % (4 * JB)) * 8;
     *reinterpret_cast<uint4*>(p) = r.q0;
     *reinterpret_cast<uint4*>(p + 16 * XLD) = r.q1;
     *reinterpret_cast<uint4*>(p + 32 * XLD) = r.q2;
@@ -233,19 +259,31 @@ __device__ __forceinline__ void stash_x(bf16_t* Xs, int tid, const XRegs r) {
 // derivative, leaves dY transposed in LDS; after the barrier it adds X_tile^T dY_tile to its 32 rows of G.
 // Matrix-core operand layout (32x32x16 bf16): lane l supplies row/column (l & 31) and the 8 consecutive reduction
 // indices 8 (l >> 5) ..; the 32 x 32 result holds row 8 (v >> 2) + 4 (l >> 5) + (v & 3), column (l & 31) in register v.
-__device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const bf16x8 (&rhi)[8], const bf16x8 (&rlo)[8],
-                                           f32x16 (&accG)[4], float& lsum, float scale, int wave, int lrow, int lk) {
+// EVEN: every tile holds 64 tokens; otherwise only the first `tokens` rows of the last one are tokens.
+template <int JB, bool EVEN>
+__device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const bf16x8 (&rhi)[2 * JB],
+                                           const bf16x8 (&rlo)[2 * JB], f32x16 (&accG)[JB], float& lsum, float scale,
+                                           int tokens, int wave, int lrow, int lk) {
+    constexpr int XLD = xld<JB>();
     f32x16 y0, y1;
 #pragma unroll
     for (int v = 0; v < 16; ++v) { y0[v] = 0.f; y1[v] = 0.f; }
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < 2 * JB; ++ks) {
         const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(Xs + lrow * XLD + ks * 16 + lk * 8);
         const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(Xs + (32 + lrow) * XLD + ks * 16 + lk * 8);
         y0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, rhi[ks], y0, 0, 0, 0);
         y1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, rhi[ks], y1, 0, 0, 0);
         y0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, rlo[ks], y0, 0, 0, 0);
         y1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, rlo[ks], y1, 0, 0, 0);
+    }
+    if (!EVEN && tokens < TT) {   // the rows behind the last token: exp(-1e30) = 0 adds nothing to the loss nor to dY
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int tok = 8 * (v >> 2) + 4 * lk + (v & 3);
+            y0[v] = tok < tokens ? y0[v] : 1e30f;
+            y1[v] = 32 + tok < tokens ? y1[v] : 1e30f;
+        }
     }
     const int j = 32 * wave + lrow;
 #pragma unroll
@@ -258,7 +296,7 @@ __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const 
             for (int q = 0; q < 4; ++q) {
                 const float y = i == 0 ? y0[4 * g + q] : y1[4 * g + q];
                 const float ex = __expf(-fabsf(y));
-                lsum += ex;   // rows past the end of the chunk hold y = 0 and add exactly 1 each: removed by the caller
+                lsum += ex;
                 // scale * sgn(y) without comparisons: y * 2^126 has modulus >= 1 for every normal y (an overflow to
                 // infinity is as good), so the median with -scale and +scale picks the signed bound; y = 0 stays 0
                 const float sg = __builtin_amdgcn_fmed3f(y * 8.507059173e37f, -scale, scale);
@@ -283,7 +321,7 @@ __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const 
         }
         const bf16x8 afr = __builtin_bit_cast(bf16x8, au);
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
+        for (int jb = 0; jb < JB; ++jb) {
             const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(dYs + (jb * 32 + lrow) * DLD + kt * 16 + lk * 8);
             accG[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afr, bfr, accG[jb], 0, 0, 0);
         }
@@ -291,14 +329,16 @@ __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const 
 }
 
 // grid (splits, b): workgroup (s, p) handles tokens [s * chunk, min(T, (s+1) * chunk)) of problem p and writes its
-// partial G to Gpart[(p * splits + s) * 128 * 128 ..] and its partial sum of exp(-|y|) to lpart[p * splits + s].
-__global__ __launch_bounds__(256, 2) void heads_rlg_kernel(const bf16_t* __restrict__ X, long ldx, long sx, int T,
+// partial G to Gpart[(p * splits + s) * (32 JB)^2 ..] and its partial sum of exp(-|y|) to lpart[p * splits + s].
+template <int JB, bool EXACT, bool EVEN>
+__global__ __launch_bounds__(64 * JB, 2) void heads_rlg_kernel(const bf16_t* __restrict__ X, long ldx, long sx, int T, int n,
                                                         const float* __restrict__ R, long ldr, long sr, float scale,
                                                         float* __restrict__ Gpart, double* __restrict__ lpart,
                                                         int chunk) {
-    __shared__ __attribute__((aligned(16))) bf16_t Xs[2][TT * XLD];
-    __shared__ __attribute__((aligned(16))) bf16_t dYs[HN * DLD];
-    __shared__ float wsum[4];
+    constexpr int NP = 32 * JB;
+    __shared__ __attribute__((aligned(16))) bf16_t Xs[2][TT * xld<JB>()];
+    __shared__ __attribute__((aligned(16))) bf16_t dYs[NP * DLD];
+    __shared__ float wsum[JB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, lk = lane >> 5;
     const int split = blockIdx.x, prob = blockIdx.y, splits = gridDim.x;
     const bf16_t* Xp = X + (long)prob * sx;
@@ -307,17 +347,18 @@ __global__ __launch_bounds__(256, 2) void heads_rlg_kernel(const bf16_t* __restr
     const int tend = (tbeg + chunk < T) ? tbeg + chunk : T;
     const int ntiles = tend > tbeg ? (tend - tbeg + TT - 1) / TT : 0;
 
-    // this wavefront's 32 columns of R as matrix-core operands: R = hi + lo, 16 mantissa bits
-    bf16x8 rhi[8], rlo[8];
+    // this wavefront's 32 columns of R as matrix-core operands: R = hi + lo, 16 mantissa bits (zero beyond n x n)
+    bf16x8 rhi[2 * JB], rlo[2 * JB];
     {
         const int j = 32 * wave + lrow;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
+        for (int ks = 0; ks < 2 * JB; ++ks) {
             u32x4 hi, lo;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float r0 = Rp[(long)(ks * 16 + lk * 8 + 2 * e) * ldr + j];
-                const float r1 = Rp[(long)(ks * 16 + lk * 8 + 2 * e + 1) * ldr + j];
+                const int k = ks * 16 + lk * 8 + 2 * e;
+                const float r0 = (EXACT || (k < n && j < n)) ? Rp[(long)k * ldr + j] : 0.f;
+                const float r1 = (EXACT || (k + 1 < n && j < n)) ? Rp[(long)(k + 1) * ldr + j] : 0.f;
                 const uint32_t h0 = to_bf16_rne(r0), h1 = to_bf16_rne(r1);
                 const uint32_t l0 = to_bf16_rne(r0 - __uint_as_float(h0 << 16));
                 const uint32_t l1 = to_bf16_rne(r1 - __uint_as_float(h1 << 16));
@@ -329,61 +370,70 @@ __global__ __launch_bounds__(256, 2) void heads_rlg_kernel(const bf16_t* __restr
         }
     }
 
-    f32x16 accG[4];
+    f32x16 accG[JB];
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
+    for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) accG[jb][v] = 0.f;
     float lsum = 0.f;
 
-    XRegs p0 = fetch_x(Xp, ldx, tbeg, tend, tid);
-    XRegs p1 = fetch_x(Xp, ldx, tbeg + TT, tend, tid);
-    stash_x(Xs[0], tid, p0);
+    XRegs p0 = fetch_x<JB, EXACT>(Xp, ldx, tbeg, tend, n, tid);
+    XRegs p1 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + TT, tend, n, tid);
+    stash_x<JB>(Xs[0], tid, p0);
     __syncthreads();
     for (int it = 0; it < ntiles; it += 2) {
         // tile `it` is in Xs[0], tile it+1 in p1; tile it+2 is requested into p0
-        p0 = fetch_x(Xp, ldx, tbeg + (it + 2) * TT, tend, tid);
-        heads_tile(Xs[0], dYs, rhi, rlo, accG, lsum, scale, wave, lrow, lk);
-        stash_x(Xs[1], tid, p1);
+        p0 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + (it + 2) * TT, tend, n, tid);
+        heads_tile<JB, EVEN>(Xs[0], dYs, rhi, rlo, accG, lsum, scale, tend - (tbeg + it * TT), wave, lrow, lk);
+        stash_x<JB>(Xs[1], tid, p1);
         __syncthreads();
         if (it + 1 < ntiles) {
-            p1 = fetch_x(Xp, ldx, tbeg + (it + 3) * TT, tend, tid);
-            heads_tile(Xs[1], dYs, rhi, rlo, accG, lsum, scale, wave, lrow, lk);
+            p1 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + (it + 3) * TT, tend, n, tid);
+            heads_tile<JB, EVEN>(Xs[1], dYs, rhi, rlo, accG, lsum, scale, tend - (tbeg + (it + 1) * TT), wave, lrow, lk);
         }
-        stash_x(Xs[0], tid, p0);
+        stash_x<JB>(Xs[0], tid, p0);
         __syncthreads();
     }
 
-    float* Gp = Gpart + ((long)prob * splits + split) * (HN * HN);
+    float* Gp = Gpart + ((long)prob * splits + split) * (NP * NP);
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
+    for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-            Gp[(32 * wave + 8 * (v >> 2) + 4 * lk + (v & 3)) * HN + jb * 32 + lrow] = accG[jb][v];
-    lsum = wave_total(lsum);
+            Gp[(32 * wave + 8 * (v >> 2) + 4 * lk + (v & 3)) * NP + jb * 32 + lrow] = accG[jb][v];
+    // columns from n on hold y = 0 throughout: they count nothing
+    lsum = wave_total(EXACT || 32 * wave + lrow < n ? lsum : 0.f);
     if (lane == 0) wsum[wave] = lsum;
     __syncthreads();
     if (tid == 0) {
-        // the zero rows that pad the last tile contributed exp(0) = 1 per element
-        const double pad = (double)(ntiles * TT - (tend > tbeg ? tend - tbeg : 0)) * HN;
-        lpart[(long)prob * splits + split] =
-            (double)wsum[0] + (double)wsum[1] + (double)wsum[2] + (double)wsum[3] - pad;
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < JB; ++w) t += (double)wsum[w];
+        lpart[(long)prob * splits + split] = t;
     }
 }
 
-// grid (16, b): G[p] = sum_s Gpart[p][s];  loss[p] = scale * sum_s lpart[p][s]
+// grid (NP^2 / 1024, b): G[p] = sum_s Gpart[p][s] (partials NP x NP, NP = 32 ceil(n / 32));  loss[p] = scale * sum_s lpart[p][s]
 __global__ __launch_bounds__(256) void heads_reduce_kernel(const float* __restrict__ Gpart, const double* __restrict__ lpart,
-                                                           int splits, float scale, float* __restrict__ G, long ldg,
-                                                           long sg, float* __restrict__ loss, unsigned* flags) {
+                                                           int splits, float scale, int n, int np, float* __restrict__ G,
+                                                           long ldg, long sg, float* __restrict__ loss, unsigned* flags) {
     const int prob = blockIdx.y;
-    const int e = (blockIdx.x * 256 + threadIdx.x) * 4;   // 16 x 256 x 4 = 128 x 128
-    const float* src = Gpart + (long)prob * splits * (HN * HN) + e;
+    const int e = (blockIdx.x * 256 + threadIdx.x) * 4;
+    const float* src = Gpart + (long)prob * splits * (np * np) + e;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s = 0; s < splits; ++s) {
-        const float4 v = *reinterpret_cast<const float4*>(src + (long)s * (HN * HN));
+        const float4 v = *reinterpret_cast<const float4*>(src + (long)s * (np * np));
         acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
-    *reinterpret_cast<float4*>(G + (long)prob * sg + (long)(e >> 7) * ldg + (e & (HN - 1))) = acc;
+    const int r = e / np, c = e % np;
+    float* o = G + (long)prob * sg + (long)r * ldg + c;
+    if (r < n && c + 3 < n) {
+        *reinterpret_cast<float4*>(o) = acc;
+    } else if (r < n) {
+        if (c < n) o[0] = acc.x;
+        if (c + 1 < n) o[1] = acc.y;
+        if (c + 2 < n) o[2] = acc.z;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         double t = 0.0;
         for (int s = 0; s < splits; ++s) t += lpart[(long)prob * splits + s];
@@ -395,26 +445,52 @@ __global__ __launch_bounds__(256) void heads_reduce_kernel(const float* __restri
 
 }  // namespace
 
-hipError_t launch_heads_qr(int b, const float* Z, long ldz, long sz, float* R, long ldr, long sr, float* U, long ldu,
+hipError_t launch_heads_qr(int b, int n, const float* Z, long ldz, long sz, float* R, long ldr, long sr, float* U, long ldu,
                            long su, unsigned* flags, hipStream_t s) {
     if (b < 1) return hipSuccess;
-    hipLaunchKernelGGL(heads_qr_kernel, dim3(b), dim3(HN * QS), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, flags);
+    if (n < 1 || n > HN) return hipErrorInvalidValue;
+    if (n == HN)
+        hipLaunchKernelGGL(heads_qr_kernel<true>, dim3(b), dim3(HN * QS), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, n, flags);
+    else
+        hipLaunchKernelGGL(heads_qr_kernel<false>, dim3(b), dim3(HN * QS), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, n, flags);
     return hipGetLastError();
 }
 
-int heads_splits(int T) { return (T + kHeadsChunk - 1) / kHeadsChunk; }
+// Tokens per workgroup.  It depends on T alone, so that a batch and its problems one by one sum in the same order: about
+// eight parts of a block, no shorter than 256 tokens (the partial gradient a workgroup leaves costs as much as 64 tokens of
+// X) and no longer than kHeadsChunk (64 blocks of 16384 tokens then make 512 workgroups, two per compute unit).
+static int heads_chunk(int T) {
+    int c = (int)round_up((T + 7) / 8, TT);
+    if (c < 256) c = 256;
+    return c < kHeadsChunk ? c : kHeadsChunk;
+}
+int heads_splits(int T) { const int c = heads_chunk(T); return (T + c - 1) / c; }
 
-hipError_t launch_heads_rlg(int b, int T, const bf16_t* X, long ldx, long sx, const float* R, long ldr, long sr,
+hipError_t launch_heads_rlg(int b, int n, int T, const bf16_t* X, long ldx, long sx, const float* R, long ldr, long sr,
                             float scale, float* Gpart, double* lpart, float* G, long ldg, long sg, float* loss,
                             unsigned* flags, hipStream_t s) {
     if (b < 1) return hipSuccess;
-    const int splits = heads_splits(T);
-    hipLaunchKernelGGL(heads_rlg_kernel, dim3(splits, b), dim3(256), 0, s, X, ldx, sx, T, R, ldr, sr, scale, Gpart,
-                       lpart, kHeadsChunk);
+    if (n < 1 || n > HN) return hipErrorInvalidValue;
+    const int splits = heads_splits(T), chunk = heads_chunk(T), jb = (n + 31) / 32;
+    const dim3 grid(splits, b), block(64 * jb);
+#define DQ_RLG1(JB, EXACT, EVEN)                                                                                             \
+    hipLaunchKernelGGL((heads_rlg_kernel<JB, EXACT, EVEN>), grid, block, 0, s, X, ldx, sx, T, n, R, ldr, sr, scale, Gpart, lpart, chunk)
+#define DQ_RLG(JB)                                                                                                            \
+    if (n == 32 * JB && T % TT == 0) DQ_RLG1(JB, true, true);                                                                 \
+    else if (n == 32 * JB) DQ_RLG1(JB, true, false);                                                                          \
+    else DQ_RLG1(JB, false, false)
+    switch (jb) {
+        case 1: DQ_RLG(1); break;
+        case 2: DQ_RLG(2); break;
+        case 3: DQ_RLG(3); break;
+        default: DQ_RLG(4); break;
+    }
+#undef DQ_RLG
+#undef DQ_RLG1
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(heads_reduce_kernel, dim3(16, b), dim3(256), 0, s, Gpart, lpart, splits, scale, G, ldg, sg, loss,
-                       flags);
+    hipLaunchKernelGGL(heads_reduce_kernel, dim3(jb * jb, b), dim3(256), 0, s, Gpart, lpart, splits, scale, n, 32 * jb, G, ldg,
+                       sg, loss, flags);
     return hipGetLastError();
 }
 

@@ -1498,6 +1498,74 @@ def test_heads_backward_batched(ctx):
     assert ctx.dq_device_flags() == 0
 
 
+@pytest.mark.parametrize("n,T,bf16", [(1, 5, True), (8, 300, True), (31, 257, True), (33, 256, False), (64, 2049, True),
+                                      (80, 3000, True), (97, 700, True), (127, 16385, True)])
+def test_small_rotations_batched(n, T, bf16):
+    """Rotations below the full 128 columns (every block count of the fused kernel, ragged columns and tokens, the shortest
+    and the longest chunk): QR, loss, gradient and the stage's derivative against the oracle; a batch that does not fit its
+    workspace runs in groups with the same bits; the Adam step's first moment against the SGD step's gradient."""
+    b = 3
+    cfg = synth.scaled_config("heads", b=b, n=n, T=T, x_dtype="bf16" if bf16 else "f32")
+    inp = synth.make_inputs(cfg, seed=31)
+    X, Z0 = inp["X"], inp["Z0"]
+    ld, ldx = (n + 7) // 8 * 8 + 8, (n + 7) // 8 * 8 + 8
+    xdt, tdt = (B.DQ_BF16, torch.bfloat16) if bf16 else (B.DQ_F32, torch.float32)
+    _, Xd = padded3(b, T, n, ldx, tdt); Xd.copy_(dev(X).to(tdt))
+    c = B.Context()
+    try:
+        c.ensure_workspace(b, n, T, xdt)
+        lr = 1e-3
+        _, Zd = padded3(b, n, n, ld); Zd.copy_(dev(Z0))
+        _, Rd = padded3(b, n, n, ld)
+        loss = torch.zeros(b, device="cuda")
+        c.dq_calib_step(Xd, xdt, Zd, lr, B.DQ_REDUCE_TOKEN_MEAN, loss, Rd)
+        _, Gd = padded3(b, n, n, ld)
+        c.dq_rotate_loss_grad(Xd, xdt, Rd, B.DQ_REDUCE_TOKEN_MEAN, torch.zeros(b, device="cuda"), Gd)
+        RU = [orc.qr_orth(z) for z in Z0]
+        R32 = np.stack([r for r, _ in RU]).astype(np.float32)
+        U32 = np.stack([u for _, u in RU]).astype(np.float32)
+        _, dZd = padded3(b, n, n, ld)
+        Gs = rng(77).standard_normal((b, n, n)).astype(np.float32)
+        c.dq_qr_backward(_copied(R32, ld), _copied(U32, ld), _copied(Gs, ld), dZd)
+        for i in range(b):
+            lo, Go, _, _ = orc.rotate_loss_grad(X[i], Rd[i].cpu().numpy())
+            assert abs(loss[i].item() - lo) <= 1e-4 * lo
+            assert rel(Gd[i].cpu().numpy(), Go) < (2e-2 if bf16 else 1e-2)
+            assert rel(Rd[i].cpu().numpy(), RU[i][0]) < max(1e-4, 2e-7 * np.linalg.cond(Z0[i].astype(np.float64)))
+            assert rel(dZd[i].cpu().numpy(), orc.qr_backward(R32[i], U32[i], Gs[i])) < 1e-4
+        # one problem's workspace for the whole batch
+        c2 = B.Context()
+        try:
+            ws = torch.empty(B.workspace_bytes(1, n, T, xdt), dtype=torch.uint8, device="cuda")
+            c2.dq_set_workspace(ws)
+            _, Z2 = padded3(b, n, n, ld); Z2.copy_(dev(Z0))
+            l2 = torch.zeros(b, device="cuda")
+            c2.dq_calib_step(Xd, xdt, Z2, lr, B.DQ_REDUCE_TOKEN_MEAN, l2)
+            assert torch.equal(Z2, Zd) and torch.equal(l2, loss)
+            _, Za = padded3(b, n, n, ld); Za.copy_(dev(Z0))
+            m, v = torch.zeros((b, n, ld), device="cuda")[:, :, :n], torch.zeros((b, n, ld), device="cuda")[:, :, :n]
+            c2.dq_calib_step_adam(Xd, xdt, Za, m, v, 1, lr, B.DQ_REDUCE_TOKEN_MEAN, l2)
+            assert torch.equal(l2, loss)
+            # Z - lr dZ is rounded to fp32: the gradient read back from it is good to 2^-24 |Z| / lr
+            dz = (Z0.astype(np.float64) - Zd.cpu().numpy().astype(np.float64)) / lr
+            err = np.linalg.norm(m.cpu().numpy() / (1.0 - 0.9) - dz)
+            assert err <= 1e-5 * np.linalg.norm(dz) + 2.0 ** -24 * np.linalg.norm(Z0) / lr
+            assert (c2.dq_device_flags() | c.dq_device_flags()) == 0
+        finally:
+            torch.cuda.synchronize()
+            c2.close()
+    finally:
+        torch.cuda.synchronize()
+        c.close()
+
+
+def _copied(a, ld):
+    """A device copy of a stack of matrices with leading dimension ld."""
+    _, d = padded3(a.shape[0], a.shape[1], a.shape[2], ld)
+    d.copy_(dev(a))
+    return d
+
+
 def test_heads_full_size_step():
     """The heads workload at its full size (64 problems, T = 16384): problems 0, 31 and 63 against the oracle,
     every problem for orthogonality, and the Adam step against the SGD step's gradient."""
