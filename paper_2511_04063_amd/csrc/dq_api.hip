@@ -96,8 +96,8 @@ struct dq_ctx {
                                      // 4 from there on, each measured best there; 1: panel by panel)
     bool fused_whip = true;          // Eq. 4 in the epilogue of the rotation product where the shape allows
     bool heads_batched = true;       // n == 128: all problems of a batch in the same launches
-    int split_gemm = 1;              // fp32 products of the derivative from three-plane bf16 splits: 0 never, 1 where the
-                                     // shape fits and is large enough to gain, 2 wherever the shape fits
+    int split_gemm = 1;              // fp32 products from three-term bf16 splits: 0 never, 1 where it is faster, 2 also from
+                                     // planes split beforehand wherever the shape fits
     bool device_sync = true;         // the QR's streams hand over through a device word where a probe allows (else events)
     unsigned long long seq = 0;      // last value handed out for the hand-over words, which only grow
     unsigned long long arrived = 0;  // workgroups counted so far by the one-launch panels' word (zeroed with the status word)
@@ -257,6 +257,13 @@ void choose_split(int tiles, int K, int kalign, int max_splits, int& splits, int
     if (splits < 1) splits = 1;
 }
 
+// An fp32 product whose operands the library has formed itself (finite unless the call has failed anyway): split operands on
+// the bf16 matrix cores where the launcher's 128 x 128 tile applies, unless DQ_OPT_SPLIT_GEMM forbids it.
+hipError_t product_f32(const dq_ctx* c, GemmF32& g, hipStream_t s) {
+    g.x3 = c->split_gemm != 0;
+    return launch_gemm_f32(g, s);
+}
+
 // ---------------------------------------------------------------- block-reflector application
 // Pieces of  Csub <- (I - V op(T) V^T) Csub = Csub - (V op(T)) (V^T Csub)  with V the unit-lower-trapezoid block
 // stored at Vp (m x jb, ldv).  Each piece takes the stream and the scratch buffers it may use, so that the look-ahead
@@ -286,7 +293,7 @@ dq_status refl_project(dq_ctx* c, hipStream_t s, const Layout& L, const ReflBufs
         g.M = jb; g.N = ncols; g.K = m;
         g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * jb * (double)ncols * m, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     *Wsum = bufs.wpart;
     if (splits > 1 && splits_out == nullptr) {   // a caller that asks for the split count sums the partials itself
@@ -306,7 +313,7 @@ dq_status refl_make_y(dq_ctx* c, hipStream_t s, const float* Vp, long ldv, int m
     g.C = Y; g.ldc = kPanel;
     g.M = m; g.N = jb; g.K = jb;
     LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * m * (double)jb * jb, 0.0);
-    DQ_HIP(launch_gemm_f32(g, s));
+    DQ_HIP(product_f32(c, g, s));
     return DQ_OK;
 }
 
@@ -321,7 +328,7 @@ dq_status refl_update(dq_ctx* c, hipStream_t s, const Layout& L, const float* Vp
     g.M = m; g.N = nc; g.K = jb;
     g.alpha = -1.f; g.beta = 1.f;
     LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * m * (double)nc * jb, 0.0);
-    DQ_HIP(launch_gemm_f32(g, s));
+    DQ_HIP(product_f32(c, g, s));
     return DQ_OK;
 }
 
@@ -345,7 +352,7 @@ dq_status accumulate_q(dq_ctx* c, hipStream_t s, const Layout& L, int n, int k0,
         g.M = n; g.N = jb; g.K = m;
         g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n * (double)jb * m, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     if (splits > 1) {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
@@ -359,7 +366,7 @@ dq_status accumulate_q(dq_ctx* c, hipStream_t s, const Layout& L, int n, int k0,
         g.M = n; g.N = m; g.K = jb;
         g.alpha = -1.f; g.beta = 1.f;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n * (double)m * jb, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     return DQ_OK;
 }
@@ -404,7 +411,7 @@ dq_status merge_yb_step(dq_ctx* c, hipStream_t s, int n, int nb, int q0, int j, 
             g.M = off; g.N = jq; g.K = mq;
             g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * off * (double)jq * mq, 0.0);
-            DQ_HIP(launch_gemm_f32(g, s));
+            DQ_HIP(product_f32(c, g, s));
         }
         if (splits > 1) {
             LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
@@ -418,7 +425,7 @@ dq_status merge_yb_step(dq_ctx* c, hipStream_t s, int n, int nb, int q0, int j, 
             g.M = mb; g.N = jq; g.K = off;
             g.alpha = -1.f; g.beta = 1.f;
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mb * (double)jq * off, 0.0);
-            DQ_HIP(launch_gemm_f32(g, s));
+            DQ_HIP(product_f32(c, g, s));
         }
     }
     return DQ_OK;
@@ -437,7 +444,7 @@ dq_status accumulate_q_apply(dq_ctx* c, hipStream_t s, const Layout& L, int n, i
     int splits, kchunk;
     int max_splits = (int)(((size_t)kMaxSplit * n * kPanel) / ((size_t)n * ldy));   // what the partial buffer holds
     if (max_splits < 1) max_splits = 1;
-    choose_split(((n + 127) / 128) * ((w + 127) / 128), mb, 16, max_splits, splits, kchunk);
+    choose_split(((n + 127) / 128) * ((w + 127) / 128), mb, 32, max_splits, splits, kchunk);
     {
         GemmF32 g;   // Wq = Qc Yb
         g.A = Qc; g.lda = ldq; g.ta = 0;
@@ -446,7 +453,7 @@ dq_status accumulate_q_apply(dq_ctx* c, hipStream_t s, const Layout& L, int n, i
         g.M = n; g.N = w; g.K = mb;
         g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n * (double)w * mb, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     if (splits > 1) {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
@@ -460,7 +467,7 @@ dq_status accumulate_q_apply(dq_ctx* c, hipStream_t s, const Layout& L, int n, i
         g.M = n; g.N = mb; g.K = w;
         g.alpha = -1.f; g.beta = 1.f;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n * (double)mb * w, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     return DQ_OK;
 }
@@ -489,7 +496,7 @@ dq_status far_update(dq_ctx* c, hipStream_t s, const Layout& L, float* wpart, fl
     float* Ablk = A + (long)k0 * ld + k0;
     float* Cf = A + (long)k0 * ld + c0;
     int splits, kchunk;
-    choose_split(((w + 127) / 128) * ((nc + 127) / 128), mb, 16, kFarSplit, splits, kchunk);
+    choose_split(((w + 127) / 128) * ((nc + 127) / 128), mb, 32, kFarSplit, splits, kchunk);
     {
         GemmF32 g;   // W = Yb^T C
         g.A = Yb; g.lda = ldy; g.ta = 1;
@@ -498,7 +505,7 @@ dq_status far_update(dq_ctx* c, hipStream_t s, const Layout& L, float* wpart, fl
         g.M = w; g.N = nc; g.K = mb;
         g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * w * (double)nc * mb, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     if (splits > 1) {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
@@ -732,7 +739,7 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
                 g.M = m; g.N = nla; g.K = jb;
                 g.alpha = -1.f; g.beta = 1.f;
                 LaunchScope sc(&c->prof, sA, DQ_K_GEMM_F32, 2.0 * m * (double)nla * jb, 0.0);
-                DQ_HIP(launch_gemm_f32(g, sA));
+                DQ_HIP(product_f32(c, g, sA));
             }
             DQ_TRY(refl_make_y(c, sA, Ap, ld, m, jb, Tp, 0, Yp));
         }
@@ -965,7 +972,7 @@ dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R,
             g.batch = nouter; g.batch_a = (long)kTrsmOuter * ldu + kTrsmOuter; g.batch_b = so; g.batch_c = stmp;
             {
                 LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * nouter * (double)h * h * h, 0.0);
-                DQ_HIP(launch_gemm_f32(g, s));
+                DQ_HIP(product_f32(c, g, s));
             }
             GemmF32 f;
             f.A = uo + (long)first * kTrsmOuter + first; f.lda = kTrsmOuter; f.ta = 0;
@@ -974,7 +981,7 @@ dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R,
             f.alpha = -1.f;
             f.batch = nouter; f.batch_a = so; f.batch_b = stmp; f.batch_c = so;
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * nouter * (double)h * h * h, 0.0);
-            DQ_HIP(launch_gemm_f32(f, s));
+            DQ_HIP(product_f32(c, f, s));
             return DQ_OK;
         };
         DQ_TRY(merge(kTrsmBlock, 0, t1, (long)2 * kTrsmBlock * kTrsmBlock));
@@ -1024,7 +1031,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         g.B = G; g.ldb = ldg; g.tb = 0;
         g.C = Bb; g.ldc = ld; g.M = n; g.N = n; g.K = n;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 16.0 * n * (double)n);
@@ -1050,7 +1057,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
                 g.C = Mb + (long)J0 * ld + J0; g.ldc = ld;
                 g.M = mrows; g.N = kTrsmOuter; g.K = kTrsmOuter;
                 LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)kTrsmOuter * kTrsmOuter, 0.0);
-                DQ_HIP(launch_gemm_f32(g, s));
+                DQ_HIP(product_f32(c, g, s));
             }
             if (J0 > 0) {
                 GemmF32 g;   // P[J0:, 0:J0] -= M[J0:, blk] * U[0:J0, blk]^T (in fp32: from three-plane splits its tiles
@@ -1061,7 +1068,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
                 g.M = mrows; g.N = J0; g.K = kTrsmOuter;
                 g.alpha = -1.f; g.beta = 1.f;
                 LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)J0 * kTrsmOuter, 0.0);
-                DQ_HIP(launch_gemm_f32(g, s));
+                DQ_HIP(product_f32(c, g, s));
             }
         }
     } else
@@ -1076,7 +1083,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
             g.C = Mb + (long)j0 * ld + j0; g.ldc = ld;
             g.M = mrows; g.N = w; g.K = w;
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)w * w, 0.0);
-            DQ_HIP(launch_gemm_f32(g, s));
+            DQ_HIP(product_f32(c, g, s));
         }
         if (j0 > 0) {
             GemmF32 g;   // P[j0:, 0:j0] -= M[j0:, blk] * U[0:j0, blk]^T
@@ -1086,7 +1093,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
             g.M = mrows; g.N = j0; g.K = w;
             g.alpha = -1.f; g.beta = 1.f;
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)j0 * w, 0.0);
-            DQ_HIP(launch_gemm_f32(g, s));
+            DQ_HIP(product_f32(c, g, s));
         }
     }
     if (x3) {
@@ -1126,7 +1133,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         if (Zupd != nullptr) { g.C = Zupd; g.ldc = ldz; g.alpha = -lr; g.beta = 1.f; }
         else { g.C = dZ; g.ldc = lddz; }
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, n3, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     return DQ_OK;
 }
@@ -1181,7 +1188,7 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
         g.C = C_; g.ldc = ldc; g.M = n; g.N = n; g.K = n;
         g.alpha = alpha; g.beta = beta_; g.alpha_dev = alpha_dev;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
         return DQ_OK;
     };
     {
@@ -1322,7 +1329,7 @@ dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, int n, const fl
         g.C = Bb; g.ldc = ld; g.batch_c = nn;
         g.M = n; g.N = n; g.K = n; g.batch = b;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 16.0 * b * (double)n * n);
@@ -1336,7 +1343,7 @@ dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, int n, const fl
         g.C = Mb; g.ldc = ld; g.batch_c = nn;
         g.M = n; g.N = n; g.K = n; g.batch = b;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     {
         GemmF32 g;   // dZ = R M  (or Z <- Z - lr R M)
@@ -1346,7 +1353,7 @@ dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, int n, const fl
         if (Zupd != nullptr) { g.C = Zupd; g.ldc = ldz; g.batch_c = (long)n * ldz; g.alpha = -lr; g.beta = 1.f; }
         else { g.C = dZ; g.ldc = lddz; g.batch_c = (long)n * lddz; }
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, n3, 0.0);
-        DQ_HIP(launch_gemm_f32(g, s));
+        DQ_HIP(product_f32(c, g, s));
     }
     return DQ_OK;
 }
@@ -1978,6 +1985,7 @@ dq_status dq_gemm_f32(dq_ctx* c, int M, int N, int K, float alpha, const float* 
     g.B = B; g.ldb = ldb; g.tb = tb ? 1 : 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.alpha = alpha; g.beta = beta;
     LaunchScope sc(&c->prof, c->stream, DQ_K_GEMM_F32, 2.0 * M * (double)N * K, 0.0);
+    g.x3 = c->split_gemm == 2;   // operands of any value by default: an infinity has no split
     DQ_HIP(launch_gemm_f32(g, c->stream));
     return DQ_OK;
 }

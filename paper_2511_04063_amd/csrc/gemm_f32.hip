@@ -18,6 +18,7 @@
 namespace dq {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 namespace {
 
@@ -107,117 +108,11 @@ __device__ __forceinline__ void stash_tile(float (*S)[ROWS + 4], int tid, const 
     }
 }
 
-// BM x BN is the workgroup tile and WT the wavefront tile in units of 32 (wavefront tile 32*WT x 32*WT, four
-// wavefronts): 128 x 128 (WT 2, waves 2 x 2), 64 x 256 (M <= 64) and 256 x 64 (N <= 64) for throughput, and
-// 64 x 64 with WT 1 and a deeper K step for small latency-bound products that need many workgroups.
-template <bool TA, bool TB, int BM, int BN, int WT, int BK>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec) {
-    __shared__ __attribute__((aligned(16))) float As[2][BK][BM + 4];
-    __shared__ __attribute__((aligned(16))) float Bs[2][BK][BN + 4];
-    constexpr int WAVES_N = BN / (32 * WT);
-    static_assert((BM / (32 * WT)) * WAVES_N == 4, "four wavefronts per workgroup");
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-
-    // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2): give each XCD a
-    // contiguous run of tiles, and walk tiles in groups of 8 tile-rows so a run shares operand panels.
-    const int nt = tiles_m * tiles_n;
-    const int bid = blockIdx.x;
-    const int q8 = nt >> 3, r8 = nt & 7;
-    const int xcd = bid & 7;
-    const int pid = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
-    const int group = 8 * tiles_n;
-    const int gid = pid / group;
-    const int first_m = gid * 8;
-    const int gsz = (tiles_m - first_m) < 8 ? (tiles_m - first_m) : 8;
-    int pid_m = first_m + (pid % group) % gsz;
-    int pid_n = (pid % group) / gsz;
-    if (g.b_strict_lower) {
-        // The K loop of a tile starts at its column offset: tile columns are dealt out whole, longest first, so that
-        // the long tiles do not start late and finish alone.
-        pid_n = bid / tiles_m;
-        pid_m = bid % tiles_m;
-    }
-    const int m0 = pid_m * BM, n0 = pid_n * BN;
-
-    const int z = blockIdx.y;
-    int kb = 0, ke = g.K;
-    if (g.splits > 1) {
-        kb = z * g.kchunk;
-        ke = kb + g.kchunk < g.K ? kb + g.kchunk : g.K;
-    }
-    if (g.b_strict_lower) {
-        const int lo = (n0 / BK) * BK;
-        kb = kb > lo ? kb : lo;
-    }
-
-    OperandView oa, ob;
-    const long bz = blockIdx.z;   // independent problem of a batched launch
-    oa.p = g.A + bz * g.batch_a; oa.ld = g.lda; oa.vec = avec;
-    oa.unit_lower_cols = g.a_unit_lower ? 0x7fffffff : 0;
-    if (TA) { oa.row_lim = ke; oa.col_lim = g.M; } else { oa.row_lim = g.M; oa.col_lim = ke; }
-    ob.p = g.B + bz * g.batch_b; ob.ld = g.ldb; ob.vec = bvec;
-    ob.unit_lower_cols = g.b_unit_lower_cols;
-    if (TB) { ob.row_lim = g.N; ob.col_lim = ke; } else { ob.row_lim = ke; ob.col_lim = g.N; }
-
-    f32x16 acc[WT][WT];
-#pragma unroll
-    for (int i = 0; i < WT; ++i)
-#pragma unroll
-        for (int j = 0; j < WT; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const int wm = (wave / WAVES_N) * 32 * WT, wn = (wave % WAVES_N) * 32 * WT;
-    const int lrow = lane & 31, lk = lane >> 5;
-
-    const int nk = ke > kb ? (ke - kb + BK - 1) / BK : 0;
-    // A tile whose operand blocks and output block lie wholly inside the matrices, with aligned rows and out of reach
-    // of the unit-lower masks, takes loaders and an epilogue without bounds checks: the checks cost more instructions
-    // than the products of a short K loop.
-    const bool inner = avec && bvec && m0 + BM <= g.M && n0 + BN <= g.N && ke > kb && (ke - kb) % BK == 0 &&
-                       (!g.a_unit_lower || (!TA && m0 >= ke)) && (g.b_unit_lower_cols == 0 || (TB && n0 >= ke));
-    float4 fa[BM * BK / 1024], fb[BN * BK / 1024];
-    auto fetch_both = [&](int k0) {
-        if (inner) {
-            fetch_tile_inner<!TA, BM, BK>(oa.p, oa.ld, m0, k0, tid, fa);
-            fetch_tile_inner<TB, BN, BK>(ob.p, ob.ld, n0, k0, tid, fb);
-        } else {
-            fetch_tile<!TA, BM, BK>(oa, m0, k0, tid, fa);
-            fetch_tile<TB, BN, BK>(ob, n0, k0, tid, fb);
-        }
-    };
-    if (nk > 0) {
-        fetch_both(kb);
-        stash_tile<!TA, BM, BK>(As[0], tid, fa);
-        stash_tile<TB, BN, BK>(Bs[0], tid, fb);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) fetch_both(kb + (kt + 1) * BK);
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            float a[WT], b[WT];
-#pragma unroll
-            for (int i = 0; i < WT; ++i) a[i] = As[cur][kk + lk][wm + i * 32 + lrow];
-#pragma unroll
-            for (int j = 0; j < WT; ++j) b[j] = Bs[cur][kk + lk][wn + j * 32 + lrow];
-#pragma unroll
-            for (int i = 0; i < WT; ++i)
-#pragma unroll
-                for (int j = 0; j < WT; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        if (kt + 1 < nk) {
-            stash_tile<!TA, BM, BK>(As[cur ^ 1], tid, fa);
-            stash_tile<TB, BN, BK>(Bs[cur ^ 1], tid, fb);
-        }
-        __syncthreads();
-    }
-
+// C tile = alpha * acc + beta * C for the wavefront block of 32 WT x 32 WT at (m0 + wm, n0 + wn); inner: the workgroup's
+// tile lies wholly inside C.
+template <int WT>
+__device__ __forceinline__ void store_tile(const GemmF32& g, long bz, int z, f32x16 (&acc)[WT][WT], int m0, int n0, int wm,
+                                           int wn, int lrow, int lk, bool inner) {
     float* C = g.C + bz * g.batch_c + (long)z * g.split_stride;
     // the scale of the product may also carry a factor that only the device knows (a step size formed by a kernel)
     const float alpha = g.alpha_dev != nullptr ? g.alpha * *g.alpha_dev : g.alpha, beta = g.beta;
@@ -298,6 +193,288 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, i
     }   // guarded epilogue
 }
 
+// BM x BN is the workgroup tile and WT the wavefront tile in units of 32 (wavefront tile 32*WT x 32*WT, four
+// wavefronts): 128 x 128 (WT 2, waves 2 x 2), 64 x 256 (M <= 64) and 256 x 64 (N <= 64) for throughput, and
+// 64 x 64 with WT 1 and a deeper K step for small latency-bound products that need many workgroups.
+template <bool TA, bool TB, int BM, int BN, int WT, int BK>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec) {
+    __shared__ __attribute__((aligned(16))) float As[2][BK][BM + 4];
+    __shared__ __attribute__((aligned(16))) float Bs[2][BK][BN + 4];
+    constexpr int WAVES_N = BN / (32 * WT);
+    static_assert((BM / (32 * WT)) * WAVES_N == 4, "four wavefronts per workgroup");
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+
+    // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2): give each XCD a
+    // contiguous run of tiles, and walk tiles in groups of 8 tile-rows so a run shares operand panels.
+    const int nt = tiles_m * tiles_n;
+    const int bid = blockIdx.x;
+    const int q8 = nt >> 3, r8 = nt & 7;
+    const int xcd = bid & 7;
+    const int pid = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
+    const int group = 8 * tiles_n;
+    const int gid = pid / group;
+    const int first_m = gid * 8;
+    const int gsz = (tiles_m - first_m) < 8 ? (tiles_m - first_m) : 8;
+    int pid_m = first_m + (pid % group) % gsz;
+    int pid_n = (pid % group) / gsz;
+    if (g.b_strict_lower) {
+        // The K loop of a tile starts at its column offset: tile columns are dealt out whole, longest first, so that
+        // the long tiles do not start late and finish alone.
+        pid_n = bid / tiles_m;
+        pid_m = bid % tiles_m;
+    }
+    const int m0 = pid_m * BM, n0 = pid_n * BN;
+
+    const int z = blockIdx.y;
+    int kb = 0, ke = g.K;
+    if (g.splits > 1) {
+        kb = z * g.kchunk;
+        ke = kb + g.kchunk < g.K ? kb + g.kchunk : g.K;
+    }
+    if (g.b_strict_lower) {
+        const int lo = (n0 / BK) * BK;
+        kb = kb > lo ? kb : lo;
+    }
+
+    OperandView oa, ob;
+    const long bz = blockIdx.z;   // independent problem of a batched launch
+    oa.p = g.A + bz * g.batch_a; oa.ld = g.lda; oa.vec = avec;
+    oa.unit_lower_cols = g.a_unit_lower ? 0x7fffffff : 0;
+    if (TA) { oa.row_lim = ke; oa.col_lim = g.M; } else { oa.row_lim = g.M; oa.col_lim = ke; }
+    ob.p = g.B + bz * g.batch_b; ob.ld = g.ldb; ob.vec = bvec;
+    ob.unit_lower_cols = g.b_unit_lower_cols;
+    if (TB) { ob.row_lim = g.N; ob.col_lim = ke; } else { ob.row_lim = ke; ob.col_lim = g.N; }
+
+    f32x16 acc[WT][WT];
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    const int wm = (wave / WAVES_N) * 32 * WT, wn = (wave % WAVES_N) * 32 * WT;
+    const int lrow = lane & 31, lk = lane >> 5;
+
+    const int nk = ke > kb ? (ke - kb + BK - 1) / BK : 0;
+    // A tile whose operand rows and output block lie wholly inside the matrices, with aligned rows and out of reach
+    // of the unit-lower masks, takes loaders and an epilogue without bounds checks: the checks cost more instructions
+    // than the products of a short K loop.  Only a last K step that is cut short reads with checks.
+    const bool inner = avec && bvec && m0 + BM <= g.M && n0 + BN <= g.N &&
+                       (!g.a_unit_lower || (!TA && m0 >= ke)) && (g.b_unit_lower_cols == 0 || (TB && n0 >= ke));
+    float4 fa[BM * BK / 1024], fb[BN * BK / 1024];
+    auto fetch_both = [&](int k0) {
+        if (inner && k0 + BK <= ke) {
+            fetch_tile_inner<!TA, BM, BK>(oa.p, oa.ld, m0, k0, tid, fa);
+            fetch_tile_inner<TB, BN, BK>(ob.p, ob.ld, n0, k0, tid, fb);
+        } else {
+            fetch_tile<!TA, BM, BK>(oa, m0, k0, tid, fa);
+            fetch_tile<TB, BN, BK>(ob, n0, k0, tid, fb);
+        }
+    };
+    if (nk > 0) {
+        fetch_both(kb);
+        stash_tile<!TA, BM, BK>(As[0], tid, fa);
+        stash_tile<TB, BN, BK>(Bs[0], tid, fb);
+    }
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        const int cur = kt & 1;
+        if (kt + 1 < nk) fetch_both(kb + (kt + 1) * BK);
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 2) {
+            float a[WT], b[WT];
+#pragma unroll
+            for (int i = 0; i < WT; ++i) a[i] = As[cur][kk + lk][wm + i * 32 + lrow];
+#pragma unroll
+            for (int j = 0; j < WT; ++j) b[j] = Bs[cur][kk + lk][wn + j * 32 + lrow];
+#pragma unroll
+            for (int i = 0; i < WT; ++i)
+#pragma unroll
+                for (int j = 0; j < WT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+        if (kt + 1 < nk) {
+            stash_tile<!TA, BM, BK>(As[cur ^ 1], tid, fa);
+            stash_tile<TB, BN, BK>(Bs[cur ^ 1], tid, fb);
+        }
+        __syncthreads();
+    }
+
+    store_tile<WT>(g, bz, z, acc, m0, n0, wm, wn, lrow, lk, inner);
+}
+
+// ---- the same products on the bf16 matrix cores ------------------------------------------------------------------
+// Every fp32 operand element is split into three bf16 terms on its way from the staging registers to LDS,
+//   x = x1 + x2 + x3,  x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2)   (24 bits, both remainders exact in fp32),
+// and six of the nine products of terms, (3,1) (1,3) (2,2) (2,1) (1,2) (1,1), small ones first, go into one fp32
+// accumulator (each bf16 product is exact there; the three left out are below 2^-26 |a| |b|): accuracy of an fp32 product.
+// Bound: the fp32 matrix instructions deliver 157 TFLOP/s at most and held the kernel above at 105 to 128; six bf16 ones do
+// the same work in 3/8 of the time.  128 x 128 tiles, K step 32, four wavefronts of 64 x 64, ONE buffer of three planes
+// per operand (60 KB) with the next K step's operands in registers: two workgroups share a compute unit, one splits and
+// stores while the other multiplies.  A plane row holds 32 k (four 16-byte chunks) in 80 bytes, chunk c of row r stored
+// at place c ^ (r / 16 % 4): the 8-byte stores of a transposed operand, whose lanes lie four rows apart, hit every bank
+// twice at most, and eight consecutive rows are read without conflicts.
+constexpr int X3K = 32, X3LD = 40, X3PLANE = 128 * X3LD;   // K step; halfwords per row; per plane
+
+__device__ __forceinline__ void split3_pair(float a, float b, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {a, b};
+    p1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    const f32x2 r = {a - __builtin_bit_cast(float, p1 << 16), b - __builtin_bit_cast(float, p1 & 0xffff0000u)};
+    p2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+    const f32x2 t = {r[0] - __builtin_bit_cast(float, p2 << 16), r[1] - __builtin_bit_cast(float, p2 & 0xffff0000u)};
+    p3 = __builtin_bit_cast(uint32_t, __builtin_convertvector(t, bf16x2));
+}
+
+// four consecutive k of one row, at halfword offset `off` of a plane
+__device__ __forceinline__ void split3_store4(bf16_t* S, int off, float e0, float e1, float e2, float e3) {
+    uint2 q1, q2, q3;
+    split3_pair(e0, e1, q1.x, q2.x, q3.x);
+    split3_pair(e2, e3, q1.y, q2.y, q3.y);
+    *reinterpret_cast<uint2*>(S + off) = q1;
+    *reinterpret_cast<uint2*>(S + X3PLANE + off) = q2;
+    *reinterpret_cast<uint2*>(S + 2 * X3PLANE + off) = q3;
+}
+
+// A thread moves four float4 of a 128 x 32 operand tile.  KC (k contiguous): row tid / 8 + 32 i, k 4 (tid % 8).  Otherwise
+// the 4 x 4 block of k 4 (tid / 32) + i and rows 4 (tid % 32) .. + 3, transposed on the way to LDS.
+template <bool KC>
+__device__ __forceinline__ void x3_fetch(const OperandView& o, bool inner, int mn0, int k0, int tid, float4 (&q)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int sr = KC ? mn0 + (tid >> 3) + 32 * i : k0 + 4 * (tid >> 5) + i;
+        const int sc = KC ? k0 + 4 * (tid & 7) : mn0 + 4 * (tid & 31);
+        q[i] = inner ? *reinterpret_cast<const float4*>(o.p + (long)sr * o.ld + sc) : load4_guarded(o, sr, sc);
+    }
+}
+
+template <bool KC>
+__device__ __forceinline__ void x3_stash(bf16_t* S, int tid, const float4 (&q)[4]) {
+    if (KC) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = (tid >> 3) + 32 * i, c = (tid & 7) >> 1;
+            split3_store4(S, r * X3LD + ((c ^ ((r >> 4) & 3)) << 3) + ((tid & 1) << 2), q[i].x, q[i].y, q[i].z, q[i].w);
+        }
+    } else {
+        const int kb = tid >> 5, r = 4 * (tid & 31);
+        const int off = r * X3LD + (((kb >> 1) ^ ((r >> 4) & 3)) << 3) + ((kb & 1) << 2);
+        split3_store4(S, off, q[0].x, q[1].x, q[2].x, q[3].x);
+        split3_store4(S, off + X3LD, q[0].y, q[1].y, q[2].y, q[3].y);
+        split3_store4(S, off + 2 * X3LD, q[0].z, q[1].z, q[2].z, q[3].z);
+        split3_store4(S, off + 3 * X3LD, q[0].w, q[1].w, q[2].w, q[3].w);
+    }
+}
+
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec) {
+    __shared__ __attribute__((aligned(16))) bf16_t As[3 * X3PLANE];
+    __shared__ __attribute__((aligned(16))) bf16_t Bs[3 * X3PLANE];
+    constexpr int BM = 128, BN = 128;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+
+    // tile order as in the fp32 kernel
+    const int nt = tiles_m * tiles_n;
+    const int bid = blockIdx.x;
+    const int q8 = nt >> 3, r8 = nt & 7;
+    const int xcd = bid & 7;
+    const int pid = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
+    const int group = 8 * tiles_n;
+    const int gid = pid / group;
+    const int first_m = gid * 8;
+    const int gsz = (tiles_m - first_m) < 8 ? (tiles_m - first_m) : 8;
+    int pid_m = first_m + (pid % group) % gsz;
+    int pid_n = (pid % group) / gsz;
+    if (g.b_strict_lower) {
+        pid_n = bid / tiles_m;
+        pid_m = bid % tiles_m;
+    }
+    const int m0 = pid_m * BM, n0 = pid_n * BN;
+
+    const int z = blockIdx.y;
+    int kb = 0, ke = g.K;
+    if (g.splits > 1) {
+        kb = z * g.kchunk;
+        ke = kb + g.kchunk < g.K ? kb + g.kchunk : g.K;
+    }
+    if (g.b_strict_lower) kb = kb > n0 ? kb : n0;   // n0 is a multiple of the K step
+
+    OperandView oa, ob;
+    const long bz = blockIdx.z;
+    oa.p = g.A + bz * g.batch_a; oa.ld = g.lda; oa.vec = avec;
+    oa.unit_lower_cols = g.a_unit_lower ? 0x7fffffff : 0;
+    if (TA) { oa.row_lim = ke; oa.col_lim = g.M; } else { oa.row_lim = g.M; oa.col_lim = ke; }
+    ob.p = g.B + bz * g.batch_b; ob.ld = g.ldb; ob.vec = bvec;
+    ob.unit_lower_cols = g.b_unit_lower_cols;
+    if (TB) { ob.row_lim = g.N; ob.col_lim = ke; } else { ob.row_lim = ke; ob.col_lim = g.N; }
+
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    const int lrow = lane & 31, lk = lane >> 5;
+
+    const int nk = ke > kb ? (ke - kb + X3K - 1) / X3K : 0;
+    // each operand takes loads without checks where its tile lies inside it and out of reach of the masks
+    const bool ina = avec && m0 + BM <= g.M && (!g.a_unit_lower || (!TA && m0 >= ke));
+    const bool inb = bvec && n0 + BN <= g.N && (g.b_unit_lower_cols == 0 || (TB && n0 >= ke));
+    float4 fa[4], fb[4];
+    auto fetch_both = [&](int k0) {
+        const bool whole = k0 + X3K <= ke;
+        if (ina && inb && whole) {
+            x3_fetch<!TA>(oa, true, m0, k0, tid, fa);
+            x3_fetch<TB>(ob, true, n0, k0, tid, fb);
+        } else {
+            x3_fetch<!TA>(oa, false, m0, k0, tid, fa);
+            x3_fetch<TB>(ob, false, n0, k0, tid, fb);
+        }
+    };
+    if (nk > 0) fetch_both(kb);
+    for (int kt = 0; kt < nk; ++kt) {
+        x3_stash<!TA>(As, tid, fa);
+        x3_stash<TB>(Bs, tid, fb);
+        __syncthreads();
+        if (kt + 1 < nk) fetch_both(kb + (kt + 1) * X3K);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 a[2][3], b[2][3];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int ra = wm + i * 32 + lrow, rb = wn + i * 32 + lrow, ch = 2 * ks + lk;
+                const int offa = ra * X3LD + ((ch ^ ((ra >> 4) & 3)) << 3), offb = rb * X3LD + ((ch ^ ((rb >> 4) & 3)) << 3);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    a[i][p] = *reinterpret_cast<const bf16x8*>(As + p * X3PLANE + offa);
+                    b[i][p] = *reinterpret_cast<const bf16x8*>(Bs + p * X3PLANE + offb);
+                }
+            }
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][PA[t]], b[j][PB[t]], acc[i][j], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    store_tile<2>(g, bz, z, acc, m0, n0, wm, wn, lrow, lk, m0 + BM <= g.M && n0 + BN <= g.N);
+}
+
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int splits, long stride,
                                                             long ldp, int rows, int cols, float alpha, float beta,
                                                             float* __restrict__ out, long ldo) {
@@ -375,6 +552,19 @@ static hipError_t launch_gemm_f32_tile(const GemmF32& g, hipStream_t s) {
     return hipGetLastError();
 }
 
+static hipError_t launch_gemm_f32x3(const GemmF32& g, hipStream_t s) {
+    const int tiles_m = (g.M + 127) / 128, tiles_n = (g.N + 127) / 128;
+    const int avec = ((reinterpret_cast<uintptr_t>(g.A) & 15) == 0 && (g.lda & 3) == 0 && (g.batch_a & 3) == 0) ? 1 : 0;
+    const int bvec = ((reinterpret_cast<uintptr_t>(g.B) & 15) == 0 && (g.ldb & 3) == 0 && (g.batch_b & 3) == 0) ? 1 : 0;
+    dim3 grid(tiles_m * tiles_n, g.splits > 1 ? g.splits : 1, g.batch > 1 ? g.batch : 1);
+    dim3 block(256, 1, 1);
+    if (g.ta && g.tb) hipLaunchKernelGGL((gemm_f32x3_kernel<true, true>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
+    else if (g.ta) hipLaunchKernelGGL((gemm_f32x3_kernel<true, false>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
+    else if (g.tb) hipLaunchKernelGGL((gemm_f32x3_kernel<false, true>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
+    else hipLaunchKernelGGL((gemm_f32x3_kernel<false, false>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
+    return hipGetLastError();
+}
+
 // 1 = 64 x 256 tile, 2 = 256 x 64, 3 = 64 x 64 (many small workgroups), 0 = 128 x 128
 static int gemm_f32_config(int M, int N, int splits) {
     const long big_tiles = (long)((M + 127) / 128) * ((N + 127) / 128) * (splits > 1 ? splits : 1);
@@ -393,7 +583,9 @@ hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t s) {
         case 1: return launch_gemm_f32_tile<64, 256, 2, 16>(g, s);
         case 2: return launch_gemm_f32_tile<256, 64, 2, 16>(g, s);
         case 3: return launch_gemm_f32_tile<64, 64, 1, 32>(g, s);
-        default: return launch_gemm_f32_tile<128, 128, 2, 16>(g, s);
+        default:
+            // a caller that allows it gets the products of this tile size from split operands
+            return g.x3 ? launch_gemm_f32x3(g, s) : launch_gemm_f32_tile<128, 128, 2, 16>(g, s);
     }
 }
 

@@ -118,6 +118,44 @@ def test_gemm_f32_rank_update(ta, tb, M, N, K):
         c.close()
 
 
+# the 128 x 128 tile with operands split into three bf16 terms (DQ_OPT_SPLIT_GEMM = 2 asks dq_gemm_f32 for it): K below, at
+# and around its step of 32, edges of the tiles, magnitudes that spread over the reduction, both layouts
+@pytest.mark.parametrize("ta,tb", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(1280, 1281, 3), (1283, 1280, 32), (1280, 1409, 65), (1537, 1411, 257), (1280, 1280, 1)])
+def test_gemm_f32_split_operands(ta, tb, M, N, K):
+    g = rng(1700 + M + N + K + 2 * ta + tb)
+    spread = np.exp2(g.integers(-6, 7, size=K)).astype(np.float32)
+    A = (g.standard_normal((M, K)) * spread).astype(np.float32)
+    Bm = g.standard_normal((K, N)).astype(np.float32)
+    C0 = g.standard_normal((M, N)).astype(np.float32)
+    As, Bs = (A.T if ta else A), (Bm.T if tb else Bm)
+    bufs = []
+    for a in (As, Bs):
+        _, d = padded(a.shape[0], a.shape[1], -(-a.shape[1] // 4) * 4 + 4)
+        d.copy_(dev(np.ascontiguousarray(a)))
+        bufs.append(d)
+    Cbuf, Cd = padded(M, N, -(-N // 4) * 4 + 8, fill=123.0)
+    ref = C0 - A.astype(np.float64) @ Bm.astype(np.float64)
+    err = {}
+    c = B.Context(); c.ensure_workspace(1, 64, 64, B.DQ_F32)
+    try:
+        for mode in (0, 2):
+            c.dq_set_option(B.DQ_OPT_SPLIT_GEMM, mode)
+            Cd.copy_(dev(C0))
+            c.dq_gemm_f32(M, N, K, -1.0, bufs[0], ta, bufs[1], tb, 1.0, Cd)
+            got = Cd.cpu().numpy()
+            err[mode] = rel(got, ref)
+            assert torch.all(Cbuf[:, N:] == 123.0)
+        Cd.fill_(float("nan"))                      # beta == 0 must not read C
+        c.dq_gemm_f32(M, N, K, -1.0, bufs[0], ta, bufs[1], tb, 0.0, Cd)
+        assert np.isfinite(Cd.cpu().numpy()).all()
+    finally:
+        torch.cuda.synchronize()
+        c.close()
+    # the fp32 route's error is the bar; below 1e-7 both are the rounding of the result itself
+    assert err[2] < max(1.2 * err[0], 1e-7)
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (0, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(300, 200, 160), (130, 258, 40), (72, 136, 1000)])
 def test_gemm_bf16(ctx, ta, tb, M, N, K):
