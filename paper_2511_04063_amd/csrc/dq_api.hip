@@ -1030,6 +1030,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         g.A = R; g.lda = ldr; g.ta = 1;
         g.B = G; g.ldb = ldg; g.tb = 0;
         g.C = Bb; g.ldc = ld; g.M = n; g.N = n; g.K = n;
+        g.tail = at<float>(c, L.gsplit); g.tail_floats = (long)L.gsplit_floats;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
         DQ_HIP(product_f32(c, g, s));
     }
@@ -1187,6 +1188,7 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
         g.B = B_; g.ldb = ldb; g.tb = tb;
         g.C = C_; g.ldc = ldc; g.M = n; g.N = n; g.K = n;
         g.alpha = alpha; g.beta = beta_; g.alpha_dev = alpha_dev;
+        g.tail = at<float>(c, L.gsplit); g.tail_floats = (long)L.gsplit_floats;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
         DQ_HIP(product_f32(c, g, s));
         return DQ_OK;

@@ -52,6 +52,8 @@ struct GemmF32 {
     int b_strict_lower = 0;
     // split-K: z-th workgroup layer reduces k in [z*kchunk, (z+1)*kchunk) and writes C + z*split_stride
     int splits = 1; int kchunk = 0; long split_stride = 0;
+    // with x3: scratch for the parts of tiles that would leave most of the chip idle (null: none)
+    float* tail = nullptr; long tail_floats = 0;
     int x3 = 0;            // the 128 x 128 tile may form its products from operands split into three bf16 terms (finite values)
     int cfg = -1;          // tile configuration (-1: chosen from the shape; 3: 64 x 64 tiles, K step 32)
     // batch > 1: that many independent products in one launch; problem i reads A + i*batch_a, B + i*batch_b and

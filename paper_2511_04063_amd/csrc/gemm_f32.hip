@@ -318,6 +318,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, i
 // stores while the other multiplies.  A plane row holds 32 k (four 16-byte chunks) in 80 bytes, chunk c of row r stored
 // at place c ^ (r / 16 % 4): the 8-byte stores of a transposed operand, whose lanes lie four rows apart, hit every bank
 // twice at most, and eight consecutive rows are read without conflicts.
+constexpr int kX3Resident = 512;   // workgroups resident at a time: two on each of 256 compute units
 constexpr int X3K = 32, X3LD = 40, X3PLANE = 128 * X3LD;   // K step; halfwords per row; per plane
 
 __device__ __forceinline__ void split3_pair(float a, float b, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
@@ -372,7 +373,8 @@ __device__ __forceinline__ void x3_stash(bf16_t* S, int tid, const float4 (&q)[4
 }
 
 template <bool TA, bool TB>
-__global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec) {
+__global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec,
+                                                                 int whole, int parts, int pchunk) {
     __shared__ __attribute__((aligned(16))) bf16_t As[3 * X3PLANE];
     __shared__ __attribute__((aligned(16))) bf16_t Bs[3 * X3PLANE];
     constexpr int BM = 128, BN = 128;
@@ -381,12 +383,15 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
     const int lane = tid & 63;
     const int wave = tid >> 6;
 
-    // tile order as in the fp32 kernel
-    const int nt = tiles_m * tiles_n;
+    // tile order as in the fp32 kernel; behind the first `whole` tiles the others follow in parts of pchunk k, all tiles of
+    // one part side by side
     const int bid = blockIdx.x;
-    const int q8 = nt >> 3, r8 = nt & 7;
+    const int q8 = whole >> 3, r8 = whole & 7;
     const int xcd = bid & 7;
-    const int pid = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
+    int pid = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
+    const int rest = tiles_m * tiles_n - whole;
+    const bool in_parts = bid >= whole;
+    if (in_parts) pid = whole + (bid - whole) % rest;
     const int group = 8 * tiles_n;
     const int gid = pid / group;
     const int first_m = gid * 8;
@@ -404,6 +409,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
     if (g.splits > 1) {
         kb = z * g.kchunk;
         ke = kb + g.kchunk < g.K ? kb + g.kchunk : g.K;
+    }
+    if (in_parts) {
+        kb = (bid - whole) / rest * pchunk;
+        ke = kb + pchunk < g.K ? kb + pchunk : g.K;
     }
     if (g.b_strict_lower) kb = kb > n0 ? kb : n0;   // n0 is a multiple of the K step
 
@@ -472,7 +481,40 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
         }
         __syncthreads();
     }
+    if (in_parts) {
+        float* t = g.tail + (long)(bid - whole) * (BM * BN) + (wm + 4 * lk) * BN + wn + lrow;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) t[(i * 32 + 8 * (v >> 2) + (v & 3)) * BN + j * 32] = acc[i][j][v];
+        return;
+    }
     store_tile<2>(g, bz, z, acc, m0, n0, wm, wn, lrow, lk, m0 + BM <= g.M && n0 + BN <= g.N);
+}
+
+// C = alpha * (sum of the parts) + beta * C for the tiles that were multiplied in parts: a workgroup takes 8 rows of a tile
+__global__ __launch_bounds__(256) void x3_parts_kernel(GemmF32 g, int tiles_m, int tiles_n, int whole, int parts) {
+    const int rest = tiles_m * tiles_n - whole;
+    const int t = blockIdx.x >> 4, pid = whole + t;
+    const int group = 8 * tiles_n;
+    const int first_m = pid / group * 8;
+    const int gsz = (tiles_m - first_m) < 8 ? (tiles_m - first_m) : 8;
+    const int m0 = (first_m + (pid % group) % gsz) * 128, n0 = (pid % group) / gsz * 128;
+    const int r = 8 * (blockIdx.x & 15) + (threadIdx.x >> 5), c = 4 * (threadIdx.x & 31);
+    const float* p = g.tail + (long)t * (128 * 128) + r * 128 + c;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int z = 0; z < parts; ++z) {
+        const float4 v = *reinterpret_cast<const float4*>(p + (long)z * rest * (128 * 128));
+        s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
+    }
+    if (m0 + r >= g.M) return;
+    const float alpha = g.alpha_dev != nullptr ? g.alpha * *g.alpha_dev : g.alpha;
+    float* C = g.C + (long)(m0 + r) * g.ldc + n0 + c;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (n0 + c + e < g.N) C[e] = g.beta != 0.f ? alpha * s[e] + g.beta * C[e] : alpha * s[e];
 }
 
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int splits, long stride,
@@ -556,12 +598,34 @@ static hipError_t launch_gemm_f32x3(const GemmF32& g, hipStream_t s) {
     const int tiles_m = (g.M + 127) / 128, tiles_n = (g.N + 127) / 128;
     const int avec = ((reinterpret_cast<uintptr_t>(g.A) & 15) == 0 && (g.lda & 3) == 0 && (g.batch_a & 3) == 0) ? 1 : 0;
     const int bvec = ((reinterpret_cast<uintptr_t>(g.B) & 15) == 0 && (g.ldb & 3) == 0 && (g.batch_b & 3) == 0) ? 1 : 0;
-    dim3 grid(tiles_m * tiles_n, g.splits > 1 ? g.splits : 1, g.batch > 1 ? g.batch : 1);
+    // 512 workgroups run at a time.  The tiles of a last round that leaves half of them idle or more are cut along K into as many
+    // parts as there is room for (at least 256 k each: a part is written and read again, 128 KB per tile), summed by a
+    // second launch: 2890^3, 529 tiles, 497 us whole; the fewer than 512 tiles of a product up to 2816 wide are all cut.
+    const int tiles = tiles_m * tiles_n, rest = tiles % kX3Resident;
+    int parts = 1;
+    if (g.tail != nullptr && g.splits <= 1 && g.batch <= 1 && !g.b_strict_lower && g.K >= 768 && rest > 0) {
+        parts = kX3Resident / rest;
+        if (parts > g.K / 256) parts = g.K / 256;
+        const long room = g.tail_floats / ((long)rest * 128 * 128);
+        if (parts > room) parts = (int)room;
+    }
+    int whole = tiles, pchunk = 0;
+    if (parts > 1) {
+        whole = tiles - rest;
+        pchunk = ((g.K + parts - 1) / parts + X3K - 1) / X3K * X3K;
+        parts = (g.K + pchunk - 1) / pchunk;
+    }
+    dim3 grid(whole + (tiles - whole) * parts, g.splits > 1 ? g.splits : 1, g.batch > 1 ? g.batch : 1);
     dim3 block(256, 1, 1);
-    if (g.ta && g.tb) hipLaunchKernelGGL((gemm_f32x3_kernel<true, true>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
-    else if (g.ta) hipLaunchKernelGGL((gemm_f32x3_kernel<true, false>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
-    else if (g.tb) hipLaunchKernelGGL((gemm_f32x3_kernel<false, true>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
-    else hipLaunchKernelGGL((gemm_f32x3_kernel<false, false>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec);
+#define DQ_LAUNCH(TA, TB)                                                                                                \
+    hipLaunchKernelGGL((gemm_f32x3_kernel<TA, TB>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec, whole, parts, pchunk)
+    if (g.ta && g.tb) DQ_LAUNCH(true, true);
+    else if (g.ta) DQ_LAUNCH(true, false);
+    else if (g.tb) DQ_LAUNCH(false, true);
+    else DQ_LAUNCH(false, false);
+#undef DQ_LAUNCH
+    if (whole < tiles)
+        hipLaunchKernelGGL(x3_parts_kernel, dim3((tiles - whole) * 16), block, 0, s, g, tiles_m, tiles_n, whole, parts);
     return hipGetLastError();
 }
 
