@@ -1900,3 +1900,31 @@ def test_errors_have_no_effect(ctx):
     torch.cuda.synchronize()
     assert torch.all(R == 7.0)
     c2.close(); c3.close()
+
+
+@pytest.mark.parametrize("n", [515, 641, 1290])
+def test_qr_backward_left_over_columns(n):
+    """S6 where the order is no multiple of the solve's 512 columns (one whole block and a left-over of 3, of 129; two and 266),
+    the preparation on the second stream; at 1290 R^T G takes 121 tiles, all of them multiplied in parts."""
+    g = rng(5100 + n)
+    R, U = orc.qr_orth(g.standard_normal((n, n)))
+    U += np.eye(n) * 0.1 * np.sqrt(n)                # conditioned well enough for the bar to be about rounding alone
+    G = g.standard_normal((n, n))
+    R32, U32, G32 = (a.astype(np.float32) for a in (R, U, G))
+    ld = -(-n // 4) * 4
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 64, B.DQ_F32)
+        bufs = []
+        for a in (R32, U32, G32):
+            _, d = padded(n, n, ld)
+            d.copy_(dev(a))
+            bufs.append(d)
+        buf, dZd = padded(n, n, ld, fill=123.0)
+        c.dq_qr_backward(*bufs, dZd)
+        assert rel(dZd.cpu().numpy(), orc.qr_backward(R32, U32, G32)) < 1e-5
+        assert torch.all(buf[:, n:] == 123.0)
+        assert c.dq_device_flags() == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
