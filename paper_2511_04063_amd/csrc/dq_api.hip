@@ -991,14 +991,32 @@ dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R,
     return DQ_OK;
 }
 
+// The same on the second stream, beside S3 .. S5 of a fused step or R^T G of S6; the caller's stream waits for *joined before
+// the solve.  Where the products of S6 run on splits made beforehand (large n), the preparation is bandwidth that the products
+// beside it need and stays in line; below, it is a chain of up to eight short launches, 60 to 100 us, that leaves the chip
+// idle (steps at n = 256 459 -> 435 us, 1024 1463 -> 1393 us).  *joined stays null where it was left in line.
+dq_status qr_backward_prepare_early(dq_ctx* c, const Layout& L, int n, const float* R, long ldr, const float* U, long ldu,
+                                    hipEvent_t* joined) {
+    *joined = nullptr;
+    if (c->single_stream || backward_uses_splits(c, L, n)) return DQ_OK;
+    DQ_HIP(hipEventRecord(c->sync_ev[0], c->stream));
+    DQ_HIP(hipStreamWaitEvent(c->stream2, c->sync_ev[0], 0));
+    DQ_TRY(qr_backward_prepare(c, L, n, R, ldr, U, ldu, c->stream2));
+    DQ_HIP(hipEventRecord(c->sync_ev[1], c->stream2));
+    *joined = c->sync_ev[1];
+    return DQ_OK;
+}
+
 // dZ = R P U^{-T},  P = strict_lower(R^T G - G^T R).  The triangular solve M U^T = P runs right-looking over
 // column blocks from the last to the first; M is strictly lower triangular, so every product skips its zero part.
-// prepared: qr_backward_prepare has already run for this R and U on this stream (or the stream has waited for it).
+// joined: qr_backward_prepare has been enqueued for this R and U on another stream, this one waits for the event before the
+// solve; null: it is done here.
 dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, long ldr, const float* U, long ldu,
                           const float* G, long ldg, float* dZ, long lddz, float* Zupd, long ldz, float lr,
-                          bool prepared = false) {
+                          hipEvent_t joined = nullptr) {
     hipStream_t s = c->stream;
-    if (!prepared) DQ_TRY(qr_backward_prepare(c, L, n, R, ldr, U, ldu, s));
+    if (joined == nullptr) DQ_TRY(qr_backward_prepare_early(c, L, n, R, ldr, U, ldu, &joined));
+    if (joined == nullptr) DQ_TRY(qr_backward_prepare(c, L, n, R, ldr, U, ldu, s));
     float* Bb = at<float>(c, L.B);
     float* Pb = at<float>(c, L.P);
     float* Mb = at<float>(c, L.M);
@@ -1038,6 +1056,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 16.0 * n * (double)n);
         DQ_HIP(launch_skew_lower(Bb, ld, n, Pb, ld, Mb, ld, s));
     }
+    if (joined != nullptr) DQ_HIP(hipStreamWaitEvent(s, joined, 0));
     // What a multiple of kTrsmOuter leaves over, the last columns, is solved by blocks of kTrsmBlock (one by one over the
     // whole width such blocks took 0.43 ms at n = 2890), the rest by blocks of kTrsmOuter.
     const int nblk = (n + kTrsmBlock - 1) / kTrsmBlock;
@@ -1574,9 +1593,11 @@ dq_status dq_calib_step(dq_ctx* c, int b, int T, int n, const void* X, dq_dtype 
         float* Gi = at<float>(c, L.G);
         const void* Xi = static_cast<const char*>(X) + (size_t)i * T * ldx * esz;
         DQ_TRY(qr_orth_one(c, L, n, Zi, ldz, Ri, ldri, Ui, L.ld));
+        hipEvent_t joined = nullptr;
+        DQ_TRY(qr_backward_prepare_early(c, L, n, Ri, ldri, Ui, L.ld, &joined));
         DQ_TRY(rotate_loss_grad_one(c, L, T, n, Xi, xdt, ldx, Ri, ldri, red, loss_dev + i, Gi, L.ld,
                                     at<float>(c, L.Y), L.ld, at<char>(c, L.dY), L.ld, false));
-        DQ_TRY(qr_backward_one(c, L, n, Ri, ldri, Ui, L.ld, Gi, L.ld, nullptr, 0, Zi, ldz, lr));
+        DQ_TRY(qr_backward_one(c, L, n, Ri, ldri, Ui, L.ld, Gi, L.ld, nullptr, 0, Zi, ldz, lr, joined));
     }
     return DQ_OK;
 }
@@ -1926,9 +1947,11 @@ dq_status dq_calib_step_adam(dq_ctx* c, int b, int T, int n, const void* X, dq_d
         float* dZi = at<float>(c, L.B);   // B = R^T G is consumed before the last product writes dZ there
         const void* Xi = static_cast<const char*>(X) + (size_t)i * T * ldx * esz;
         DQ_TRY(qr_orth_one(c, L, n, Zi, ldz, Ri, ldri, Ui, L.ld));
+        hipEvent_t joined = nullptr;
+        DQ_TRY(qr_backward_prepare_early(c, L, n, Ri, ldri, Ui, L.ld, &joined));
         DQ_TRY(rotate_loss_grad_one(c, L, T, n, Xi, xdt, ldx, Ri, ldri, red, loss_dev + i, Gi, L.ld,
                                     at<float>(c, L.Y), L.ld, at<char>(c, L.dY), L.ld, false));
-        DQ_TRY(qr_backward_one(c, L, n, Ri, ldri, Ui, L.ld, Gi, L.ld, dZi, L.ld, nullptr, 0, 0.f));
+        DQ_TRY(qr_backward_one(c, L, n, Ri, ldri, Ui, L.ld, Gi, L.ld, dZi, L.ld, nullptr, 0, 0.f, joined));
         LaunchScope sc(&c->prof, c->stream, DQ_K_SMALL, 12.0 * n * (double)n, 28.0 * n * (double)n);
         DQ_HIP(launch_adam2d(Zi, ldz, dZi, L.ld, m + (long)i * n * ldm, ldm, v + (long)i * n * ldv, ldv, n, lr, beta1,
                              beta2, eps, c1, c2, c->stream));
