@@ -137,8 +137,8 @@ typedef enum {
                                        this, its panels' reflectors are applied one by one only to the 320 columns after the
                                        block's start; everything further right gets ONE update per block with the block's
                                        merged reflector (reduction length 256 instead of 64: a quarter of the passes over the
-                                       trailing matrix).  Needs DQ_OPT_DEVICE_SYNC's hand-over and n a multiple of 256.
-                                       0: never; -1 (default): 2048 rows in matrices of order 6144 or more, never below. */
+                                       trailing matrix).  Needs DQ_OPT_DEVICE_SYNC's hand-over.
+                                       0: never; -1 (default): 2048 rows in matrices of order 5120 or more, never below. */
 } dq_option;
 dq_status dq_set_option(dq_ctx* ctx, dq_option option, int value);
 

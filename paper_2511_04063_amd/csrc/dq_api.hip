@@ -522,8 +522,9 @@ constexpr long kSyncLimitUs = 5L * 1000 * 1000;   // a hand-over that takes this
 constexpr long kProbeLimitUs = 2000;
 constexpr int kFusedPanelRows = 8192;   // tallest panel that takes the one-launch route by default
 constexpr int kTwoLevelRows = 2048;     // blocks of 256 columns taller than this take the two-level route by default ...
-constexpr int kTwoLevelMinN = 6144;     // ... in matrices of at least this order (measured: 8192 27.7 -> 26.0 ms; 5120 and
-                                        // 4096, where the panel chain and not the rank-64 updates sets the pace: +-1 %, +3 %)
+constexpr int kTwoLevelMinN = 5120;     // ... in matrices of at least this order (QR measured with / without: 8192 19.2 / 22.6
+                                        // ms, 7168 14.4 / 16.4, 6144 10.6 / 11.5, 5120 7.73 / 8.06; at 4096, where the panel chain
+                                        // and not the updates sets the pace, 5.49 / 5.44)
 unsigned long long* sync_words(dq_ctx* c) { return reinterpret_cast<unsigned long long*>(c->ws + 128); }
 
 // Device-side hand-over needs the consumer's wait kernel and the producer's signal kernel to run at the same time.
@@ -630,8 +631,10 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
     const int ob = kAccumPanels * kPanel;
     const int two_rows = c->two_level_rows < 0 ? (n >= kTwoLevelMinN ? kTwoLevelRows : 0) : c->two_level_rows;
     int tl_blocks = 0;
-    if (dsync && !c->single_stream && two_rows > 0 && n % ob == 0 && c->chol_min_m > 0 && c->chol_min_m <= 4 * nb)
-        while ((tl_blocks + 1) * ob < n && n - tl_blocks * ob > two_rows) ++tl_blocks;
+    // (behind the last such block at least one more block's columns: its first panel then is a full one with a full look-ahead,
+    // the only kind that waits for the far-near update)
+    if (dsync && !c->single_stream && two_rows > 0 && c->chol_min_m > 0 && c->chol_min_m <= 4 * nb)
+        while ((tl_blocks + 2) * ob <= n && n - tl_blocks * ob > two_rows) ++tl_blocks;
     unsigned long long* wF = words + 11;    // far-near of block b done: seq0 + b + 1
     unsigned long long* wF2 = words + 12;   // far-rest of block b done
     unsigned long long* wF3 = words + 13;   // accumulation of block b done

@@ -1928,3 +1928,33 @@ def test_qr_backward_left_over_columns(n):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n", [770, 896, 1025, 1471])
+def test_qr_orth_two_level_ragged_order(n):
+    """Two-level blocking at orders that are no multiple of its 256 columns (2, 128, 1 and 191 columns left over): deferred
+    down to the last block that may be, within rounding of the one-level route, orthogonal, the same bits twice."""
+    g = rng(6400 + n)
+    Z = g.standard_normal((n, n)) + 2.0 * np.sqrt(n) * np.eye(n)      # well conditioned: both routes are rounding apart
+    ld = -(-n // 4) * 4
+    _, Zd = padded(n, n, ld)
+    Zd.copy_(dev(Z.astype(np.float32)))
+    out = {}
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 64, B.DQ_F32)
+        for rows in (0, 256, 256):
+            c.dq_set_option(B.DQ_OPT_TWO_LEVEL_ROWS, rows)
+            (_, Rd), (_, Ud) = padded(n, n, ld), padded(n, n, ld)
+            c.dq_qr_orth(Zd, Rd, Ud)
+            R, U = Rd.cpu().numpy(), Ud.cpu().numpy()
+            if rows in out:
+                assert np.array_equal(R, out[rows][0]) and np.array_equal(U, out[rows][1])
+            out[rows] = (R, U)
+            assert np.abs(R.T.astype(np.float64) @ R - np.eye(n)).max() < 1e-5
+            assert rel(R.astype(np.float64) @ U, Zd.cpu().numpy()) < 5e-6
+        assert rel(out[256][0], out[0][0]) < 1e-5 and rel(out[256][1], out[0][1]) < 1e-5
+        assert c.dq_device_flags() == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
