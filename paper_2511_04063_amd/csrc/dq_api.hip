@@ -1260,7 +1260,7 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
 // Every problem of the batch runs in the same launches.  The path's buffers (b matrices each, n rows of stride
 // kHeadDim) sit behind the general layout in the workspace.
 struct HeadsLayout {
-    size_t R = 0, U = 0, G = 0, B = 0, P = 0, M = 0, uinv = 0, gpart = 0, lpart = 0, total = 0;
+    size_t R = 0, U = 0, G = 0, dZ = 0, gpart = 0, lpart = 0, total = 0;
 };
 
 HeadsLayout make_heads_layout(size_t base, int b, int T) {
@@ -1271,10 +1271,7 @@ HeadsLayout make_heads_layout(size_t base, int b, int T) {
     H.R = bump(cur, mat);
     H.U = bump(cur, mat);
     H.G = bump(cur, mat);
-    H.B = bump(cur, mat);
-    H.P = bump(cur, mat);
-    H.M = bump(cur, mat);
-    H.uinv = bump(cur, mat);
+    H.dZ = bump(cur, mat);
     H.gpart = bump(cur, mat * sp);
     H.lpart = bump(cur, (size_t)(b > 0 ? b : 1) * sp * 8);
     H.total = cur;
@@ -1317,70 +1314,18 @@ dq_status heads_rotate_loss_grad(dq_ctx* c, const HeadsLayout& H, int b, int n, 
     return DQ_OK;
 }
 
-// inv(U_i) for every problem on the second stream, beside whatever the caller's stream does next: it depends on the
-// factorisation only, and the 64 workgroups that form it (a quarter of the device, 30 us) need not sit between the
-// gradient and the derivative through the QR.  The caller's stream must wait for sync_ev[1] before inv(U) is used.
-dq_status heads_uinv_early(dq_ctx* c, const HeadsLayout& H, int b, int n, const float* U, long ldu) {
-    DQ_HIP(hipEventRecord(c->sync_ev[0], c->stream));
-    DQ_HIP(hipStreamWaitEvent(c->stream2, c->sync_ev[0], 0));
-    {
-        LaunchScope sc(&c->prof, c->stream2, DQ_K_SMALL, 0.0, 8.0 * b * (double)n * n);
-        DQ_HIP(launch_trinv_blocks(U, ldu, n, at<float>(c, H.uinv), at<unsigned>(c, 0), c->stream2, b, (long)n * ldu,
-                                   (long)kTrsmBlock * kTrsmBlock));
-    }
-    DQ_HIP(hipEventRecord(c->sync_ev[1], c->stream2));
-    return DQ_OK;
-}
-
-// dZ_i = R_i P_i U_i^{-T} for every problem (or Z_i -= lr dZ_i when Zupd != null): the steps of qr_backward_one with
-// one block, as batched launches.  have_uinv: inv(U_i) is already in the workspace (heads_uinv_early).
-static_assert(kTrsmBlock >= kHeadDim, "one diagonal block of the triangular solve holds a whole small rotation");
-dq_status heads_backward(dq_ctx* c, const HeadsLayout& H, int b, int n, const float* R, long ldr, const float* U, long ldu,
-                         const float* G, long ldg, float* dZ, long lddz, float* Zupd, long ldz, float lr,
-                         bool have_uinv = false) {
-    const long ld = kHeadDim, nn = (long)n * ld;
-    const long sinv = (long)kTrsmBlock * kTrsmBlock;
+// dZ_i = R_i P_i U_i^{-T} for every problem (or Z_i -= lr dZ_i when Zupd != null): the steps of qr_backward_one in one
+// launch, a workgroup per problem.
+dq_status heads_backward(dq_ctx* c, int b, int n, const float* R, long ldr, const float* U, long ldu, const float* G, long ldg,
+                         float* dZ, long lddz, float* Zupd, long ldz, float lr) {
     if (b < 1) return DQ_OK;
-    hipStream_t s = c->stream;
-    unsigned* flags = at<unsigned>(c, 0);
-    float* Bb = at<float>(c, H.B);
-    float* Pb = at<float>(c, H.P);
-    float* Mb = at<float>(c, H.M);
-    float* uinv = at<float>(c, H.uinv);
-    const double n3 = (double)b * n * n * n;
-    {
-        GemmF32 g;   // B = R^T G
-        g.A = R; g.lda = ldr; g.ta = 1; g.batch_a = (long)n * ldr;
-        g.B = G; g.ldb = ldg; g.tb = 0; g.batch_b = (long)n * ldg;
-        g.C = Bb; g.ldc = ld; g.batch_c = nn;
-        g.M = n; g.N = n; g.K = n; g.batch = b;
-        LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(product_f32(c, g, s));
-    }
-    {
-        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 16.0 * b * (double)n * n);
-        DQ_HIP(launch_skew_lower(Bb, ld, n, Pb, ld, nullptr, 0, s, b, nn, nn, 0));
-        if (!have_uinv) DQ_HIP(launch_trinv_blocks(U, ldu, n, uinv, flags, s, b, (long)n * ldu, sinv));
-    }
-    {
-        GemmF32 g;   // M = P inv(U)^T
-        g.A = Pb; g.lda = ld; g.ta = 0; g.batch_a = nn;
-        g.B = uinv; g.ldb = kTrsmBlock; g.tb = 1; g.batch_b = sinv;
-        g.C = Mb; g.ldc = ld; g.batch_c = nn;
-        g.M = n; g.N = n; g.K = n; g.batch = b;
-        LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(product_f32(c, g, s));
-    }
-    {
-        GemmF32 g;   // dZ = R M  (or Z <- Z - lr R M)
-        g.A = R; g.lda = ldr; g.ta = 0; g.batch_a = (long)n * ldr;
-        g.B = Mb; g.ldb = ld; g.tb = 0; g.b_strict_lower = 1; g.batch_b = nn;
-        g.M = n; g.N = n; g.K = n; g.batch = b;
-        if (Zupd != nullptr) { g.C = Zupd; g.ldc = ldz; g.batch_c = (long)n * ldz; g.alpha = -lr; g.beta = 1.f; }
-        else { g.C = dZ; g.ldc = lddz; g.batch_c = (long)n * lddz; }
-        LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, n3, 0.0);
-        DQ_HIP(product_f32(c, g, s));
-    }
+    const bool update = Zupd != nullptr;
+    float* out = update ? Zupd : dZ;
+    const long ldo = update ? ldz : lddz;
+    LaunchScope sc(&c->prof, c->stream, DQ_K_GEMM_F32, 4.0 * b * (double)n * n * n, 0.0);
+    DQ_HIP(launch_heads_backward(b, n, R, ldr, (long)n * ldr, G, ldg, (long)n * ldg, U, ldu, (long)n * ldu,
+                                 update ? -lr : 1.f, update ? 1.f : 0.f, out, ldo, (long)n * ldo, at<unsigned>(c, 0),
+                                 c->stream));
     return DQ_OK;
 }
 
@@ -1395,8 +1340,6 @@ dq_status heads_step(dq_ctx* c, const Layout& L, int b, int T, int n, const void
     float* Uh = at<float>(c, H.U);
     float* Gh = at<float>(c, H.G);
     DQ_TRY(heads_qr(c, b, n, Z, ldz, Rh, ldrh, Uh, kHeadDim));
-    const bool early = !c->single_stream && b >= 1;
-    if (early) DQ_TRY(heads_uinv_early(c, H, b, n, Uh, kHeadDim));
     if (heads_fused_route(c, n, xdt)) {
         DQ_TRY(heads_rotate_loss_grad(c, H, b, n, T, X, ldx, Rh, ldrh, red, loss_dev, Gh, kHeadDim));
     } else {
@@ -1406,8 +1349,7 @@ dq_status heads_step(dq_ctx* c, const Layout& L, int b, int T, int n, const void
                                         Rh + (long)i * n * ldrh, ldrh, red, loss_dev + i, Gh + (long)i * n * kHeadDim,
                                         kHeadDim, at<float>(c, L.Y), L.ld, at<char>(c, L.dY), L.ld, false));
     }
-    if (early) DQ_HIP(hipStreamWaitEvent(c->stream, c->sync_ev[1], 0));
-    return heads_backward(c, H, b, n, Rh, ldrh, Uh, kHeadDim, Gh, kHeadDim, dZ, lddz, Zupd, ldz, lr, early);
+    return heads_backward(c, b, n, Rh, ldrh, Uh, kHeadDim, Gh, kHeadDim, dZ, lddz, Zupd, ldz, lr);
 }
 
 }  // namespace
@@ -1801,13 +1743,7 @@ dq_status dq_qr_backward(dq_ctx* c, int b, int n, const float* R, long ldr, cons
     if (heads_route(c, n)) {
         const int gb = heads_group(c, L.total, b, 1);
         if (gb < 1) return DQ_ERR_WORKSPACE;
-        const HeadsLayout H = make_heads_layout(L.total, gb, 1);
-        for (int i = 0; i < b; i += gb) {
-            const long r0 = (long)i * n;
-            DQ_TRY(heads_backward(c, H, b - i < gb ? b - i : gb, n, R + r0 * ldr, ldr, U + r0 * ldu, ldu, G + r0 * ldg, ldg,
-                                  dZ + r0 * lddz, lddz, nullptr, 0, 0.f));
-        }
-        return DQ_OK;
+        return heads_backward(c, b, n, R, ldr, U, ldu, G, ldg, dZ, lddz, nullptr, 0, 0.f);
     }
     for (int i = 0; i < b; ++i)
         DQ_TRY(qr_backward_one(c, L, n, R + (long)i * n * ldr, ldr, U + (long)i * n * ldu, ldu, G + (long)i * n * ldg,
@@ -1927,8 +1863,7 @@ dq_status dq_calib_step_adam(dq_ctx* c, int b, int T, int n, const void* X, dq_d
     if (heads_route(c, n)) {
         const int gb = heads_group(c, L.total, b, T);
         if (gb < 1) return DQ_ERR_WORKSPACE;
-        // B = R^T G is consumed before the last product writes dZ there
-        float* dZh = at<float>(c, make_heads_layout(L.total, gb, T).B);
+        float* dZh = at<float>(c, make_heads_layout(L.total, gb, T).dZ);
         for (int i = 0; i < b; i += gb) {
             const int g = b - i < gb ? b - i : gb;
             const long r0 = (long)i * n;

@@ -207,6 +207,11 @@ hipError_t launch_sign_normalise(const float* Afac, long lda, int n, float* R, l
 // R (orthogonal, diag(U) >= 0) and U (optional) of b latents; problem i at Z + i*sz etc. (element strides).
 hipError_t launch_heads_qr(int b, int n, const float* Z, long ldz, long sz, float* R, long ldr, long sr, float* U, long ldu,
                            long su, unsigned* flags, hipStream_t s);
+// out_i = alpha R_i M_i + beta out_i with M_i U_i^T = strict_lower(R_i^T G_i - G_i^T R_i); a zero on U_i's diagonal raises
+// DQ_FLAG_SINGULAR.  A problem is read whole before its result is written.
+hipError_t launch_heads_backward(int b, int n, const float* R, long ldr, long sr, const float* G, long ldg, long sg,
+                                 const float* U, long ldu, long su, float alpha, float beta, float* out, long ldo, long so,
+                                 unsigned* flags, hipStream_t s);
 // loss[i] = scale * sum exp(-|X_i R_i|) and G_i = X_i^T dY_i for bf16 X_i (T x n), fused.  Gpart needs
 // b * heads_splits(T) * 128 * 128 floats, lpart b * heads_splits(T) doubles.
 int heads_splits(int T);
@@ -225,12 +230,9 @@ hipError_t launch_gather_rows(const void* src, long src_stride_bytes, int rows_i
 
 // ---- backward pieces --------------------------------------------------------------
 // P = strict_lower(B - B^T); Mzero gets zeros everywhere (if non-null).
-// batch > 1: that many problems in one launch, problem i at the given element strides.
-hipError_t launch_skew_lower(const float* B, long ldb, int n, float* P, long ldp, float* Mzero, long ldm, hipStream_t s,
-                             int batch = 1, long stride_b = 0, long stride_p = 0, long stride_m = 0);
+hipError_t launch_skew_lower(const float* B, long ldb, int n, float* P, long ldp, float* Mzero, long ldm, hipStream_t s);
 // Inverse of every kTrsmBlock x kTrsmBlock diagonal block of the upper-triangular U: Uinv[blk] row-major, ld kTrsmBlock.
-hipError_t launch_trinv_blocks(const float* U, long ldu, int n, float* Uinv, unsigned* flags, hipStream_t s,
-                               int batch = 1, long stride_u = 0, long stride_inv = 0);
+hipError_t launch_trinv_blocks(const float* U, long ldu, int n, float* Uinv, unsigned* flags, hipStream_t s);
 hipError_t launch_axpy2d(float* Z, long ldz, const float* D, long ldd, int n, float a, hipStream_t s);
 // out (n / kTrsmOuter row-major blocks of kTrsmOuter x kTrsmOuter; n a multiple of kTrsmOuter) = the kTrsmBlock x kTrsmBlock
 // inverses of launch_trinv_blocks on the block diagonal, zero elsewhere

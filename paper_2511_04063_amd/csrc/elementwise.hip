@@ -399,14 +399,11 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const char* __restrict
     }
 }
 
-// P[i][j] = B[i][j] - B[j][i] for i > j, else 0.  Mzero (optional) is cleared.  blockIdx.z: problem of a batch.
+// P[i][j] = B[i][j] - B[j][i] for i > j, else 0.  Mzero (optional) is cleared.
 __global__ __launch_bounds__(256) void skew_lower_kernel(const float* __restrict__ B, long ldb, int n,
                                                          float* __restrict__ P, long ldp, float* __restrict__ Mz,
-                                                         long ldm, long sb, long sp, long sm) {
+                                                         long ldm) {
     __shared__ float tile[32][33];
-    B += (long)blockIdx.z * sb;
-    P += (long)blockIdx.z * sp;
-    if (Mz != nullptr) Mz += (long)blockIdx.z * sm;
     const int bx = blockIdx.x * 32, by = blockIdx.y * 32;   // output tile: rows by.., cols bx..
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const bool need = by + 31 > bx;   // some i > j in this tile
@@ -431,12 +428,8 @@ __global__ __launch_bounds__(256) void skew_lower_kernel(const float* __restrict
 
 // The same for n a multiple of 64 and 16-byte aligned rows everywhere: 64 x 64 tiles, 16-byte loads and stores.
 __global__ __launch_bounds__(256) void skew_lower64_kernel(const float* __restrict__ B, long ldb, float* __restrict__ P,
-                                                           long ldp, float* __restrict__ Mz, long ldm, long sb, long sp,
-                                                           long sm) {
+                                                           long ldp, float* __restrict__ Mz, long ldm) {
     __shared__ float tile[64][65];
-    B += (long)blockIdx.z * sb;
-    P += (long)blockIdx.z * sp;
-    if (Mz != nullptr) Mz += (long)blockIdx.z * sm;
     const int bx = blockIdx.x * 64, by = blockIdx.y * 64;   // output tile: rows by.., cols bx..
     const int tid = threadIdx.x;
     const bool need = by + 63 > bx;                          // some i > j in this tile
@@ -491,10 +484,7 @@ __device__ __forceinline__ void store_block64(const float* src, float* __restric
     }
 }
 __global__ __launch_bounds__(NTHR) void trinv_blocks_kernel(const float* __restrict__ U, long ldu, int n,
-                                                            float* __restrict__ Uinv, unsigned* flags, long su,
-                                                            long sinv) {
-    U += (long)blockIdx.y * su;       // problem of a batch
-    Uinv += (long)blockIdx.y * sinv;
+                                                            float* __restrict__ Uinv, unsigned* flags) {
     __shared__ float Bs[3 * B64 * LS];
     float* B0 = Bs;
     float* B1 = Bs + B64 * LS;
@@ -715,27 +705,21 @@ hipError_t launch_gather_rows(const void* src, long src_stride_bytes, int rows_i
 }
 
 hipError_t launch_skew_lower(const float* B, long ldb, int n, float* P, long ldp, float* Mzero, long ldm,
-                             hipStream_t s, int batch, long stride_b, long stride_p, long stride_m) {
+                             hipStream_t s) {
     const int tb = (n + 31) / 32;
-    if (batch < 1) return hipSuccess;
-    const bool al = n % 64 == 0 && ((ldb | ldp | stride_b | stride_p) & 3) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0 &&
+    const bool al = n % 64 == 0 && ((ldb | ldp) & 3) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0 &&
                     (reinterpret_cast<uintptr_t>(P) & 15) == 0 &&
-                    (Mzero == nullptr || (((ldm | stride_m) & 3) == 0 && (reinterpret_cast<uintptr_t>(Mzero) & 15) == 0));
+                    (Mzero == nullptr || ((ldm & 3) == 0 && (reinterpret_cast<uintptr_t>(Mzero) & 15) == 0));
     if (al)
-        hipLaunchKernelGGL(skew_lower64_kernel, dim3(n / 64, n / 64, batch), dim3(256), 0, s, B, ldb, P, ldp, Mzero, ldm,
-                           stride_b, stride_p, stride_m);
+        hipLaunchKernelGGL(skew_lower64_kernel, dim3(n / 64, n / 64), dim3(256), 0, s, B, ldb, P, ldp, Mzero, ldm);
     else
-        hipLaunchKernelGGL(skew_lower_kernel, dim3(tb, tb, batch), dim3(256), 0, s, B, ldb, n, P, ldp, Mzero, ldm,
-                           stride_b, stride_p, stride_m);
+        hipLaunchKernelGGL(skew_lower_kernel, dim3(tb, tb), dim3(256), 0, s, B, ldb, n, P, ldp, Mzero, ldm);
     return hipGetLastError();
 }
 
-hipError_t launch_trinv_blocks(const float* U, long ldu, int n, float* Uinv, unsigned* flags, hipStream_t s,
-                               int batch, long stride_u, long stride_inv) {
+hipError_t launch_trinv_blocks(const float* U, long ldu, int n, float* Uinv, unsigned* flags, hipStream_t s) {
     const int nb = (n + kTrsmBlock - 1) / kTrsmBlock;
-    if (batch < 1) return hipSuccess;
-    hipLaunchKernelGGL(trinv_blocks_kernel, dim3(nb, batch), dim3(NTHR), 0, s, U, ldu, n, Uinv, flags, stride_u,
-                       stride_inv);
+    hipLaunchKernelGGL(trinv_blocks_kernel, dim3(nb), dim3(NTHR), 0, s, U, ldu, n, Uinv, flags);
     return hipGetLastError();
 }
 

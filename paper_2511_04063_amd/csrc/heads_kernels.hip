@@ -55,13 +55,16 @@ __device__ __forceinline__ uint32_t to_bf16_rne(float f) {
 // zero above it.
 constexpr int QS = 4;                   // lanes per column / row
 constexpr int QB = 16;                  // rows per block = 4 groups, one per lane part
-constexpr int NG = HN / 4 / QS;         // 4-row groups held by a thread (of its column and of its row)
+// NG: 4-row groups held by a thread (of its column and of its row) = blocks of 16 rows carried, 4, 6 or 8: the rest of a
+// smaller matrix is zero (32 problems of order 80: 91 us with all 8 carried, 74 with 6).  Bound: the vector ALU and the
+// chain of dependent operations of a step, half and half; four workgroups per problem, each with all of A and a quarter
+// of Q's rows, took as long as one.
 
 __device__ __forceinline__ int item_column(int item) { return 8 * (item & 15) + (item >> 4); }
 __device__ __forceinline__ int column_item(int c) { return 16 * (c & 7) + (c >> 3); }
 
 // rows of this thread's k-th group: 4 * (k * QS + h) .. + 3
-template <int JB>
+template <int JB, int NG>
 __device__ __forceinline__ void publish_from(float* cb, const float (&x)[4 * NG], int h, int j) {
 #pragma unroll
     for (int k = JB; k < NG; ++k) {
@@ -76,7 +79,7 @@ __device__ __forceinline__ void publish_from(float* cb, const float (&x)[4 * NG]
 
 // x <- x - gamma (u . x) u for this thread's part of its column (if live) and of its row of Q, for block row JB = j / 16
 // of the pivot; u is the published column with u_0 = uj in place of the raw pivot.
-template <int JB>
+template <int JB, int NG>
 __device__ __forceinline__ void reflect_from(const float* cb, float (&xc)[4 * NG], float (&xq)[4 * NG], bool col_live,
                                              int h, int j, float uj, float gamma) {
     float4 u[NG - JB];
@@ -110,18 +113,19 @@ __device__ __forceinline__ void reflect_from(const float* cb, float (&xc)[4 * NG
 
 #define DQ_BLOCK_SWITCH(jb, CALL)                                                                  \
     switch (jb) {                                                                                  \
-        case 0: CALL(0); break;                                                                    \
-        case 1: CALL(1); break;                                                                    \
-        case 2: CALL(2); break;                                                                    \
-        case 3: CALL(3); break;                                                                    \
-        case 4: CALL(4); break;                                                                    \
-        case 5: CALL(5); break;                                                                    \
-        case 6: CALL(6); break;                                                                    \
-        default: CALL(7); break;                                                                   \
+        case 0: if constexpr (NG > 0) { CALL(0); } break;                                          \
+        case 1: if constexpr (NG > 1) { CALL(1); } break;                                          \
+        case 2: if constexpr (NG > 2) { CALL(2); } break;                                          \
+        case 3: if constexpr (NG > 3) { CALL(3); } break;                                          \
+        case 4: if constexpr (NG > 4) { CALL(4); } break;                                          \
+        case 5: if constexpr (NG > 5) { CALL(5); } break;                                          \
+        case 6: if constexpr (NG > 6) { CALL(6); } break;                                          \
+        case 7: if constexpr (NG > 7) { CALL(7); } break;                                          \
+        default: break;                                                                            \
     }
 
 // FULL: n == 128, nothing to guard.
-template <bool FULL>
+template <bool FULL, int NG>
 __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restrict__ Z, long ldz, long sz,
                                                            float* __restrict__ R, long ldr, long sr,
                                                            float* __restrict__ U, long ldu, long su, int n_,
@@ -143,7 +147,9 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
             xq[4 * k + e] = (i == item) ? 1.f : 0.f;
         }
     float mydiag = 0.f;
-    if (col == 0) publish_from<0>(cbuf[0], xc, h, 0);
+    if (tid < HN) { cbuf[0][tid] = 0.f; cbuf[1][tid] = 0.f; }   // what lies beyond the carried blocks reads as zero
+    __syncthreads();
+    if (col == 0) publish_from<0, NG>(cbuf[0], xc, h, 0);
     __syncthreads();
     for (int j = 0; j < n; ++j) {           // (rows and columns from n on are zero and stay zero)
         const float* cb = cbuf[j & 1];
@@ -164,7 +170,7 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
             beta = alpha >= 0.f ? -nrm : nrm;
             const float uj = alpha - beta;
             const float gamma = 2.f * __builtin_amdgcn_rcpf(s + uj * uj);
-#define DQ_CALL(JB) reflect_from<JB>(cb, xc, xq, col > j, h, j, uj, gamma)
+#define DQ_CALL(JB) reflect_from<JB, NG>(cb, xc, xq, col > j, h, j, uj, gamma)
             DQ_BLOCK_SWITCH(j / QB, DQ_CALL)
 #undef DQ_CALL
         }
@@ -172,7 +178,7 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
         if (tid == 0) sgn[j] = beta >= 0.f ? 1.f : -1.f;
         if (col == j + 1) {
             float* nb = cbuf[(j + 1) & 1];
-#define DQ_CALL(JB) publish_from<JB>(nb, xc, h, j + 1)
+#define DQ_CALL(JB) publish_from<JB, NG>(nb, xc, h, j + 1)
             DQ_BLOCK_SWITCH((j + 1) / QB, DQ_CALL)
 #undef DQ_CALL
         }
@@ -443,16 +449,184 @@ __global__ __launch_bounds__(256) void heads_reduce_kernel(const float* __restri
     }
 }
 
+// ------------------------------------------------------------------------------------------------ S6 (+ S7)
+// The derivative through the QR of one problem per workgroup, out = alpha R M + beta out with
+//   B = R^T G,  P = strict_lower(B - B^T),  M U^T = P
+// (alpha = 1, beta = 0: dZ;  alpha = -lr, beta = 1: the updated latent).  Everything between R, G, U and the result stays in
+// LDS.  64 problems of order 128: 38 us, 32 of order 80: 25 us.  Before: the inverse of U in a launch beside the gradient's, which held its compute units' registers (24 us alone, done
+// 20 us after it at 64 x 128), and four batched launches, 31 us, nearly all of it launches, gaps and trips through memory.
+// Bound: the fp32 matrix instructions of ONE compute unit (B 7 us at order 128, the triangular product, which skips its zero
+// blocks, 5 us) and the chain of the solve (four blocks of 32 columns from the right, about 1 us each).  16 wavefronts, one
+// 32 x 32 block each, dealt out so that every SIMD gets one of each block column (they differ in length).  LDS rows of 129
+// floats: a matrix is an operand along its rows and along its columns without bank conflicts.  P and M are held transposed.
+// Rows and columns from n on are zero (of U: the identity).
+constexpr int HBL = HN + 1, HIL = 33;
+
+__global__ __launch_bounds__(1024) void heads_backward_kernel(const float* R, long ldr, long sr, const float* G, long ldg,
+                                                              long sg, const float* U, long ldu, long su, int n, float alpha,
+                                                              float beta, float* out, long ldo, long so, unsigned* flags) {
+    __shared__ float Rs[HN * HBL];
+    __shared__ float Bs[HN * HBL];
+    __shared__ float Xs[4 * 32 * HIL];      // inverses of the 32 x 32 diagonal blocks of U
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, lk = lane >> 5;
+    const int wi = wave >> 2, wj = (wave + wi) & 3;
+    R += (long)blockIdx.x * sr;
+    G += (long)blockIdx.x * sg;
+    U += (long)blockIdx.x * su;
+    out += (long)blockIdx.x * so;
+    const int nb = (n + 31) >> 5;           // blocks of 32 that hold anything
+    {
+        float r[16], g[16], u[4];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int e = tid + 1024 * q, i = e >> 7, c = e & 127;
+            const bool in = i < n && c < n;
+            r[q] = in ? R[(long)i * ldr + c] : 0.f;
+            g[q] = in ? G[(long)i * ldg + c] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {       // diagonal block q of U, entry (tid / 32, tid % 32)
+            const int i = 32 * q + (tid >> 5), c = 32 * q + (tid & 31);
+            u[q] = (i < n && c < n) ? U[(long)i * ldu + c] : (i == c ? 1.f : 0.f);
+            if (i == c && u[q] == 0.f) atomicOr(flags, DQ_FLAG_SINGULAR);
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int e = tid + 1024 * q, i = e >> 7, c = e & 127;
+            Rs[i * HBL + c] = r[q];
+            Bs[i * HBL + c] = g[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Xs[(32 * q + (tid >> 5)) * HIL + (tid & 31)] = u[q];
+    }
+    const bool live = wi < nb && wj < nb;
+    const int r0 = 32 * wi + 4 * lk, cc = 32 * wj + lrow;   // accumulator v: row r0 + 8 (v / 4) + v % 4, column cc
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    __syncthreads();
+    if (wave < nb) {
+        // one wavefront per diagonal block: lane c solves U x = e_c from the last row up (the upper lanes repeat the lower ones)
+        float* X = Xs + 32 * wave * HIL;
+        float x[32];
+#pragma unroll
+        for (int i = 31; i >= 0; --i) {
+            float t0 = i == lrow ? 1.f : 0.f, t1 = 0.f;
+#pragma unroll
+            for (int k = i + 1; k < 32; ++k) {
+                if (k & 1) t1 -= X[i * HIL + k] * x[k];
+                else t0 -= X[i * HIL + k] * x[k];
+            }
+            x[i] = (t0 + t1) / X[i * HIL + i];
+        }
+#pragma unroll
+        for (int i = 0; i < 32; ++i) X[i * HIL + lrow] = x[i];   // (zero below the diagonal by itself)
+    }
+    if (live) {                         // B = R^T G
+        for (int k0 = 0; k0 < 32 * nb; k0 += 32)
+#pragma unroll
+            for (int k = k0; k < k0 + 32; k += 2)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Rs[(k + lk) * HBL + 32 * wi + lrow], Bs[(k + lk) * HBL + cc], acc, 0, 0, 0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 16; ++v) Bs[(r0 + 8 * (v >> 2) + (v & 3)) * HBL + cc] = acc[v];
+    __syncthreads();
+    // P^T (k, i) = B(i, k) - B(k, i) for i > k, zero elsewhere
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int k = r0 + 8 * (v >> 2) + (v & 3);
+        acc[v] = cc > k ? Bs[cc * HBL + k] - acc[v] : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 16; ++v) Bs[(r0 + 8 * (v >> 2) + (v & 3)) * HBL + cc] = acc[v];
+    // M by block columns J from the right (block rows of M^T):  M^T_J = inv(U_JJ) P^T_J,  P^T_K -= U_KJ M^T_J for K < J; both
+    // only for the rows i >= 32 J of M, the columns right of there in M^T
+    for (int J = nb - 1; J >= 0; --J) {
+        const int cols = nb - J;            // blocks of i
+        const int K = wave / cols, ib = J + wave % cols;
+        const bool upd = K < J;
+        // the block U_KJ of this wavefront's update: row 32 K + lrow, k = 8 q + 4 lk + 0 .. 3 in step q
+        float u[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int c = 32 * J + 8 * q + 4 * lk + e;
+                u[4 * q + e] = (upd && c < n) ? U[(long)(32 * K + lrow) * ldu + c] : 0.f;
+            }
+        __syncthreads();
+        if (wave < cols) {
+            const int i0 = 32 * (J + wave) + lrow;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+            for (int k = 0; k < 32; k += 2)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Xs[(32 * J + lrow) * HIL + k + lk], Bs[(32 * J + k + lk) * HBL + i0], acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) Bs[(32 * J + 8 * (v >> 2) + 4 * lk + (v & 3)) * HBL + i0] = acc[v];   // own columns only
+        }
+        __syncthreads();
+        if (upd) {
+            const int i0 = 32 * ib + lrow;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u[4 * q + e], Bs[(32 * J + 8 * q + 4 * lk + e) * HBL + i0], acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) Bs[(32 * K + 8 * (v >> 2) + 4 * lk + (v & 3)) * HBL + i0] -= acc[v];
+        }
+    }
+    __syncthreads();
+    if (!live) return;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int k0 = 32 * wj; k0 < 32 * nb; k0 += 32)      // R M; M is strictly lower triangular
+#pragma unroll
+        for (int k = k0; k < k0 + 32; k += 2)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Rs[(32 * wi + lrow) * HBL + k + lk], Bs[cc * HBL + k + lk], acc, 0, 0, 0);
+    if (cc >= n) return;
+    float* o = out + (long)r0 * ldo + cc;
+    float old[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int r = 8 * (v >> 2) + (v & 3);
+        old[v] = (beta != 0.f && r0 + r < n) ? o[(long)r * ldo] : 0.f;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int r = 8 * (v >> 2) + (v & 3);
+        if (r0 + r < n) o[(long)r * ldo] = beta != 0.f ? alpha * acc[v] + beta * old[v] : alpha * acc[v];
+    }
+}
+
 }  // namespace
 
 hipError_t launch_heads_qr(int b, int n, const float* Z, long ldz, long sz, float* R, long ldr, long sr, float* U, long ldu,
                            long su, unsigned* flags, hipStream_t s) {
     if (b < 1) return hipSuccess;
     if (n < 1 || n > HN) return hipErrorInvalidValue;
-    if (n == HN)
-        hipLaunchKernelGGL(heads_qr_kernel<true>, dim3(b), dim3(HN * QS), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, n, flags);
-    else
-        hipLaunchKernelGGL(heads_qr_kernel<false>, dim3(b), dim3(HN * QS), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, n, flags);
+#define DQ_LAUNCH(FULL, NG)                                                                                              \
+    hipLaunchKernelGGL((heads_qr_kernel<FULL, NG>), dim3(b), dim3(HN * QS), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, n, flags)
+    if (n == HN) DQ_LAUNCH(true, 8);
+    else if (n > 96) DQ_LAUNCH(false, 8);
+    else if (n > 64) DQ_LAUNCH(false, 6);
+    else DQ_LAUNCH(false, 4);
+#undef DQ_LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_heads_backward(int b, int n, const float* R, long ldr, long sr, const float* G, long ldg, long sg,
+                                 const float* U, long ldu, long su, float alpha, float beta, float* out, long ldo, long so,
+                                 unsigned* flags, hipStream_t s) {
+    if (b < 1) return hipSuccess;
+    if (n < 1 || n > HN) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(heads_backward_kernel, dim3(b), dim3(1024), 0, s, R, ldr, sr, G, ldg, sg, U, ldu, su, n, alpha, beta,
+                       out, ldo, so, flags);
     return hipGetLastError();
 }
 

@@ -1958,3 +1958,49 @@ def test_qr_orth_two_level_ragged_order(n):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n", [1, 17, 32, 64, 65, 96, 97, 127, 128])
+def test_heads_qr_and_backward_orders(n):
+    """The batched factorisation and derivative at the edges of the blocks of 16 rows carried (64, 96) and of the 32 x 32
+    blocks of the derivative: the same bits alone and in a batch, the derivative against the oracle, also written over G."""
+    g = rng(9300 + n)
+    b = 65
+    Z = g.standard_normal((b, n, n)).astype(np.float32)
+    G = g.standard_normal((b, n, n)).astype(np.float32)
+    ld = -(-n // 4) * 4
+    def batch(a):
+        m = torch.full((a.shape[0], n, ld), 7.0, device="cuda")
+        m[..., :n] = dev(a)
+        return m, m[..., :n]
+    c = B.Context()
+    try:
+        c.ensure_workspace(b, n, 64, B.DQ_F32)
+        _, Zd = batch(Z)
+        Rb, Rd = batch(0 * Z)
+        Ub, Ud = batch(0 * Z)
+        c.dq_qr_orth(Zd, Rd, Ud)
+        R1b, R1 = batch(0 * Z)
+        U1b, U1 = batch(0 * Z)
+        c.dq_qr_orth(Zd[:3], R1[:3], U1[:3])
+        c.dq_qr_orth(Zd[3:4], R1[3:4], U1[3:4])
+        assert torch.equal(R1[:4], Rd[:4]) and torch.equal(U1[:4], Ud[:4])
+        for buf in (Rb, Ub, R1b, U1b):
+            assert torch.all(buf[..., n:] == 7.0)
+        Gb, Gd = batch(G)
+        dZb, dZd = batch(0 * Z)
+        c.dq_qr_backward(Rd, Ud, Gd, dZd)
+        got = dZd.cpu().numpy()
+        R, U = Rd.cpu().numpy().astype(np.float64), Ud.cpu().numpy().astype(np.float64)
+        for i in (0, 1, 31, 64):
+            # products of 2^-24 accuracy over three steps, magnified by inv(U)
+            ref = orc.qr_backward(R[i], U[i], G[i].astype(np.float64))
+            bar = 3e-6 * np.sqrt(n) * np.linalg.norm(G[i]) * np.linalg.norm(np.linalg.inv(U[i]), 2)
+            assert np.linalg.norm(got[i] - ref) <= max(bar, 1e-6 * np.linalg.norm(ref))
+        assert torch.all(dZb[..., n:] == 7.0)
+        c.dq_qr_backward(Rd, Ud, Gd, Gd)
+        assert torch.equal(Gd, dZd) and torch.all(Gb[..., n:] == 7.0)
+        assert c.dq_device_flags() & ~B.DQ_FLAG_ILLCOND_PANEL == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
