@@ -9,17 +9,15 @@
 namespace dq {
 namespace {
 
-// M <- beta M - G  (Alg. 3, momentum update)
+// M <- beta M - G  (Alg. 3, momentum update).  This pass and the sums below move three matrices and are bound by memory: at n =
+// 4096 63 us before, with a division per piece and 4-byte accesses.
 __global__ __launch_bounds__(256) void cayley_momentum_kernel(float* __restrict__ M, long ldm, const float* __restrict__ G,
                                                              long ldg, int n, float beta) {
-    const int q = (n + 3) >> 2;
-    const long total = (long)n * q;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long)gridDim.x * 256) {
-        const int r = (int)(e / q), c0 = (int)(e % q) << 2;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (c0 + j < n) M[(long)r * ldm + c0 + j] = beta * M[(long)r * ldm + c0 + j] - G[(long)r * ldg + c0 + j];
-    }
+    for_quads(n, n, [&](long r, int c, int left) {
+        const float4 m = load_quad(M + r * ldm + c, left), g = load_quad(G + r * ldg + c, left);
+        store_quad(M + r * ldm + c, left,
+                   make_float4(beta * m.x - g.x, beta * m.y - g.y, beta * m.z - g.z, beta * m.w - g.w));
+    });
 }
 
 // W = What - What^T (Alg. 3, skew-symmetrisation) on 32 x 32 tiles: tile (bi, bj) and its mirror are both read row-wise (coalesced)
@@ -53,14 +51,20 @@ __global__ __launch_bounds__(256) void cayley_skew_kernel(const float* __restric
 }
 
 // alpha = min(lr, 2 q / (||W||_F + eps))  (Alg. 3, step-size rule); out[0] = alpha, out[1] = alpha / 2
-__global__ __launch_bounds__(256) void cayley_alpha_kernel(const double* __restrict__ partials, int count, float lr, float q,
+__global__ __launch_bounds__(1024) void cayley_alpha_kernel(const double* __restrict__ partials, int count, float lr, float q,
                                                           float eps, float* __restrict__ out) {
-    __shared__ double sh[256];
-    double t = 0.0;
-    for (int i = threadIdx.x; i < count; i += 256) t += partials[i];
-    sh[threadIdx.x] = t;
+    // one workgroup, a chain of loads: four in flight per thread (16384 partials at n = 4096: 18 us with 256 threads and one, 5 now)
+    __shared__ double sh[1024];
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    int i = threadIdx.x;
+    for (; i + 3 * 1024 < count; i += 4 * 1024) {
+        const double a = partials[i], b = partials[i + 1024], c = partials[i + 2048], d = partials[i + 3072];
+        t[0] += a; t[1] += b; t[2] += c; t[3] += d;
+    }
+    for (; i < count; i += 1024) t[0] += partials[i];
+    sh[threadIdx.x] = (t[0] + t[1]) + (t[2] + t[3]);
     __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
+    for (int o = 512; o >= 1; o >>= 1) {
         if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }
@@ -77,26 +81,16 @@ __global__ __launch_bounds__(256) void cayley_alpha_kernel(const double* __restr
 __global__ __launch_bounds__(256) void add_scaled_kernel(float* out, long ldo, const float* A, long lda, const float* B,
                                                         long ldb, int n, float scale_host, const float* __restrict__ scale_dev) {
     const float sc = scale_dev != nullptr ? scale_host * *scale_dev : scale_host;
-    const int q = (n + 3) >> 2;
-    const long total = (long)n * q;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long)gridDim.x * 256) {
-        const int r = (int)(e / q), c0 = (int)(e % q) << 2;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (c0 + j < n) out[(long)r * ldo + c0 + j] = A[(long)r * lda + c0 + j] + sc * B[(long)r * ldb + c0 + j];
-    }
-}
-
-unsigned elementwise_grid(int n) {
-    long b = ((long)n * ((n + 3) / 4) + 255) / 256;
-    if (b > 8192) b = 8192;
-    return (unsigned)(b < 1 ? 1 : b);
+    for_quads(n, n, [&](long r, int c, int left) {
+        const float4 x = load_quad(A + r * lda + c, left), y = load_quad(B + r * ldb + c, left);
+        store_quad(out + r * ldo + c, left, make_float4(x.x + sc * y.x, x.y + sc * y.y, x.z + sc * y.z, x.w + sc * y.w));
+    });
 }
 
 }  // namespace
 
 hipError_t launch_cayley_momentum(float* M, long ldm, const float* G, long ldg, int n, float beta, hipStream_t s) {
-    hipLaunchKernelGGL(cayley_momentum_kernel, dim3(elementwise_grid(n)), dim3(256), 0, s, M, ldm, G, ldg, n, beta);
+    hipLaunchKernelGGL(cayley_momentum_kernel, quad_grid(n, n), dim3(256), 0, s, M, ldm, G, ldg, n, beta);
     return hipGetLastError();
 }
 
@@ -112,13 +106,13 @@ hipError_t launch_cayley_skew(const float* What, long ldh, int n, float* W, long
 
 hipError_t launch_cayley_alpha(const double* partials, int count, float lr, float q, float eps, float* alpha_dev,
                                hipStream_t s) {
-    hipLaunchKernelGGL(cayley_alpha_kernel, dim3(1), dim3(256), 0, s, partials, count, lr, q, eps, alpha_dev);
+    hipLaunchKernelGGL(cayley_alpha_kernel, dim3(1), dim3(1024), 0, s, partials, count, lr, q, eps, alpha_dev);
     return hipGetLastError();
 }
 
 hipError_t launch_add_scaled(float* out, long ldo, const float* A, long lda, const float* B, long ldb, int n,
                              float scale_host, const float* scale_dev, hipStream_t s) {
-    hipLaunchKernelGGL(add_scaled_kernel, dim3(elementwise_grid(n)), dim3(256), 0, s, out, ldo, A, lda, B, ldb, n,
+    hipLaunchKernelGGL(add_scaled_kernel, quad_grid(n, n), dim3(256), 0, s, out, ldo, A, lda, B, ldb, n,
                        scale_host, scale_dev);
     return hipGetLastError();
 }

@@ -33,6 +33,34 @@ struct LaunchScope {
     Profiler* prof; hipStream_t stream; int klass; int slot;
 };
 
+// ---- elementwise passes over matrices with 16-byte aligned rows ---------------------
+// A thread takes pieces of four columns, one row of every 4 gridDim.y, launched as quad_grid() workgroups of 256; a piece
+// that the last column cuts short is read and written element by element.
+inline dim3 quad_grid(int rows, int n) {
+    const int gy = (rows + 3) / 4;
+    return dim3((unsigned)((n + 255) / 256), (unsigned)(gy < 2048 ? gy : 2048));
+}
+__device__ __forceinline__ float4 load_quad(const float* p, int left) {
+    if (left >= 4) return *reinterpret_cast<const float4*>(p);
+    return make_float4(p[0], left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, 0.f);
+}
+__device__ __forceinline__ void store_quad(float* p, int left, float4 v) {
+    if (left >= 4) {
+        *reinterpret_cast<float4*>(p) = v;
+        return;
+    }
+    p[0] = v.x;
+    if (left > 1) p[1] = v.y;
+    if (left > 2) p[2] = v.z;
+}
+// body(r, c, left): the piece of row r that starts at column c, `left` columns from the end
+template <class F>
+__device__ __forceinline__ void for_quads(int rows, int n, F body) {
+    const int c = (int)(blockIdx.x * 64 + (threadIdx.x & 63)) * 4;
+    if (c >= n) return;
+    for (int r = (int)(blockIdx.y * 4 + (threadIdx.x >> 6)); r < rows; r += (int)gridDim.y * 4) body((long)r, c, n - c);
+}
+
 // ---- fp32 matrix-core GEMM --------------------------------------------------------
 struct GemmF32 {
     const float* A = nullptr; long lda = 0;

@@ -536,11 +536,10 @@ __global__ __launch_bounds__(256) void place_diag_blocks_kernel(const float* __r
 
 __global__ __launch_bounds__(256) void axpy2d_kernel(float* __restrict__ Z, long ldz, const float* __restrict__ D,
                                                      long ldd, int n, float a) {
-    const long total = (long)n * n;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long)gridDim.x * 256) {
-        const int r = (int)(e / n), c = (int)(e % n);
-        Z[(long)r * ldz + c] += a * D[(long)r * ldd + c];
-    }
+    for_quads(n, n, [&](long r, int c, int left) {
+        const float4 z = load_quad(Z + r * ldz + c, left), d = load_quad(D + r * ldd + c, left);
+        store_quad(Z + r * ldz + c, left, make_float4(z.x + a * d.x, z.y + a * d.y, z.z + a * d.z, z.w + a * d.w));
+    });
 }
 
 // Adam (bias-corrected) and heavy-ball momentum on the latent: HBM-bound elementwise passes over n x n matrices
@@ -550,35 +549,35 @@ __global__ __launch_bounds__(256) void adam2d_kernel(float* __restrict__ Z, long
                                                      float* __restrict__ m, long ldm, float* __restrict__ v, long ldv, int rows,
                                                      int n, float lr, float beta1, float beta2, float omb1, float omb2, float eps, float c1,
                                                      float c2) {
-    const int q = (n + 3) >> 2;
-    const long total = (long)rows * q;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long)gridDim.x * 256) {
-        const int r = (int)(e / q), c0 = (int)(e % q) << 2;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = c0 + j;
-            if (c < n) {
-                const float g = D[(long)r * ldd + c];
-                const float mn = beta1 * m[(long)r * ldm + c] + omb1 * g;
-                const float vn = beta2 * v[(long)r * ldv + c] + omb2 * g * g;
-                m[(long)r * ldm + c] = mn;
-                v[(long)r * ldv + c] = vn;
-                Z[(long)r * ldz + c] -= lr * (mn * c1) / (sqrtf(vn * c2) + eps);
-            }
-        }
-    }
+    for_quads(rows, n, [&](long r, int c, int left) {
+        const float4 g4 = load_quad(D + r * ldd + c, left);
+        float4 z4 = load_quad(Z + r * ldz + c, left), m4 = load_quad(m + r * ldm + c, left), v4 = load_quad(v + r * ldv + c, left);
+        auto one = [&](float g, float& z, float& mo, float& vo) {
+            mo = beta1 * mo + omb1 * g;
+            vo = beta2 * vo + omb2 * g * g;
+            z -= lr * (mo * c1) / (sqrtf(vo * c2) + eps);
+        };
+        one(g4.x, z4.x, m4.x, v4.x);
+        one(g4.y, z4.y, m4.y, v4.y);
+        one(g4.z, z4.z, m4.z, v4.z);
+        one(g4.w, z4.w, m4.w, v4.w);
+        store_quad(m + r * ldm + c, left, m4);
+        store_quad(v + r * ldv + c, left, v4);
+        store_quad(Z + r * ldz + c, left, z4);
+    });
 }
 
 __global__ __launch_bounds__(256) void momentum2d_kernel(float* __restrict__ Z, long ldz, const float* __restrict__ D,
                                                          long ldd, float* __restrict__ buf, long ldb, int n, float lr,
                                                          float mu) {
-    const long total = (long)n * n;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long)gridDim.x * 256) {
-        const int r = (int)(e / n), c = (int)(e % n);
-        const float bn = mu * buf[(long)r * ldb + c] + D[(long)r * ldd + c];
-        buf[(long)r * ldb + c] = bn;
-        Z[(long)r * ldz + c] -= lr * bn;
-    }
+    for_quads(n, n, [&](long r, int c, int left) {
+        const float4 d = load_quad(D + r * ldd + c, left);
+        float4 b = load_quad(buf + r * ldb + c, left), z = load_quad(Z + r * ldz + c, left);
+        b = make_float4(mu * b.x + d.x, mu * b.y + d.y, mu * b.z + d.z, mu * b.w + d.w);
+        z = make_float4(z.x - lr * b.x, z.y - lr * b.y, z.z - lr * b.z, z.w - lr * b.w);
+        store_quad(buf + r * ldb + c, left, b);
+        store_quad(Z + r * ldz + c, left, z);
+    });
 }
 
 // ------------------------------------------------------------------------------------------------ stream hand-over
@@ -736,26 +735,20 @@ hipError_t launch_adam2d(float* Z, long ldz, const float* D, long ldd, float* m,
     if (rows < 0) rows = n;
     // 1 - beta in double: in fp32 the difference 1 - 0.999 alone is off by 6e-5 relative
     const float omb1 = (float)(1.0 - (double)beta1), omb2 = (float)(1.0 - (double)beta2);
-    long b = ((long)rows * ((n + 3) / 4) + 255) / 256;
-    if (b > 8192) b = 8192;
-    if (b < 1) return hipSuccess;
-    hipLaunchKernelGGL(adam2d_kernel, dim3((unsigned)b), dim3(256), 0, s, Z, ldz, D, ldd, m, ldm, v, ldv, rows, n, lr, beta1,
+    if (rows < 1) return hipSuccess;
+    hipLaunchKernelGGL(adam2d_kernel, quad_grid(rows, n), dim3(256), 0, s, Z, ldz, D, ldd, m, ldm, v, ldv, rows, n, lr, beta1,
                        beta2, omb1, omb2, eps, c1, c2);
     return hipGetLastError();
 }
 
 hipError_t launch_momentum2d(float* Z, long ldz, const float* D, long ldd, float* buf, long ldb, int n, float lr,
                              float mu, hipStream_t s) {
-    long b = ((long)n * n + 255) / 256;
-    if (b > 8192) b = 8192;
-    hipLaunchKernelGGL(momentum2d_kernel, dim3((unsigned)b), dim3(256), 0, s, Z, ldz, D, ldd, buf, ldb, n, lr, mu);
+    hipLaunchKernelGGL(momentum2d_kernel, quad_grid(n, n), dim3(256), 0, s, Z, ldz, D, ldd, buf, ldb, n, lr, mu);
     return hipGetLastError();
 }
 
 hipError_t launch_axpy2d(float* Z, long ldz, const float* D, long ldd, int n, float a, hipStream_t s) {
-    long b = ((long)n * n + 255) / 256;
-    if (b > 8192) b = 8192;
-    hipLaunchKernelGGL(axpy2d_kernel, dim3((unsigned)b), dim3(256), 0, s, Z, ldz, D, ldd, n, a);
+    hipLaunchKernelGGL(axpy2d_kernel, quad_grid(n, n), dim3(256), 0, s, Z, ldz, D, ldd, n, a);
     return hipGetLastError();
 }
 
