@@ -123,7 +123,7 @@ constexpr int kFarSplit = 4;  // most split-K layers of a deferred update's proj
 struct Layout {
     long ld = 0;          // leading dimension of every internal n x n fp32 matrix
     size_t flags = 0, A = 0, R = 0, U = 0, G = 0, B = 0, P = 0, M = 0, tau = 0, Tall = 0, wpart = 0, w2 = 0, wpartB = 0, w2B = 0, qpart = 0, qw = 0, yblk = 0, spart = 0, yring = 0, spartB = 0, wpartF1 = 0, w2F1 = 0, wpartF2 = 0, w2F2 = 0,
-           vs = 0, cq = 0, tsl = 0, yall = 0, uinv = 0, uinvo = 0, utmp = 0, x3a = 0, x3b = 0, x3c = 0, x3d = 0, Y = 0, dY = 0, xt = 0, dyt = 0, rbt = 0, losspart = 0, scal = 0, gsplit = 0;
+           vs = 0, cq = 0, tsl = 0, yall = 0, uinv = 0, uinvo = 0, utmp = 0, x3a = 0, x3b = 0, x3c = 0, x3d = 0, Y = 0, dY = 0, xt = 0, dyt = 0, rbt = 0, losspart = 0, guard = 0, scal = 0, gsplit = 0;
     size_t gsplit_floats = 0;
     size_t total = 0;
 };
@@ -188,6 +188,7 @@ Layout make_layout(int n, int T) {
     L.dyt = bump(cur, (size_t)round_up(n, 64) * tld * 2);
     L.rbt = bump(cur, (size_t)n * 2 * round_up(n, 32) * 2);
     L.losspart = bump(cur, (size_t)kLossPartials * 8);
+    L.guard = bump(cur, (size_t)kGuardWords * 4);   // whether fp32 activations and the rotation have values without a split
     L.scal = bump(cur, 256);   // device scalars (the step size of the Cayley update)
     L.gsplit_floats = (size_t)kMaxSplit * n2;
     if (L.gsplit_floats > ((size_t)16 << 20)) L.gsplit_floats = (size_t)16 << 20;
@@ -820,6 +821,17 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
     const bool g_transposed = xdt == DQ_BF16 && n % 128 == 0 && T % 128 == 0 && (n / 128) * (n / 128) >= 256 &&
                               (ldx & 7) == 0 && aligned16(X) && aligned16(G) && (ldg & 3) == 0;
     bool fused = false;   // S4 done in the epilogue of S3
+    // fp32 activations: both products on split operands, if a scan of X and R finds none that has no split (an infinite
+    // activation gives a finite loss on the fp32 matrix cores, a NaN from split terms).  The scan and the two launches that
+    // return at once cost some 25 us; from 4e9 multiplications on (100 us on the fp32 matrix cores) it pays: 4099 x 1536 471 -> 300
+    // us for S3 and S5.  Eq. 4's derivative is finite wherever Y is; of the other objectives that is not known.
+    const unsigned* guard = nullptr;
+    if (xdt == DQ_F32 && c->split_gemm != 0 && c->objective == DQ_OBJ_WHIP && gemm_flops >= 8e9) {
+        unsigned* words = at<unsigned>(c, L.guard);
+        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * ((double)T + n));
+        DQ_HIP(launch_range_scan(static_cast<const float*>(X), ldx, T, R, ldr, n, n, words, s));
+        guard = words;
+    }
     // S3: Y = X @ R
     if (xdt == DQ_BF16) {
         bf16_t* rbt = at<bf16_t>(c, L.rbt);
@@ -856,6 +868,10 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
         g.A = static_cast<const float*>(X); g.lda = ldx; g.ta = 0;
         g.B = R; g.ldb = ldr; g.tb = 0;
         g.C = Y; g.ldc = ldy; g.M = T; g.N = n; g.K = n;
+        if (guard != nullptr && gemm_f32_split_applies(T, n, 1)) {
+            g.x3 = 1;
+            g.guard = guard;
+        }
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, gemm_flops, 0.0);
         DQ_HIP(launch_gemm_f32(g, s));
     }
@@ -917,6 +933,10 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
             g.B = static_cast<const float*>(dY); g.ldb = lddy; g.tb = 0;
             g.C = out; g.ldc = ldo; g.M = n; g.N = n; g.K = T;
             g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
+            if (guard != nullptr && gemm_f32_split_applies(n, n, splits)) {
+                g.x3 = 1;
+                g.guard = guard;
+            }
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, gemm_flops, 0.0);
             DQ_HIP(launch_gemm_f32(g, s));
         }

@@ -83,12 +83,21 @@ struct GemmF32 {
     // with x3: scratch for the parts of tiles that would leave most of the chip idle (null: none)
     float* tail = nullptr; long tail_floats = 0;
     int x3 = 0;            // the 128 x 128 tile may form its products from operands split into three bf16 terms (finite values)
+    // with x3, for operands that a caller supplies: words of launch_range_scan over them.  Both kernels are launched, the one
+    // on split operands returns at once where a word is set, the fp32 one where none is.  Needs gemm_f32_split_applies().
+    const unsigned* guard = nullptr;
     int cfg = -1;          // tile configuration (-1: chosen from the shape; 3: 64 x 64 tiles, K step 32)
     // batch > 1: that many independent products in one launch; problem i reads A + i*batch_a, B + i*batch_b and
     // writes C + i*batch_c (element offsets)
     int batch = 1; long batch_a = 0, batch_b = 0, batch_c = 0;
 };
 hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t s);
+bool gemm_f32_split_applies(int M, int N, int splits);   // the launcher picks the tile that x3 speaks of
+// words[0 .. kGuardWords): non-zero somewhere if an entry of A (rows_a x cols) or B (rows_b x cols) is infinite, a NaN or
+// 2^127 or more in magnitude: such an entry has no split into finite bf16 terms
+constexpr int kGuardWords = 256;
+hipError_t launch_range_scan(const float* A, long lda, int rows_a, const float* B, long ldb, int rows_b, int cols,
+                             unsigned* words, hipStream_t s);
 int gemm_f32_tile_n(int M, int N);   // width of the workgroup tile the launcher picks
 
 // ---- bf16 matrix-core GEMM (fp32 accumulate, fp32 out) ------------------------------

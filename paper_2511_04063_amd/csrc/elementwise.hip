@@ -542,6 +542,26 @@ __global__ __launch_bounds__(256) void axpy2d_kernel(float* __restrict__ Z, long
     });
 }
 
+// (see launch_range_scan)  Bound by one read of the matrices: 4099 x 1536 and 1536 x 1536 in 13 us.
+__global__ __launch_bounds__(256) void range_scan_kernel(const float* __restrict__ A, long lda, int rows_a,
+                                                         const float* __restrict__ B, long ldb, int rows_b, int cols,
+                                                         unsigned* __restrict__ words) {
+    bool bad = false;
+    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6), waves = gridDim.x * 4, c0 = (threadIdx.x & 63) * 4;
+    for (int r = wave; r < rows_a + rows_b; r += waves) {
+        const float* p = r < rows_a ? A + (long)r * lda : B + (long)(r - rows_a) * ldb;
+#pragma unroll 4
+        for (int c = c0; c < cols; c += 256) {
+            const float4 v = load_quad(p + c, cols - c);
+            // false for a NaN as well
+            bad |= !(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))) < 0x1p127f) || v.x != v.x ||
+                   v.y != v.y || v.z != v.z || v.w != v.w;
+        }
+    }
+    const bool any = __syncthreads_or(bad) != 0;
+    if (threadIdx.x == 0) words[blockIdx.x] = any ? 1u : 0u;
+}
+
 // Adam (bias-corrected) and heavy-ball momentum on the latent: HBM-bound elementwise passes over n x n matrices
 // (Adam: 16 B read + 12 B written per element).  Row/column indexing because every matrix has its own leading
 // dimension.
@@ -727,6 +747,12 @@ hipError_t launch_place_diag_blocks(const float* inv, float* out, int n, hipStre
     long b = (total4 + 255) / 256;
     if (b > 4096) b = 4096;
     hipLaunchKernelGGL(place_diag_blocks_kernel, dim3((unsigned)b), dim3(256), 0, s, inv, out, total4);
+    return hipGetLastError();
+}
+
+hipError_t launch_range_scan(const float* A, long lda, int rows_a, const float* B, long ldb, int rows_b, int cols,
+                             unsigned* words, hipStream_t s) {
+    hipLaunchKernelGGL(range_scan_kernel, dim3(kGuardWords), dim3(256), 0, s, A, lda, rows_a, B, ldb, rows_b, cols, words);
     return hipGetLastError();
 }
 

@@ -193,6 +193,14 @@ __device__ __forceinline__ void store_tile(const GemmF32& g, long bz, int z, f32
     }   // guarded epilogue
 }
 
+// Is this launch the one of the two that a guarded product makes whose turn it is?  (256 threads; see GemmF32::guard)
+__device__ __forceinline__ bool guard_admits(const unsigned* guard, bool split) {
+    static_assert(kGuardWords == 256, "one word per thread");
+    if (guard == nullptr) return true;
+    const bool any = __syncthreads_or(guard[threadIdx.x] != 0u) != 0;
+    return any != split;
+}
+
 // BM x BN is the workgroup tile and WT the wavefront tile in units of 32 (wavefront tile 32*WT x 32*WT, four
 // wavefronts): 128 x 128 (WT 2, waves 2 x 2), 64 x 256 (M <= 64) and 256 x 64 (N <= 64) for throughput, and
 // 64 x 64 with WT 1 and a deeper K step for small latency-bound products that need many workgroups.
@@ -200,6 +208,7 @@ template <bool TA, bool TB, int BM, int BN, int WT, int BK>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec) {
     __shared__ __attribute__((aligned(16))) float As[2][BK][BM + 4];
     __shared__ __attribute__((aligned(16))) float Bs[2][BK][BN + 4];
+    if (!guard_admits(g.guard, false)) return;
     constexpr int WAVES_N = BN / (32 * WT);
     static_assert((BM / (32 * WT)) * WAVES_N == 4, "four wavefronts per workgroup");
 
@@ -378,6 +387,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
     __shared__ __attribute__((aligned(16))) bf16_t As[3 * X3PLANE];
     __shared__ __attribute__((aligned(16))) bf16_t Bs[3 * X3PLANE];
     constexpr int BM = 128, BN = 128;
+    if (!guard_admits(g.guard, true)) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -639,6 +649,8 @@ static int gemm_f32_config(int M, int N, int splits) {
     return 0;
 }
 
+bool gemm_f32_split_applies(int M, int N, int splits) { return gemm_f32_config(M, N, splits) == 0; }
+
 int gemm_f32_tile_n(int M, int N) { return N <= 128 ? 64 : ((M <= 64) ? 256 : 128); }
 
 hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t s) {
@@ -649,7 +661,11 @@ hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t s) {
         case 3: return launch_gemm_f32_tile<64, 64, 1, 32>(g, s);
         default:
             // a caller that allows it gets the products of this tile size from split operands
-            return g.x3 ? launch_gemm_f32x3(g, s) : launch_gemm_f32_tile<128, 128, 2, 16>(g, s);
+            if (g.x3) {
+                const hipError_t e = launch_gemm_f32x3(g, s);
+                if (e != hipSuccess || g.guard == nullptr) return e;
+            }
+            return launch_gemm_f32_tile<128, 128, 2, 16>(g, s);
     }
 }
 

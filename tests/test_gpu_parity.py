@@ -2004,3 +2004,41 @@ def test_heads_qr_and_backward_orders(n):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("where", ["none", "X inf", "X nan", "X huge", "R inf"])
+def test_rotate_fp32_split_operands(where):
+    """fp32 activations large enough for the products on split operands: finite values agree with the fp32 matrix cores
+    within rounding; a value that has no split sends both products back there, bit for bit."""
+    n, T = 1028, 4099
+    g = torch.Generator(device="cuda")
+    g.manual_seed(77)
+    X = torch.randn(T, n, device="cuda", generator=g)
+    R = torch.linalg.qr(torch.randn(n, n, device="cuda", generator=g))[0].contiguous()
+    if where == "X inf":
+        X[T - 1, n - 1] = float("-inf")
+    elif where == "X nan":
+        X[17, 1025] = float("nan")
+    elif where == "X huge":
+        X[4000, 3] = 3.39e38
+    elif where == "R inf":
+        R[n - 1, 5] = float("inf")
+    out = {}
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, T, B.DQ_F32)
+        for mode in (0, 1):
+            c.dq_set_option(B.DQ_OPT_SPLIT_GEMM, mode)
+            loss, G = torch.zeros(1, device="cuda"), torch.zeros(n, n, device="cuda")
+            c.dq_rotate_loss_grad(X, B.DQ_F32, R, B.DQ_REDUCE_TOKEN_MEAN, loss, G)
+            out[mode] = (loss, G)
+        if where == "none":
+            assert abs(out[1][0].item() - out[0][0].item()) < 1e-6 * abs(out[0][0].item())
+            # a sign of Y at rounding level flips: about T n 2 phi(0) 1e-6 of the entries, each worth 2 x_t / T in its column
+            assert float((out[1][1] - out[0][1]).norm() / out[0][1].norm()) < 5e-3
+        else:
+            for a, b in zip(out[0], out[1]):
+                assert torch.equal(a.nan_to_num(7.0, 8.0, 9.0), b.nan_to_num(7.0, 8.0, 9.0))
+    finally:
+        torch.cuda.synchronize()
+        c.close()
