@@ -126,7 +126,7 @@ typedef enum {
                                        24 mantissa bits; the six pairs of terms above fp32 rounding are accumulated in
                                        fp32).  0: never (fp32 matrix cores); 1 (default): where it is faster: products
                                        that fill the 128 x 128 tiles, split while they are read, and the n x n x n ones
-                                       from planes split beforehand when n is a multiple of 256 and at least 2560;
+                                       from planes split beforehand when n is a multiple of 4096;
                                        2: those of planes whenever n is a multiple of 256. */
     DQ_OPT_FUSED_PANEL = 7,         /* S1: a tall 64-column panel that follows a tall panel and is followed by one as ONE
                                        launch whose workgroups hand over to each other through words in device memory

@@ -954,8 +954,13 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
 // R^T G in x3a, as stored for R M in x3c).  (Run on the second stream beside S3-S5 it gained nothing, 8.83 ms per step
 // either way at n = 4096 and 45.8 -> 46.2 at 8192: the split passes and small products land on compute units whose one
 // 256 x 256 tile of the bf16 product then finishes last.  The batched 128 x 128 route does run its inverses there.)
+// Planes pay where their 256 x 256 tiles come in whole rounds of the 256 compute units, n a multiple of 4096; elsewhere the
+// 128 x 128 tiles that split while they read are ahead (dq_qr_backward with planes / without, us: n = 2560 820 / 636, 3072
+// 1043 / 885, 4096 1660 / 1673, 5120 2997 / 2952, 6144 5040 / 4719, 7168 7841 / 7719, 8192 9982 / 11288; the Cayley update 2074 /
+// 1360 at 2560, 9356 / 8719 at 5120, 4404 / 4401 at 4096, 32715 / 36914 at 8192).
+constexpr int kPlanesN = 4096;
 bool backward_uses_splits(const dq_ctx* c, const Layout& L, int n) {
-    return c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && L.ld == n && (c->split_gemm == 2 || n >= 2560);
+    return c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && L.ld == n && (c->split_gemm == 2 || n % kPlanesN == 0);
 }
 
 dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R, long ldr, const float* U, long ldu,
@@ -1046,10 +1051,8 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
     float* uinv = at<float>(c, L.uinv);
     const long ld = L.ld;
     const double n3 = (double)n * n * n;
-    // The two full n x n x n products run on the bf16 matrix cores from three-plane splits of their operands when the
-    // shape fits those tiles (fp32-level accuracy: six plane pairs, fp32 accumulation), else on the fp32 ones.
-    // (256 x 256 tiles at six times the matrix-core work: ahead of the fp32 kernel's 128 x 128 tiles once about a hundred of
-    // them keep the compute units busy, n >= 2560)
+    // The two full n x n x n products run on the bf16 matrix cores from splits of their operands (fp32-level accuracy: six
+    // pairs of terms, fp32 accumulation): from planes split beforehand where backward_uses_splits() says so.
     const bool x3 = backward_uses_splits(c, L, n);
     bf16_t* pa3 = at<bf16_t>(c, L.x3a);   // planes of R^T (qr_backward_prepare)
     bf16_t* pb3 = at<bf16_t>(c, L.x3b);   // planes of G^T, later of M
@@ -1203,7 +1206,7 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
     // As in S6, the products run on the bf16 matrix cores from three-plane splits when the shape fits (DQ_OPT_SPLIT_GEMM):
     // `pa` holds the planes of op(A) (n x n, reduction index contiguous), `pb` those of op(B)^T; a null `A_` / `B_` means
     // that the buffer already holds them from an earlier product.
-    const bool x3 = c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && ld == n && (c->split_gemm == 2 || n >= 2560);
+    const bool x3 = c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && ld == n && (c->split_gemm == 2 || n % kPlanesN == 0);
     const long plane = (long)n * ld;
     bf16_t* pl0 = at<bf16_t>(c, L.x3a);
     bf16_t* pl1 = at<bf16_t>(c, L.x3b);
