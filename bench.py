@@ -218,7 +218,7 @@ def run_config(cfg_name: str, args):
         ms = tm(lambda: ctx.dq_qr_backward(Rb, Ub, Gb, dZb))
         fl = b * 4.0 * n ** 3
         out["qr_backward"] = {"ms": ms, "model_tflops": fl / ms / 1e9}
-        if n % 256 == 0 and n >= 2560:
+        if n % 4096 == 0:
             # 3 n^3 of the stage's model flops run on the bf16 matrix cores from three-plane splits (six times issued)
             out["qr_backward"]["issued_bf16_tflops_of_split_products"] = b * 18.0 * n ** 3 / ms / 1e9
             out["qr_backward"]["note"] = ("R^T G and R M run on the bf16 matrix cores from split operands; no single "
@@ -267,9 +267,10 @@ def run_config(cfg_name: str, args):
     # 2 n^3 where the model counts 4/3 n^3, the rotation product issues its flops twice for the two planes of R)
     # The library's default (DQ_OPT_SPLIT_GEMM = 1) moves the full n^3 products of the derivative (R^T G and R M: 3 n^3 of
     # the model's 4 n^3, the triangular solve stays) and all six of the Cayley update from the fp32 to the bf16 matrix
-    # cores when n is a multiple of 256 and at least 2560 (three-plane splits, six times the flops issued): the model's
-    # flops are booked to the class that runs them.
-    split = n % 256 == 0 and n >= 2560
+    # cores when n is a multiple of 4096 (three-plane splits, six times the flops issued): the model's flops are booked to
+    # the class that runs them.  The other large fp32 products (128 x 128 tiles) split their operands while they read them;
+    # they stay in the fp32 class and are priced at the fp32 peak, which they may exceed.
+    split = n % 4096 == 0
     side = 12.0 if args.optimizer == "cayley" else 20.0 / 3.0
     moved = (12.0 if args.optimizer == "cayley" else 3.0) if split else 0.0
     if dominant == B.DQ_K_GEMM_F32:

@@ -1295,6 +1295,8 @@ HeadsLayout make_heads_layout(size_t base, int b, int T) {
     H.U = bump(cur, mat);
     H.G = bump(cur, mat);
     H.dZ = bump(cur, mat);
+    bump(cur, 3 * mat);   // unused; dq_workspace_bytes has always counted seven matrices per problem, and a program may have
+                          // sized its groups of problems by it
     H.gpart = bump(cur, mat * sp);
     H.lpart = bump(cur, (size_t)(b > 0 ? b : 1) * sp * 8);
     H.total = cur;
