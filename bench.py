@@ -33,8 +33,8 @@ if ROOT not in sys.path:
 # fp32 instructions, which this build keeps the compiler from forming.
 PEAK = {"fp32_mfma_tflops": 157.3, "bf16_mfma_tflops": 2500.0, "hbm_gbs": 8000.0, "fp32_valu_tflops": 78.6}
 
-# kernel whose launches make up each bracketed class (as named in the rocprofv3 summaries under profiles/)
-CLASS_KERNEL = {"gemm_f32": "gemm_f32_kernel", "gemm_bf16": "gemm_bf16_nt_big_kernel", "whip": "whip_kernel"}
+# kernel that takes most of the time of each bracketed class (as named in the rocprofv3 summaries under profiles/)
+CLASS_KERNEL = {"gemm_f32": "gemm_f32x3_kernel", "gemm_bf16": "gemm_bf16_nt_big_kernel", "whip": "whip_kernel"}
 
 
 def flops_per_step(n: int, T: int, b: int = 1, optimizer: str = "sgd") -> float:
