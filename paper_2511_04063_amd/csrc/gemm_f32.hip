@@ -435,13 +435,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
     ob.unit_lower_cols = g.b_unit_lower_cols;
     if (TB) { ob.row_lim = g.N; ob.col_lim = ke; } else { ob.row_lim = ke; ob.col_lim = g.N; }
 
-    f32x16 acc[2][2];
+    f32x16 acc[2][2], low[2][2];        // the products of the leading terms; the five small ones
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
 
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
     const int lrow = lane & 31, lk = lane >> 5;
@@ -486,11 +486,19 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][PA[t]], b[j][PB[t]], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < 2; ++j) {
+                        f32x16& d = t < 5 ? low[i][j] : acc[i][j];
+                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][PA[t]], b[j][PB[t]], d, 0, 0, 0);
+                    }
         }
         __syncthreads();
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] += low[i][j][v];
     if (in_parts) {
         float* t = g.tail + (long)(bid - whole) * (BM * BN) + (wm + 4 * lk) * BN + wn + lrow;
 #pragma unroll
