@@ -951,13 +951,13 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
 // ---------------------------------------------------------------- S6 (+ S7 when Zupd != null)
 // What S6 needs of R and U alone, on stream s: the inverses of the diagonal blocks of U (128 x 128, merged to 512 x 512
 // where the solve works on such blocks) and, for the products on three-plane splits, the planes of R (transposed for
-// R^T G in x3a, as stored for R M in x3c).  (Run on the second stream beside S3-S5 it gained nothing, 8.83 ms per step
-// either way at n = 4096 and 45.8 -> 46.2 at 8192: the split passes and small products land on compute units whose one
-// 256 x 256 tile of the bf16 product then finishes last.  The batched 128 x 128 route does run its inverses there.)
+// R^T G in x3a, as stored for R M in x3c).  (With planes, run on the second stream beside S3-S5 it gained nothing, 8.83 ms per
+// step either way at n = 4096 and 45.8 -> 46.2 at 8192: the split passes and small products land on compute units whose one
+// 256 x 256 tile of the bf16 product then finishes last.  Without planes it does run there.)
 // Planes pay where their 256 x 256 tiles come in whole rounds of the 256 compute units, n a multiple of 4096; elsewhere the
 // 128 x 128 tiles that split while they read are ahead (dq_qr_backward with planes / without, us: n = 2560 820 / 636, 3072
-// 1043 / 885, 4096 1660 / 1673, 5120 2997 / 2952, 6144 5040 / 4719, 7168 7841 / 7719, 8192 9982 / 11288; the Cayley update 2074 /
-// 1360 at 2560, 9356 / 8719 at 5120, 4404 / 4401 at 4096, 32715 / 36914 at 8192).
+// 1043 / 900, 4096 1660 / 1670, 5120 2997 / 3000, 6144 5040 / 4800, 7168 7841 / 7800, 8192 9982 / 11288; the Cayley update 2074 /
+// 1360 at 2560, 9356 / 8676 at 5120, 4404 / 4401 at 4096, 32715 / 36914 at 8192; their errors are the same).
 constexpr int kPlanesN = 4096;
 bool backward_uses_splits(const dq_ctx* c, const Layout& L, int n) {
     return c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && L.ld == n && (c->split_gemm == 2 || n % kPlanesN == 0);
