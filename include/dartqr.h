@@ -121,13 +121,16 @@ typedef enum {
                                        call on a stream shows that the streams involved make progress independently
                                        (they do unless they share a hardware queue); otherwise events.  Every poll is
                                        bounded (DQ_FLAG_SYNC_TIMEOUT). */
-    DQ_OPT_SPLIT_GEMM = 6,          /* fp32 products of the library's own matrices (updates of the QR, S6, Cayley) on the bf16
-                                       matrix cores from three-term bf16 splits of both operands (x = x1 + x2 + x3 carries
-                                       24 mantissa bits; the six pairs of terms above fp32 rounding are accumulated in
-                                       fp32).  0: never (fp32 matrix cores); 1 (default): where it is faster: products
-                                       that fill the 128 x 128 tiles, split while they are read, and the n x n x n ones
-                                       from planes split beforehand when n is a multiple of 4096;
-                                       2: those of planes whenever n is a multiple of 256. */
+    DQ_OPT_SPLIT_GEMM = 6,          /* fp32 products (updates of the QR, S6, Cayley; X R and X^T dY of large fp32 blocks under
+                                       Eq. 4) on the bf16 matrix cores from three-term bf16 splits of both operands (x = x1 +
+                                       x2 + x3 carries 24 mantissa bits where x is zero or 2^-102 <= |x| < 2^127; the six
+                                       pairs of terms above fp32 rounding are accumulated in fp32).  0: never (fp32 matrix
+                                       cores); 1 (default): where it is faster: products that fill the 128 x 128 tiles, split
+                                       while they are read, and the n x n x n ones from planes split beforehand when n is
+                                       a multiple of 4096; 2: those of planes whenever n is a multiple of 256.
+                                       A caller's X and R (S3, S5), G (S6) and M (Cayley) are scanned first, and an entry
+                                       outside that range sends the products on it back to the fp32 matrix cores; not
+                                       scanned are operands of planes, and those of dq_gemm_f32 under 2. */
     DQ_OPT_FUSED_PANEL = 7,         /* S1: a tall 64-column panel that follows a tall panel and is followed by one as ONE
                                        launch whose workgroups hand over to each other through words in device memory
                                        (bounded polls, DQ_FLAG_SYNC_TIMEOUT) instead of three dependent launches.  Only
@@ -308,7 +311,7 @@ dq_status dq_cayley_step(dq_ctx* ctx, int b, int T, int n, const void* X, dq_dty
 /* The matrix-core GEMMs the path is built from, exported for kernel-level parity tests:
  *   C (M x N, fp32) = alpha * op(A) op(B) + beta * C.
  * f32: A, B fp32; ta != 0 means A is stored K x M, tb != 0 means B is stored N x K.  On the fp32 matrix cores, or, with
- * DQ_OPT_SPLIT_GEMM = 2 and finite operands, as the library's own large products.
+ * DQ_OPT_SPLIT_GEMM = 2 and values in the range given there, as the library's own large products.
  * bf16: A, B bf16, fp32 accumulate; ta/tb as above. */
 dq_status dq_gemm_f32(dq_ctx* ctx, int M, int N, int K, float alpha,
                       const float* A, long lda, int ta, const float* B, long ldb, int tb,

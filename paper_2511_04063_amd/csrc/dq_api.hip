@@ -258,10 +258,13 @@ void choose_split(int tiles, int K, int kalign, int max_splits, int& splits, int
     if (splits < 1) splits = 1;
 }
 
-// An fp32 product whose operands the library has formed itself (finite unless the call has failed anyway): split operands on
-// the bf16 matrix cores where the launcher's 128 x 128 tile applies, unless DQ_OPT_SPLIT_GEMM forbids it.
-hipError_t product_f32(const dq_ctx* c, GemmF32& g, hipStream_t s) {
+// An fp32 product: split operands on the bf16 matrix cores where the launcher's 128 x 128 tile applies, unless
+// DQ_OPT_SPLIT_GEMM forbids it.  guard: the words of a scan over the caller's operands that the product's own derive from
+// (GemmF32::guard).  The QR needs none: the squares of a column's entries have to stay inside fp32's range for it to work at all,
+// so a column's norm lies above 2^-63, and what an entry below 2^-110 loses (2^-134) is nothing beside it.
+hipError_t product_f32(const dq_ctx* c, GemmF32& g, hipStream_t s, const unsigned* guard = nullptr) {
     g.x3 = c->split_gemm != 0;
+    g.guard = guard;
     return launch_gemm_f32(g, s);
 }
 
@@ -822,15 +825,16 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
                               (ldx & 7) == 0 && aligned16(X) && aligned16(G) && (ldg & 3) == 0;
     bool fused = false;   // S4 done in the epilogue of S3
     // fp32 activations: both products on split operands, if a scan of X and R finds none that has no split (an infinite
-    // activation gives a finite loss on the fp32 matrix cores, a NaN from split terms).  The scan and the two launches that
-    // return at once cost some 25 us; from 4e9 multiplications on (100 us on the fp32 matrix cores) it pays: 4099 x 1536 471 -> 300
-    // us for S3 and S5.  Eq. 4's derivative is finite wherever Y is; of the other objectives that is not known.
-    const unsigned* guard = nullptr;
+    // activation gives a finite loss on the fp32 matrix cores, a NaN from split terms).  The scan costs some 10 us; from 4e9
+    // multiplications on (100 us on the fp32 matrix cores) it pays: 4099 x 1536 471 -> 300 us for S3 and S5.  Eq. 4's derivative is
+    // finite wherever Y is; of the other objectives that is not known.  Its entries may be tiny, but the largest is no less
+    // than the loss divided by the count: with a sum of exp(-|y|) of 1 or more, what entries below 2^-110 lose does not show in G.
+    unsigned* guard = nullptr;
     if (xdt == DQ_F32 && c->split_gemm != 0 && c->objective == DQ_OBJ_WHIP && gemm_flops >= 8e9) {
-        unsigned* words = at<unsigned>(c, L.guard);
+        guard = at<unsigned>(c, L.guard);
+        const ScanList list{{{static_cast<const float*>(X), ldx, T}, {R, ldr, n}}};
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * ((double)T + n));
-        DQ_HIP(launch_range_scan(static_cast<const float*>(X), ldx, T, R, ldr, n, n, words, s));
-        guard = words;
+        DQ_HIP(launch_range_scan(list, n, guard, s));
     }
     // S3: Y = X @ R
     if (xdt == DQ_BF16) {
@@ -887,7 +891,7 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
                                          lpart, grid, s));
         }
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
-        DQ_HIP(launch_loss_finish(lpart, grid, scale, loss_dev, flags, s));
+        DQ_HIP(launch_loss_finish(lpart, grid, scale, loss_dev, flags, s, 1, guard));
     }
     // S5: G = X^T @ dY (reduction over the tokens; split when the n x n output has few tiles)
     {
@@ -1043,6 +1047,14 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
                           const float* G, long ldg, float* dZ, long lddz, float* Zupd, long ldz, float lr,
                           hipEvent_t joined = nullptr) {
     hipStream_t s = c->stream;
+    // Without planes: a G with entries that have no split sends the products below back to the fp32 matrix cores.  R's columns
+    // have norm 1 and U's the norms of a latent that the QR can work on: their small entries do not show (see product_f32).
+    unsigned* guard = nullptr;
+    if (!backward_uses_splits(c, L, n) && c->split_gemm != 0 && gemm_f32_split_applies(n, n, 1)) {
+        guard = at<unsigned>(c, L.guard);
+        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * (double)n);
+        DQ_HIP(launch_range_scan(ScanList{{{G, ldg, n}, {}}}, n, guard, s));
+    }
     if (joined == nullptr) DQ_TRY(qr_backward_prepare_early(c, L, n, R, ldr, U, ldu, &joined));
     if (joined == nullptr) DQ_TRY(qr_backward_prepare(c, L, n, R, ldr, U, ldu, s));
     float* Bb = at<float>(c, L.B);
@@ -1076,7 +1088,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         g.C = Bb; g.ldc = ld; g.M = n; g.N = n; g.K = n;
         g.tail = at<float>(c, L.gsplit); g.tail_floats = (long)L.gsplit_floats;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(product_f32(c, g, s));
+        DQ_HIP(product_f32(c, g, s, guard));
     }
     {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 16.0 * n * (double)n);
@@ -1098,7 +1110,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
             g.C = Mb + (long)j0 * ld + j0; g.ldc = ld;
             g.M = mrows; g.N = w; g.K = w;
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)w * w, 0.0);
-            DQ_HIP(product_f32(c, g, s));
+            DQ_HIP(product_f32(c, g, s, guard));
         }
         if (j0 > 0) {
             GemmF32 g;   // P[j0:, 0:j0] -= M[j0:, blk] * U[0:j0, blk]^T
@@ -1108,7 +1120,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
             g.M = mrows; g.N = j0; g.K = w;
             g.alpha = -1.f; g.beta = 1.f;
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)j0 * w, 0.0);
-            DQ_HIP(product_f32(c, g, s));
+            DQ_HIP(product_f32(c, g, s, guard));
         }
     }
     if (nouter > 0) {
@@ -1129,7 +1141,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
                 g.C = Mb + (long)J0 * ld + J0; g.ldc = ld;
                 g.M = mrows; g.N = kTrsmOuter; g.K = kTrsmOuter;
                 LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)kTrsmOuter * kTrsmOuter, 0.0);
-                DQ_HIP(product_f32(c, g, s));
+                DQ_HIP(product_f32(c, g, s, guard));
             }
             if (J0 > 0) {
                 GemmF32 g;   // P[J0:, 0:J0] -= M[J0:, blk] * U[0:J0, blk]^T (in fp32: from three-plane splits its tiles
@@ -1140,7 +1152,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
                 g.M = mrows; g.N = J0; g.K = kTrsmOuter;
                 g.alpha = -1.f; g.beta = 1.f;
                 LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)J0 * kTrsmOuter, 0.0);
-                DQ_HIP(product_f32(c, g, s));
+                DQ_HIP(product_f32(c, g, s, guard));
             }
         }
     }
@@ -1181,7 +1193,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         if (Zupd != nullptr) { g.C = Zupd; g.ldc = ldz; g.alpha = -lr; g.beta = 1.f; }
         else { g.C = dZ; g.ldc = lddz; }
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, n3, 0.0);
-        DQ_HIP(product_f32(c, g, s));
+        DQ_HIP(product_f32(c, g, s, guard));
     }
     return DQ_OK;
 }
@@ -1212,6 +1224,7 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
     bf16_t* pl1 = at<bf16_t>(c, L.x3b);
     bf16_t* pl2 = at<bf16_t>(c, L.x3c);
     bf16_t* pl3 = at<bf16_t>(c, L.x3d);
+    unsigned* guard = nullptr;
     auto product = [&](const float* A_, long lda, int ta, bf16_t* pa, const float* B_, long ldb, int tb, bf16_t* pb,
                        float* C_, long ldc, float alpha, float beta_, const float* alpha_dev) -> dq_status {
         if (x3) {
@@ -1237,12 +1250,17 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
         g.alpha = alpha; g.beta = beta_; g.alpha_dev = alpha_dev;
         g.tail = at<float>(c, L.gsplit); g.tail_floats = (long)L.gsplit_floats;
         LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n3, 0.0);
-        DQ_HIP(product_f32(c, g, s));
+        DQ_HIP(product_f32(c, g, s, guard));
         return DQ_OK;
     };
     {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 2.0 * n * (double)n, 12.0 * n * (double)n);
         DQ_HIP(launch_cayley_momentum(M, ldm, G, ldg, n, beta, s));
+    }
+    if (!x3 && c->split_gemm != 0 && gemm_f32_split_applies(n, n, 1)) {   // (as in S6: R is a rotation)
+        guard = at<unsigned>(c, L.guard);
+        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * (double)n);
+        DQ_HIP(launch_range_scan(ScanList{{{M, ldm, n}, {}}}, n, guard, s));
     }
     DQ_TRY(product(M, ldm, 0, pl0, R, ldr, 1, pl1, What, ld, 1.f, 0.f, nullptr));          // A = M R^T
     DQ_TRY(product(R, ldr, 1, pl2, What, ld, 0, pl0, Tmp, ld, 1.f, 0.f, nullptr));         // R^T A
@@ -1975,7 +1993,7 @@ dq_status dq_gemm_f32(dq_ctx* c, int M, int N, int K, float alpha, const float* 
     g.B = B; g.ldb = ldb; g.tb = tb ? 1 : 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.alpha = alpha; g.beta = beta;
     LaunchScope sc(&c->prof, c->stream, DQ_K_GEMM_F32, 2.0 * M * (double)N * K, 0.0);
-    g.x3 = c->split_gemm == 2;   // operands of any value by default: an infinity has no split
+    g.x3 = c->split_gemm == 2;   // operands of any value by default: not every value has a split
     DQ_HIP(launch_gemm_f32(g, c->stream));
     return DQ_OK;
 }

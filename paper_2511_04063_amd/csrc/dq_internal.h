@@ -83,8 +83,8 @@ struct GemmF32 {
     // with x3: scratch for the parts of tiles that would leave most of the chip idle (null: none)
     float* tail = nullptr; long tail_floats = 0;
     int x3 = 0;            // the 128 x 128 tile may form its products from operands split into three bf16 terms (finite values)
-    // with x3, for operands that a caller supplies: words of launch_range_scan over them.  Both kernels are launched, the one
-    // on split operands returns at once where a word is set, the fp32 one where none is.  Needs gemm_f32_split_applies().
+    // with x3, for operands whose values are not known to have a split: kGuardWords words of launch_range_scan over them.  Where
+    // one is set, the kernel forms the same product on the fp32 matrix cores, with the bits of the tile without x3.
     const unsigned* guard = nullptr;
     int cfg = -1;          // tile configuration (-1: chosen from the shape; 3: 64 x 64 tiles, K step 32)
     // batch > 1: that many independent products in one launch; problem i reads A + i*batch_a, B + i*batch_b and
@@ -93,11 +93,13 @@ struct GemmF32 {
 };
 hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t s);
 bool gemm_f32_split_applies(int M, int N, int splits);   // the launcher picks the tile that x3 speaks of
-// words[0 .. kGuardWords): non-zero somewhere if an entry of A (rows_a x cols) or B (rows_b x cols) is infinite, a NaN or
-// 2^127 or more in magnitude: such an entry has no split into finite bf16 terms
+// words[0 .. kGuardWords): non-zero somewhere if an entry of the matrices (rows x cols each) has no split into three normal bf16
+// terms that hold its 24 bits: infinite, a NaN, 2^127 or more in magnitude, or below 2^-102 and not zero
 constexpr int kGuardWords = 256;
-hipError_t launch_range_scan(const float* A, long lda, int rows_a, const float* B, long ldb, int rows_b, int cols,
-                             unsigned* words, hipStream_t s);
+struct ScanPart { const float* p = nullptr; long ld = 0; int rows = 0; };
+constexpr int kScanParts = 2;
+struct ScanList { ScanPart part[kScanParts]; };
+hipError_t launch_range_scan(const ScanList& list, int cols, unsigned* words, hipStream_t s);
 int gemm_f32_tile_n(int M, int N);   // width of the workgroup tile the launcher picks
 
 // ---- bf16 matrix-core GEMM (fp32 accumulate, fp32 out) ------------------------------
@@ -301,12 +303,13 @@ hipError_t launch_add_scaled(float* out, long ldo, const float* A, long lda, con
 hipError_t launch_transpose_bf16(const bf16_t* src, long lds_, int rows, int cols, bf16_t* dst, long ldd, hipStream_t s);
 hipError_t launch_split_transpose_bf16(const float* R, long ldr, int n, bf16_t* RbT, long ldt, int koff, hipStream_t s);
 // Fused Whip loss + gradient pass: partial sums to `partials` (double, one per workgroup), then
-// launch_loss_finish adds them up: loss = scale * sum.  dy_is_bf16 selects the dtype of dY.
+// launch_loss_finish adds them up: loss = scale * sum.  dy_is_bf16 selects the dtype of dY.  small (optional): set to 1 where
+// the sum is below 1 or a NaN, left alone otherwise.
 int whip_grid(long rows, int cols);
 hipError_t launch_whip(const float* Y, long ldy, int T, int n, float scale, void* dY, int dy_is_bf16, long lddy,
                        double* partials, int grid, hipStream_t s, int batch = 1, long stride_y = 0, long stride_dy = 0);
 hipError_t launch_loss_finish(const double* partials, int count, float scale, float* loss_dev, unsigned* flags,
-                              hipStream_t s, int batch = 1);
+                              hipStream_t s, int batch = 1, unsigned* small = nullptr);
 
 // Row-wise objectives (1 variance, 2 kurtosis, 3 quantisation error): one partial per workgroup like the Whip pass.
 int objective_grid(int T, int n);

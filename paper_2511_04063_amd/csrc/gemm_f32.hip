@@ -193,12 +193,51 @@ __device__ __forceinline__ void store_tile(const GemmF32& g, long bz, int z, f32
     }   // guarded epilogue
 }
 
-// Is this launch the one of the two that a guarded product makes whose turn it is?  (256 threads; see GemmF32::guard)
-__device__ __forceinline__ bool guard_admits(const unsigned* guard, bool split) {
-    static_assert(kGuardWords == 256, "one word per thread");
-    if (guard == nullptr) return true;
-    const bool any = __syncthreads_or(guard[threadIdx.x] != 0u) != 0;
-    return any != split;
+// acc += the k in [kb, ke) of a workgroup's BM x BN tile at (m0, n0) on the fp32 matrix cores; inner: rows and block wholly
+// inside the matrices, with aligned rows and out of reach of the unit-lower masks.
+template <bool TA, bool TB, int BM, int BN, int WT, int BK>
+__device__ __forceinline__ void multiply_f32(const OperandView& oa, const OperandView& ob, bool inner, int m0, int n0, int kb,
+                                             int ke, float (*As)[BK][BM + 4], float (*Bs)[BK][BN + 4], int tid, int wm, int wn,
+                                             int lrow, int lk, f32x16 (&acc)[WT][WT]) {
+    const int nk = ke > kb ? (ke - kb + BK - 1) / BK : 0;
+    float4 fa[BM * BK / 1024], fb[BN * BK / 1024];
+    auto fetch_both = [&](int k0) {
+        if (inner && k0 + BK <= ke) {
+            fetch_tile_inner<!TA, BM, BK>(oa.p, oa.ld, m0, k0, tid, fa);
+            fetch_tile_inner<TB, BN, BK>(ob.p, ob.ld, n0, k0, tid, fb);
+        } else {
+            fetch_tile<!TA, BM, BK>(oa, m0, k0, tid, fa);
+            fetch_tile<TB, BN, BK>(ob, n0, k0, tid, fb);
+        }
+    };
+    if (nk > 0) {
+        fetch_both(kb);
+        stash_tile<!TA, BM, BK>(As[0], tid, fa);
+        stash_tile<TB, BN, BK>(Bs[0], tid, fb);
+    }
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        const int cur = kt & 1;
+        if (kt + 1 < nk) fetch_both(kb + (kt + 1) * BK);
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 2) {
+            float a[WT], b[WT];
+#pragma unroll
+            for (int i = 0; i < WT; ++i) a[i] = As[cur][kk + lk][wm + i * 32 + lrow];
+#pragma unroll
+            for (int j = 0; j < WT; ++j) b[j] = Bs[cur][kk + lk][wn + j * 32 + lrow];
+#pragma unroll
+            for (int i = 0; i < WT; ++i)
+#pragma unroll
+                for (int j = 0; j < WT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+        if (kt + 1 < nk) {
+            stash_tile<!TA, BM, BK>(As[cur ^ 1], tid, fa);
+            stash_tile<TB, BN, BK>(Bs[cur ^ 1], tid, fb);
+        }
+        __syncthreads();
+    }
 }
 
 // BM x BN is the workgroup tile and WT the wavefront tile in units of 32 (wavefront tile 32*WT x 32*WT, four
@@ -208,7 +247,6 @@ template <bool TA, bool TB, int BM, int BN, int WT, int BK>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec) {
     __shared__ __attribute__((aligned(16))) float As[2][BK][BM + 4];
     __shared__ __attribute__((aligned(16))) float Bs[2][BK][BN + 4];
-    if (!guard_admits(g.guard, false)) return;
     constexpr int WAVES_N = BN / (32 * WT);
     static_assert((BM / (32 * WT)) * WAVES_N == 4, "four wavefronts per workgroup");
 
@@ -268,51 +306,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, i
     const int wm = (wave / WAVES_N) * 32 * WT, wn = (wave % WAVES_N) * 32 * WT;
     const int lrow = lane & 31, lk = lane >> 5;
 
-    const int nk = ke > kb ? (ke - kb + BK - 1) / BK : 0;
     // A tile whose operand rows and output block lie wholly inside the matrices, with aligned rows and out of reach
     // of the unit-lower masks, takes loaders and an epilogue without bounds checks: the checks cost more instructions
     // than the products of a short K loop.  Only a last K step that is cut short reads with checks.
     const bool inner = avec && bvec && m0 + BM <= g.M && n0 + BN <= g.N &&
                        (!g.a_unit_lower || (!TA && m0 >= ke)) && (g.b_unit_lower_cols == 0 || (TB && n0 >= ke));
-    float4 fa[BM * BK / 1024], fb[BN * BK / 1024];
-    auto fetch_both = [&](int k0) {
-        if (inner && k0 + BK <= ke) {
-            fetch_tile_inner<!TA, BM, BK>(oa.p, oa.ld, m0, k0, tid, fa);
-            fetch_tile_inner<TB, BN, BK>(ob.p, ob.ld, n0, k0, tid, fb);
-        } else {
-            fetch_tile<!TA, BM, BK>(oa, m0, k0, tid, fa);
-            fetch_tile<TB, BN, BK>(ob, n0, k0, tid, fb);
-        }
-    };
-    if (nk > 0) {
-        fetch_both(kb);
-        stash_tile<!TA, BM, BK>(As[0], tid, fa);
-        stash_tile<TB, BN, BK>(Bs[0], tid, fb);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) fetch_both(kb + (kt + 1) * BK);
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            float a[WT], b[WT];
-#pragma unroll
-            for (int i = 0; i < WT; ++i) a[i] = As[cur][kk + lk][wm + i * 32 + lrow];
-#pragma unroll
-            for (int j = 0; j < WT; ++j) b[j] = Bs[cur][kk + lk][wn + j * 32 + lrow];
-#pragma unroll
-            for (int i = 0; i < WT; ++i)
-#pragma unroll
-                for (int j = 0; j < WT; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        if (kt + 1 < nk) {
-            stash_tile<!TA, BM, BK>(As[cur ^ 1], tid, fa);
-            stash_tile<TB, BN, BK>(Bs[cur ^ 1], tid, fb);
-        }
-        __syncthreads();
-    }
-
+    multiply_f32<TA, TB, BM, BN, WT, BK>(oa, ob, inner, m0, n0, kb, ke, As, Bs, tid, wm, wn, lrow, lk, acc);
     store_tile<WT>(g, bz, z, acc, m0, n0, wm, wn, lrow, lk, inner);
 }
 
@@ -385,13 +384,78 @@ __device__ __forceinline__ void x3_stash(bf16_t* S, int tid, const float4 (&q)[4
     }
 }
 
+// acc += the k in [kb, ke) of a workgroup's 128 x 128 tile at (m0, n0) from split operands (inner: as in multiply_f32)
+template <bool TA, bool TB>
+__device__ __forceinline__ void multiply_x3(const OperandView& oa, const OperandView& ob, bool inner, int m0, int n0, int kb,
+                                            int ke, bf16_t* As, bf16_t* Bs, int tid, int wm, int wn, int lrow, int lk,
+                                            f32x16 (&acc)[2][2]) {
+    const int nk = ke > kb ? (ke - kb + X3K - 1) / X3K : 0;
+    f32x16 low[2][2];   // the five small products of a pair of terms
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) low[i][j][v] = 0.f;
+    float4 fa[4], fb[4];
+    auto fetch_both = [&](int k0) {
+        if (inner && k0 + X3K <= ke) {
+            x3_fetch<!TA>(oa, true, m0, k0, tid, fa);
+            x3_fetch<TB>(ob, true, n0, k0, tid, fb);
+        } else {
+            x3_fetch<!TA>(oa, false, m0, k0, tid, fa);
+            x3_fetch<TB>(ob, false, n0, k0, tid, fb);
+        }
+    };
+    if (nk > 0) fetch_both(kb);
+    for (int kt = 0; kt < nk; ++kt) {
+        x3_stash<!TA>(As, tid, fa);
+        x3_stash<TB>(Bs, tid, fb);
+        __syncthreads();
+        if (kt + 1 < nk) fetch_both(kb + (kt + 1) * X3K);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 a[2][3], b[2][3];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int ra = wm + i * 32 + lrow, rb = wn + i * 32 + lrow, ch = 2 * ks + lk;
+                const int offa = ra * X3LD + ((ch ^ ((ra >> 4) & 3)) << 3), offb = rb * X3LD + ((ch ^ ((rb >> 4) & 3)) << 3);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    a[i][p] = *reinterpret_cast<const bf16x8*>(As + p * X3PLANE + offa);
+                    b[i][p] = *reinterpret_cast<const bf16x8*>(Bs + p * X3PLANE + offb);
+                }
+            }
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        f32x16& d = t < 5 ? low[i][j] : acc[i][j];
+                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][PA[t]], b[j][PB[t]], d, 0, 0, 0);
+                    }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] += low[i][j][v];
+}
+
 template <bool TA, bool TB>
 __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec,
                                                                  int whole, int parts, int pchunk) {
-    __shared__ __attribute__((aligned(16))) bf16_t As[3 * X3PLANE];
-    __shared__ __attribute__((aligned(16))) bf16_t Bs[3 * X3PLANE];
+    __shared__ __attribute__((aligned(16))) bf16_t lds[6 * X3PLANE];
+    bf16_t* const As = lds;
+    bf16_t* const Bs = lds + 3 * X3PLANE;
     constexpr int BM = 128, BN = 128;
-    if (!guard_admits(g.guard, true)) return;
+    static_assert(kGuardWords == 256, "one word per thread");
+    const bool split = g.guard == nullptr || __syncthreads_or(g.guard[threadIdx.x] != 0u) == 0;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -439,70 +503,28 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
     ob.unit_lower_cols = g.b_unit_lower_cols;
     if (TB) { ob.row_lim = g.N; ob.col_lim = ke; } else { ob.row_lim = ke; ob.col_lim = g.N; }
 
-    f32x16 acc[2][2], low[2][2];        // the products of the leading terms; the five small ones
+    f32x16 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
     const int lrow = lane & 31, lk = lane >> 5;
 
-    const int nk = ke > kb ? (ke - kb + X3K - 1) / X3K : 0;
-    // each operand takes loads without checks where its tile lies inside it and out of reach of the masks
-    const bool ina = avec && m0 + BM <= g.M && (!g.a_unit_lower || (!TA && m0 >= ke));
-    const bool inb = bvec && n0 + BN <= g.N && (g.b_unit_lower_cols == 0 || (TB && n0 >= ke));
-    float4 fa[4], fb[4];
-    auto fetch_both = [&](int k0) {
-        const bool whole = k0 + X3K <= ke;
-        if (ina && inb && whole) {
-            x3_fetch<!TA>(oa, true, m0, k0, tid, fa);
-            x3_fetch<TB>(ob, true, n0, k0, tid, fb);
-        } else {
-            x3_fetch<!TA>(oa, false, m0, k0, tid, fa);
-            x3_fetch<TB>(ob, false, n0, k0, tid, fb);
-        }
-    };
-    if (nk > 0) fetch_both(kb);
-    for (int kt = 0; kt < nk; ++kt) {
-        x3_stash<!TA>(As, tid, fa);
-        x3_stash<TB>(Bs, tid, fb);
-        __syncthreads();
-        if (kt + 1 < nk) fetch_both(kb + (kt + 1) * X3K);
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 a[2][3], b[2][3];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int ra = wm + i * 32 + lrow, rb = wn + i * 32 + lrow, ch = 2 * ks + lk;
-                const int offa = ra * X3LD + ((ch ^ ((ra >> 4) & 3)) << 3), offb = rb * X3LD + ((ch ^ ((rb >> 4) & 3)) << 3);
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    a[i][p] = *reinterpret_cast<const bf16x8*>(As + p * X3PLANE + offa);
-                    b[i][p] = *reinterpret_cast<const bf16x8*>(Bs + p * X3PLANE + offb);
-                }
-            }
-            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-            for (int t = 0; t < 6; ++t)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        f32x16& d = t < 5 ? low[i][j] : acc[i][j];
-                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][PA[t]], b[j][PB[t]], d, 0, 0, 0);
-                    }
-        }
-        __syncthreads();
+    // loads without checks where the tile lies inside both operands and out of reach of their masks
+    const bool inner = avec && bvec && m0 + BM <= g.M && n0 + BN <= g.N && (!g.a_unit_lower || (!TA && m0 >= ke)) &&
+                       (g.b_unit_lower_cols == 0 || (TB && n0 >= ke));
+    if (split) {
+        multiply_x3<TA, TB>(oa, ob, inner, m0, n0, kb, ke, As, Bs, tid, wm, wn, lrow, lk, acc);
+    } else {            // an operand entry has no split (see GemmF32::guard)
+        constexpr int BK = 16;
+        static_assert(2 * BK * (BM + 4) * sizeof(float) <= 3 * X3PLANE * sizeof(bf16_t), "both buffers in an operand's planes");
+        multiply_f32<TA, TB, BM, BN, 2, BK>(oa, ob, inner, m0, n0, kb, ke, reinterpret_cast<float (*)[BK][BM + 4]>(As),
+                                            reinterpret_cast<float (*)[BK][BN + 4]>(Bs), tid, wm, wn, lrow, lk, acc);
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] += low[i][j][v];
     if (in_parts) {
         float* t = g.tail + (long)(bid - whole) * (BM * BN) + (wm + 4 * lk) * BN + wn + lrow;
 #pragma unroll
@@ -673,10 +695,7 @@ hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t s) {
         case 3: return launch_gemm_f32_tile<64, 64, 1, 32>(g, s);
         default:
             // a caller that allows it gets the products of this tile size from split operands
-            if (g.x3) {
-                const hipError_t e = launch_gemm_f32x3(g, s);
-                if (e != hipSuccess || g.guard == nullptr) return e;
-            }
+            if (g.x3) return launch_gemm_f32x3(g, s);
             return launch_gemm_f32_tile<128, 128, 2, 16>(g, s);
     }
 }

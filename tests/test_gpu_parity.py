@@ -2006,10 +2006,11 @@ def test_heads_qr_and_backward_orders(n):
         c.close()
 
 
-@pytest.mark.parametrize("where", ["none", "X inf", "X nan", "X huge", "R inf"])
+@pytest.mark.parametrize("where", ["none", "X inf", "X nan", "X huge", "X tiny", "R inf", "R tiny", "Y large"])
 def test_rotate_fp32_split_operands(where):
     """fp32 activations large enough for the products on split operands: finite values agree with the fp32 matrix cores
-    within rounding; a value that has no split sends both products back there, bit for bit."""
+    within rounding; a value that has no split sends both products back there, bit for bit, and so does a loss so small
+    that the derivative may hold no other (then the gradient's product alone: Y = X is exact either way)."""
     n, T = 1028, 4099
     g = torch.Generator(device="cuda")
     g.manual_seed(77)
@@ -2021,8 +2022,15 @@ def test_rotate_fp32_split_operands(where):
         X[17, 1025] = float("nan")
     elif where == "X huge":
         X[4000, 3] = 3.39e38
+    elif where == "X tiny":
+        X[2049, 511] = -(2.0 ** -103)
     elif where == "R inf":
         R[n - 1, 5] = float("inf")
+    elif where == "R tiny":
+        R[511, n - 1] = 2.0 ** -120
+    elif where == "Y large":
+        X = 75.0 + 14.0 * torch.rand(T, n, device="cuda", generator=g)
+        R = torch.eye(n, device="cuda")
     out = {}
     c = B.Context()
     try:
@@ -2033,12 +2041,68 @@ def test_rotate_fp32_split_operands(where):
             c.dq_rotate_loss_grad(X, B.DQ_F32, R, B.DQ_REDUCE_TOKEN_MEAN, loss, G)
             out[mode] = (loss, G)
         if where == "none":
+            assert not torch.equal(out[1][1], out[0][1])      # another kernel has run
             assert abs(out[1][0].item() - out[0][0].item()) < 1e-6 * abs(out[0][0].item())
             # a sign of Y at rounding level flips: about T n 2 phi(0) 1e-6 of the entries, each worth 2 x_t / T in its column
             assert float((out[1][1] - out[0][1]).norm() / out[0][1].norm()) < 5e-3
         else:
             for a, b in zip(out[0], out[1]):
                 assert torch.equal(a.nan_to_num(7.0, 8.0, 9.0), b.nan_to_num(7.0, 8.0, 9.0))
+    finally:
+        torch.cuda.synchronize()
+        c.close()
+
+
+def _copied_to_f32(a, ld):
+    """The fp32 rounding of a device matrix, with leading dimension ld."""
+    _, d = padded(a.shape[0], a.shape[1], ld)
+    return d.copy_(a)
+
+
+@pytest.mark.parametrize("what", ["backward", "cayley"])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -118])
+def test_split_products_of_small_values(what, scale):
+    """The products of S6 and of the Cayley update keep the fp32 matrix cores' accuracy where an operand of the caller's has
+    values whose third term would lie below the smallest bf16 value.  The strictly lower part of U is not looked at."""
+    n = 1290
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31)
+    R = torch.linalg.qr(torch.randn(n, n, device="cuda", generator=g, dtype=torch.float64))[0]
+    U = torch.eye(n, device="cuda", dtype=torch.float64) + torch.triu(
+        torch.randn(n, n, device="cuda", generator=g, dtype=torch.float64)) * 0.02
+    G = torch.randn(n, n, device="cuda", generator=g, dtype=torch.float64) * scale
+    R, U, G = (_copied_to_f32(a, 1292) for a in (R, U, G))
+    err, got = {}, {}
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 64, B.DQ_F32)
+        R6, U6, G6 = R.double(), U.double(), G.double()
+        if what == "cayley":
+            W = -G6 @ R6.T.contiguous()
+            W = W - 0.5 * R6 @ (R6.T.contiguous() @ W)
+            ref = (W - W.T) @ R6
+        else:
+            P = R6.T.contiguous() @ G6
+            P = torch.tril(P - P.T, -1)
+            ref = R6 @ torch.linalg.solve_triangular(U6, P.T.contiguous(), upper=True).T
+        i = torch.arange(n, device="cuda")
+        U[i[:, None] > i[None, :]] = float("nan")
+        for mode in (0, 1):
+            c.dq_set_option(B.DQ_OPT_SPLIT_GEMM, mode)
+            if what == "cayley":
+                Rc, M = _copied_to_f32(R6, 1296), _copied_to_f32(0 * R6, 1292)
+                c.dq_cayley_update(Rc, G, M, 1e-3)
+                got[mode] = M.clone()
+            else:
+                dZ = _copied_to_f32(0 * R6, 1292)
+                c.dq_qr_backward(R, U, G, dZ)
+                got[mode] = dZ.clone()
+            err[mode] = float((got[mode].double() - ref).norm() / ref.norm())
+        if scale == 1.0:
+            assert not torch.equal(got[0], got[1]) and err[1] < err[0]
+        else:
+            assert err[1] < 1.1 * err[0]
+        assert c.dq_device_flags() == 0
     finally:
         torch.cuda.synchronize()
         c.close()
