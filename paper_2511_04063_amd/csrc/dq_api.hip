@@ -824,13 +824,22 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
     const bool g_transposed = xdt == DQ_BF16 && n % 128 == 0 && T % 128 == 0 && (n / 128) * (n / 128) >= 256 &&
                               (ldx & 7) == 0 && aligned16(X) && aligned16(G) && (ldg & 3) == 0;
     bool fused = false;   // S4 done in the epilogue of S3
+    // split of S5's reduction over the tokens when the n x n output has few tiles
+    int splits, kchunk;
+    {
+        int max_splits = (int)(L.gsplit_floats / ((size_t)n * L.ld));
+        if (max_splits > kMaxSplit) max_splits = kMaxSplit;
+        if (max_splits < 1) max_splits = 1;
+        choose_split(((n + 127) / 128) * ((n + 127) / 128), T, 32, max_splits, splits, kchunk);
+    }
     // fp32 activations: both products on split operands, if a scan of X and R finds none that has no split (an infinite
     // activation gives a finite loss on the fp32 matrix cores, a NaN from split terms).  The scan costs some 10 us; from 4e9
     // multiplications on (100 us on the fp32 matrix cores) it pays: 4099 x 1536 471 -> 300 us for S3 and S5.  Eq. 4's derivative is
     // finite wherever Y is; of the other objectives that is not known.  Its entries may be tiny, but the largest is no less
     // than the loss divided by the count: with a sum of exp(-|y|) of 1 or more, what entries below 2^-110 lose does not show in G.
+    const bool split_y = gemm_f32_split_applies(T, n, 1), split_g = gemm_f32_split_applies(n, n, splits);
     unsigned* guard = nullptr;
-    if (xdt == DQ_F32 && c->split_gemm != 0 && c->objective == DQ_OBJ_WHIP && gemm_flops >= 8e9) {
+    if (xdt == DQ_F32 && c->split_gemm != 0 && c->objective == DQ_OBJ_WHIP && gemm_flops >= 8e9 && (split_y || split_g)) {
         guard = at<unsigned>(c, L.guard);
         const ScanList list{{{static_cast<const float*>(X), ldx, T}, {R, ldr, n}}};
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * ((double)T + n));
@@ -872,7 +881,7 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
         g.A = static_cast<const float*>(X); g.lda = ldx; g.ta = 0;
         g.B = R; g.ldb = ldr; g.tb = 0;
         g.C = Y; g.ldc = ldy; g.M = T; g.N = n; g.K = n;
-        if (guard != nullptr && gemm_f32_split_applies(T, n, 1)) {
+        if (guard != nullptr && split_y) {
             g.x3 = 1;
             g.guard = guard;
         }
@@ -893,14 +902,8 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
         DQ_HIP(launch_loss_finish(lpart, grid, scale, loss_dev, flags, s, 1, guard));
     }
-    // S5: G = X^T @ dY (reduction over the tokens; split when the n x n output has few tiles)
+    // S5: G = X^T @ dY (reduction over the tokens)
     {
-        const int tiles = ((n + 127) / 128) * ((n + 127) / 128);
-        int max_splits = (int)(L.gsplit_floats / ((size_t)n * L.ld));
-        if (max_splits > kMaxSplit) max_splits = kMaxSplit;
-        if (max_splits < 1) max_splits = 1;
-        int splits, kchunk;
-        choose_split(tiles, T, 32, max_splits, splits, kchunk);
         float* gs = at<float>(c, L.gsplit);
         float* out = splits > 1 ? gs : G;
         const long ldo = splits > 1 ? L.ld : ldg;
@@ -937,7 +940,7 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
             g.B = static_cast<const float*>(dY); g.ldb = lddy; g.tb = 0;
             g.C = out; g.ldc = ldo; g.M = n; g.N = n; g.K = T;
             g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
-            if (guard != nullptr && gemm_f32_split_applies(n, n, splits)) {
+            if (guard != nullptr && split_g) {
                 g.x3 = 1;
                 g.guard = guard;
             }

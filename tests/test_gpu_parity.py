@@ -2106,3 +2106,24 @@ def test_split_products_of_small_values(what, scale):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+def test_no_scan_where_no_product_is_split():
+    """A narrow fp32 block, however long, has no product that the split-operand tiles would take: it is not scanned for one."""
+    n, T = 64, 1 << 20
+    X = torch.randn(T, n, device="cuda")
+    R = torch.linalg.qr(torch.randn(n, n, device="cuda"))[0].contiguous()
+    loss, G = torch.zeros(1, device="cuda"), torch.zeros(n, n, device="cuda")
+    launches = {}
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, T, B.DQ_F32)
+        for mode in (0, 1):
+            c.dq_set_option(B.DQ_OPT_SPLIT_GEMM, mode)
+            c.dq_profile_enable(1 << B.DQ_K_SMALL)
+            c.dq_rotate_loss_grad(X, B.DQ_F32, R, B.DQ_REDUCE_TOKEN_MEAN, loss, G)
+            launches[mode] = c.dq_profile_read(B.DQ_K_SMALL)["launches"]
+        assert launches[1] == launches[0]
+    finally:
+        torch.cuda.synchronize()
+        c.close()
