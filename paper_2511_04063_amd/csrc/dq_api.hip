@@ -970,6 +970,15 @@ bool backward_uses_splits(const dq_ctx* c, const Layout& L, int n) {
     return c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && L.ld == n && (c->split_gemm == 2 || n % kPlanesN == 0);
 }
 
+// Outer blocks of kTrsmOuter columns that the solve works on; what they leave over goes by blocks of kTrsmBlock.  The explicit
+// inverse of a wider block is a little less accurate (n = 1000: dZ 7.6e-7 -> 8.0e-7 of its norm): an order that is no multiple
+// takes them where the products on split operands, whose errors are a third of the fp32 ones, more than make up for it (n =
+// 1200 7.8e-7 -> 5.4e-7, 2890 1.1e-6 -> 6.4e-7) and the longer updates pay (n = 2890: 23 pairs of launches, 0.43 ms, before).
+int solve_outer_blocks(const dq_ctx* c, int n) {
+    const bool wide = n % kTrsmOuter == 0 || (c->split_gemm != 0 && gemm_f32_split_applies(n, n, 1));
+    return wide ? n / kTrsmOuter : 0;
+}
+
 dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R, long ldr, const float* U, long ldu,
                               hipStream_t s) {
     unsigned* flags = at<unsigned>(c, L.flags);
@@ -985,13 +994,13 @@ dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R,
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 8.0 * n * (double)kTrsmBlock);
         DQ_HIP(launch_trinv_blocks(U, ldu, n, uinv, flags, s));
     }
-    if (n >= kTrsmOuter) {
+    const int nouter = solve_outer_blocks(c, n);
+    if (nouter > 0) {
         // The inverses of the whole 512 x 512 diagonal blocks are merged from the 128 x 128 ones, inv [[A, B], [0, C]] =
         // [[A^-1, -A^-1 B C^-1], [0, C^-1]], two levels of batched products.
         float* uo = at<float>(c, L.uinvo);
         float* t1 = at<float>(c, L.utmp);                               // n / 256 blocks of 128 x 128
         float* t2 = t1 + (size_t)n * 64;                                // n / 512 blocks of 256 x 256
-        const int nouter = n / kTrsmOuter;
         const long so = (long)kTrsmOuter * kTrsmOuter;
         {
             LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * (double)kTrsmOuter);
@@ -1098,10 +1107,9 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         DQ_HIP(launch_skew_lower(Bb, ld, n, Pb, ld, Mb, ld, s));
     }
     if (joined != nullptr) DQ_HIP(hipStreamWaitEvent(s, joined, 0));
-    // What a multiple of kTrsmOuter leaves over, the last columns, is solved by blocks of kTrsmBlock (one by one over the
-    // whole width such blocks took 0.43 ms at n = 2890), the rest by blocks of kTrsmOuter.
+    // the last columns, which the outer blocks leave over, by blocks of kTrsmBlock
     const int nblk = (n + kTrsmBlock - 1) / kTrsmBlock;
-    const int nouter = n / kTrsmOuter;
+    const int nouter = solve_outer_blocks(c, n);
     for (int j = nblk - 1; j >= nouter * (kTrsmOuter / kTrsmBlock); --j) {
         const int j0 = j * kTrsmBlock;
         const int w = (n - j0) < kTrsmBlock ? (n - j0) : kTrsmBlock;

@@ -2127,3 +2127,31 @@ def test_no_scan_where_no_product_is_split():
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n", [700, 1000, 1100])
+def test_qr_backward_solve_is_as_accurate_as_narrow_blocks(n):
+    """The triangular solve of S6 at orders below the split-operand products: with R = I, dZ U^T = P, and the residual is that
+    of a solve by blocks of 128 columns with exact inverses in fp32 (the sums' order moves it by a few per cent; by blocks
+    of 512 it is a third larger)."""
+    g = rng(5200 + n)
+    U = (np.eye(n) + 0.02 * np.triu(g.standard_normal((n, n)), 1)).astype(np.float32)
+    G = g.standard_normal((n, n)).astype(np.float32)
+    P = np.tril(G - G.T, -1)
+    M, rest = np.zeros_like(P), P.copy()
+    for j0 in reversed(range(0, n, 128)):
+        j1 = min(n, j0 + 128)
+        M[:, j0:j1] = rest[:, j0:j1] @ np.linalg.inv(U[j0:j1, j0:j1].astype(np.float64)).astype(np.float32).T
+        rest[:, :j0] -= M[:, j0:j1] @ U[:j0, j0:j1].T
+    def residual(x):
+        return np.linalg.norm(x.astype(np.float64) @ U.T.astype(np.float64) - P) / np.linalg.norm(P)
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 64, B.DQ_F32)
+        dZ = torch.zeros((n, n), device="cuda")
+        c.dq_qr_backward(torch.eye(n, device="cuda"), dev(U), dev(G), dZ)
+        assert residual(dZ.cpu().numpy()) < 1.15 * residual(M)
+        assert c.dq_device_flags() == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
