@@ -1035,10 +1035,10 @@ dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R,
     return DQ_OK;
 }
 
-// The same on the second stream, beside S3 .. S5 of a fused step or R^T G of S6; the caller's stream waits for *joined before
-// the solve.  Where the products of S6 run on splits made beforehand (large n), the preparation is bandwidth that the products
-// beside it need and stays in line; below, it is a chain of up to eight short launches, 60 to 100 us, that leaves the chip
-// idle (steps at n = 256 459 -> 435 us, 1024 1463 -> 1393 us).  *joined stays null where it was left in line.
+// The same on the second stream, beside S3 .. S5 of a fused step; the caller's stream waits for *joined before the solve.
+// Where the products of S6 run on splits made beforehand (large n), the preparation is bandwidth that the products beside it
+// need and stays in line; below, it is a chain of up to eight short launches, 60 to 100 us, that leaves the chip idle (steps
+// at n = 256 459 -> 435 us, 1024 1463 -> 1393 us).  *joined stays null where it was left in line.
 dq_status qr_backward_prepare_early(dq_ctx* c, const Layout& L, int n, const float* R, long ldr, const float* U, long ldu,
                                     hipEvent_t* joined) {
     *joined = nullptr;
@@ -1054,7 +1054,9 @@ dq_status qr_backward_prepare_early(dq_ctx* c, const Layout& L, int n, const flo
 // dZ = R P U^{-T},  P = strict_lower(R^T G - G^T R).  The triangular solve M U^T = P runs right-looking over
 // column blocks from the last to the first; M is strictly lower triangular, so every product skips its zero part.
 // joined: qr_backward_prepare has been enqueued for this R and U on another stream, this one waits for the event before the
-// solve; null: it is done here.
+// solve; null: it is done here, beside R^T G where that takes long enough to hide it and the events (n = 1290 338 -> 322 us,
+// 1536 316 -> 299, 2890 1014 -> 957), in line for small orders (192 60 -> 54 us, 640 136 -> 132, 1024 201 -> 196; ragged ones
+// gain 3 % from 900 on) and for large ones, whose R^T G then finishes later by more (5120 3020 -> 2860, 6144 4870 -> 4700).
 dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, long ldr, const float* U, long ldu,
                           const float* G, long ldg, float* dZ, long lddz, float* Zupd, long ldz, float lr,
                           hipEvent_t joined = nullptr) {
@@ -1067,7 +1069,8 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * (double)n);
         DQ_HIP(launch_range_scan(ScanList{{{G, ldg, n}, {}}}, n, guard, s));
     }
-    if (joined == nullptr) DQ_TRY(qr_backward_prepare_early(c, L, n, R, ldr, U, ldu, &joined));
+    const bool beside = n < 5120 && (gemm_f32_split_applies(n, n, 1) || (n >= 896 && n % 128 != 0));
+    if (joined == nullptr && beside) DQ_TRY(qr_backward_prepare_early(c, L, n, R, ldr, U, ldu, &joined));
     if (joined == nullptr) DQ_TRY(qr_backward_prepare(c, L, n, R, ldr, U, ldu, s));
     float* Bb = at<float>(c, L.B);
     float* Pb = at<float>(c, L.P);
