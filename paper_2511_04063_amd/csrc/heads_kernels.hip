@@ -23,7 +23,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int HN = kHeadDim;     // largest matrix size of this path
 
-__device__ __forceinline__ float wave_total(float v) {
+__device__ __forceinline__ double wave_total(double v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
     return v;
@@ -268,7 +268,7 @@ __device__ __forceinline__ void stash_x(bf16_t* Xs, int tid, const XRegs r) {
 // EVEN: every tile holds 64 tokens; otherwise only the first `tokens` rows of the last one are tokens.
 template <int JB, bool EVEN>
 __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const bf16x8 (&rhi)[2 * JB],
-                                           const bf16x8 (&rlo)[2 * JB], f32x16 (&accG)[JB], float& lsum, float scale,
+                                           const bf16x8 (&rlo)[2 * JB], f32x16 (&accG)[JB], double& loss, float scale,
                                            int tokens, int wave, int lrow, int lk) {
     constexpr int XLD = xld<JB>();
     f32x16 y0, y1;
@@ -292,6 +292,7 @@ __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const 
         }
     }
     const int j = 32 * wave + lrow;
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};   // eight terms each, then to 64 bits
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
@@ -302,7 +303,7 @@ __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const 
             for (int q = 0; q < 4; ++q) {
                 const float y = i == 0 ? y0[4 * g + q] : y1[4 * g + q];
                 const float ex = __expf(-fabsf(y));
-                lsum += ex;
+                sum[q] += ex;
                 // scale * sgn(y) without comparisons: y * 2^126 has modulus >= 1 for every normal y (an overflow to
                 // infinity is as good), so the median with -scale and +scale picks the signed bound; y = 0 stays 0
                 const float sg = __builtin_amdgcn_fmed3f(y * 8.507059173e37f, -scale, scale);
@@ -314,6 +315,7 @@ __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const 
                 make_uint2(__builtin_bit_cast(uint32_t, b01), __builtin_bit_cast(uint32_t, b23));
         }
     }
+    loss += (double)((sum[0] + sum[1]) + (sum[2] + sum[3]));
     __syncthreads();
     const int ch = 32 * wave + lrow;   // this lane's row of G
 #pragma unroll
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(64 * JB, 2) void heads_rlg_kernel(const bf16_t* __r
     constexpr int NP = 32 * JB;
     __shared__ __attribute__((aligned(16))) bf16_t Xs[2][TT * xld<JB>()];
     __shared__ __attribute__((aligned(16))) bf16_t dYs[NP * DLD];
-    __shared__ float wsum[JB];
+    __shared__ double wsum[JB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, lk = lane >> 5;
     const int split = blockIdx.x, prob = blockIdx.y, splits = gridDim.x;
     const bf16_t* Xp = X + (long)prob * sx;
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(64 * JB, 2) void heads_rlg_kernel(const bf16_t* __r
     for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) accG[jb][v] = 0.f;
-    float lsum = 0.f;
+    double lsum = 0.0;
 
     XRegs p0 = fetch_x<JB, EXACT>(Xp, ldx, tbeg, tend, n, tid);
     XRegs p1 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + TT, tend, n, tid);
@@ -408,13 +410,13 @@ __global__ __launch_bounds__(64 * JB, 2) void heads_rlg_kernel(const bf16_t* __r
         for (int v = 0; v < 16; ++v)
             Gp[(32 * wave + 8 * (v >> 2) + 4 * lk + (v & 3)) * NP + jb * 32 + lrow] = accG[jb][v];
     // columns from n on hold y = 0 throughout: they count nothing
-    lsum = wave_total(EXACT || 32 * wave + lrow < n ? lsum : 0.f);
+    lsum = wave_total(EXACT || 32 * wave + lrow < n ? lsum : 0.0);
     if (lane == 0) wsum[wave] = lsum;
     __syncthreads();
     if (tid == 0) {
         double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < JB; ++w) t += (double)wsum[w];
+        for (int w = 0; w < JB; ++w) t += wsum[w];
         lpart[(long)prob * splits + split] = t;
     }
 }

@@ -2155,3 +2155,22 @@ def test_qr_backward_solve_is_as_accurate_as_narrow_blocks(n):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n,T,y", [(20, 16384, 0.375), (64, 16384, 0.625), (80, 16384, 1.5), (112, 16300, 0.25), (128, 16384, 0.375)])
+def test_small_rotation_loss_of_equal_terms(n, T, y):
+    """A sum of equal terms, whose fp32 rounding errors all point the same way: exp(-y) to its last bit or two, eight of them in
+    fp32 (four roundings) before the wider sum, where a thousand were off by 1e-6 and more."""
+    X = torch.zeros((1, T, -(-n // 8) * 8), dtype=torch.bfloat16, device="cuda")
+    X[..., 0] = 1.0
+    R = torch.zeros((1, n, -(-n // 4) * 4), device="cuda")
+    R[:, 0] = y
+    loss, G = torch.zeros(1, device="cuda"), torch.zeros((1, n, -(-n // 4) * 4), device="cuda")
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, T, B.DQ_BF16)
+        c.dq_rotate_loss_grad(X[..., :n], B.DQ_BF16, R[..., :n], B.DQ_REDUCE_TOKEN_MEAN, loss, G[..., :n])
+        assert abs(loss.item() / (n * np.exp(-y)) - 1.0) < 6e-7
+    finally:
+        torch.cuda.synchronize()
+        c.close()
