@@ -92,7 +92,7 @@ dq_status dq_destroy(dq_ctx* ctx);
  * x_dtype is the storage type of X.  *out receives the size.  Problems of a batch run one after
  * another and share the workspace, except for n <= 128 (per-head rotations): there all b problems
  * run in the same kernel launches and the size grows with b (7 matrices of 64 KiB and up to
- * max(8, ceil(T/2048)) partial gradients per problem); with a smaller workspace such a batch runs in
+ * max(16, ceil(T/1024)) partial gradients per problem); with a smaller workspace such a batch runs in
  * groups.  A batch gives the same bits as its problems run one by one. */
 dq_status dq_workspace_bytes(int b, int n, int T, dq_dtype x_dtype, size_t* out);
 

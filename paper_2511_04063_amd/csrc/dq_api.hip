@@ -1318,11 +1318,11 @@ struct HeadsLayout {
     size_t R = 0, U = 0, G = 0, dZ = 0, gpart = 0, lpart = 0, total = 0;
 };
 
-HeadsLayout make_heads_layout(size_t base, int b, int T) {
+HeadsLayout make_heads_layout(size_t base, int b, int T, int n) {
     HeadsLayout H;
     size_t cur = base;
     const size_t mat = (size_t)(b > 0 ? b : 1) * kHeadDim * kHeadDim * 4;
-    const size_t sp = (size_t)heads_splits(T > 0 ? T : 1);
+    const size_t sp = (size_t)heads_splits(T > 0 ? T : 1, n);
     H.R = bump(cur, mat);
     H.U = bump(cur, mat);
     H.G = bump(cur, mat);
@@ -1345,10 +1345,10 @@ bool heads_fused_route(const dq_ctx* c, int n, dq_dtype xdt) {
 
 // Problems of a batch that the workspace holds at a time (a workspace sized for fewer problems than the call has still
 // serves it, group by group, with the same bits); 0: not even one.
-int heads_group(const dq_ctx* c, size_t base, int b, int T) {
+int heads_group(const dq_ctx* c, size_t base, int b, int T, int n) {
     if (c->ws == nullptr) return 0;
     int g = b > 0 ? b : 1;
-    while (g > 0 && c->ws_bytes < make_heads_layout(base, g, T).total) --g;
+    while (g > 0 && c->ws_bytes < make_heads_layout(base, g, T, n).total) --g;
     return g;
 }
 
@@ -1391,7 +1391,7 @@ dq_status heads_backward(dq_ctx* c, int b, int n, const float* R, long ldr, cons
 dq_status heads_step(dq_ctx* c, const Layout& L, int b, int T, int n, const void* X, dq_dtype xdt, long ldx, const float* Z,
                      long ldz, dq_reduce red, float* loss_dev, float* R, long ldr, float* dZ, long lddz, float* Zupd,
                      float lr) {
-    const HeadsLayout H = make_heads_layout(L.total, b, T);
+    const HeadsLayout H = make_heads_layout(L.total, b, T, n);
     float* Rh = R ? R : at<float>(c, H.R);
     const long ldrh = R ? ldr : kHeadDim;
     float* Uh = at<float>(c, H.U);
@@ -1481,7 +1481,7 @@ dq_status dq_workspace_bytes(int b, int n, int T, dq_dtype x_dtype, size_t* out)
     DQ_TRY(check_n(n));
     if (x_dtype != DQ_F32 && x_dtype != DQ_BF16) return DQ_ERR_DTYPE;
     const Layout L = make_layout(n, T);
-    *out = n <= kHeadDim ? make_heads_layout(L.total, b, T).total : L.total;
+    *out = n <= kHeadDim ? make_heads_layout(L.total, b, T, n).total : L.total;
     return DQ_OK;
 }
 
@@ -1539,9 +1539,9 @@ dq_status dq_rotate_loss_grad(dq_ctx* c, int b, int T, int n, const void* X, dq_
     const Layout L = make_layout(n, T);
     DQ_TRY(check_ws(c, L));
     if (heads_fused_route(c, n, xdt) && Y == nullptr && dY == nullptr) {
-        const int gb = heads_group(c, L.total, b, T);
+        const int gb = heads_group(c, L.total, b, T, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
-        const HeadsLayout H = make_heads_layout(L.total, gb, T);
+        const HeadsLayout H = make_heads_layout(L.total, gb, T, n);
         for (int i = 0; i < b; i += gb)
             DQ_TRY(heads_rotate_loss_grad(c, H, b - i < gb ? b - i : gb, n, T, static_cast<const bf16_t*>(X) + (long)i * T * ldx,
                                           ldx, R + (long)i * n * ldr, ldr, red, loss_dev + i, G + (long)i * n * ldg, ldg));
@@ -1574,7 +1574,7 @@ dq_status dq_calib_step(dq_ctx* c, int b, int T, int n, const void* X, dq_dtype 
     DQ_TRY(check_ws(c, L));
     const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
     if (heads_route(c, n)) {
-        const int gb = heads_group(c, L.total, b, T);
+        const int gb = heads_group(c, L.total, b, T, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
         for (int i = 0; i < b; i += gb) {
             float* Zi = Z + (long)i * n * ldz;
@@ -1798,7 +1798,7 @@ dq_status dq_qr_backward(dq_ctx* c, int b, int n, const float* R, long ldr, cons
     const Layout L = make_layout(n, 1);
     DQ_TRY(check_ws(c, L));
     if (heads_route(c, n)) {
-        const int gb = heads_group(c, L.total, b, 1);
+        const int gb = heads_group(c, L.total, b, 1, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
         return heads_backward(c, b, n, R, ldr, U, ldu, G, ldg, dZ, lddz, nullptr, 0, 0.f);
     }
@@ -1918,9 +1918,9 @@ dq_status dq_calib_step_adam(dq_ctx* c, int b, int T, int n, const void* X, dq_d
     const float c1 = (float)(1.0 / (1.0 - pow((double)beta1, (double)step)));
     const float c2 = (float)(1.0 / (1.0 - pow((double)beta2, (double)step)));
     if (heads_route(c, n)) {
-        const int gb = heads_group(c, L.total, b, T);
+        const int gb = heads_group(c, L.total, b, T, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
-        float* dZh = at<float>(c, make_heads_layout(L.total, gb, T).dZ);
+        float* dZh = at<float>(c, make_heads_layout(L.total, gb, T, n).dZ);
         for (int i = 0; i < b; i += gb) {
             const int g = b - i < gb ? b - i : gb;
             const long r0 = (long)i * n;

@@ -252,8 +252,8 @@ hipError_t launch_heads_backward(int b, int n, const float* R, long ldr, long sr
                                  const float* U, long ldu, long su, float alpha, float beta, float* out, long ldo, long so,
                                  unsigned* flags, hipStream_t s);
 // loss[i] = scale * sum exp(-|X_i R_i|) and G_i = X_i^T dY_i for bf16 X_i (T x n), fused.  Gpart needs
-// b * heads_splits(T) * 128 * 128 floats, lpart b * heads_splits(T) doubles.
-int heads_splits(int T);
+// b * heads_splits(T, n) * 128 * 128 floats, lpart b * heads_splits(T, n) doubles.
+int heads_splits(int T, int n);
 hipError_t launch_heads_rlg(int b, int n, int T, const bf16_t* X, long ldx, long sx, const float* R, long ldr, long sr,
                             float scale, float* Gpart, double* lpart, float* G, long ldg, long sg, float* loss,
                             unsigned* flags, hipStream_t s);

@@ -227,38 +227,66 @@ template <int JB> constexpr int xld() { return 32 * JB + 8; }   // halfwords per
 
 struct XRegs { uint4 q0, q1, q2, q3; };
 
-// columns [col, col + 8) of one row; columns from n on read as zero (EXACT: there are none, n == 32 JB)
-template <bool EXACT>
-__device__ __forceinline__ uint4 load8(const bf16_t* p, int col, int n) {
-    if (EXACT || col + 8 <= n) return *reinterpret_cast<const uint4*>(p);
+// A thread's share of a tile: columns [col, col + 8) of the rows row0 + 16 i.  n no multiple of 32 (not EXACT): what lies beyond
+// column n is masked on the way to LDS, where the loads have arrived anyway (a test or a mask at the load waits for it there and
+// then: n = 100 on 16384 tokens 134 us).  A piece that the last column cuts short is read whole, its row goes on for ldx
+// elements, a multiple of 8; only that of the last row, which may end where the buffer ends, is read element by element.
+template <int JB, bool EXACT>
+struct XPiece {
+    int col, row0;
+    bool cut;
+    uint4 mask;
+    __device__ __forceinline__ XPiece(int n, int tid) {
+        col = tid % (4 * JB) * 8;
+        row0 = tid / (4 * JB);
+        cut = !EXACT && col < n && col + 8 > n;
+        auto m = [&](int c) { return (EXACT || c < n ? 0xffffu : 0u) | (EXACT || c + 1 < n ? 0xffff0000u : 0u); };
+        mask = make_uint4(m(col), m(col + 2), m(col + 4), m(col + 6));
+        if (!EXACT && col >= n) col = 0;    // (masked)
+    }
+};
+
+__device__ __forceinline__ uint4 load_cut(const bf16_t* p, int count) {
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int e = 0; e < 8; ++e)
-        if (col + e < n) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+        if (e < count) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// tile rows [t0, t0 + 64) of X (tokens >= tend and columns >= n read as zero): 4 JB threads per row, 16 bytes each
+// tile rows [t0, t0 + 64) of X (tokens >= tend read as zero): 4 JB threads per row, 16 bytes each; T: its rows
 template <int JB, bool EXACT>
-__device__ __forceinline__ XRegs fetch_x(const bf16_t* __restrict__ Xp, long ldx, int t0, int tend, int n, int tid) {
-    const int col = (tid % (4 * JB)) * 8, row = t0 + tid / (4 * JB);
-    const bf16_t* p = Xp + (long)row * ldx + col;
+__device__ __forceinline__ XRegs fetch_x(const bf16_t* __restrict__ Xp, long ldx, int t0, int tend, int T, int n,
+                                         const XPiece<JB, EXACT>& x) {
+    const int row = t0 + x.row0;
+    const bf16_t* p = Xp + (long)row * ldx + x.col;
+    const int last = x.cut ? T - 1 : T;     // first row that is not read whole
+    const int end = tend < last ? tend : last;
     XRegs r;
     r.q0 = r.q1 = r.q2 = r.q3 = make_uint4(0u, 0u, 0u, 0u);
-    if (row < tend) r.q0 = load8<EXACT>(p, col, n);
-    if (row + 16 < tend) r.q1 = load8<EXACT>(p + 16 * ldx, col, n);
-    if (row + 32 < tend) r.q2 = load8<EXACT>(p + 32 * ldx, col, n);
-    if (row + 48 < tend) r.q3 = load8<EXACT>(p + 48 * ldx, col, n);
+    if (row < end) r.q0 = *reinterpret_cast<const uint4*>(p);
+    if (row + 16 < end) r.q1 = *reinterpret_cast<const uint4*>(p + 16 * ldx);
+    if (row + 32 < end) r.q2 = *reinterpret_cast<const uint4*>(p + 32 * ldx);
+    if (row + 48 < end) r.q3 = *reinterpret_cast<const uint4*>(p + 48 * ldx);
+    if (!EXACT && t0 <= T - 1 && T - 1 < t0 + TT && T == tend) {    // (uniform) the tile holds the last row
+        if (x.cut && row == T - 1) r.q0 = load_cut(p, n - x.col);
+        if (x.cut && row + 16 == T - 1) r.q1 = load_cut(p + 16 * ldx, n - x.col);
+        if (x.cut && row + 32 == T - 1) r.q2 = load_cut(p + 32 * ldx, n - x.col);
+        if (x.cut && row + 48 == T - 1) r.q3 = load_cut(p + 48 * ldx, n - x.col);
+    }
     return r;
 }
-template <int JB>
-__device__ __forceinline__ void stash_x(bf16_t* Xs, int tid, const XRegs r) {
+template <int JB, bool EXACT>
+__device__ __forceinline__ void stash_x(bf16_t* Xs, int tid, XRegs r, const XPiece<JB, EXACT>& x) {
     constexpr int XLD = xld<JB>();
     bf16_t* p = Xs + (tid / (4 * JB)) * XLD + (tid % (4 * JB)) * 8;
-    *reinterpret_cast<uint4*>(p) = r.q0;
-    *reinterpret_cast<uint4*>(p + 16 * XLD) = r.q1;
-    *reinterpret_cast<uint4*>(p + 32 * XLD) = r.q2;
-    *reinterpret_cast<uint4*>(p + 48 * XLD) = r.q3;
+    auto masked = [&](uint4 q) {
+        return EXACT ? q : make_uint4(q.x & x.mask.x, q.y & x.mask.y, q.z & x.mask.z, q.w & x.mask.w);
+    };
+    *reinterpret_cast<uint4*>(p) = masked(r.q0);
+    *reinterpret_cast<uint4*>(p + 16 * XLD) = masked(r.q1);
+    *reinterpret_cast<uint4*>(p + 32 * XLD) = masked(r.q2);
+    *reinterpret_cast<uint4*>(p + 48 * XLD) = masked(r.q3);
 }
 
 // One 64-token tile.  Wavefront w forms Y[:, 32w .. 32w+32) (two 32 x 32 accumulators), applies Eq. 4 and its
@@ -385,21 +413,22 @@ __global__ __launch_bounds__(64 * JB, 2) void heads_rlg_kernel(const bf16_t* __r
         for (int v = 0; v < 16; ++v) accG[jb][v] = 0.f;
     double lsum = 0.0;
 
-    XRegs p0 = fetch_x<JB, EXACT>(Xp, ldx, tbeg, tend, n, tid);
-    XRegs p1 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + TT, tend, n, tid);
-    stash_x<JB>(Xs[0], tid, p0);
+    const XPiece<JB, EXACT> piece(n, tid);
+    XRegs p0 = fetch_x<JB, EXACT>(Xp, ldx, tbeg, tend, T, n, piece);
+    XRegs p1 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + TT, tend, T, n, piece);
+    stash_x<JB, EXACT>(Xs[0], tid, p0, piece);
     __syncthreads();
     for (int it = 0; it < ntiles; it += 2) {
         // tile `it` is in Xs[0], tile it+1 in p1; tile it+2 is requested into p0
-        p0 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + (it + 2) * TT, tend, n, tid);
+        p0 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + (it + 2) * TT, tend, T, n, piece);
         heads_tile<JB, EVEN>(Xs[0], dYs, rhi, rlo, accG, lsum, scale, tend - (tbeg + it * TT), wave, lrow, lk);
-        stash_x<JB>(Xs[1], tid, p1);
+        stash_x<JB, EXACT>(Xs[1], tid, p1, piece);
         __syncthreads();
         if (it + 1 < ntiles) {
-            p1 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + (it + 3) * TT, tend, n, tid);
+            p1 = fetch_x<JB, EXACT>(Xp, ldx, tbeg + (it + 3) * TT, tend, T, n, piece);
             heads_tile<JB, EVEN>(Xs[1], dYs, rhi, rlo, accG, lsum, scale, tend - (tbeg + (it + 1) * TT), wave, lrow, lk);
         }
-        stash_x<JB>(Xs[0], tid, p0);
+        stash_x<JB, EXACT>(Xs[0], tid, p0, piece);
         __syncthreads();
     }
 
@@ -429,9 +458,13 @@ __global__ __launch_bounds__(256) void heads_reduce_kernel(const float* __restri
     const int e = (blockIdx.x * 256 + threadIdx.x) * 4;
     const float* src = Gpart + (long)prob * splits * (np * np) + e;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s = 0; s < splits; ++s) {
-        const float4 v = *reinterpret_cast<const float4*>(src + (long)s * (np * np));
-        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    for (int s0 = 0; s0 < splits; s0 += 8) {     // eight loads in flight
+        float4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            v[k] = s0 + k < splits ? *reinterpret_cast<const float4*>(src + (long)(s0 + k) * (np * np)) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) { acc.x += v[k].x; acc.y += v[k].y; acc.z += v[k].z; acc.w += v[k].w; }
     }
     const int r = e / np, c = e % np;
     float* o = G + (long)prob * sg + (long)r * ldg + c;
@@ -632,22 +665,31 @@ hipError_t launch_heads_backward(int b, int n, const float* R, long ldr, long sr
     return hipGetLastError();
 }
 
-// Tokens per workgroup.  It depends on T alone, so that a batch and its problems one by one sum in the same order: about
-// eight parts of a block, no shorter than 256 tokens (the partial gradient a workgroup leaves costs as much as 64 tokens of
-// X) and no longer than kHeadsChunk (64 blocks of 16384 tokens then make 512 workgroups, two per compute unit).
-static int heads_chunk(int T) {
-    int c = (int)round_up((T + 7) / 8, TT);
-    if (c < 256) c = 256;
-    return c < kHeadsChunk ? c : kHeadsChunk;
+// Tokens per workgroup.  It depends on T and n alone, so that a batch and its problems one by one sum in the same order; the
+// partial gradient a workgroup leaves costs as much as 64 tokens of X, and few blocks in long parts leave the chip idle (one of
+// 16384 tokens in eight: the general route's tiles take 47 us for it at n = 80).
+//   n = 128, 96: about eight parts, 256 to 2048 tokens each: 64 blocks of 16384 tokens make 512 workgroups, two per compute unit.
+//   Others above 64: the same up to 12288 tokens, from there sixteen parts of 1024 at most, us for 1 / 32 / 64 blocks of 16384 tokens in
+//   eight and in sixteen: n = 80 74 / 83 / 99 and 45 / 63 / 117, n = 112 86 / 99 / 129 and 53 / 82 / 166 (element by element loads,
+//   eight parts: 87 / 113 / 125, 109 / 136 / 176).  At n = 96 64 blocks would lose too much, 91 -> 109.
+//   Up to 64, whose partials are small, sixteen parts, no shorter than 256 tokens above 32 (n = 64, 512 tokens, 1000 blocks: 270 us
+//   a step, in parts of 128 294) and than 128 below: 1 / 32 / 64 blocks as above n = 64 61 / 67 / 79 -> 36 / 49 / 55, n = 16 57 / 70 / 76
+//   -> 26 / 28 / 29.
+static int heads_chunk(int T, int n) {
+    const bool even = n % 32 == 0;
+    const int parts = n > 64 && (even || T <= 12288) ? 8 : 16;
+    const int lo = n > 64 ? 256 : (n > 32 ? 256 : 128), hi = n > 64 && even ? kHeadsChunk : (parts == 8 ? 1536 : 1024);
+    const int c = (int)round_up((T + parts - 1) / parts, TT);
+    return c < lo ? lo : (c < hi ? c : hi);
 }
-int heads_splits(int T) { const int c = heads_chunk(T); return (T + c - 1) / c; }
+int heads_splits(int T, int n) { const int c = heads_chunk(T, n); return (T + c - 1) / c; }
 
 hipError_t launch_heads_rlg(int b, int n, int T, const bf16_t* X, long ldx, long sx, const float* R, long ldr, long sr,
                             float scale, float* Gpart, double* lpart, float* G, long ldg, long sg, float* loss,
                             unsigned* flags, hipStream_t s) {
     if (b < 1) return hipSuccess;
     if (n < 1 || n > HN) return hipErrorInvalidValue;
-    const int splits = heads_splits(T), chunk = heads_chunk(T), jb = (n + 31) / 32;
+    const int splits = heads_splits(T, n), chunk = heads_chunk(T, n), jb = (n + 31) / 32;
     const dim3 grid(splits, b), block(64 * jb);
 #define DQ_RLG1(JB, EXACT, EVEN)                                                                                             \
     hipLaunchKernelGGL((heads_rlg_kernel<JB, EXACT, EVEN>), grid, block, 0, s, X, ldx, sx, T, n, R, ldr, sr, scale, Gpart, lpart, chunk)

@@ -2174,3 +2174,38 @@ def test_small_rotation_loss_of_equal_terms(n, T, y):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n,T", [(1, 1), (5, 129), (36, 2049), (60, 16448), (68, 260), (90, 8256), (100, 8193), (124, 4097), (127, 64)])
+def test_small_rotation_block_that_ends_with_its_last_row(n, T):
+    """A block whose buffer ends with the last element of its last row, NaN in the padding of every other row, at the edges of
+    the parts of a block: loss and gradient of a batch and of its last problem alone."""
+    b, ldx = 3, -(-n // 8) * 8 + 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + T)
+    flat = torch.full((b * T * ldx,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    X = torch.as_strided(flat, (b, T, n), (T * ldx, ldx, 1))
+    X.copy_(torch.randn(b, T, n, device="cuda", generator=g))
+    end = (b * T - 1) * ldx + n
+    X = torch.as_strided(flat[:end].clone(), (b, T, n), (T * ldx, ldx, 1))
+    _, R = padded3(b, n, n, -(-n // 4) * 4)
+    R.copy_(torch.linalg.qr(torch.randn(b, n, n, device="cuda", generator=g))[0])
+    _, G = padded3(b, n, n, -(-n // 4) * 4)
+    loss, one = torch.zeros(b, device="cuda"), torch.zeros(1, device="cuda")
+    c = B.Context()
+    try:
+        c.ensure_workspace(b, n, T, B.DQ_BF16)
+        c.dq_rotate_loss_grad(X, B.DQ_BF16, R, B.DQ_REDUCE_TOKEN_MEAN, loss, G)
+        X6, R6 = X.double(), R.double()
+        for i in range(b):
+            Y = X6[i] @ R6[i]
+            assert abs(loss[i].item() / (float(torch.exp(-Y.abs()).sum()) / T) - 1.0) < 1e-5
+            ref = X6[i].T.contiguous() @ (-torch.sign(Y) * torch.exp(-Y.abs()) / T)
+            # dY rounded to bf16 (2^-9); a sign of Y within its rounding (2^-17 |x| |r|) of zero may flip
+            assert float((G[i].double() - ref).norm() / ref.norm()) < 2e-2
+        _, G1 = padded3(1, n, n, -(-n // 4) * 4)
+        c.dq_rotate_loss_grad(X[2:], B.DQ_BF16, R[2:], B.DQ_REDUCE_TOKEN_MEAN, one, G1)
+        assert torch.equal(G1[0], G[2]) and torch.equal(one, loss[2:])
+    finally:
+        torch.cuda.synchronize()
+        c.close()
