@@ -91,9 +91,9 @@ dq_status dq_destroy(dq_ctx* ctx);
 /* Bytes of device workspace that any call with these sizes needs (a host computation).
  * x_dtype is the storage type of X.  *out receives the size.  Problems of a batch run one after
  * another and share the workspace, except for n <= 128 (per-head rotations): there all b problems
- * run in the same kernel launches and the size grows with b (7 matrices of 64 KiB and up to
- * max(16, ceil(T/1024)) partial gradients per problem); with a smaller workspace such a batch runs in
- * groups.  A batch gives the same bits as its problems run one by one. */
+ * run in the same kernel launches and the size grows with b, up to the 1024 problems of a group (4 matrices
+ * and up to max(16, ceil(T/1024)) partial gradients per problem; n == 128: 7 matrices of 64 KiB and up to
+ * max(8, ceil(T/2048))); with a smaller workspace the groups are smaller.  A batch gives the same bits as its problems run one by one. */
 dq_status dq_workspace_bytes(int b, int n, int T, dq_dtype x_dtype, size_t* out);
 
 /* Hand the context a caller-owned device buffer (256-byte aligned).  Enqueues one small kernel

@@ -1312,25 +1312,24 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
 }
 
 // ---------------------------------------------------------------- batched small rotations (n <= kHeadDim)
-// Every problem of the batch runs in the same launches.  The path's buffers (b matrices each, n rows of stride
-// kHeadDim) sit behind the general layout in the workspace.
+// Every problem of a group runs in the same launches.  The path's buffers (a matrix per problem each, n rows of the general
+// layout's stride) sit behind the general layout in the workspace.
 struct HeadsLayout {
     size_t R = 0, U = 0, G = 0, dZ = 0, gpart = 0, lpart = 0, total = 0;
 };
 
-HeadsLayout make_heads_layout(size_t base, int b, int T, int n) {
+HeadsLayout make_heads_layout(const Layout& L, int b, int T, int n) {
     HeadsLayout H;
-    size_t cur = base;
-    const size_t mat = (size_t)(b > 0 ? b : 1) * kHeadDim * kHeadDim * 4;
-    const size_t sp = (size_t)heads_splits(T > 0 ? T : 1, n);
+    size_t cur = L.total;
+    const size_t problems = b > 0 ? b : 1, np = round_up(n, 32), sp = heads_splits(T > 0 ? T : 1, n);
+    const size_t mat = problems * n * L.ld * 4;
     H.R = bump(cur, mat);
     H.U = bump(cur, mat);
     H.G = bump(cur, mat);
     H.dZ = bump(cur, mat);
-    bump(cur, 3 * mat);   // unused; dq_workspace_bytes has always counted seven matrices per problem, and a program may have
-                          // sized its groups of problems by it
-    H.gpart = bump(cur, mat * sp);
-    H.lpart = bump(cur, (size_t)(b > 0 ? b : 1) * sp * 8);
+    if (n == kHeadDim) bump(cur, 3 * mat);   // unused: the size at n = 128 is a documented one, seven matrices per problem
+    H.gpart = bump(cur, problems * sp * np * np * 4);
+    H.lpart = bump(cur, problems * sp * 8);
     H.total = cur;
     return H;
 }
@@ -1343,12 +1342,21 @@ bool heads_fused_route(const dq_ctx* c, int n, dq_dtype xdt) {
     return heads_route(c, n) && c->objective == DQ_OBJ_WHIP && xdt == DQ_BF16;
 }
 
+// Most problems in one group of launches: four times the compute units.  A larger batch runs in groups, which asks for no more
+// workspace than one of them and costs nothing beside their work.
+constexpr int kHeadsGroup = 1024;
+int heads_group_limit(int b) { return b < 1 ? 1 : (b < kHeadsGroup ? b : kHeadsGroup); }
+
 // Problems of a batch that the workspace holds at a time (a workspace sized for fewer problems than the call has still
 // serves it, group by group, with the same bits); 0: not even one.
-int heads_group(const dq_ctx* c, size_t base, int b, int T, int n) {
+int heads_group(const dq_ctx* c, const Layout& L, int b, int T, int n) {
     if (c->ws == nullptr) return 0;
-    int g = b > 0 ? b : 1;
-    while (g > 0 && c->ws_bytes < make_heads_layout(base, g, T, n).total) --g;
+    int g = 0, too_many = heads_group_limit(b) + 1;
+    while (too_many - g > 1) {
+        const int mid = g + (too_many - g) / 2;
+        if (c->ws_bytes >= make_heads_layout(L, mid, T, n).total) g = mid;
+        else too_many = mid;
+    }
     return g;
 }
 
@@ -1391,22 +1399,22 @@ dq_status heads_backward(dq_ctx* c, int b, int n, const float* R, long ldr, cons
 dq_status heads_step(dq_ctx* c, const Layout& L, int b, int T, int n, const void* X, dq_dtype xdt, long ldx, const float* Z,
                      long ldz, dq_reduce red, float* loss_dev, float* R, long ldr, float* dZ, long lddz, float* Zupd,
                      float lr) {
-    const HeadsLayout H = make_heads_layout(L.total, b, T, n);
+    const HeadsLayout H = make_heads_layout(L, b, T, n);
     float* Rh = R ? R : at<float>(c, H.R);
-    const long ldrh = R ? ldr : kHeadDim;
+    const long ldrh = R ? ldr : L.ld;
     float* Uh = at<float>(c, H.U);
     float* Gh = at<float>(c, H.G);
-    DQ_TRY(heads_qr(c, b, n, Z, ldz, Rh, ldrh, Uh, kHeadDim));
+    DQ_TRY(heads_qr(c, b, n, Z, ldz, Rh, ldrh, Uh, L.ld));
     if (heads_fused_route(c, n, xdt)) {
-        DQ_TRY(heads_rotate_loss_grad(c, H, b, n, T, X, ldx, Rh, ldrh, red, loss_dev, Gh, kHeadDim));
+        DQ_TRY(heads_rotate_loss_grad(c, H, b, n, T, X, ldx, Rh, ldrh, red, loss_dev, Gh, L.ld));
     } else {
         const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
         for (int i = 0; i < b; ++i)
             DQ_TRY(rotate_loss_grad_one(c, L, T, n, static_cast<const char*>(X) + (size_t)i * T * ldx * esz, xdt, ldx,
-                                        Rh + (long)i * n * ldrh, ldrh, red, loss_dev + i, Gh + (long)i * n * kHeadDim,
-                                        kHeadDim, at<float>(c, L.Y), L.ld, at<char>(c, L.dY), L.ld, false));
+                                        Rh + (long)i * n * ldrh, ldrh, red, loss_dev + i, Gh + (long)i * n * L.ld,
+                                        L.ld, at<float>(c, L.Y), L.ld, at<char>(c, L.dY), L.ld, false));
     }
-    return heads_backward(c, b, n, Rh, ldrh, Uh, kHeadDim, Gh, kHeadDim, dZ, lddz, Zupd, ldz, lr);
+    return heads_backward(c, b, n, Rh, ldrh, Uh, L.ld, Gh, L.ld, dZ, lddz, Zupd, ldz, lr);
 }
 
 }  // namespace
@@ -1481,7 +1489,7 @@ dq_status dq_workspace_bytes(int b, int n, int T, dq_dtype x_dtype, size_t* out)
     DQ_TRY(check_n(n));
     if (x_dtype != DQ_F32 && x_dtype != DQ_BF16) return DQ_ERR_DTYPE;
     const Layout L = make_layout(n, T);
-    *out = n <= kHeadDim ? make_heads_layout(L.total, b, T, n).total : L.total;
+    *out = n <= kHeadDim ? make_heads_layout(L, heads_group_limit(b), T, n).total : L.total;
     return DQ_OK;
 }
 
@@ -1539,9 +1547,9 @@ dq_status dq_rotate_loss_grad(dq_ctx* c, int b, int T, int n, const void* X, dq_
     const Layout L = make_layout(n, T);
     DQ_TRY(check_ws(c, L));
     if (heads_fused_route(c, n, xdt) && Y == nullptr && dY == nullptr) {
-        const int gb = heads_group(c, L.total, b, T, n);
+        const int gb = heads_group(c, L, b, T, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
-        const HeadsLayout H = make_heads_layout(L.total, gb, T, n);
+        const HeadsLayout H = make_heads_layout(L, gb, T, n);
         for (int i = 0; i < b; i += gb)
             DQ_TRY(heads_rotate_loss_grad(c, H, b - i < gb ? b - i : gb, n, T, static_cast<const bf16_t*>(X) + (long)i * T * ldx,
                                           ldx, R + (long)i * n * ldr, ldr, red, loss_dev + i, G + (long)i * n * ldg, ldg));
@@ -1574,7 +1582,7 @@ dq_status dq_calib_step(dq_ctx* c, int b, int T, int n, const void* X, dq_dtype 
     DQ_TRY(check_ws(c, L));
     const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
     if (heads_route(c, n)) {
-        const int gb = heads_group(c, L.total, b, T, n);
+        const int gb = heads_group(c, L, b, T, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
         for (int i = 0; i < b; i += gb) {
             float* Zi = Z + (long)i * n * ldz;
@@ -1798,7 +1806,7 @@ dq_status dq_qr_backward(dq_ctx* c, int b, int n, const float* R, long ldr, cons
     const Layout L = make_layout(n, 1);
     DQ_TRY(check_ws(c, L));
     if (heads_route(c, n)) {
-        const int gb = heads_group(c, L.total, b, 1, n);
+        const int gb = heads_group(c, L, b, 1, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
         return heads_backward(c, b, n, R, ldr, U, ldu, G, ldg, dZ, lddz, nullptr, 0, 0.f);
     }
@@ -1918,17 +1926,17 @@ dq_status dq_calib_step_adam(dq_ctx* c, int b, int T, int n, const void* X, dq_d
     const float c1 = (float)(1.0 / (1.0 - pow((double)beta1, (double)step)));
     const float c2 = (float)(1.0 / (1.0 - pow((double)beta2, (double)step)));
     if (heads_route(c, n)) {
-        const int gb = heads_group(c, L.total, b, T, n);
+        const int gb = heads_group(c, L, b, T, n);
         if (gb < 1) return DQ_ERR_WORKSPACE;
-        float* dZh = at<float>(c, make_heads_layout(L.total, gb, T, n).dZ);
+        float* dZh = at<float>(c, make_heads_layout(L, gb, T, n).dZ);
         for (int i = 0; i < b; i += gb) {
             const int g = b - i < gb ? b - i : gb;
             const long r0 = (long)i * n;
             DQ_TRY(heads_step(c, L, g, T, n, static_cast<const char*>(X) + (size_t)i * T * ldx * esz, xdt, ldx, Z + r0 * ldz, ldz,
-                              red, loss_dev + i, R ? R + r0 * ldr : nullptr, ldr, dZh, kHeadDim, nullptr, 0.f));
+                              red, loss_dev + i, R ? R + r0 * ldr : nullptr, ldr, dZh, L.ld, nullptr, 0.f));
             // the problems are stacked row-wise with a common row stride: one elementwise pass over g * n rows
             LaunchScope sc(&c->prof, c->stream, DQ_K_SMALL, 12.0 * g * n * (double)n, 28.0 * g * n * (double)n);
-            DQ_HIP(launch_adam2d(Z + r0 * ldz, ldz, dZh, kHeadDim, m + r0 * ldm, ldm, v + r0 * ldv, ldv, n, lr, beta1, beta2, eps,
+            DQ_HIP(launch_adam2d(Z + r0 * ldz, ldz, dZh, L.ld, m + r0 * ldm, ldm, v + r0 * ldv, ldv, n, lr, beta1, beta2, eps,
                                  c1, c2, c->stream, g * n));
         }
         return DQ_OK;

@@ -2209,3 +2209,31 @@ def test_small_rotation_block_that_ends_with_its_last_row(n, T):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+def test_small_rotations_beyond_one_group():
+    """More problems than one group of launches takes: the step and the Adam step have the bits of their problems one by one
+    at both sides of the group's end."""
+    b, n, T = 1030, 12, 70
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    X = torch.randn(b, T, 16, device="cuda", generator=g).to(torch.bfloat16)[..., :n]
+    Z0 = torch.randn(b, n, n, device="cuda", generator=g)
+    c = B.Context()
+    try:
+        c.ensure_workspace(b, n, T, B.DQ_BF16)
+        Z, loss = Z0.clone(), torch.zeros(b, device="cuda")
+        c.dq_calib_step(X, B.DQ_BF16, Z, 1e-2, B.DQ_REDUCE_TOKEN_MEAN, loss)
+        Za, m, v, la = Z0.clone(), torch.zeros_like(Z0), torch.zeros_like(Z0), torch.zeros(b, device="cuda")
+        c.dq_calib_step_adam(X, B.DQ_BF16, Za, m, v, 1, 1e-2, B.DQ_REDUCE_TOKEN_MEAN, la)
+        assert torch.equal(la, loss)
+        for i in (0, 1022, 1023, 1024, 1029):
+            Z1, Z2, l1 = Z0[i:i + 1].clone(), Z0[i:i + 1].clone(), torch.zeros(1, device="cuda")
+            m1, v1 = torch.zeros_like(Z1), torch.zeros_like(Z1)
+            c.dq_calib_step(X[i:i + 1], B.DQ_BF16, Z1, 1e-2, B.DQ_REDUCE_TOKEN_MEAN, l1)
+            c.dq_calib_step_adam(X[i:i + 1], B.DQ_BF16, Z2, m1, v1, 1, 1e-2, B.DQ_REDUCE_TOKEN_MEAN, l1)
+            assert torch.equal(Z1[0], Z[i]) and torch.equal(Z2[0], Za[i]) and torch.equal(m1[0], m[i]) and l1[0] == loss[i]
+        assert c.dq_device_flags() == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()

@@ -87,3 +87,13 @@ def test_null_context_is_refused_everywhere(lib):
 def test_missing_library_fails_loudly(tmp_path):
     with pytest.raises(RuntimeError, match="no CPU fallback"):
         B.load_library(str(tmp_path / "libdartqr.so"))
+
+
+def test_workspace_of_small_batches():
+    """A batch of small rotations asks for matrices of its own order and for no more than a group of problems."""
+    one = B.workspace_bytes(1, 16, 512, B.DQ_BF16)
+    many = B.workspace_bytes(4096, 16, 512, B.DQ_BF16)
+    # 1024 problems: four 16 x 16 matrices and up to 16 partial gradients of 32 x 32 each
+    assert many - one <= 1024 * (4 * 1024 + 16 * (4096 + 8))
+    assert B.workspace_bytes(100000, 16, 512, B.DQ_BF16) == many
+    assert B.workspace_bytes(64, 128, 16384, B.DQ_BF16) - B.workspace_bytes(1, 128, 16384, B.DQ_BF16) <= 63 * 15 * 65536 + 63 * 64
