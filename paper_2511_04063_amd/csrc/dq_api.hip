@@ -1805,11 +1805,7 @@ dq_status dq_qr_backward(dq_ctx* c, int b, int n, const float* R, long ldr, cons
     DQ_TRY(check_f32(dZ, lddz, n));
     const Layout L = make_layout(n, 1);
     DQ_TRY(check_ws(c, L));
-    if (heads_route(c, n)) {
-        const int gb = heads_group(c, L, b, 1, n);
-        if (gb < 1) return DQ_ERR_WORKSPACE;
-        return heads_backward(c, b, n, R, ldr, U, ldu, G, ldg, dZ, lddz, nullptr, 0, 0.f);
-    }
+    if (heads_route(c, n)) return heads_backward(c, b, n, R, ldr, U, ldu, G, ldg, dZ, lddz, nullptr, 0, 0.f);
     for (int i = 0; i < b; ++i)
         DQ_TRY(qr_backward_one(c, L, n, R + (long)i * n * ldr, ldr, U + (long)i * n * ldu, ldu, G + (long)i * n * ldg,
                                ldg, dZ + (long)i * n * lddz, lddz, nullptr, 0, 0.f));

@@ -2211,6 +2211,34 @@ def test_small_rotation_block_that_ends_with_its_last_row(n, T):
         c.close()
 
 
+def test_qr_backward_of_small_rotations_needs_no_room_per_problem():
+    """dq_qr_backward keeps nothing of n <= 128 in the workspace: it runs where the gradient's partials have no room."""
+    n, b = 100, 40
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    R = torch.linalg.qr(torch.randn(b, n, n, device="cuda", generator=g, dtype=torch.float64))[0].float().contiguous()
+    U = (torch.eye(n, device="cuda") + 0.05 * torch.triu(torch.randn(b, n, n, device="cuda", generator=g))).contiguous()
+    G = torch.randn(b, n, n, device="cuda", generator=g)
+    room = 4 * (n * 104 * 4) + 128 * 128 * 4 + 256      # one problem's matrices, its partial gradient and loss
+    ws = torch.empty(B.workspace_bytes(1, n, 1, B.DQ_F32) - room, dtype=torch.uint8, device="cuda")
+    c, c2 = B.Context(), B.Context()
+    try:
+        c.dq_set_workspace(ws)
+        c2.ensure_workspace(b, n, 1, B.DQ_F32)
+        out = [torch.zeros(b, n, n, device="cuda") for _ in range(2)]
+        c.dq_qr_backward(R, U, G, out[0])
+        c2.dq_qr_backward(R, U, G, out[1])
+        assert torch.equal(out[0], out[1]) and float(out[0].norm()) > 0.0
+        X = torch.randn(b, 64, 104, device="cuda").to(torch.bfloat16)[..., :n]
+        with pytest.raises(B.DartQRError) as e:
+            c.dq_rotate_loss_grad(X, B.DQ_BF16, R, B.DQ_REDUCE_TOKEN_MEAN, torch.zeros(b, device="cuda"), out[0])
+        assert e.value.status == B.DQ_ERR_WORKSPACE
+    finally:
+        torch.cuda.synchronize()
+        c.close()
+        c2.close()
+
+
 def test_small_rotations_beyond_one_group():
     """More problems than one group of launches takes: the step and the Adam step have the bits of their problems one by one
     at both sides of the group's end."""
