@@ -8,6 +8,8 @@
 //     contribution to G = X^T dY are formed on chip: Y and dY never reach HBM.
 //   * heads_reduce_kernel: sums the per-workgroup partial G and loss.
 // The derivative through the QR runs through the batched forms of the general kernels.
+#include <type_traits>
+
 #include "dq_internal.h"
 #include "dq_wave.h"
 
@@ -78,10 +80,10 @@ __device__ __forceinline__ void publish_from(float* cb, const float (&x)[4 * NG]
 }
 
 // x <- x - gamma (u . x) u for this thread's part of its column (if live) and of its row of Q, for block row JB = j / 16
-// of the pivot; u is the published column with u_0 = uj in place of the raw pivot.
-template <int JB, int NG>
+// of the pivot; u is the published column with u_0 = uj in place of the raw pivot.  LARGE: gamma times g2 in place of gamma
+template <int JB, int NG, bool LARGE>
 __device__ __forceinline__ void reflect_from(const float* cb, float (&xc)[4 * NG], float (&xq)[4 * NG], bool col_live,
-                                             int h, int j, float uj, float gamma) {
+                                             int h, int j, float uj, float gamma, float g2) {
     float4 u[NG - JB];
 #pragma unroll
     for (int k = JB; k < NG; ++k) u[k - JB] = *reinterpret_cast<const float4*>(cb + 4 * (k * QS + h));
@@ -101,8 +103,8 @@ __device__ __forceinline__ void reflect_from(const float* cb, float (&xc)[4 * NG
     float dc = (c0 + c1) + (c2 + c3), dq = (q0 + q1) + (q2 + q3);
     dc += lane_xor<1>(dc); dq += lane_xor<1>(dq);
     dc += lane_xor<2>(dc); dq += lane_xor<2>(dq);
-    const float fc = col_live ? gamma * dc : 0.f;
-    const float fq = gamma * dq;
+    const float fc = col_live ? gamma * (LARGE ? g2 * dc : dc) : 0.f;
+    const float fq = gamma * (LARGE ? g2 * dq : dq);
 #pragma unroll
     for (int k = JB; k < NG; ++k) {
         const float4 v = u[k - JB];
@@ -137,53 +139,68 @@ __global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restri
     const int item = tid / QS, h = tid % QS;
     const int col = item_column(item);   // this thread's column of A; its row of Q is `item`
     const float* Zp = Z + (long)blockIdx.x * sz;
-    float xc[4 * NG], xq[4 * NG];
+    float xc[4 * NG], xq[4 * NG], mydiag = 0.f;
+    // The factorisation.  Columns of norm 2^62 and more: 2 / u . u is no normal fp32 number though the squares are; they are
+    // noticed (returned) and the factorisation is done again with that factor in two, which costs 3 % where it always is.
+    auto factor = [&](auto large) -> bool {
+        constexpr bool LARGE = decltype(large)::value;
+        bool met = false;
 #pragma unroll
-    for (int k = 0; k < NG; ++k)
+        for (int k = 0; k < NG; ++k)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 4 * (k * QS + h) + e;
-            xc[4 * k + e] = (i < n && col < n) ? Zp[(long)i * ldz + col] : 0.f;
-            xq[4 * k + e] = (i == item) ? 1.f : 0.f;
-        }
-    float mydiag = 0.f;
-    if (tid < HN) { cbuf[0][tid] = 0.f; cbuf[1][tid] = 0.f; }   // what lies beyond the carried blocks reads as zero
-    __syncthreads();
-    if (col == 0) publish_from<0, NG>(cbuf[0], xc, h, 0);
-    __syncthreads();
-    for (int j = 0; j < n; ++j) {           // (rows and columns from n on are zero and stay zero)
-        const float* cb = cbuf[j & 1];
-        // column norm below the pivot: DPP inside the rows of 16 lanes, then the four row sums through scalar registers
-        const float a0 = cb[lane], a1 = cb[lane + 64];
-        const float alpha = cb[j];
-        float sr_ = (lane > j ? a0 * a0 : 0.f) + (lane + 64 > j ? a1 * a1 : 0.f);
-        sr_ += lane_xor<1>(sr_);
-        sr_ += lane_xor<2>(sr_);
-        sr_ += lane_xor<4>(sr_);
-        sr_ += lane_xor<8>(sr_);
-        const float s = (lane_value(sr_, 0) + lane_value(sr_, 16)) + (lane_value(sr_, 32) + lane_value(sr_, 48));
-        float beta = alpha;   // nothing below the pivot: H = I
-        if (s != 0.f) {
-            // hardware square root (1 ulp): beta only decides how exactly the column is annihilated; gamma is formed
-            // from the u that is applied, so that H is orthogonal whatever the rounding of beta
-            const float nrm = __builtin_amdgcn_sqrtf(alpha * alpha + s);
-            beta = alpha >= 0.f ? -nrm : nrm;
-            const float uj = alpha - beta;
-            const float gamma = 2.f * __builtin_amdgcn_rcpf(s + uj * uj);
-#define DQ_CALL(JB) reflect_from<JB, NG>(cb, xc, xq, col > j, h, j, uj, gamma)
-            DQ_BLOCK_SWITCH(j / QB, DQ_CALL)
-#undef DQ_CALL
-        }
-        if (col == j) mydiag = beta;
-        if (tid == 0) sgn[j] = beta >= 0.f ? 1.f : -1.f;
-        if (col == j + 1) {
-            float* nb = cbuf[(j + 1) & 1];
-#define DQ_CALL(JB) publish_from<JB, NG>(nb, xc, h, j + 1)
-            DQ_BLOCK_SWITCH((j + 1) / QB, DQ_CALL)
-#undef DQ_CALL
-        }
+            for (int e = 0; e < 4; ++e) {
+                const int i = 4 * (k * QS + h) + e;
+                xc[4 * k + e] = (i < n && col < n) ? Zp[(long)i * ldz + col] : 0.f;
+                xq[4 * k + e] = (i == item) ? 1.f : 0.f;
+            }
+        if (tid < HN) { cbuf[0][tid] = 0.f; cbuf[1][tid] = 0.f; }   // what lies beyond the carried blocks reads as zero
         __syncthreads();
-    }
+        if (col == 0) publish_from<0, NG>(cbuf[0], xc, h, 0);
+        __syncthreads();
+        for (int j = 0; j < n; ++j) {           // (rows and columns from n on are zero and stay zero)
+            const float* cb = cbuf[j & 1];
+            // column norm below the pivot: DPP inside the rows of 16 lanes, then the four row sums through scalar registers
+            const float a0 = cb[lane], a1 = cb[lane + 64];
+            const float alpha = cb[j];
+            float sr_ = (lane > j ? a0 * a0 : 0.f) + (lane + 64 > j ? a1 * a1 : 0.f);
+            sr_ += lane_xor<1>(sr_);
+            sr_ += lane_xor<2>(sr_);
+            sr_ += lane_xor<4>(sr_);
+            sr_ += lane_xor<8>(sr_);
+            const float s = (lane_value(sr_, 0) + lane_value(sr_, 16)) + (lane_value(sr_, 32) + lane_value(sr_, 48));
+            float beta = alpha;   // nothing below the pivot: H = I
+            if (s != 0.f) {
+                // hardware square root (1 ulp): beta only decides how exactly the column is annihilated; 2 / u . u is formed
+                // from the u that is applied, so that H is orthogonal whatever the rounding of beta
+                const float nrm = __builtin_amdgcn_sqrtf(alpha * alpha + s);
+                beta = alpha >= 0.f ? -nrm : nrm;
+                const float uj = alpha - beta;
+                const float uu = fmaf(uj, uj, s);
+                float gamma = 2.f * __builtin_amdgcn_rcpf(uu), g2 = 1.f;
+                if (LARGE) {    // from u at a norm of 1 to 2
+                    const int ex = __builtin_amdgcn_frexp_expf(nrm);
+                    const float us = ldexpf(uj, -ex);
+                    gamma = ldexpf(2.f * __builtin_amdgcn_rcpf(fmaf(us, us, ldexpf(s, -2 * ex))), -ex);
+                    g2 = ldexpf(1.f, -ex);
+                }
+                met = met || !(uu < 0x1p125f);
+#define DQ_CALL(JB) reflect_from<JB, NG, LARGE>(cb, xc, xq, col > j, h, j, uj, gamma, g2)
+                DQ_BLOCK_SWITCH(j / QB, DQ_CALL)
+#undef DQ_CALL
+            }
+            if (col == j) mydiag = beta;
+            if (tid == 0) sgn[j] = beta >= 0.f ? 1.f : -1.f;
+            if (col == j + 1) {
+                float* nb = cbuf[(j + 1) & 1];
+#define DQ_CALL(JB) publish_from<JB, NG>(nb, xc, h, j + 1)
+                DQ_BLOCK_SWITCH((j + 1) / QB, DQ_CALL)
+#undef DQ_CALL
+            }
+            __syncthreads();
+        }
+        return met;
+    };
+    if (factor(std::false_type{})) factor(std::true_type{});    // (the same for every thread: all see the same columns)
     if (h == 0 && col < n) {
         if (!(fabsf(mydiag) <= 3.0e38f)) atomicOr(flags, DQ_FLAG_NONFINITE);
         else if (mydiag == 0.f) atomicOr(flags, DQ_FLAG_SINGULAR);

@@ -2265,3 +2265,30 @@ def test_small_rotations_beyond_one_group():
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n,k", [(1, 61), (20, 60), (80, 59), (80, 60), (127, 59), (128, 59), (127, -45), (64, -45)])
+def test_small_qr_of_scaled_latents(n, k):
+    """A latent scaled by a power of two has the same R and the scaled U, bit for bit, as long as the squares of its columns
+    stay inside fp32's range (norms from 2^-63 to 2^63; the reciprocal of a square does not where the square itself does)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(60 + n)
+    Z = torch.zeros((n, -(-n // 4) * 4), device="cuda")[:, :n]
+    Z.copy_(torch.randn(n, n, device="cuda", generator=g))
+    out = {}
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 1, B.DQ_F32)
+        if k > 0:
+            Z[:, 0] *= 2.0 ** -30   # a column far smaller than the others (2^-45 2^-30 would leave the range)
+        for e in (0, k):
+            (_, Rd), (_, Ud) = padded(n, n, -(-n // 4) * 4), padded(n, n, -(-n // 4) * 4)
+            Ze = torch.zeros((n, -(-n // 4) * 4), device="cuda")[:, :n]
+            Ze.copy_(Z.double() * 2.0 ** e)
+            c.dq_qr_orth(Ze, Rd, Ud)
+            out[e] = (Rd.clone(), Ud.double() * 2.0 ** -e)
+        assert torch.equal(out[k][0], out[0][0]) and torch.equal(out[k][1], out[0][1])
+        assert c.dq_device_flags() == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
