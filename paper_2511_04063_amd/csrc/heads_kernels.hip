@@ -349,9 +349,9 @@ __device__ __forceinline__ void heads_tile(const bf16_t* Xs, bf16_t* dYs, const 
                 const float y = i == 0 ? y0[4 * g + q] : y1[4 * g + q];
                 const float ex = __expf(-fabsf(y));
                 sum[q] += ex;
-                // scale * sgn(y) without comparisons: y * 2^126 has modulus >= 1 for every normal y (an overflow to
+                // scale * sgn(y) without comparisons: y * 2^150 has modulus 2 or more for every y but 0 (an overflow to
                 // infinity is as good), so the median with -scale and +scale picks the signed bound; y = 0 stays 0
-                const float sg = __builtin_amdgcn_fmed3f(y * 8.507059173e37f, -scale, scale);
+                const float sg = __builtin_amdgcn_fmed3f(ldexpf(y, 150), -scale, scale);
                 d[q] = -sg * ex;
             }
             const f32x2 d01 = {d[0], d[1]}, d23 = {d[2], d[3]};

@@ -2292,3 +2292,27 @@ def test_small_qr_of_scaled_latents(n, k):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n", [80, 128])
+def test_small_rotation_derivative_of_subnormal_entries(n):
+    """Entries of Y below the smallest normal number have a sign like any other: the gradient of the general route, which compares
+    them with zero, to the rounding of dY (2^-9)."""
+    T = 512
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    X = torch.randn(1, T, n, device="cuda", generator=g).to(torch.bfloat16)
+    R = (torch.linalg.qr(torch.randn(1, n, n, device="cuda", generator=g, dtype=torch.float64))[0] * 2.0 ** -124).float().contiguous()
+    out = {}
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, T, B.DQ_BF16)
+        for batched in (0, 1):
+            c.dq_set_option(B.DQ_OPT_HEADS_BATCHED, batched)
+            loss, out[batched] = torch.zeros(1, device="cuda"), torch.zeros(1, n, n, device="cuda")
+            c.dq_rotate_loss_grad(X, B.DQ_BF16, R, B.DQ_REDUCE_SUM, loss, out[batched])
+            assert loss.item() == n * T
+        assert float((out[1] - out[0]).norm() / out[0].norm()) < 2.0 ** -9
+    finally:
+        torch.cuda.synchronize()
+        c.close()
