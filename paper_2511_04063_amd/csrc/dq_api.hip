@@ -979,6 +979,12 @@ int solve_outer_blocks(const dq_ctx* c, int n) {
     return wide ? n / kTrsmOuter : 0;
 }
 
+// Does the solve multiply by the inverse of a whole outer block, or go through it by blocks of kTrsmBlock?  By those it is more
+// accurate and slower (n = 2816, a latent moved from a rotation: dZ 4.5e-7 against 5.6e-7, 876 against 712 us).  From 2560 on the
+// orders that are multiples of 256 had R^T G and R M from split operands already when their solve went by kTrsmBlock all the
+// way (4.2e-7, 1035 us): with the wider inverse alone their error would grow, while elsewhere the products make up for it.
+bool solve_wide_inverse(int n) { return n < 2560 || n % kTrsmOuter == 0 || n % 256 != 0; }
+
 dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R, long ldr, const float* U, long ldu,
                               hipStream_t s) {
     unsigned* flags = at<unsigned>(c, L.flags);
@@ -995,7 +1001,7 @@ dq_status qr_backward_prepare(dq_ctx* c, const Layout& L, int n, const float* R,
         DQ_HIP(launch_trinv_blocks(U, ldu, n, uinv, flags, s));
     }
     const int nouter = solve_outer_blocks(c, n);
-    if (nouter > 0) {
+    if (nouter > 0 && solve_wide_inverse(n)) {
         // The inverses of the whole 512 x 512 diagonal blocks are merged from the 128 x 128 ones, inv [[A, B], [0, C]] =
         // [[A^-1, -A^-1 B C^-1], [0, C^-1]], two levels of batched products.
         float* uo = at<float>(c, L.uinvo);
@@ -1113,7 +1119,8 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
     // the last columns, which the outer blocks leave over, by blocks of kTrsmBlock
     const int nblk = (n + kTrsmBlock - 1) / kTrsmBlock;
     const int nouter = solve_outer_blocks(c, n);
-    for (int j = nblk - 1; j >= nouter * (kTrsmOuter / kTrsmBlock); --j) {
+    // block j of kTrsmBlock columns, and what it gives to the columns from `left` up to it
+    auto narrow = [&](int j, int left) -> dq_status {
         const int j0 = j * kTrsmBlock;
         const int w = (n - j0) < kTrsmBlock ? (n - j0) : kTrsmBlock;
         const int mrows = n - j0;
@@ -1126,17 +1133,20 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
             LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)w * w, 0.0);
             DQ_HIP(product_f32(c, g, s, guard));
         }
-        if (j0 > 0) {
-            GemmF32 g;   // P[j0:, 0:j0] -= M[j0:, blk] * U[0:j0, blk]^T
+        if (j0 > left) {
+            GemmF32 g;   // P[j0:, left:j0] -= M[j0:, blk] * U[left:j0, blk]^T
             g.A = Mb + (long)j0 * ld + j0; g.lda = ld; g.ta = 0;
-            g.B = U + j0; g.ldb = ldu; g.tb = 1;
-            g.C = Pb + (long)j0 * ld; g.ldc = ld;
-            g.M = mrows; g.N = j0; g.K = w;
+            g.B = U + (long)left * ldu + j0; g.ldb = ldu; g.tb = 1;
+            g.C = Pb + (long)j0 * ld + left; g.ldc = ld;
+            g.M = mrows; g.N = j0 - left; g.K = w;
             g.alpha = -1.f; g.beta = 1.f;
-            LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)j0 * w, 0.0);
+            LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * mrows * (double)(j0 - left) * w, 0.0);
             DQ_HIP(product_f32(c, g, s, guard));
         }
-    }
+        return DQ_OK;
+    };
+    constexpr int per = kTrsmOuter / kTrsmBlock;
+    for (int j = nblk - 1; j >= nouter * per; --j) DQ_TRY(narrow(j, 0));
     if (nouter > 0) {
         // M U^T = P by block columns of kTrsmOuter from the right:  M_J = P_J inv(U_JJ)^T, then everything left of the
         // block gets ONE update with K = kTrsmOuter (K = 128 updates over the whole width move P at the rate of the
@@ -1148,7 +1158,9 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
         for (int J = nouter - 1; J >= 0; --J) {
             const int J0 = J * kTrsmOuter;
             const int mrows = n - J0;
-            {
+            if (!solve_wide_inverse(n)) {
+                for (int j = J * per + per - 1; j >= J * per; --j) DQ_TRY(narrow(j, J0));
+            } else {
                 GemmF32 g;   // M[J0:, blk] = P[J0:, blk] * inv(U_JJ)^T
                 g.A = Pb + (long)J0 * ld + J0; g.lda = ld; g.ta = 0;
                 g.B = uo + (long)J * so; g.ldb = kTrsmOuter; g.tb = 1;
@@ -1158,8 +1170,7 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
                 DQ_HIP(product_f32(c, g, s, guard));
             }
             if (J0 > 0) {
-                GemmF32 g;   // P[J0:, 0:J0] -= M[J0:, blk] * U[0:J0, blk]^T (in fp32: from three-plane splits its tiles
-                             // fill the compute units too unevenly to gain, 8192: 12.1 against 11.5 ms for the whole call)
+                GemmF32 g;   // P[J0:, 0:J0] -= M[J0:, blk] * U[0:J0, blk]^T
                 g.A = Mb + (long)J0 * ld + J0; g.lda = ld; g.ta = 0;
                 g.B = U + J0; g.ldb = ldu; g.tb = 1;
                 g.C = Pb + (long)J0 * ld; g.ldc = ld;
