@@ -127,7 +127,8 @@ typedef enum {
                                        pairs of terms above fp32 rounding are accumulated in fp32).  0: never (fp32 matrix
                                        cores); 1 (default): where it is faster: products that fill the 128 x 128 tiles, split
                                        while they are read, and the n x n x n ones from planes split beforehand when n is
-                                       a multiple of 4096; 2: those of planes whenever n is a multiple of 256.
+                                       a multiple of 256 whose 256 x 256 tiles fill the compute units (4096, 5632, 6656,
+                                       6912, 7680, 7936, 8192); 2: those of planes whenever n is a multiple of 256.
                                        A caller's X and R (S3, S5), G (S6) and M (Cayley) are scanned first, and an entry
                                        outside that range sends the products on it back to the fp32 matrix cores; not
                                        scanned are operands of planes, and those of dq_gemm_f32 under 2. */

@@ -961,13 +961,19 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
 // R^T G in x3a, as stored for R M in x3c).  (With planes, run on the second stream beside S3-S5 it gained nothing, 8.83 ms per
 // step either way at n = 4096 and 45.8 -> 46.2 at 8192: the split passes and small products land on compute units whose one
 // 256 x 256 tile of the bf16 product then finishes last.  Without planes it does run there.)
-// Planes pay where their 256 x 256 tiles come in whole rounds of the 256 compute units, n a multiple of 4096; elsewhere the
-// 128 x 128 tiles that split while they read are ahead (dq_qr_backward with planes / without, us: n = 2560 820 / 636, 3072
-// 1043 / 900, 4096 1660 / 1670, 5120 2997 / 3000, 6144 5040 / 4800, 7168 7841 / 7800, 8192 9982 / 11288; the Cayley update 2074 /
-// 1360 at 2560, 9356 / 8676 at 5120, 4404 / 4401 at 4096, 32715 / 36914 at 8192; their errors are the same).
-constexpr int kPlanesN = 4096;
+// Planes pay where the last round of their 256 x 256 tiles on the 256 compute units is nearly full, from order 4096 on; elsewhere
+// the 128 x 128 tiles that split while they read are ahead.  Share of the rounds that is filled: dq_qr_backward / Cayley update
+// with planes, without, us:  3840 .88: 1482, 1355 / 3827, 3851;  4096 1: 1647, 1716 / 4358, 4415;  5120 .78: 3008, 2851 / 9269, 8793;
+// 5376 .86: 3317, 3245 / 10227, 10216;  5632 .95: 3660, 3728 / 11124, 11963;  6400 .81: 5709, 5559 / 18009, 17703;  6656 .88: 6134, 6151 /
+// 19127, 19740;  6912 .95: 6680, 6985 / 20463, 22977;  7168 .77: 8005, 7560 / 27528, 24652;  7680 .88: 8951, 9163 / 29589, 30279;
+// 7936 .94: 9507, 10306 / 30961, 35081;  8192 1: 10021, 10823 / 32452, 36395.  (A whole step at 4096 takes 7920, 7830: the preparation
+// then has no place beside S3-S5.)  Errors at 4096: dZ 5.2e-7 with planes, 5.7e-7 without.
+bool planes_pay(int n) {
+    const int tiles = (n / 256) * (n / 256), rounds = (tiles + 255) / 256;
+    return n >= 4096 && 100 * tiles >= 87 * 256 * rounds;
+}
 bool backward_uses_splits(const dq_ctx* c, const Layout& L, int n) {
-    return c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && L.ld == n && (c->split_gemm == 2 || n % kPlanesN == 0);
+    return c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && L.ld == n && (c->split_gemm == 2 || planes_pay(n));
 }
 
 // Outer blocks of kTrsmOuter columns that the solve works on; what they leave over goes by blocks of kTrsmBlock.  The explicit
@@ -1243,7 +1249,7 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
     // As in S6, the products run on the bf16 matrix cores from three-plane splits when the shape fits (DQ_OPT_SPLIT_GEMM):
     // `pa` holds the planes of op(A) (n x n, reduction index contiguous), `pb` those of op(B)^T; a null `A_` / `B_` means
     // that the buffer already holds them from an earlier product.
-    const bool x3 = c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && ld == n && (c->split_gemm == 2 || n % kPlanesN == 0);
+    const bool x3 = c->split_gemm != 0 && gemm_bf16x3_fits(n, n, n) && ld == n && (c->split_gemm == 2 || planes_pay(n));
     const long plane = (long)n * ld;
     bf16_t* pl0 = at<bf16_t>(c, L.x3a);
     bf16_t* pl1 = at<bf16_t>(c, L.x3b);

@@ -2344,3 +2344,27 @@ def test_qr_backward_error_where_planes_were():
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n,planes", [(3840, 0), (4096, 6), (5376, 0), (5632, 6), (5888, 0)])
+def test_planes_where_their_tiles_fill_the_chip(n, planes):
+    """The Cayley update's products run from planes split beforehand where the 256 x 256 tiles leave little of their last round
+    idle, and split while they read elsewhere; both keep the rotation orthogonal."""
+    k = torch.arange(n, device="cuda", dtype=torch.float64)
+    R = torch.cos((np.pi / (2 * n)) * k[:, None] * (2 * k + 1)[None, :]) * (2.0 / n) ** 0.5
+    R[0] *= 0.5 ** 0.5
+    R = R.float().contiguous()
+    G, M = torch.randn(n, n, device="cuda") * 1e-2, torch.zeros(n, n, device="cuda")
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 1, B.DQ_F32)
+        c.dq_profile_enable(1 << B.DQ_K_GEMM_BF16)
+        c.dq_cayley_update(R, G, M, 1e-3)
+        assert c.dq_profile_read(B.DQ_K_GEMM_BF16)["launches"] == planes
+        c.dq_profile_enable(0)
+        E = R.T.contiguous() @ R
+        E.diagonal().sub_(1.0)
+        assert float(E.abs().max()) < 1e-5
+    finally:
+        torch.cuda.synchronize()
+        c.close()
