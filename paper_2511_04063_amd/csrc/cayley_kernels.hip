@@ -53,23 +53,26 @@ __global__ __launch_bounds__(256) void cayley_skew_kernel(const float* __restric
 // alpha = min(lr, 2 q / (||W||_F + eps))  (Alg. 3, step-size rule); out[0] = alpha, out[1] = alpha / 2
 __global__ __launch_bounds__(1024) void cayley_alpha_kernel(const double* __restrict__ partials, int count, float lr, float q,
                                                           float eps, float* __restrict__ out) {
-    // one workgroup, a chain of loads: four in flight per thread (16384 partials at n = 4096: 18 us with 256 threads and one, 5 now)
-    __shared__ double sh[1024];
+    // one workgroup, a chain of loads: four in flight per thread (16384 partials at n = 4096: 18 us with 256 threads and one load,
+    // 5 with 1024; the few hundred of small orders are summed by 256 threads, and by lane exchanges instead of ten barriers)
+    __shared__ double sh[16];
+    const int nt = (int)blockDim.x;
     double t[4] = {0.0, 0.0, 0.0, 0.0};
     int i = threadIdx.x;
-    for (; i + 3 * 1024 < count; i += 4 * 1024) {
-        const double a = partials[i], b = partials[i + 1024], c = partials[i + 2048], d = partials[i + 3072];
+    for (; i + 3 * nt < count; i += 4 * nt) {
+        const double a = partials[i], b = partials[i + nt], c = partials[i + 2 * nt], d = partials[i + 3 * nt];
         t[0] += a; t[1] += b; t[2] += c; t[3] += d;
     }
-    for (; i < count; i += 1024) t[0] += partials[i];
-    sh[threadIdx.x] = (t[0] + t[1]) + (t[2] + t[3]);
+    for (; i < count; i += nt) t[0] += partials[i];
+    double sum = (t[0] + t[1]) + (t[2] + t[3]);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sum;
     __syncthreads();
-    for (int o = 512; o >= 1; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        const float norm = (float)sqrt(sh[0]);
+        double total = 0.0;
+        for (int w = 0; w < nt / 64; ++w) total += sh[w];
+        const float norm = (float)sqrt(total);
         const float cap = 2.f * q / (norm + eps);
         const float alpha = lr < cap ? lr : cap;        // a NaN norm leaves lr
         out[0] = alpha;
@@ -106,7 +109,7 @@ hipError_t launch_cayley_skew(const float* What, long ldh, int n, float* W, long
 
 hipError_t launch_cayley_alpha(const double* partials, int count, float lr, float q, float eps, float* alpha_dev,
                                hipStream_t s) {
-    hipLaunchKernelGGL(cayley_alpha_kernel, dim3(1), dim3(1024), 0, s, partials, count, lr, q, eps, alpha_dev);
+    hipLaunchKernelGGL(cayley_alpha_kernel, dim3(1), dim3(count <= 2048 ? 256 : 1024), 0, s, partials, count, lr, q, eps, alpha_dev);
     return hipGetLastError();
 }
 
