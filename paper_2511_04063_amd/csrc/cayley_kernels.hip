@@ -20,6 +20,43 @@ __global__ __launch_bounds__(256) void cayley_momentum_kernel(float* __restrict_
     });
 }
 
+// The same with the scan of the new M for values without a split (launch_range_scan) on the way: a word per workgroup, four
+// pieces of M and G in flight per lane.  (A scan of its own costs 9 us at n = 1290 to 2560.)
+__global__ __launch_bounds__(1024) void cayley_momentum_scan_kernel(float* __restrict__ M, long ldm, const float* __restrict__ G,
+                                                                   long ldg, int n, float beta, unsigned* __restrict__ words) {
+    unsigned bad = 0u;
+    const int lane = threadIdx.x & 63, whole = n >> 2;
+    for (int r = blockIdx.x * 16 + (threadIdx.x >> 6); r < n; r += gridDim.x * 16) {
+        float* m = M + (long)r * ldm;
+        const float* g = G + (long)r * ldg;
+        for (int q = lane; q < whole; q += 256) {
+            float4 a[4], b[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                a[k] = b[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (q + 64 * k < whole) {
+                    a[k] = *reinterpret_cast<const float4*>(m + 4 * (q + 64 * k));
+                    b[k] = *reinterpret_cast<const float4*>(g + 4 * (q + 64 * k));
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 v = make_float4(beta * a[k].x - b[k].x, beta * a[k].y - b[k].y, beta * a[k].z - b[k].z,
+                                             beta * a[k].w - b[k].w);
+                bad |= no_split(v);
+                if (q + 64 * k < whole) *reinterpret_cast<float4*>(m + 4 * (q + 64 * k)) = v;
+            }
+        }
+        if (4 * whole + lane < n) {             // at most three columns are left
+            const float v = beta * m[4 * whole + lane] - g[4 * whole + lane];
+            bad |= no_split(v);
+            m[4 * whole + lane] = v;
+        }
+    }
+    const bool any = __syncthreads_or(bad != 0u) != 0;
+    if (threadIdx.x == 0) words[blockIdx.x] = any ? 1u : 0u;
+}
+
 // W = What - What^T (Alg. 3, skew-symmetrisation) on 32 x 32 tiles: tile (bi, bj) and its mirror are both read row-wise (coalesced)
 // and the mirror is transposed through LDS.  Each block also leaves the sum of squares of the entries it wrote.
 __global__ __launch_bounds__(256) void cayley_skew_kernel(const float* __restrict__ H, long ldh, int n, float* __restrict__ W,
@@ -92,7 +129,11 @@ __global__ __launch_bounds__(256) void add_scaled_kernel(float* out, long ldo, c
 
 }  // namespace
 
-hipError_t launch_cayley_momentum(float* M, long ldm, const float* G, long ldg, int n, float beta, hipStream_t s) {
+hipError_t launch_cayley_momentum(float* M, long ldm, const float* G, long ldg, int n, float beta, unsigned* words, hipStream_t s) {
+    if (words != nullptr) {
+        hipLaunchKernelGGL(cayley_momentum_scan_kernel, dim3(kGuardWords), dim3(1024), 0, s, M, ldm, G, ldg, n, beta, words);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(cayley_momentum_kernel, quad_grid(n, n), dim3(256), 0, s, M, ldm, G, ldg, n, beta);
     return hipGetLastError();
 }

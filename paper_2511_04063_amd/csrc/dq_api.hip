@@ -1285,13 +1285,10 @@ dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ld
         return DQ_OK;
     };
     {
+        // the new M is scanned for values without a split as in S6 (R is a rotation)
+        if (!x3 && c->split_gemm != 0 && gemm_f32_split_applies(n, n, 1)) guard = at<unsigned>(c, L.guard);
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 2.0 * n * (double)n, 12.0 * n * (double)n);
-        DQ_HIP(launch_cayley_momentum(M, ldm, G, ldg, n, beta, s));
-    }
-    if (!x3 && c->split_gemm != 0 && gemm_f32_split_applies(n, n, 1)) {   // (as in S6: R is a rotation)
-        guard = at<unsigned>(c, L.guard);
-        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 4.0 * n * (double)n);
-        DQ_HIP(launch_range_scan(ScanList{{{M, ldm, n}, {}}}, n, guard, s));
+        DQ_HIP(launch_cayley_momentum(M, ldm, G, ldg, n, beta, guard, s));
     }
     DQ_TRY(product(M, ldm, 0, pl0, R, ldr, 1, pl1, What, ld, 1.f, 0.f, nullptr));          // A = M R^T
     DQ_TRY(product(R, ldr, 1, pl2, What, ld, 0, pl0, Tmp, ld, 1.f, 0.f, nullptr));         // R^T A

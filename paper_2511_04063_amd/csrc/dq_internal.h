@@ -93,6 +93,14 @@ struct GemmF32 {
 };
 hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t s);
 bool gemm_f32_split_applies(int M, int N, int splits);   // the launcher picks the tile that x3 speaks of
+// 1 for a value that has no split into three normal bf16 terms holding its 24 bits: 0 and the patterns from 2^-102 up to 2^127 have
+// one, a NaN and an infinity lie above
+__device__ __forceinline__ unsigned no_split(float x) {
+    const unsigned u = __float_as_uint(x) & 0x7fffffffu;
+    constexpr unsigned lo = (127u - 102u) << 23, hi = (127u + 127u) << 23;
+    return u != 0u && u - lo >= hi - lo ? 1u : 0u;
+}
+__device__ __forceinline__ unsigned no_split(float4 v) { return no_split(v.x) | no_split(v.y) | no_split(v.z) | no_split(v.w); }
 // words[0 .. kGuardWords): non-zero somewhere if an entry of the matrices (rows x cols each) has no split into three normal bf16
 // terms that hold its 24 bits: infinite, a NaN, 2^127 or more in magnitude, or below 2^-102 and not zero
 constexpr int kGuardWords = 256;
@@ -284,8 +292,8 @@ hipError_t launch_momentum2d(float* Z, long ldz, const float* D, long ldd, float
                              float mu, hipStream_t s);
 
 // ---- Cayley SGD pieces (Alg. 3, App. B.2) -------------------------------------------
-// M <- beta M - G
-hipError_t launch_cayley_momentum(float* M, long ldm, const float* G, long ldg, int n, float beta, hipStream_t s);
+// M <- beta M - G; words (optional): those of launch_range_scan over the new M
+hipError_t launch_cayley_momentum(float* M, long ldm, const float* G, long ldg, int n, float beta, unsigned* words, hipStream_t s);
 // W = What - What^T and partials[block] = sum of squares of this block's entries of W (cayley_skew_grid(n) blocks)
 int cayley_skew_grid(int n);
 hipError_t launch_cayley_skew(const float* What, long ldh, int n, float* W, long ldw, double* partials, hipStream_t s);

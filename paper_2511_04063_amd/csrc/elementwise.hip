@@ -554,12 +554,6 @@ __global__ __launch_bounds__(1024) void range_scan_kernel(ScanList list, int col
     unsigned bad = 0u;
     const int row0 = (blockIdx.x * 1024 + threadIdx.x) / lanes, step = gridDim.x * 1024 / lanes, lane = threadIdx.x % lanes;
     const int whole = cols >> 2;                    // whole pieces of a row
-    // 0 and the patterns from 2^-102 up to 2^127 have a split; a NaN and an infinity lie above
-    auto outside = [](float x) -> unsigned {
-        const unsigned u = __float_as_uint(x) & 0x7fffffffu;
-        constexpr unsigned lo = (127u - 102u) << 23, hi = (127u + 127u) << 23;
-        return u != 0u && u - lo >= hi - lo ? 1u : 0u;
-    };
 #pragma unroll
     for (int i = 0; i < kScanParts; ++i) {
         const ScanPart& a = list.part[i];
@@ -572,11 +566,11 @@ __global__ __launch_bounds__(1024) void range_scan_kernel(ScanList list, int col
                     v[k] = *reinterpret_cast<const float4*>(a.p + (long)rk * a.ld + 4 * qk);
                 }
 #pragma unroll
-                for (int k = 0; k < 8; ++k) bad |= outside(v[k].x) | outside(v[k].y) | outside(v[k].z) | outside(v[k].w);
+                for (int k = 0; k < 8; ++k) bad |= no_split(v[k]);
             }
             if (4 * whole + lane < cols)            // at most three columns are left
                 for (int k = 0; k < ROWS && r + k * step < a.rows; ++k)
-                    bad |= outside(a.p[(long)(r + k * step) * a.ld + 4 * whole + lane]);
+                    bad |= no_split(a.p[(long)(r + k * step) * a.ld + 4 * whole + lane]);
         }
     }
     const bool any = __syncthreads_or(bad != 0u) != 0;
