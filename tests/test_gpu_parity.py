@@ -2368,3 +2368,44 @@ def test_planes_where_their_tiles_fill_the_chip(n, planes):
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+@pytest.mark.parametrize("n", [1290, 2890])
+def test_cayley_update_of_tiles_in_parts(n):
+    """The Cayley update where its products run on split operands, all tiles in parts (1290) and a remainder of them (512 + 17 at
+    2890): the sums of the parts carry beta != 0 and the step size formed on the device.  M, R and the step size against fp64,
+    and no less accurate than the fp32 matrix cores."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    ld = -(-n // 4) * 4
+    R0 = _copied_to_f32(torch.linalg.qr(torch.randn(n, n, device="cuda", generator=g, dtype=torch.float64))[0], ld)
+    M0 = _copied_to_f32(torch.randn(n, n, device="cuda", generator=g) * 0.3, ld)
+    G = _copied_to_f32(torch.randn(n, n, device="cuda", generator=g), ld)
+    R6, M6 = R0.double(), 0.9 * M0.double() - G.double()
+    What = M6 @ R6.T.contiguous()
+    What = What - 0.5 * R6 @ (R6.T.contiguous() @ What)
+    W = What - What.T
+    alpha = 1.0 / float(W.norm())                  # the step size rule's cap with q = 1/2: far below lr
+    Mref = W @ R6
+    Y = R6 + alpha * Mref
+    for _ in range(2):
+        Y = R6 + 0.5 * alpha * (W @ (R6 + Y))
+    err = {}
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 1, B.DQ_F32)
+        for mode in (0, 1):
+            c.dq_set_option(B.DQ_OPT_SPLIT_GEMM, mode)
+            R, M, a = _copied_to_f32(R0, ld), _copied_to_f32(M0, ld), torch.zeros(1, device="cuda")
+            c.dq_cayley_update(R, G, M, 1e9, iters=2, alpha=a)
+            assert abs(a.item() / alpha - 1.0) < 1e-6
+            step = Y - R6                          # the update alone: R's own rounding (2^-25 of its norm) is its bar
+            err[mode] = (float((M.double() - Mref).norm() / Mref.norm()),
+                         float(((R.double() - R6) - step).norm() / step.norm()))
+        bar = 2.0 ** -24 * float(R6.norm()) / float(step.norm())
+        assert err[1][0] < 0.6 * err[0][0] and err[1][0] < 1e-6
+        assert err[1][1] < min(err[0][1] * 1.05, 1e-5) + bar
+        assert c.dq_device_flags() == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
