@@ -136,15 +136,15 @@ def test_gemm_f32_split_operands(ta, tb, M, N, K):
         bufs.append(d)
     Cbuf, Cd = padded(M, N, -(-N // 4) * 4 + 8, fill=123.0)
     ref = C0 - A.astype(np.float64) @ Bm.astype(np.float64)
-    err = {}
+    err, got = {}, {}
     c = B.Context(); c.ensure_workspace(1, 64, 64, B.DQ_F32)
     try:
         for mode in (0, 2):
             c.dq_set_option(B.DQ_OPT_SPLIT_GEMM, mode)
             Cd.copy_(dev(C0))
             c.dq_gemm_f32(M, N, K, -1.0, bufs[0], ta, bufs[1], tb, 1.0, Cd)
-            got = Cd.cpu().numpy()
-            err[mode] = rel(got, ref)
+            got[mode] = Cd.cpu().numpy()
+            err[mode] = rel(got[mode], ref)
             assert torch.all(Cbuf[:, N:] == 123.0)
         Cd.fill_(float("nan"))                      # beta == 0 must not read C
         c.dq_gemm_f32(M, N, K, -1.0, bufs[0], ta, bufs[1], tb, 0.0, Cd)
@@ -154,6 +154,11 @@ def test_gemm_f32_split_operands(ta, tb, M, N, K):
         c.close()
     # the fp32 route's error is the bar; below 1e-7 both are the rounding of the result itself
     assert err[2] < max(1.2 * err[0], 1e-7)
+    if K >= 32:
+        assert not np.array_equal(got[0], got[2])       # another kernel has run
+    if K == 257:
+        # enough terms to stand out of the rounding of C: two accumulators give 0.32 to 0.38 of the fp32 error, one 0.8
+        assert err[2] < 0.6 * err[0]
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (0, 0), (1, 1)])
