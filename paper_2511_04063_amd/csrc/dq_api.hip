@@ -95,7 +95,7 @@ struct dq_ctx {
     int accum_panels = 0;            // panels merged per update of the accumulated R (0: by size, 2 below n = 8192 and
                                      // 4 from there on, each measured best there; 1: panel by panel)
     bool fused_whip = true;          // Eq. 4 in the epilogue of the rotation product where the shape allows
-    bool heads_batched = true;       // n == 128: all problems of a batch in the same launches
+    bool heads_batched = true;       // n <= 128: all problems of a batch in the same launches
     int split_gemm = 1;              // fp32 products from three-term bf16 splits: 0 never, 1 where it is faster, 2 also from
                                      // planes split beforehand wherever the shape fits
     bool device_sync = true;         // the QR's streams hand over through a device word where a probe allows (else events)
@@ -957,7 +957,7 @@ dq_status rotate_loss_grad_one(dq_ctx* c, const Layout& L, int T, int n, const v
 
 // ---------------------------------------------------------------- S6 (+ S7 when Zupd != null)
 // What S6 needs of R and U alone, on stream s: the inverses of the diagonal blocks of U (128 x 128, merged to 512 x 512
-// where the solve works on such blocks) and, for the products on three-plane splits, the planes of R (transposed for
+// where the solve multiplies by such) and, for the products on three-plane splits, the planes of R (transposed for
 // R^T G in x3a, as stored for R M in x3c).  (With planes, run on the second stream beside S3-S5 it gained nothing, 8.83 ms per
 // step either way at n = 4096 and 45.8 -> 46.2 at 8192: the split passes and small products land on compute units whose one
 // 256 x 256 tile of the bf16 product then finishes last.  Without planes it does run there.)
@@ -1233,7 +1233,8 @@ dq_status qr_backward_one(dq_ctx* c, const Layout& L, int n, const float* R, lon
 // One update of the rotation R (the algorithm's X_k) from its Euclidean gradient G, in the algorithm's own order:
 //   M <- beta M - G;  W^ = M R^T - 1/2 R (R^T M R^T);  W = W^ - W^^T;  M <- W R;  alpha = min(lr, 2q / (||W||_F + eps));
 //   Y = R + alpha M;  s times: Y <- R + alpha/2 W (R + Y);  R <- Y.
-// Six n x n products on the fp32 matrix cores; the step size stays on the device.
+// Six n x n products from split operands where they fill the tiles (see product_f32), else on the fp32 matrix cores; the step
+// size stays on the device.
 dq_status cayley_update_one(dq_ctx* c, const Layout& L, int n, float* R, long ldr, const float* G, long ldg, float* M,
                             long ldm, float lr, float beta, float q, int iters, float eps, float* alpha_out) {
     hipStream_t s = c->stream;

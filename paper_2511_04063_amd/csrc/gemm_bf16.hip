@@ -513,8 +513,8 @@ __device__ __forceinline__ void big_kstep(BigAcc& acc, BigFrags& f0, BigFrags& f
 // X3: the operands are three bf16 planes each (x = x1 + x2 + x3 to 24 mantissa bits, plane p at + p * a_plane / b_plane
 // elements) and the reduction runs over six segments of K indices, one per pair of planes whose product is not below
 // fp32 rounding -- (3,1) (1,3) (2,2) (2,1) (1,2) (1,1), small terms first -- into the same fp32 accumulators: an fp32
-// product on the bf16 matrix cores (each bf16 x bf16 product is exact in fp32; the three pairs left out are below
-// 2^-26 of |a| |b|).  Epilogue C = alpha * acc + beta * C.  With b_strict_lower the segments start at the tile's
+// product on the bf16 matrix cores (each bf16 x bf16 product is exact in fp32; the three pairs left out are at most
+// 2^-24 of |a| |b| together, below 2^-26 for all but a few per cent of pairs).  Epilogue C = alpha * acc + beta * C.  With b_strict_lower the segments start at the tile's
 // first column (B^T vanishes on and above the diagonal) and tiles are taken column block by column block, the
 // longest reductions first.
 template <bool WHIP, bool X3 = false>

@@ -319,7 +319,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, i
 // Every fp32 operand element is split into three bf16 terms on its way from the staging registers to LDS,
 //   x = x1 + x2 + x3,  x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2)   (24 bits, both remainders exact in fp32),
 // and six of the nine products of terms, (3,1) (1,3) (2,2) (2,1) (1,2) (1,1), are accumulated in fp32 (each bf16 product is
-// exact there; the three left out are below 2^-26 |a| |b|): the five small ones apart from (1,1), so that the large
+// exact there; with |x2| <= 2^-8 |x| and |x3| <= 2^-17 |x| the three left out are at most 2^-24 |a| |b| together, one fp32 rounding
+// of the product, and below 2^-26 for all but a few per cent of pairs): the five small ones apart from (1,1), so that the large
 // accumulator is rounded once per 16 k where the fp32 instruction rounds it 8 times.
 // Bound: the fp32 matrix instructions deliver 157 TFLOP/s at most and held the kernel above at 105 to 128; six bf16 ones do
 // the same work in 3/8 of the time.  Measured before / after: 8192 x 8192 x 256 with beta = 1 408 / 251 us, 4096 x 4096 x 64
@@ -449,7 +450,7 @@ __device__ __forceinline__ void multiply_x3(const OperandView& oa, const Operand
 
 template <bool TA, bool TB>
 __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec,
-                                                                 int whole, int parts, int pchunk) {
+                                                                 int whole, int pchunk) {
     __shared__ __attribute__((aligned(16))) bf16_t lds[6 * X3PLANE];
     bf16_t* const As = lds;
     bf16_t* const Bs = lds + 3 * X3PLANE;
@@ -662,7 +663,7 @@ static hipError_t launch_gemm_f32x3(const GemmF32& g, hipStream_t s) {
     dim3 grid(whole + (tiles - whole) * parts, g.splits > 1 ? g.splits : 1, g.batch > 1 ? g.batch : 1);
     dim3 block(256, 1, 1);
 #define DQ_LAUNCH(TA, TB)                                                                                                \
-    hipLaunchKernelGGL((gemm_f32x3_kernel<TA, TB>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec, whole, parts, pchunk)
+    hipLaunchKernelGGL((gemm_f32x3_kernel<TA, TB>), grid, block, 0, s, g, tiles_m, tiles_n, avec, bvec, whole, pchunk)
     if (g.ta && g.tb) DQ_LAUNCH(true, true);
     else if (g.ta) DQ_LAUNCH(true, false);
     else if (g.tb) DQ_LAUNCH(false, true);

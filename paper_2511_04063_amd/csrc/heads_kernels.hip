@@ -7,7 +7,7 @@
 //     Y = X R (R as two bf16 planes held in registers), the Whip loss and its gradient (Eq. 4) and the tile's
 //     contribution to G = X^T dY are formed on chip: Y and dY never reach HBM.
 //   * heads_reduce_kernel: sums the per-workgroup partial G and loss.
-// The derivative through the QR runs through the batched forms of the general kernels.
+//   * heads_backward_kernel: the derivative through the QR and the update, one problem per workgroup, out of LDS.
 #include <type_traits>
 
 #include "dq_internal.h"
@@ -505,8 +505,9 @@ __global__ __launch_bounds__(256) void heads_reduce_kernel(const float* __restri
 // The derivative through the QR of one problem per workgroup, out = alpha R M + beta out with
 //   B = R^T G,  P = strict_lower(B - B^T),  M U^T = P
 // (alpha = 1, beta = 0: dZ;  alpha = -lr, beta = 1: the updated latent).  Everything between R, G, U and the result stays in
-// LDS.  64 problems of order 128: 38 us, 32 of order 80: 25 us.  Before: the inverse of U in a launch beside the gradient's, which held its compute units' registers (24 us alone, done
-// 20 us after it at 64 x 128), and four batched launches, 31 us, nearly all of it launches, gaps and trips through memory.
+// LDS.  64 problems of order 128: 38 us, 32 of order 80: 25 us.  Before: the inverse of U in a launch beside the gradient's,
+// which held its compute units' registers (24 us alone, done 20 us after it at 64 x 128), and four batched launches, 31 us,
+// nearly all of it launches, gaps and trips through memory.
 // Bound: the fp32 matrix instructions of ONE compute unit (B 7 us at order 128, the triangular product, which skips its zero
 // blocks, 5 us) and the chain of the solve (four blocks of 32 columns from the right, about 1 us each).  16 wavefronts, one
 // 32 x 32 block each, dealt out so that every SIMD gets one of each block column (they differ in length).  LDS rows of 129
