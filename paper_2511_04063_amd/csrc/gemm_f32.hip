@@ -329,8 +329,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, i
 // 128 x 128 tiles, K step 32, four wavefronts of 64 x 64, ONE buffer of three planes per operand (60 KB) with the next K
 // step's operands in registers: two workgroups share a compute unit, one splits and stores while the other multiplies.  A
 // plane row holds 32 k (four 16-byte chunks) in 80 bytes, chunk c of row r stored at place c ^ (r / 16 % 4): the 8-byte stores
-// of a transposed operand, whose lanes lie four rows apart, hit every bank twice at most, and eight consecutive rows are
-// read without conflicts.
+// of a transposed operand, whose lanes lie four rows apart, hit every bank twice, and eight consecutive rows are read without
+// conflicts.  Counters at 5120^3: matrix cores 60 % busy, LDS 60 %, half of that bank conflicts.
 constexpr int kX3Resident = 512;   // workgroups resident at a time: two on each of 256 compute units
 constexpr int X3K = 32, X3LD = 40, X3PLANE = 128 * X3LD;   // K step; halfwords per row; per plane
 
