@@ -267,7 +267,7 @@ def run_config(cfg_name: str, args):
     # 2 n^3 where the model counts 4/3 n^3, the rotation product issues its flops twice for the two planes of R)
     # The library's default (DQ_OPT_SPLIT_GEMM = 1) moves the full n^3 products of the derivative (R^T G and R M: 3 n^3 of
     # the model's 4 n^3, the triangular solve stays) and all six of the Cayley update from the fp32 to the bf16 matrix
-    # cores when n is a multiple of 4096 (three-plane splits, six times the flops issued): the model's flops are booked to
+    # cores where planes pay, 4096 and 8192 of the workloads here (six times the flops issued): the model's flops are booked to
     # the class that runs them.  The other large fp32 products (128 x 128 tiles) split their operands while they read them;
     # they stay in the fp32 class and are priced at the fp32 peak, which they may exceed.
     split = n % 4096 == 0
@@ -277,6 +277,8 @@ def run_config(cfg_name: str, args):
         work = b * ((side - moved) * n ** 3 + (0.0 if bf16 else 4.0 * T * n * n))
         roof = {"bound": "mfma", "achieved": work * args.steps / class_s / 1e12, "peak": PEAK["fp32_mfma_tflops"],
                 "unit": "TFLOP/s"}
+        # the tiles that split their operands run on the bf16 matrix cores, six products each
+        roof["frac_split_peak"] = roof["achieved"] / (PEAK["bf16_mfma_tflops"] / 6.0)
     elif dominant == B.DQ_K_GEMM_BF16:
         work = b * ((4.0 * T * n * n if bf16 else 0.0) + moved * n ** 3)
         roof = {"bound": "mfma", "achieved": work * args.steps / class_s / 1e12, "peak": PEAK["bf16_mfma_tflops"],
