@@ -1563,7 +1563,7 @@ dq_status dq_rotate_loss_grad(dq_ctx* c, int b, int T, int n, const void* X, dq_
     DQ_TRY(check_ws(c, L));
     if (heads_fused_route(c, n, xdt) && Y == nullptr && dY == nullptr) {
         const int gb = heads_group(c, L, b, T, n);
-        if (gb < 1) return DQ_ERR_WORKSPACE;
+        if (gb < 1 && b > 0) return DQ_ERR_WORKSPACE;
         const HeadsLayout H = make_heads_layout(L, gb, T, n);
         for (int i = 0; i < b; i += gb)
             DQ_TRY(heads_rotate_loss_grad(c, H, b - i < gb ? b - i : gb, n, T, static_cast<const bf16_t*>(X) + (long)i * T * ldx,
@@ -1598,7 +1598,7 @@ dq_status dq_calib_step(dq_ctx* c, int b, int T, int n, const void* X, dq_dtype 
     const size_t esz = (xdt == DQ_BF16) ? 2 : 4;
     if (heads_route(c, n)) {
         const int gb = heads_group(c, L, b, T, n);
-        if (gb < 1) return DQ_ERR_WORKSPACE;
+        if (gb < 1 && b > 0) return DQ_ERR_WORKSPACE;
         for (int i = 0; i < b; i += gb) {
             float* Zi = Z + (long)i * n * ldz;
             DQ_TRY(heads_step(c, L, b - i < gb ? b - i : gb, T, n, static_cast<const char*>(X) + (size_t)i * T * ldx * esz, xdt,
@@ -1938,7 +1938,7 @@ dq_status dq_calib_step_adam(dq_ctx* c, int b, int T, int n, const void* X, dq_d
     const float c2 = (float)(1.0 / (1.0 - pow((double)beta2, (double)step)));
     if (heads_route(c, n)) {
         const int gb = heads_group(c, L, b, T, n);
-        if (gb < 1) return DQ_ERR_WORKSPACE;
+        if (gb < 1 && b > 0) return DQ_ERR_WORKSPACE;
         float* dZh = at<float>(c, make_heads_layout(L, gb, T, n).dZ);
         for (int i = 0; i < b; i += gb) {
             const int g = b - i < gb ? b - i : gb;

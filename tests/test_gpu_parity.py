@@ -2238,6 +2238,12 @@ def test_qr_backward_of_small_rotations_needs_no_room_per_problem():
         with pytest.raises(B.DartQRError) as e:
             c.dq_rotate_loss_grad(X, B.DQ_BF16, R, B.DQ_REDUCE_TOKEN_MEAN, torch.zeros(b, device="cuda"), out[0])
         assert e.value.status == B.DQ_ERR_WORKSPACE
+        # no problems: nothing to do, whatever the room
+        loss = torch.zeros(b, device="cuda")
+        assert c.lib.dq_rotate_loss_grad(c.h, 0, 1, n, X.data_ptr(), B.DQ_BF16, 104, R.data_ptr(), n, B.DQ_REDUCE_TOKEN_MEAN,
+                                         loss.data_ptr(), out[0].data_ptr(), n, None, 0, None, 0) == B.DQ_OK
+        assert c.lib.dq_calib_step(c.h, 0, 1, n, X.data_ptr(), B.DQ_BF16, 104, U.data_ptr(), n, 1e-3, B.DQ_REDUCE_TOKEN_MEAN,
+                                   loss.data_ptr(), None, 0) == B.DQ_OK
     finally:
         torch.cuda.synchronize()
         c.close()
