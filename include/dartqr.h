@@ -74,9 +74,10 @@ typedef enum { DQ_OBJ_WHIP = 0, DQ_OBJ_VARIANCE = 1, DQ_OBJ_KURTOSIS = 2, DQ_OBJ
 /* bits of the device status word */
 #define DQ_FLAG_SINGULAR   1u   /* a zero appeared on diag(U): Z is singular (dZ undefined)  */
 #define DQ_FLAG_NONFINITE  2u   /* a NaN or Inf was seen in a pivot or in the loss           */
-#define DQ_FLAG_ILLCOND_PANEL 4u /* informational: a tall 64-column panel of the QR was too ill-conditioned for the
-                                   many-CU panel route and was factored by the one-workgroup Householder kernel
-                                   instead; results are valid */
+#define DQ_FLAG_ILLCOND_PANEL 4u /* informational: columns of one block of the QR cancel against each other by more than 2^14 in
+                                   length (with a Householder option set: a tall 64-column panel was too ill-conditioned for
+                                   the many-CU panel route and was factored by the one-workgroup Householder kernel
+                                   instead); results are valid */
 #define DQ_FLAG_BAD_INDEX  8u   /* dq_gather_rows met an index outside [0, T_all): that row was not written  */
 #define DQ_FLAG_SYNC_TIMEOUT 16u /* a device-side wait between the library's streams (DQ_OPT_DEVICE_SYNC) ran into its
                                    time limit: the results of that call are invalid */
@@ -107,6 +108,8 @@ const char* dq_status_string(dq_status s);
  * best.  Takes effect for the calls that follow.  DQ_ERR_DTYPE for an unknown option, DQ_ERR_SHAPE for a value out of
  * range; the setting is unchanged on error. */
 typedef enum {
+    /* DQ_OPT_ACCUM_PANELS, _TALL_PANEL_MIN_ROWS, _FUSED_PANEL and _TWO_LEVEL_ROWS speak of the pieces of the blocked
+     * Householder QR; a value other than its default in any of them chooses that QR for n > 128. */
     DQ_OPT_ACCUM_PANELS = 0,        /* panels whose reflectors are merged before they are applied to the accumulated
                                        rotation: 1, 2 or 4; 0 (default): by size, 2 below n = 8192 and 4 from there on */
     DQ_OPT_TALL_PANEL_MIN_ROWS = 1, /* 64-column panels at least this tall take the many-compute-unit route
@@ -159,8 +162,9 @@ dq_status dq_device_flags(dq_ctx* ctx, unsigned* host_out);
 /* ---- the hot path ------------------------------------------------------------------- */
 
 /* Sec. 4.3 / the QR step of Alg. 1:  Z (n x n) -> orthogonal R and, optionally, upper-triangular U with
- * Z = R U.  Computed by blocked Householder QR (Alg. 2 in blocked compact-WY form) followed by
- * sign normalisation so that diag(U) >= 0, which makes R unique for nonsingular Z.
+ * Z = R U and diag(U) >= 0, which makes R unique for nonsingular Z.  n <= 128: Alg. 2 as printed, one workgroup a problem.
+ * Above: by blocks of 256 columns, Cholesky of their Gram matrices in fp64, twice; blocked Householder QR (Alg. 2 in
+ * blocked compact-WY form) followed by sign normalisation where one of its options below is set.
  * Z: in, b x (n x n) fp32.  R: out, fp32.  U_or_null: out, fp32, strictly-lower part written as 0. */
 dq_status dq_qr_orth(dq_ctx* ctx, int b, int n,
                      const float* Z, long ldz, float* R, long ldr,

@@ -574,8 +574,231 @@ bool device_sync_usable(dq_ctx* c) {
     return ok;
 }
 
+// ---------------------------------------------------------------- S1 + S2 from Gram matrices
+// A product cut along K where its 128 x 128 tiles leave compute units idle, its parts in `part`; products of fewer than 96 parts of
+// that size take 64 x 64 tiles.  Parts: how many there are (1 only if `whole` allows it: then C itself is written) and how they lie.
+struct Parts { int splits = 1; long stride = 0, ld = 0; };
+dq_status multiply_in_parts(dq_ctx* c, hipStream_t s, GemmF32 g, float* part, size_t part_floats, bool whole, Parts& p) {
+    p.ld = round_up(g.N, 4);
+    p.stride = (long)g.M * p.ld;
+    const long room = (long)(part_floats / (size_t)p.stride);
+    if (room < 1) return DQ_ERR_WORKSPACE;
+    const int tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+    int kchunk;
+    p.splits = 512 / tiles;                    // two workgroups of that tile share a compute unit
+    if (p.splits > g.K / 256) p.splits = g.K / 256;
+    if (p.splits > room) p.splits = (int)room;
+    if (p.splits < 1) p.splits = 1;
+    if (tiles * p.splits < 96) {
+        g.cfg = 3;
+        choose_split(((g.M + 63) / 64) * ((g.N + 63) / 64), g.K, 32, room < kMaxSplit ? (int)room : kMaxSplit, p.splits, kchunk);
+    } else {
+        kchunk = (int)round_up((g.K + p.splits - 1) / p.splits, 32);
+        p.splits = (g.K + kchunk - 1) / kchunk;
+    }
+    g.splits = p.splits; g.kchunk = kchunk; g.split_stride = p.stride;
+    if (p.splits > 1 || !whole) {
+        g.C = part; g.ldc = p.ld; g.alpha = 1.f; g.beta = 0.f;
+    }
+    LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * g.M * (double)g.N * g.K, 0.0);
+    DQ_HIP(product_f32(c, g, s));
+    return DQ_OK;
+}
+
+// C = alpha op(A) op(B) + beta C in parts and a second launch that sums them
+dq_status product_in_parts(dq_ctx* c, hipStream_t s, const GemmF32& g, float* part, size_t part_floats) {
+    Parts p;
+    DQ_TRY(multiply_in_parts(c, s, g, part, part_floats, true, p));
+    if (p.splits > 1) {
+        LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
+        DQ_HIP(launch_splitk_reduce(part, p.splits, p.stride, p.ld, g.M, g.N, g.alpha, g.beta, g.C, g.ldc, s));
+    }
+    return DQ_OK;
+}
+
+// A block's scratch on one stream: its Gram matrix, the inverses of the 64 x 64 diagonal blocks, the words that ask for refinement and
+// for a third projection, and room for partial sums.
+struct GramScratch {
+    double* G; double* dev; float* inv; unsigned* refine; unsigned* again; float* part; size_t part_floats;
+    GramScratch(char* base, size_t bytes) {
+        size_t cur = 0;
+        G = reinterpret_cast<double*>(base + bump(cur, (size_t)kGramBlock * kGramBlock * 8));
+        dev = reinterpret_cast<double*>(base + bump(cur, (size_t)kGramSums * 8));
+        inv = reinterpret_cast<float*>(base + bump(cur, (size_t)kGramBlock * 64 * 4));
+        refine = reinterpret_cast<unsigned*>(base + bump(cur, 256));
+        again = refine + 1;
+        part = reinterpret_cast<float*>(base + cur);
+        part_floats = (bytes - cur) / 4;
+    }
+};
+
+// G = V^T V, U made ready for gram_factor
+dq_status gram_form(dq_ctx* c, hipStream_t s, const GramScratch& w, int n, int nc, const float* V, long ldv, float* U, long ldu,
+                    const SecondPass& second = SecondPass()) {
+    if (gram64_part_doubles(n, nc) * 2 > w.part_floats) return DQ_ERR_WORKSPACE;
+    LaunchScope sc(&c->prof, s, DQ_K_PANEL, (double)n * nc * nc, 0.0);
+    DQ_HIP(launch_gram64(V, ldv, n, nc, reinterpret_cast<double*>(w.part), w.G, U, ldu, w.inv, second, s));
+    return DQ_OK;
+}
+
+// V (n x nc) <- Q with V = Q U, U upper triangular, from G; a copy of Q to `copy` (may be null).  started: as for launch_chol64
+dq_status gram_factor(dq_ctx* c, hipStream_t s, const GramScratch& w, int n, int nc, float* V, long ldv, float* U, long ldu,
+                      float* copy, long ldcopy, unsigned long long* started, unsigned long long value,
+                      const SecondPass& second = SecondPass()) {
+    LaunchScope sc(&c->prof, s, DQ_K_PANEL, (double)n * nc * nc, 0.0);
+    DQ_HIP(launch_chol64(w.G, nc, U, ldu, w.inv, w.refine, at<unsigned>(c, 0), second, started, value, s));
+    DQ_HIP(launch_block_solve(V, ldv, n, nc, U, ldu, w.inv, w.refine, copy, ldcopy, s));
+    return DQ_OK;
+}
+
+// The QR by blocks of 256 columns.  For block J, on three streams:
+//   caller's   Q_J U_JJ = A_J by Cholesky of A_J^T A_J in fp64; W = Q_J^T A and A -= Q_J W for the next block's columns
+//   second     the same for the columns behind those
+//   third      Q_J once more against the finished columns of R, S = R_<J^T Q_J, V = Q_J - R_<J S, and against itself,
+//              R_J T_JJ = V; then U's column block, U = T U' with U' what the first pass gave and T = [S; T_JJ]
+// The first pass leaves Z = Q U' to rounding whatever Q's orthogonality (U' holds what was taken off), and Q^T Q - I at rounding
+// times the condition number; the second brings that to rounding.  Error against 64 bits at n = 700 and 2048, Gaussian
+// latents, latents near a rotation, with columns parallel to 1e-5 and with columns of all lengths: half to a third of
+// LAPACK's fp32 Householder QR in R^T R - I, R U - Z and U.
+dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long ldz, float* R, long ldr, float* U, long ldu) {
+    hipStream_t sA = c->stream, sB = c->single_stream ? sA : c->stream2, sC = c->single_stream ? sA : c->stream3;
+    const bool many = !c->single_stream;
+    float* A = at<float>(c, L.A);
+    float* U1 = at<float>(c, L.B);        // free until S6
+    float* Tm = at<float>(c, L.M);
+    float* T2 = at<float>(c, L.qw);       // n x 256
+    const long ld = L.ld;
+    const GramScratch wA(at<char>(c, L.wpart), L.w2 - L.wpart), wC(at<char>(c, L.qpart), L.qw - L.qpart);
+    float* farpart = at<float>(c, L.gsplit);
+    auto order = [&](hipStream_t after, hipStream_t s, int ev) -> hipError_t {   // s goes on behind what `after` holds now
+        hipError_t e = hipEventRecord(c->sync_ev[ev], after);
+        return e != hipSuccess ? e : hipStreamWaitEvent(s, c->sync_ev[ev], 0);
+    };
+    const int nb = (n + kGramBlock - 1) / kGramBlock;
+    const int ev_start = 4 * nb, ev_end = 4 * nb + 1;
+    if (many) DQ_HIP(order(sA, sC, ev_start));     // (the second stream is joined and left again block by block)
+    {
+        LaunchScope sc(&c->prof, sA, DQ_K_SMALL, 0.0, 8.0 * n * (double)n);
+        DQ_HIP(launch_copy2d(Z, ldz, A, ld, n, n, sA));
+    }
+    if (U != nullptr) {
+        LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 4.0 * n * (double)n);
+        DQ_HIP(launch_copy2d(nullptr, 0, U, ldu, n, n, sC));
+    }
+    auto take_off = [&](hipStream_t s, int c0, int nc, int c1, int n1, float* part, size_t part_floats) -> dq_status {
+        if (n1 < 1) return DQ_OK;
+        GemmF32 g;    // U1[J, c1 ..] = Q_J^T A[:, c1 ..]
+        g.A = A + c0; g.lda = ld; g.ta = 1;
+        g.B = A + c1; g.ldb = ld;
+        g.C = U1 + (long)c0 * ld + c1; g.ldc = ld;
+        g.M = nc; g.N = n1; g.K = n;
+        DQ_TRY(product_in_parts(c, s, g, part, part_floats));
+        GemmF32 u;    // A[:, c1 ..] -= Q_J U1[J, c1 ..]
+        u.A = A + c0; u.lda = ld;
+        u.B = U1 + (long)c0 * ld + c1; u.ldb = ld;
+        u.C = A + c1; u.ldc = ld;
+        u.M = n; u.N = n1; u.K = nc;
+        u.alpha = -1.f; u.beta = 1.f;
+        LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * n * (double)n1 * nc, 0.0);
+        DQ_HIP(product_f32(c, u, s));
+        return DQ_OK;
+    };
+    auto col = [&](int J) { return J * kGramBlock < n ? J * kGramBlock : n; };
+    auto second_pass = [&](int J) -> dq_status {
+        const int c0 = col(J), c1 = col(J + 1), nc = c1 - c0;
+        SecondPass second;
+        second.dev = wC.dev; second.again = wC.again;
+        if (J > 0) {
+            GemmF32 g;    // S = R_<J^T Q_J
+            g.A = R; g.lda = ldr; g.ta = 1;
+            g.B = A + c0; g.ldb = ld;
+            g.M = c0; g.N = nc; g.K = n;
+            Parts p;
+            DQ_TRY(multiply_in_parts(c, sC, g, wC.part, wC.part_floats, false, p));
+            {
+                LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
+                DQ_HIP(launch_second_sum(wC.part, p.splits, p.stride, p.ld, c0, nc, Tm + c0, ld, wC.again, sC));
+            }
+            GemmF32 v;    // V = Q_J - R_<J S
+            v.A = R; v.lda = ldr;
+            v.B = Tm + c0; v.ldb = ld;
+            v.C = R + c0; v.ldc = ldr;
+            v.M = n; v.N = nc; v.K = c0;
+            v.alpha = -1.f; v.beta = 1.f;
+            DQ_TRY(product_in_parts(c, sC, v, wC.part, wC.part_floats));
+            // Where that was most of a column, what is left is orthogonal to R_<J to rounding of what was taken off only: once more,
+            // S2 = R_<J^T V, V -= R_<J S2, S += S2.  (Two launches that do nothing otherwise.)
+            second.T = Tm + c0; second.ldt = ld; second.T2 = T2; second.ldt2 = kGramBlock; second.trows = c0;
+            LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
+            g.B = R + c0; g.ldb = ldr;
+            g.C = T2; g.ldc = kGramBlock;
+            g.only_if = wC.again; g.cfg = 3;
+            DQ_HIP(launch_gemm_f32(g, sC));
+            v.B = T2; v.ldb = kGramBlock;
+            v.only_if = wC.again; v.cfg = 3;
+            DQ_HIP(launch_gemm_f32(v, sC));
+        }
+        float* T = Tm + (long)c0 * ld + c0;
+        DQ_TRY(gram_form(c, sC, wC, n, nc, R + c0, ldr, T, ld, second));
+        DQ_TRY(gram_factor(c, sC, wC, n, nc, R + c0, ldr, T, ld, nullptr, 0, nullptr, 0, second));
+        if (U != nullptr) {
+            GemmF32 g;    // the column block of U
+            g.A = Tm; g.lda = ld; g.a_upper = 1;
+            g.B = U1 + c0; g.ldb = ld;
+            g.C = U + c0; g.ldc = ldu;
+            g.M = c1; g.N = nc; g.K = c1;
+            DQ_TRY(product_in_parts(c, sC, g, wC.part, wC.part_floats));
+        }
+        return DQ_OK;
+    };
+    // The products behind a block start when one workgroup has begun to factor the next block's Gram matrix: they have the chip
+    // meanwhile, and the short kernels of the chain have it in between.  Started right behind the block they slow those down (n =
+    // 4096: 3.77 ms), and started before that workgroup they keep it from a compute unit until the first of them end (3.48 ms).
+    // Without a hand-over between streams they follow the Gram matrix.  The wait orders nothing that the result depends on
+    // (events do), so that one that runs into its limit costs time only.
+    constexpr long kHintUs = 1000;
+    const bool hint = many && device_sync_usable(c);
+    unsigned long long* started = hint ? sync_words(c) + 14 : nullptr;
+    const unsigned long long seq0 = c->seq;
+    c->seq += nb + 1;
+    for (int J = 0; J < nb; ++J) {
+        const int c0 = col(J), c1 = col(J + 1), c2 = col(J + 2), nc = c1 - c0;
+        float* Uj = U1 + (long)c0 * ld + c0;
+        DQ_TRY(gram_form(c, sA, wA, n, nc, A + c0, ld, Uj, ld));
+        if (many && !hint && J > 0) DQ_HIP(hipEventRecord(c->sync_ev[2 * J], sA));
+        DQ_TRY(gram_factor(c, sA, wA, n, nc, A + c0, ld, Uj, ld, R + c0, ldr, started, seq0 + J + 1));
+        if (J > 0) {
+            for (hipStream_t s : {sB, sC}) {
+                if (!many || (s == sB && c1 >= n)) continue;
+                DQ_HIP(hipStreamWaitEvent(s, c->sync_ev[2 * J], 0));
+                if (hint) DQ_HIP(launch_stream_wait(started, seq0 + J + 1, kHintUs, nullptr, nullptr, s));
+            }
+            DQ_TRY(take_off(sB, col(J - 1), kGramBlock, c1, n - c1, farpart, L.gsplit_floats));
+            if (many && c1 < n) {
+                DQ_HIP(hipEventRecord(c->sync_ev[2 * J + 1], sB));
+                DQ_HIP(hipStreamWaitEvent(sA, c->sync_ev[2 * J + 1], 0));
+            }
+            DQ_TRY(second_pass(J - 1));
+        }
+        if (c1 < n) {
+            if (hint) DQ_HIP(hipEventRecord(c->sync_ev[2 * J + 2], sA));
+            DQ_TRY(take_off(sA, c0, nc, c1, c2 - c1, wA.part, wA.part_floats));
+        }
+    }
+    if (many) DQ_HIP(order(sA, sC, 0));
+    DQ_TRY(second_pass(nb - 1));
+    if (many) DQ_HIP(order(sC, sA, ev_end));
+    return DQ_OK;
+}
+
+// The settings that speak of the blocked Householder route's pieces choose that route.
+bool gram_route(const dq_ctx* c, int n) {
+    return n > kHeadDim && c->accum_panels == 0 && c->chol_min_m == kPanel && c->fused_panel == 1 && c->two_level_rows < 0;
+}
+
 dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ldz, float* R, long ldr, float* U,
                       long ldu) {
+    if (gram_route(c, n)) return qr_orth_gram(c, L, n, Z, ldz, R, ldr, U, ldu);
     hipStream_t sA = c->stream, sB = c->single_stream ? c->stream : c->stream2,
                 sC = c->single_stream ? c->stream : c->stream3;
     float* A = at<float>(c, L.A);

@@ -18,6 +18,7 @@ constexpr int kHeadsChunk = 2048;     // most tokens per workgroup of its fused 
 constexpr int kLossPartials = 65536; // upper bound on workgroups of the Whip pass (one partial each)
 constexpr int kAccumPanels = 4;      // panels whose reflectors are merged before they are applied to the accumulated R
 constexpr int kCholMaxParts = 64;    // upper bound on the Gram partials of the tall-panel path
+constexpr int kGramBlock = 256;      // columns of a block of the QR by fp64 Gram matrices
 
 typedef uint16_t bf16_t;             // raw bfloat16 storage
 
@@ -78,6 +79,8 @@ struct GemmF32 {
     int b_unit_lower_cols = 0;
     // B(k, n) is known to vanish for k <= n (strictly lower triangular, tb == 0): K loop starts at the tile's n0.
     int b_strict_lower = 0;
+    // A(m, k) is known to vanish for k < m (upper triangular, ta == 0): K loop starts at the tile's m0.
+    int a_upper = 0;
     // split-K: z-th workgroup layer reduces k in [z*kchunk, (z+1)*kchunk) and writes C + z*split_stride
     int splits = 1; int kchunk = 0; long split_stride = 0;
     // with x3: scratch for the parts of tiles that would leave most of the chip idle (null: none)
@@ -86,6 +89,7 @@ struct GemmF32 {
     // with x3, for operands whose values are not known to have a split: kGuardWords words of launch_range_scan over them.  Where
     // one is set, the kernel forms the same product on the fp32 matrix cores, with the bits of the tile without x3.
     const unsigned* guard = nullptr;
+    const unsigned* only_if = nullptr;   // 64 x 64 tiles only: a device word; where it is 0 the launch does nothing
     int cfg = -1;          // tile configuration (-1: chosen from the shape; 3: 64 x 64 tiles, K step 32)
     // batch > 1: that many independent products in one launch; problem i reads A + i*batch_a, B + i*batch_b and
     // writes C + i*batch_c (element offsets)
@@ -235,6 +239,34 @@ hipError_t launch_cholqr_fused(float* A, long lda, int m, float* Tout, float* Yp
                                float* tslices, unsigned* status, unsigned long long* words, unsigned long long epoch,
                                unsigned long long target, unsigned long long target_rows, long limit_us, hipStream_t s,
                                const HandOver* ho);
+
+// ---- QR by blocks of kGramBlock columns from fp64 Gram matrices ---------------------
+// G (kGramBlock x kGramBlock row-major, upper triangle, the identity past the last column) = A^T A of a rows x cols block; part:
+// gram64_part_doubles() of scratch.  U and inv: those of launch_chol64, made ready for it (zeros below U's diagonal).
+constexpr int kGramSums = 160;
+size_t gram64_part_doubles(int rows, int cols);
+// What the second pass has beside that.  dev (kGramSums doubles): U and inv get what launch_chol64 gives where G is the identity up to
+// a first pass's rounding, and dev what tells it so.  T (trows x cols) += T2 where *again is set.
+struct SecondPass {
+    double* dev = nullptr; float* T = nullptr; long ldt = 0; const float* T2 = nullptr; long ldt2 = 0; int trows = 0;
+    unsigned* again = nullptr;
+};
+hipError_t launch_gram64(const float* A, long lda, int rows, int cols, double* part, double* G, float* U, long ldu, float* inv,
+                         const SecondPass& second, hipStream_t s);
+// S (rows x cols) = the sum of `splits` parts, as launch_splitk_reduce; *again = 1 where an entry of it is above 2^-9: what the second
+// pass takes off a column may then be most of it, and has to be taken off once more
+hipError_t launch_second_sum(const float* part, int splits, long stride, long ldp, int rows, int cols, float* S, long lds_,
+                             unsigned* again, hipStream_t s);
+// U (cols x cols, zeros below the diagonal) with U^T U = G; inv: the inverses of its 64 x 64 diagonal blocks (row-major, the last
+// one filled up with the identity); *refine: whether launch_block_solve needs its step of refinement.  A column that vanishes
+// raises DQ_FLAG_SINGULAR and, in the first pass, DQ_FLAG_ILLCOND_PANEL, which strong cancellation raises as well.
+// second: as for launch_gram64; *second.again is cleared for the next block.  started (optional): a word that takes `value` as soon
+// as the kernel has its compute unit.
+hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, unsigned* refine, unsigned* flags,
+                         const SecondPass& second, unsigned long long* started, unsigned long long value, hipStream_t s);
+// A (rows x cols) <- A U^-1, and a copy of it to R (may be null)
+hipError_t launch_block_solve(float* A, long lda, int rows, int cols, const float* U, long ldu, const float* inv,
+                              const unsigned* refine, float* R, long ldr, hipStream_t s);
 
 // T (kPanel x kPanel, upper, zero beyond jb) of the compact-WY form from the slice T factors and the split-K
 // partials of V^T [V | C] (gpart[z] at stride, leading dimension ldp: jb Gram columns, then nla columns of V^T C).

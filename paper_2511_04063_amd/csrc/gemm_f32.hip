@@ -247,6 +247,7 @@ template <bool TA, bool TB, int BM, int BN, int WT, int BK>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, int tiles_n, int avec, int bvec) {
     __shared__ __attribute__((aligned(16))) float As[2][BK][BM + 4];
     __shared__ __attribute__((aligned(16))) float Bs[2][BK][BN + 4];
+    if (BM == 64 && BN == 64 && g.only_if != nullptr && *g.only_if == 0u) return;
     constexpr int WAVES_N = BN / (32 * WT);
     static_assert((BM / (32 * WT)) * WAVES_N == 4, "four wavefronts per workgroup");
 
@@ -285,6 +286,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g, int tiles_m, i
         const int lo = (n0 / BK) * BK;
         kb = kb > lo ? kb : lo;
     }
+    if (g.a_upper) kb = kb > m0 ? kb : m0;
 
     OperandView oa, ob;
     const long bz = blockIdx.z;   // independent problem of a batched launch
@@ -494,6 +496,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(GemmF32 g, int tiles
         ke = kb + pchunk < g.K ? kb + pchunk : g.K;
     }
     if (g.b_strict_lower) kb = kb > n0 ? kb : n0;   // n0 is a multiple of the K step
+    if (g.a_upper) kb = kb > m0 ? kb : m0;
 
     OperandView oa, ob;
     const long bz = blockIdx.z;
@@ -648,7 +651,7 @@ static hipError_t launch_gemm_f32x3(const GemmF32& g, hipStream_t s) {
     // second launch: 2890^3, 529 tiles, 497 us whole; the fewer than 512 tiles of a product up to 2816 wide are all cut.
     const int tiles = tiles_m * tiles_n, rest = tiles % kX3Resident;
     int parts = 1;
-    if (g.tail != nullptr && g.splits <= 1 && g.batch <= 1 && !g.b_strict_lower && g.K >= 768 && rest > 0) {
+    if (g.tail != nullptr && g.splits <= 1 && g.batch <= 1 && !g.b_strict_lower && !g.a_upper && g.K >= 768 && rest > 0) {
         parts = kX3Resident / rest;
         if (parts > g.K / 256) parts = g.K / 256;
         const long room = g.tail_floats / ((long)rest * 128 * 128);

@@ -1,0 +1,102 @@
+"""The QR by blocks of 256 columns (fp64 Gram matrices, two passes) at the edges of its tiles and blocks, against 64 bits."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2511_04063_amd import binding as B  # noqa: E402
+
+
+def _latent(n, kind):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31 * n + len(kind))
+    Z = torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64)
+    if kind == "rotation":       # a rotation as the start, moved by the steps since
+        Z = torch.linalg.qr(Z)[0] + 0.3 / np.sqrt(n) * torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64)
+    elif kind == "lengths":      # columns of all lengths, 2^-40 to 2^40 among them
+        Z *= torch.exp2(torch.linspace(-40, 40, n, device="cuda", dtype=torch.float64)[torch.randperm(n, generator=g, device="cuda")])
+    elif kind == "parallel":     # columns of one block parallel to 1e-5: its factor asks for refinement
+        Z[:, n // 2 + 3] = Z[:, n // 2] + 1e-5 * torch.randn(n, generator=g, device="cuda", dtype=torch.float64)
+    elif kind == "spanned":      # the last column nearly spanned by the first ones: the second pass has most of it to take off
+        Z[:, n - 1] = Z[:, :40] @ torch.randn(40, generator=g, device="cuda", dtype=torch.float64) / 6.0 + 1e-5 * Z[:, n - 1]
+    ld = -(-n // 4) * 4
+    out = torch.full((n, ld), float("nan"), device="cuda")
+    out[:, :n] = Z
+    return out[:, :n]
+
+
+def _padded(n):
+    buf = torch.full((n, -(-n // 4) * 4 + 4), 7.0, device="cuda")
+    return buf, buf[:, :n]
+
+
+@pytest.mark.parametrize("kind", ["gauss", "rotation", "lengths", "parallel", "spanned"])
+@pytest.mark.parametrize("n", [129, 144, 191, 255, 256, 257, 272, 511, 513, 770])
+def test_blocks_of_256_columns(n, kind):
+    """Last blocks of 1 to 256 columns, full and cut 16- and 64-column tiles.  R^T R - I, R U - Z column by column and the form of
+    U; the same bits whichever way the streams wait for each other, on one stream, call after call and without U; nothing
+    written beside R and U.  Bars: an fp32 factor can be orthogonal and reproduce Z to some 2^-24 (measured up to 2.6e-7 and
+    7e-7 over all kinds, LAPACK's fp32 QR 8e-7 and 1.2e-6)."""
+    Z = _latent(n, kind)
+    # what cancels strongly inside a block is reported
+    inside = (kind == "parallel" and n // 2 // 256 == (n // 2 + 3) // 256) or (kind == "spanned" and n <= 256)
+    first = None
+    for device_sync, single in ((1, 0), (1, 0), (0, 0), (0, 1)):
+        c = B.Context()
+        try:
+            c.ensure_workspace(1, n, 1, B.DQ_F32)
+            c.dq_set_option(B.DQ_OPT_DEVICE_SYNC, device_sync)
+            c.dq_set_option(B.DQ_OPT_SINGLE_STREAM, single)
+            (Rb, R), (Ub, U) = _padded(n), _padded(n)
+            c.dq_qr_orth(Z, R, U)
+            R2 = torch.empty_like(Rb)[:, :n]
+            c.dq_qr_orth(Z, R2, None)
+            assert c.dq_device_flags() == (B.DQ_FLAG_ILLCOND_PANEL if inside else 0)
+            assert torch.equal(R, R2) and torch.all(Rb[:, n:] == 7.0) and torch.all(Ub[:, n:] == 7.0)
+            if first is None:
+                first = (R.clone(), U.clone())
+            assert torch.equal(R, first[0]) and torch.equal(U, first[1])
+        finally:
+            torch.cuda.synchronize()
+            c.close()
+    R, U = first[0].double(), first[1].double()
+    assert float((R.T.contiguous() @ R - torch.eye(n, device="cuda", dtype=torch.float64)).abs().max()) < 1e-6
+    res = (R @ U - Z.double()).norm(dim=0) / Z.double().norm(dim=0)
+    assert float(res.max()) < 2e-6
+    assert int(torch.count_nonzero(torch.tril(U, -1))) == 0 and bool((U.diagonal() > 0).all())
+
+
+@pytest.mark.parametrize("n", [300, 770])
+def test_blocks_under_capture(n):
+    """The same launches recorded into a graph, in a context that has met its stream before and in one that has not: every replay, on
+    other latents and with eager calls in between, gives the eager call's bits."""
+    latents = [_latent(n, k) for k in ("gauss", "rotation", "lengths", "gauss")]
+    for met in (True, False):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            c, e = B.Context(s), B.Context(s)
+            Z, R, U, Re, Ue = (_padded(n)[1] for _ in range(5))
+            Z.copy_(latents[0])
+            try:
+                for x in (c, e):
+                    x.ensure_workspace(1, n, 1, B.DQ_F32)
+                if met:
+                    c.dq_qr_orth(Z, R, U)
+                s.synchronize()
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=s):
+                    c.dq_qr_orth(Z, R, U)
+                for Zi in latents:
+                    Z.copy_(Zi)
+                    graph.replay()
+                    e.dq_qr_orth(Zi, Re, Ue)
+                    s.synchronize()
+                    assert torch.equal(R, Re) and torch.equal(U, Ue)
+                assert c.dq_device_flags() == 0
+            finally:
+                s.synchronize()
+                c.close()
+                e.close()
