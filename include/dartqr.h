@@ -77,7 +77,8 @@ typedef enum { DQ_OBJ_WHIP = 0, DQ_OBJ_VARIANCE = 1, DQ_OBJ_KURTOSIS = 2, DQ_OBJ
 #define DQ_FLAG_ILLCOND_PANEL 4u /* informational: columns of one block of the QR cancel against each other by more than 2^14 in
                                    length (with a Householder option set: a tall 64-column panel was too ill-conditioned for
                                    the many-CU panel route and was factored by the one-workgroup Householder kernel
-                                   instead); results are valid */
+                                   instead); results are valid.  Also: Z, singular in fp32 (condition number beyond 2^24), has left R
+                                   orthogonal to no better than 1e-6 */
 #define DQ_FLAG_BAD_INDEX  8u   /* dq_gather_rows met an index outside [0, T_all): that row was not written  */
 #define DQ_FLAG_SYNC_TIMEOUT 16u /* a device-side wait between the library's streams (DQ_OPT_DEVICE_SYNC) ran into its
                                    time limit: the results of that call are invalid */

@@ -575,43 +575,37 @@ bool device_sync_usable(dq_ctx* c) {
 }
 
 // ---------------------------------------------------------------- S1 + S2 from Gram matrices
-// A product cut along K where its 128 x 128 tiles leave compute units idle, its parts in `part`; products of fewer than 96 parts of
-// that size take 64 x 64 tiles.  Parts: how many there are (1 only if `whole` allows it: then C itself is written) and how they lie.
-struct Parts { int splits = 1; long stride = 0, ld = 0; };
-dq_status multiply_in_parts(dq_ctx* c, hipStream_t s, GemmF32 g, float* part, size_t part_floats, bool whole, Parts& p) {
-    p.ld = round_up(g.N, 4);
-    p.stride = (long)g.M * p.ld;
-    const long room = (long)(part_floats / (size_t)p.stride);
+// C = alpha op(A) op(B) + beta C, cut along K where the 128 x 128 tiles leave compute units idle, its parts in `part` and summed by a
+// second launch; products of fewer than 96 parts of that size take 64 x 64 tiles.
+dq_status product_in_parts(dq_ctx* c, hipStream_t s, GemmF32 g, float* part, size_t part_floats) {
+    const long ldp = round_up(g.N, 4), stride = (long)g.M * ldp, room = (long)(part_floats / (size_t)stride);
     if (room < 1) return DQ_ERR_WORKSPACE;
     const int tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    int kchunk;
-    p.splits = 512 / tiles;                    // two workgroups of that tile share a compute unit
-    if (p.splits > g.K / 256) p.splits = g.K / 256;
-    if (p.splits > room) p.splits = (int)room;
-    if (p.splits < 1) p.splits = 1;
-    if (tiles * p.splits < 96) {
+    int kchunk, splits = 512 / tiles;          // two workgroups of that tile share a compute unit
+    if (splits > g.K / 256) splits = g.K / 256;
+    if (splits > room) splits = (int)room;
+    if (splits < 1) splits = 1;
+    if (tiles * splits < 96) {
         g.cfg = 3;
-        choose_split(((g.M + 63) / 64) * ((g.N + 63) / 64), g.K, 32, room < kMaxSplit ? (int)room : kMaxSplit, p.splits, kchunk);
+        choose_split(((g.M + 63) / 64) * ((g.N + 63) / 64), g.K, 32, room < kMaxSplit ? (int)room : kMaxSplit, splits, kchunk);
     } else {
-        kchunk = (int)round_up((g.K + p.splits - 1) / p.splits, 32);
-        p.splits = (g.K + kchunk - 1) / kchunk;
+        kchunk = (int)round_up((g.K + splits - 1) / splits, 32);
+        splits = (g.K + kchunk - 1) / kchunk;
     }
-    g.splits = p.splits; g.kchunk = kchunk; g.split_stride = p.stride;
-    if (p.splits > 1 || !whole) {
-        g.C = part; g.ldc = p.ld; g.alpha = 1.f; g.beta = 0.f;
+    g.splits = splits; g.kchunk = kchunk; g.split_stride = stride;
+    float *const out = g.C;
+    const long ldo = g.ldc;
+    const float alpha = g.alpha, beta = g.beta;
+    if (splits > 1) {
+        g.C = part; g.ldc = ldp; g.alpha = 1.f; g.beta = 0.f;
     }
-    LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * g.M * (double)g.N * g.K, 0.0);
-    DQ_HIP(product_f32(c, g, s));
-    return DQ_OK;
-}
-
-// C = alpha op(A) op(B) + beta C in parts and a second launch that sums them
-dq_status product_in_parts(dq_ctx* c, hipStream_t s, const GemmF32& g, float* part, size_t part_floats) {
-    Parts p;
-    DQ_TRY(multiply_in_parts(c, s, g, part, part_floats, true, p));
-    if (p.splits > 1) {
+    {
+        LaunchScope sc(&c->prof, s, DQ_K_GEMM_F32, 2.0 * g.M * (double)g.N * g.K, 0.0);
+        DQ_HIP(product_f32(c, g, s));
+    }
+    if (splits > 1) {
         LaunchScope sc(&c->prof, s, DQ_K_SMALL, 0.0, 0.0);
-        DQ_HIP(launch_splitk_reduce(part, p.splits, p.stride, p.ld, g.M, g.N, g.alpha, g.beta, g.C, g.ldc, s));
+        DQ_HIP(launch_splitk_reduce(part, splits, stride, ldp, g.M, g.N, alpha, beta, out, ldo, s));
     }
     return DQ_OK;
 }
@@ -620,13 +614,13 @@ dq_status product_in_parts(dq_ctx* c, hipStream_t s, const GemmF32& g, float* pa
 // for a third projection, and room for partial sums.
 struct GramScratch {
     double* G; double* dev; float* inv; unsigned* refine; unsigned* again; float* part; size_t part_floats;
-    GramScratch(char* base, size_t bytes) {
+    GramScratch(char* base, size_t bytes, size_t blocks) {
         size_t cur = 0;
         G = reinterpret_cast<double*>(base + bump(cur, (size_t)kGramBlock * kGramBlock * 8));
         dev = reinterpret_cast<double*>(base + bump(cur, (size_t)kGramSums * 8));
         inv = reinterpret_cast<float*>(base + bump(cur, (size_t)kGramBlock * 64 * 4));
         refine = reinterpret_cast<unsigned*>(base + bump(cur, 256));
-        again = refine + 1;
+        again = reinterpret_cast<unsigned*>(base + bump(cur, (blocks + 1) * 4));
         part = reinterpret_cast<float*>(base + cur);
         part_floats = (bytes - cur) / 4;
     }
@@ -646,7 +640,7 @@ dq_status gram_factor(dq_ctx* c, hipStream_t s, const GramScratch& w, int n, int
                       float* copy, long ldcopy, unsigned long long* started, unsigned long long value,
                       const SecondPass& second = SecondPass()) {
     LaunchScope sc(&c->prof, s, DQ_K_PANEL, (double)n * nc * nc, 0.0);
-    DQ_HIP(launch_chol64(w.G, nc, U, ldu, w.inv, w.refine, at<unsigned>(c, 0), second, started, value, s));
+    DQ_HIP(launch_chol64(w.G, nc, U, ldu, w.inv, V, ldv, n, w.refine, at<unsigned>(c, 0), second, started, value, s));
     DQ_HIP(launch_block_solve(V, ldv, n, nc, U, ldu, w.inv, w.refine, copy, ldcopy, s));
     return DQ_OK;
 }
@@ -656,6 +650,8 @@ dq_status gram_factor(dq_ctx* c, hipStream_t s, const GramScratch& w, int n, int
 //   second     the same for the columns behind those
 //   third      Q_J once more against the finished columns of R, S = R_<J^T Q_J, V = Q_J - R_<J S, and against itself,
 //              R_J T_JJ = V; then U's column block, U = T U' with U' what the first pass gave and T = [S; T_JJ]
+// Where V was small or ill-conditioned, R_J is orthogonal to R_<J only to rounding times that: R_J -= R_<J S with S = R_<J^T R_J once
+// more, and at the end U <- (I + S) U and a first-order correction of what S^T S has taken off the columns' orthogonality.
 // The first pass leaves Z = Q U' to rounding whatever Q's orthogonality (U' holds what was taken off), and Q^T Q - I at rounding
 // times the condition number; the second brings that to rounding.  Error against 64 bits at n = 700 and 2048, Gaussian
 // latents, latents near a rotation, with columns parallel to 1e-5 and with columns of all lengths: half to a third of
@@ -666,15 +662,14 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
     float* A = at<float>(c, L.A);
     float* U1 = at<float>(c, L.B);        // free until S6
     float* Tm = at<float>(c, L.M);
-    float* T2 = at<float>(c, L.qw);       // n x 256
     const long ld = L.ld;
-    const GramScratch wA(at<char>(c, L.wpart), L.w2 - L.wpart), wC(at<char>(c, L.qpart), L.qw - L.qpart);
+    const int nb = (n + kGramBlock - 1) / kGramBlock;
+    const GramScratch wA(at<char>(c, L.wpart), L.w2 - L.wpart, nb), wC(at<char>(c, L.qpart), L.qw - L.qpart, nb);
     float* farpart = at<float>(c, L.gsplit);
     auto order = [&](hipStream_t after, hipStream_t s, int ev) -> hipError_t {   // s goes on behind what `after` holds now
         hipError_t e = hipEventRecord(c->sync_ev[ev], after);
         return e != hipSuccess ? e : hipStreamWaitEvent(s, c->sync_ev[ev], 0);
     };
-    const int nb = (n + kGramBlock - 1) / kGramBlock;
     const int ev_start = 4 * nb, ev_end = 4 * nb + 1;
     if (many) DQ_HIP(order(sA, sC, ev_start));     // (the second stream is joined and left again block by block)
     {
@@ -707,18 +702,14 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
     auto second_pass = [&](int J) -> dq_status {
         const int c0 = col(J), c1 = col(J + 1), nc = c1 - c0;
         SecondPass second;
-        second.dev = wC.dev; second.again = wC.again;
+        second.dev = wC.dev; second.again = wC.again; second.block = J;
         if (J > 0) {
             GemmF32 g;    // S = R_<J^T Q_J
             g.A = R; g.lda = ldr; g.ta = 1;
             g.B = A + c0; g.ldb = ld;
             g.M = c0; g.N = nc; g.K = n;
-            Parts p;
-            DQ_TRY(multiply_in_parts(c, sC, g, wC.part, wC.part_floats, false, p));
-            {
-                LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
-                DQ_HIP(launch_second_sum(wC.part, p.splits, p.stride, p.ld, c0, nc, Tm + c0, ld, wC.again, sC));
-            }
+            g.C = Tm + c0; g.ldc = ld;
+            DQ_TRY(product_in_parts(c, sC, g, wC.part, wC.part_floats));
             GemmF32 v;    // V = Q_J - R_<J S
             v.A = R; v.lda = ldr;
             v.B = Tm + c0; v.ldb = ld;
@@ -726,17 +717,6 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
             v.M = n; v.N = nc; v.K = c0;
             v.alpha = -1.f; v.beta = 1.f;
             DQ_TRY(product_in_parts(c, sC, v, wC.part, wC.part_floats));
-            // Where that was most of a column, what is left is orthogonal to R_<J to rounding of what was taken off only: once more,
-            // S2 = R_<J^T V, V -= R_<J S2, S += S2.  (Two launches that do nothing otherwise.)
-            second.T = Tm + c0; second.ldt = ld; second.T2 = T2; second.ldt2 = kGramBlock; second.trows = c0;
-            LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
-            g.B = R + c0; g.ldb = ldr;
-            g.C = T2; g.ldc = kGramBlock;
-            g.only_if = wC.again; g.cfg = 3;
-            DQ_HIP(launch_gemm_f32(g, sC));
-            v.B = T2; v.ldb = kGramBlock;
-            v.only_if = wC.again; v.cfg = 3;
-            DQ_HIP(launch_gemm_f32(v, sC));
         }
         float* T = Tm + (long)c0 * ld + c0;
         DQ_TRY(gram_form(c, sC, wC, n, nc, R + c0, ldr, T, ld, second));
@@ -749,6 +729,23 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
             g.M = c1; g.N = nc; g.K = c1;
             DQ_TRY(product_in_parts(c, sC, g, wC.part, wC.part_floats));
         }
+        if (J == 0) return DQ_OK;
+        GemmF32 g;    // a third projection: two launches that do nothing otherwise.  S takes the place of the first pass's factor, now spent.
+        g.A = R; g.lda = ldr; g.ta = 1;
+        g.B = R + c0; g.ldb = ldr;
+        g.C = U1 + c0; g.ldc = ld;
+        g.M = c0; g.N = nc; g.K = n;
+        g.only_if = wC.again + J; g.cfg = 3;
+        GemmF32 v;
+        v.A = R; v.lda = ldr;
+        v.B = U1 + c0; v.ldb = ld;
+        v.C = R + c0; v.ldc = ldr;
+        v.M = n; v.N = nc; v.K = c0;
+        v.alpha = -1.f; v.beta = 1.f;
+        v.only_if = wC.again + J; v.cfg = 3;
+        LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
+        DQ_HIP(launch_gemm_f32(g, sC));
+        DQ_HIP(launch_gemm_f32(v, sC));
         return DQ_OK;
     };
     // The products behind a block start when one workgroup has begun to factor the next block's Gram matrix: they have the chip
@@ -787,6 +784,10 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
     }
     if (many) DQ_HIP(order(sA, sC, 0));
     DQ_TRY(second_pass(nb - 1));
+    if (nb > 1) {
+        LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
+        DQ_HIP(launch_third_pass(R, ldr, n, U1, ld, A, ld, U, ldu, wC.again, at<unsigned>(c, 0), sC));
+    }
     if (many) DQ_HIP(order(sC, sA, ev_end));
     return DQ_OK;
 }

@@ -246,27 +246,28 @@ hipError_t launch_cholqr_fused(float* A, long lda, int m, float* Tout, float* Yp
 constexpr int kGramSums = 160;
 size_t gram64_part_doubles(int rows, int cols);
 // What the second pass has beside that.  dev (kGramSums doubles): U and inv get what launch_chol64 gives where G is the identity up to
-// a first pass's rounding, and dev what tells it so.  T (trows x cols) += T2 where *again is set.
-struct SecondPass {
-    double* dev = nullptr; float* T = nullptr; long ldt = 0; const float* T2 = nullptr; long ldt2 = 0; int trows = 0;
-    unsigned* again = nullptr;
-};
+// a first pass's rounding, and dev what tells it so.  again: word J is raised where block J needs a third projection, word 0 where any
+// block does (cleared as the blocks go by; one word more than there are blocks).
+struct SecondPass { double* dev = nullptr; unsigned* again = nullptr; int block = 0; };
 hipError_t launch_gram64(const float* A, long lda, int rows, int cols, double* part, double* G, float* U, long ldu, float* inv,
                          const SecondPass& second, hipStream_t s);
-// S (rows x cols) = the sum of `splits` parts, as launch_splitk_reduce; *again = 1 where an entry of it is above 2^-9: what the second
-// pass takes off a column may then be most of it, and has to be taken off once more
-hipError_t launch_second_sum(const float* part, int splits, long stride, long ldp, int rows, int cols, float* S, long lds_,
-                             unsigned* again, hipStream_t s);
-// U (cols x cols, zeros below the diagonal) with U^T U = G; inv: the inverses of its 64 x 64 diagonal blocks (row-major, the last
-// one filled up with the identity); *refine: whether launch_block_solve needs its step of refinement.  A column that vanishes
-// raises DQ_FLAG_SINGULAR and, in the first pass, DQ_FLAG_ILLCOND_PANEL, which strong cancellation raises as well.
-// second: as for launch_gram64; *second.again is cleared for the next block.  started (optional): a word that takes `value` as soon
+// U (cols x cols, zeros below the diagonal) with U^T U = G = A^T A (A: rows x cols); inv: the inverses of its 64 x 64 diagonal blocks
+// (row-major, the last one filled up with the identity); *refine: what launch_block_solve has to do.  A block too ill-conditioned for
+// its Gram matrix is orthogonalised here, slowly: A <- Q.  A column that vanishes raises DQ_FLAG_SINGULAR and, in the first pass,
+// DQ_FLAG_ILLCOND_PANEL, which strong cancellation raises as well.
+// second: as for launch_gram64.  started (optional): a word that takes `value` as soon
 // as the kernel has its compute unit.
-hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, unsigned* refine, unsigned* flags,
-                         const SecondPass& second, unsigned long long* started, unsigned long long value, hipStream_t s);
+hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, float* A, long lda, int rows, unsigned* refine,
+                         unsigned* flags, const SecondPass& second, unsigned long long* started, unsigned long long value,
+                         hipStream_t s);
 // A (rows x cols) <- A U^-1, and a copy of it to R (may be null)
 hipError_t launch_block_solve(float* A, long lda, int rows, int cols, const float* U, long ldu, const float* inv,
                               const unsigned* refine, float* R, long ldr, hipStream_t s);
+// Where again[0]: U (may be null) <- (I + S) U, S (strictly upper by blocks, those where again[J] is not set taken as zero) from the third
+// projections, then R and U corrected for E = R^T R - I (n x n, scratch) to first order; entries of E above 2^-10, which only a latent
+// with a condition number beyond 2^24 leaves, raise DQ_FLAG_ILLCOND_PANEL.
+hipError_t launch_third_pass(float* R, long ldr, int n, const float* S, long lds_, float* E, long lde, float* U, long ldu,
+                             const unsigned* again, unsigned* flags, hipStream_t s);
 
 // T (kPanel x kPanel, upper, zero beyond jb) of the compact-WY form from the slice T factors and the split-K
 // partials of V^T [V | C] (gpart[z] at stride, leading dimension ldp: jb Gram columns, then nla columns of V^T C).

@@ -3,30 +3,31 @@
 // A block A_J is orthogonalised against itself by Cholesky: G = A_J^T A_J in fp64 on the fp64 matrix cores, G = U^T U in one
 // workgroup, Q_J = A_J U^-1 with the inverses of U's 64 x 64 diagonal blocks; then everything right of it loses its part along
 // Q_J.  A second pass orthogonalises Q_J once more, against the finished columns of R and against itself by the same
-// kernels, which leaves R orthogonal to rounding whenever Z's condition number is below 2^24.
+// kernels, and where that finds a block ill-conditioned a third projection and a correction at the end follow: R is orthogonal to
+// rounding whenever Z's condition number is below 2^24.
 //   gram64_kernel / gram64_sum_kernel   G of an m x <= 256 block: partial sums of row chunks, then their sum
 //   chol64_kernel                       U and the inverses of its 64 x 64 diagonal blocks
 //   block_solve_kernel                  A U^-1, rows dealt to the whole chip, with a step of refinement where U asks for it
-// fp64 holds the squares of any fp32 column and resolves condition numbers of a block up to 2^22, so that a block needs no other
-// factorisation beside this one.
+//   third_pass_kernel / correct_kernel  what the third projections mean for U, and the correction
+// fp64 holds the squares of any fp32 column and resolves condition numbers of a block up to 2^22; a block beyond that is orthogonalised
+// column by column in the Cholesky's workgroup.
+#include "dq_chol16.h"
 #include "dq_internal.h"
 #include "dq_wave.h"
 
 namespace dq {
 namespace {
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int GB = kGramBlock;        // columns of a block
 constexpr int GT = GB / 16;           // 16 x 16 tiles across
 static_assert(kGramSums == GB / 64 * (GB / 64 + 1) / 2 * 16, "workgroups of gram64_sum_kernel, 256 entries each");
-#define MFMA64(a, b, c) __builtin_amdgcn_mfma_f64_16x16x4f64((a), (b), (c), 0, 0, 0)
+constexpr unsigned kDone = 2u;        // *refine
+// The second pass's G = I + E.  Up to here U = I + X, and from there on its columns may have lost half their length or cancel against
+// each other, and what they have left along R_<J grows as much: once more.
+constexpr double kNear = 1e-8, kFar = 0.25;      // |E|_F^2
 #define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_16x16x4f32((a), (b), (c), 0, 0, 0)
-
-// v_mfma_f64_16x16x4: A[m = l % 16][k = l / 16], B[k = l / 16][n = l % 16], register r of the result D[m = 4 r + l / 16][n = l % 16].
-// Register r of a tile that was a result is therefore the operand of the 4 k from 4 r of the same tile, as B and, transposed, as A:
-// C -= P^T Q takes three such tiles as they lie.
 
 // ---- G = A^T A ----------------------------------------------------------------------------------------------------
 // A workgroup forms one 64 x 64 tile of the upper triangle over one chunk of rows, a wavefront a 32 x 32 quarter of it.
@@ -38,15 +39,9 @@ __device__ __forceinline__ void gram_tile(int t, int nt, int& ti, int& tj) {
     tj = ti + t;
 }
 
-__global__ __launch_bounds__(256) void gram64_kernel(const float* __restrict__ A, long lda, int rows, int cols, int nt,
-                                                     int chunk, double* __restrict__ part) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int ti, tj;
-    gram_tile(blockIdx.x, nt, ti, tj);
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    if (ti == tj && wm > wn) return;      // below the diagonal
-    const int r0 = blockIdx.y * chunk, r1 = r0 + chunk < rows ? r0 + chunk : rows;
-    const int c = lane & 15, g = lane >> 4;
+// rows r0 .. r1 of the quarter at (wm, wn) of tile (ti, tj)
+__device__ __forceinline__ void gram_rows(const float* __restrict__ A, long lda, int cols, int ti, int tj, int wm, int wn, int r0,
+                                          int r1, int c, int g, f64x4 (&acc)[2][2]) {
     // columns past the last are read as the last one: nobody uses what they give
     const float* pa[2];
     const float* pb[2];
@@ -56,7 +51,6 @@ __global__ __launch_bounds__(256) void gram64_kernel(const float* __restrict__ A
         pa[i] = A + (long)(r0 + g) * lda + (ca < cols ? ca : cols - 1);
         pb[i] = A + (long)(r0 + g) * lda + (cb < cols ? cb : cols - 1);
     }
-    f64x4 acc[2][2] = {};
     constexpr int STEP = 4;               // groups of four rows in flight
     int r = r0;
     for (; r + 4 * STEP <= r1; r += 4 * STEP) {
@@ -90,6 +84,19 @@ __global__ __launch_bounds__(256) void gram64_kernel(const float* __restrict__ A
 #pragma unroll
             for (int j = 0; j < 2; ++j) acc[i][j] = MFMA64(a[i], b[j], acc[i][j]);
     }
+}
+
+__global__ __launch_bounds__(256) void gram64_kernel(const float* __restrict__ A, long lda, int rows, int cols, int nt,
+                                                     int chunk, double* __restrict__ part) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int ti, tj;
+    gram_tile(blockIdx.x, nt, ti, tj);
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    if (ti == tj && wm > wn) return;      // below the diagonal
+    const int r0 = blockIdx.y * chunk, r1 = r0 + chunk < rows ? r0 + chunk : rows;
+    const int c = lane & 15, g = lane >> 4;
+    f64x4 acc[2][2] = {};
+    gram_rows(A, lda, cols, ti, tj, wm, wn, r0, r1, c, g, acc);
     double* out = part + ((long)blockIdx.y * gridDim.x + blockIdx.x) * 4096;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -102,7 +109,7 @@ __global__ __launch_bounds__(256) void gram64_kernel(const float* __restrict__ A
 // G (GB x GB row-major: the upper triangle and, within the 64 x 64 tiles on the diagonal, its mirror image; past the last column the
 // identity) = sum of the chunks' tiles, in order.  U gets zeros below its diagonal and inv the identity, which chol64_kernel fills in.
 // second.dev (second pass, else null): U and inv as they are where G = I + E is so near to I that U = I + X with X the upper half of E (half
-// of its diagonal), U^-1 = I - X, to |E|^2; dev takes each workgroup's share of |E|_F^2, which decides.  T += T2 where that is asked for.
+// of its diagonal), U^-1 = I - X, to |E|^2; dev takes each workgroup's share of |E|_F^2, which decides.
 __global__ __launch_bounds__(256) void gram64_sum_kernel(const double* __restrict__ part, int chunks, int cols,
                                                          double* __restrict__ G, float* __restrict__ U, long ldu,
                                                          float* __restrict__ inv, SecondPass second) {
@@ -143,11 +150,6 @@ __global__ __launch_bounds__(256) void gram64_sum_kernel(const double* __restric
         if (r < c) o[(c & 63) * 64 + (r & 63)] = 0.f;
     }
     if (!near) return;
-    if (second.trows > 0 && *second.again != 0u) {
-        const int q = threadIdx.x;
-        if (q < cols)
-            for (int i = blockIdx.x; i < second.trows; i += kGramSums) second.T[(long)i * second.ldt + q] += second.T2[(long)i * second.ldt2 + q];
-    }
     const double d = r == c ? s - 1.0 : s;
     double q = r < c ? 2.0 * d * d : (r == c ? d * d : 0.0);
 #pragma unroll
@@ -155,29 +157,6 @@ __global__ __launch_bounds__(256) void gram64_sum_kernel(const double* __restric
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = q;
     __syncthreads();
     if (threadIdx.x == 0) dev[blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
-}
-
-__global__ __launch_bounds__(256) void second_sum_kernel(const float* __restrict__ part, int splits, long stride, long ldp, int rows,
-                                                         int cols, float* __restrict__ S, long lds_, unsigned* again) {
-    const int c = threadIdx.x;
-    unsigned large = 0u;
-    if (c < cols)
-        for (int r = blockIdx.x; r < rows; r += gridDim.x) {
-            const float* p = part + (long)r * ldp + c;
-            float s = 0.f;
-            int z = 0;
-            for (; z + 4 <= splits; z += 4) {
-                float v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = p[(z + u) * stride];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) s += v[u];
-            }
-            for (; z < splits; ++z) s += p[z * stride];
-            S[(long)r * lds_ + c] = s;
-            if (!(fabsf(s) < 0x1p-9f)) large = 1u;
-        }
-    if (large) atomicOr(again, 1u);
 }
 
 // ---- U and the inverses of its 64 x 64 diagonal blocks ------------------------------------------------------------
@@ -194,9 +173,6 @@ constexpr int CHOL_WAVES = 12;
 constexpr int CW = 9;                             // wavefronts that hold tiles
 constexpr int CSLOTS = (GT * (GT + 1) / 2 + CW - 1) / CW;
 constexpr int DEFER = 4;                          // first rows that the lower right quarter takes later
-constexpr int DLD = 18;                           // row stride of the diagonal tile's copy: 16-byte reads of rows without conflicts
-constexpr double kRefine = 1024.0;                // (square of) the cancellation from which A U^-1 gets a step of refinement
-constexpr double kIllcond = 268435456.0;          // ... and from which the block counts as ill-conditioned, 2^14 in length
 
 struct TileMap {
     unsigned char i[CW * CSLOTS + 1], j[CW * CSLOTS + 1];
@@ -209,97 +185,9 @@ struct TileMap {
 };
 __constant__ const TileMap kTiles;
 
-template <int L>
-__device__ __forceinline__ double row_lane(double v) {   // the value of lane L of this lane's row of 16
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + L, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + L, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-// the g-th of four values, without a branch
-__device__ __forceinline__ unsigned pick(unsigned mask, unsigned a, unsigned b) { return (mask & a) | (~mask & b); }
-__device__ __forceinline__ double pick4(int g, double a, double b, double c, double d) {
-    const unsigned m0 = 0u - (unsigned)(g & 1), m1 = 0u - (unsigned)(g >> 1);
-    auto two = [&](int v0, int v1, int v2, int v3) {
-        return (int)pick(m1, pick(m0, (unsigned)v3, (unsigned)v2), pick(m0, (unsigned)v1, (unsigned)v0));
-    };
-    return __hiloint2double(two(__double2hiint(a), __double2hiint(b), __double2hiint(c), __double2hiint(d)),
-                            two(__double2loint(a), __double2loint(b), __double2loint(c), __double2loint(d)));
-}
-
-// acc - (lane I's value of u in this lane's row of 16) v, the broadcast in the instruction; nu = -u.  (s_nop: two wait states between
-// a write of nu and a read of it from another lane)
-template <int I>
-__device__ __forceinline__ void take_off(double& acc, double nu, double v) {
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(nu), "v"(v), "i"(I));
-}
-template <int P, int I>
-__device__ __forceinline__ void take_off_rows(double (&d)[16], double (&x)[16], double nu, double u, double w) {
-    if constexpr (I < 16) {
-        take_off<I>(d[I], nu, u);
-        take_off<I>(x[I], nu, w);
-        take_off_rows<P, I + 1>(d, x, nu, u, w);
-    }
-}
-
-// d[i], x[i]: rows of this lane's column of the symmetric tile and of the identity.  Afterwards d[p] = U[p][lane] for p <= lane, x[p] =
-// W[p][lane] with W = U^-T.  piv: the pivot; least: what this lane's pivot is kept above; mine: 1 / U[lane][lane].
-// The chain: pivot, reciprocal root (2^-24, and one step: 1e-15), the pivot's row, the next pivot; the rest of the row goes off the
-// rows below in its shadow.
-template <int P>
-__device__ __forceinline__ void factor_pivots(double (&d)[16], double (&x)[16], int col, double least, double piv, double& mine) {
-    asm("v_max_f64 %0, %1, %2" : "=v"(piv) : "v"(piv), "v"(row_lane<P>(least)));   // (fmax quiets both operands first)
-    const double r0 = __builtin_amdgcn_rsq(piv);
-    const double e = __builtin_fma(-(piv * r0), r0, 1.0), r = r0 * __builtin_fma(e, 0.5, 1.0);
-    const double u = (col == P ? piv : d[P]) * r, w = x[P] * r;
-    mine = col == P ? r : mine;
-    d[P] = u;
-    x[P] = w;
-    if constexpr (P < 15) {
-        const double next = row_lane<P + 1>(__builtin_fma(-u, u, d[P + 1]));   // lane P + 1's own
-        double nu = -u;
-        asm volatile("s_nop 1" : "+v"(nu));
-        take_off_rows<P, P + 1>(d, x, nu, u, w);
-        factor_pivots<P + 1>(d, x, col, least, next, mine);
-    }
-}
-
-// keeps what is derived from a loop-invariant value inside the loop: twenty slots' addresses do not fit the registers
-__device__ __forceinline__ int opaque(int v) {
-    asm volatile("" : "+s"(v));
-    return v;
-}
-
-__device__ __forceinline__ f64x4 tile_read(const double* t, int lane) {
-    f64x4 v;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = t[64 * r + lane];
-    return v;
-}
-__device__ __forceinline__ f64x4 inverse_read(const double* w, int c, int g) {   // the tile W^T
-    f64x4 v;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = w[c * DLD + 4 * r + g];
-    return v;
-}
-__device__ __forceinline__ void tile_write(double* t, int lane, f64x4 v) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) t[64 * r + lane] = v[r];
-}
-// p^T q in two sums: a product waits 105 cycles for the one before it in the same sum, 64 for one in another
-__device__ __forceinline__ f64x4 tile_mul2(f64x4 p, f64x4 q) {
-    f64x4 a = MFMA64(p[0], q[0], f64x4{}), b = MFMA64(p[1], q[1], f64x4{});
-    a = MFMA64(p[2], q[2], a);
-    b = MFMA64(p[3], q[3], b);
-    return a + b;
-}
-__device__ __forceinline__ f64x4 tile_sub(f64x4 p, f64x4 q, f64x4 c) {   // c - p^T q (blgp negates the first operand of an fp64 product)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f64_16x16x4f64(p[r], q[r], c, 0, 0, 1);
-    return c;
-}
-
 // U: the block's place in the triangular factor (cols x cols, zeros below the diagonal).  inv: GB / 64 row-major 64 x 64 inverses.
-// refine: set to 1 where A U^-1 needs the step of refinement, else 0.  second.dev: the sums of gram64_sum_kernel (second pass) or null;
+// refine: 1 where A U^-1 needs the step of refinement, kDone where A is Q already (a block that the Gram matrix does not hold), else 0.
+// second.dev: the sums of gram64_sum_kernel (second pass) or null;
 // where they say that G is I to |E|_F < 1e-4, U and inv are there already.  started (optional) takes `value` when the kernel runs.
 // The slots from `first` on, in order: a jump into code that names each slot's registers.
 #define DQ_SLOT(s, BODY) case s: if constexpr (s < CSLOTS) { BODY(s) } [[fallthrough]];
@@ -340,32 +228,37 @@ __device__ __forceinline__ f64x4 tile_sub(f64x4 p, f64x4 q, f64x4 c) {   // c - 
 static_assert(CSLOTS <= 20 && 2 * DEFER == GT / 2, "cases of DQ_SLOTS; the quarter is up to date when its first row is due");
 
 __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* __restrict__ G, int cols, float* __restrict__ U, long ldu,
-                                                     float* __restrict__ inv, unsigned* refine, unsigned* flags,
-                                                     SecondPass second, unsigned long long* started, unsigned long long value) {
+                                                     float* __restrict__ inv, float* A, long lda, int rows, unsigned* refine,
+                                                     unsigned* flags, SecondPass second, unsigned long long* started, unsigned long long value) {
     __shared__ __attribute__((aligned(16))) double rowbuf[GT * 256];   // the step's row of U, tile by tile
-    __shared__ __attribute__((aligned(16))) double winv[2][16 * DLD];  // W = U^-T of the step's diagonal tile; of this and the last step
+    __shared__ __attribute__((aligned(16))) double winv[2][16 * CLD];  // W = U^-T of the step's diagonal tile; of this and the last step
     __shared__ __attribute__((aligned(16))) double udiag[GT][256];     // U's diagonal tiles
     __shared__ __attribute__((aligned(16))) double keep[DEFER][GT / 2 * 256];   // right halves of U's first rows
     __shared__ __attribute__((aligned(16))) double nextbuf[2][256];    // tiles (k, k + 1) and (k + 1, k + 1) as step k finds them
     __shared__ __attribute__((aligned(16))) double diagbuf[2][256];
-    __shared__ __attribute__((aligned(16))) double dcopy[16 * DLD];    // wavefront 0's
+    __shared__ __attribute__((aligned(16))) double dcopy[16 * CLD];    // wavefront 0's
+    __shared__ double cancels[2];                                      // of the columns of W that wavefronts 4 and 8 carry
     __shared__ int rows_done;                                          // counts them at the end of each step's row
     __shared__ double norm2[GB];                                       // squared column lengths
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int nt = (cols + 15) / 16;
     const double* const dev = second.dev;
-    if (dev != nullptr && tid == 0) *second.again = 0u;
+    if (dev != nullptr && tid == 0) {
+        if (second.block == 0) second.again[0] = 0u;
+        second.again[second.block + 1] = 0u;
+    }
     if (started != nullptr && tid == 0) __hip_atomic_store(started, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (dev != nullptr) {
         double s = 0.0;
         for (int i = lane; i < kGramSums; i += 64) s += dev[i];
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-        if (__builtin_amdgcn_readfirstlane((int)(s < 1e-8))) {
+        if (__builtin_amdgcn_readfirstlane((int)(s < kNear))) {
             if (tid == 0) *refine = 0u;
             return;
         }
+        if (!(s < kFar) && second.block > 0 && tid == 0) second.again[0] = second.again[second.block] = 1u;
     }
     if (tid == 0) rows_done = 0;
     if (tid < GB) {
@@ -377,7 +270,6 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
     __syncthreads();
     // Three loops with the same barriers, so that none's registers are live in another.
     if (wave == 0) {
-        double worst = 0.0;              // largest (length / what is left of it)^2 of this lane's columns
         f64x4 dk;                        // the diagonal tile of the step
 #pragma unroll
         for (int r = 0; r < 4; ++r) dk[r] = G[(4 * r + g) * GB + c];
@@ -391,14 +283,14 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
         }
         for (int k = 0; k < nt; ++k) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dcopy[(4 * r + g) * DLD + c] = dk[r];
+            for (int r = 0; r < 4; ++r) dcopy[(4 * r + g) * CLD + c] = dk[r];
             __builtin_amdgcn_wave_barrier();       // one wavefront's LDS accesses are in order
             double d[16], x[16];
             int cc = c;
             asm volatile("" : "+v"(cc));           // sixteen comparisons and ones of the identity do not fit the registers across steps
 #pragma unroll
             for (int i = 0; i < 16; i += 2) {      // a row of the symmetric tile is its column
-                const double2 v = *reinterpret_cast<const double2*>(&dcopy[c * DLD + i]);
+                const double2 v = *reinterpret_cast<const double2*>(&dcopy[c * CLD + i]);
                 d[i] = v.x; d[i + 1] = v.y;
             }
             const double len2 = norm2[16 * k + c];
@@ -409,11 +301,10 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
 #pragma unroll
             for (int i = 0; i < 16; ++i) x[i] = i == cc ? one : 0.0;
             factor_pivots<0>(d, x, cc, least, row_lane<0>(d[0]), mine);
-            worst = __builtin_fmax(worst, len2 * mine * mine);
             // each row of 16 lanes writes four rows of W and of U's tile
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                winv[k & 1][(4 * g + q) * DLD + c] = pick4(g, x[q], x[4 + q], x[8 + q], x[12 + q]);
+                winv[k & 1][(4 * g + q) * CLD + c] = pick4(g, x[q], x[4 + q], x[8 + q], x[12 + q]);
                 udiag[k][(4 * g + q) * 16 + c] = pick4(g, d[q], d[4 + q], d[8 + q], d[12 + q]);
             }
             lds_barrier();                         // step k's inverse and the tiles of step k are there
@@ -430,17 +321,12 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
                 dk = tile_sub(u, u, diag);
             }
         }
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) worst = __builtin_fmax(worst, __shfl_xor(worst, o));
-        if (lane == 0) {
-            if (dev == nullptr && worst > kIllcond) atomicOr(flags, DQ_FLAG_ILLCOND_PANEL);
-            *refine = worst > kRefine ? 1u : 0u;
-        }
     } else if ((wave & 3) == 0) {
         // Columns of W within the 64 x 64 block: 0 and 3 (wavefront 4), 1 and 2 (wavefront 8); slots 0 .. split - 1 are the first's rows
         // from the diagonal down, the others the second's.
         const int ja = wave == 4 ? 0 : 1, jb = wave == 4 ? 3 : 2, split = 4 - ja;
         f64x4 wacc[5] = {};
+        double cancel = 0.0;
         for (int k = 0; k < nt; ++k) {
             const int kk = k & 3;
             if (kk == 0) {
@@ -456,7 +342,7 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
                 if (i == kk) {
                     if (j == kk) {                 // the diagonal tile: the transposed inverse itself
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) wacc[s][r] = winv[k & 1][(4 * r + g) * DLD + c];
+                        for (int r = 0; r < 4; ++r) wacc[s][r] = winv[k & 1][(4 * r + g) * CLD + c];
                     } else {
                         wacc[s] = tile_mul2(ik, wacc[s]);
                     }
@@ -478,12 +364,19 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
                 for (int s = 0; s < 5; ++s) {
                     const int j = s < split ? ja : jb, i = s < split ? ja + s : jb + s - split;
                     if (i <= kk) {
+                        const double len2 = norm2[16 * (k - kk + j) + c];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) o[(16 * j + c) * 64 + 16 * i + 4 * r + g] = (float)wacc[s][r];
+                        for (int r = 0; r < 4; ++r) {
+                            o[(16 * j + c) * 64 + 16 * i + 4 * r + g] = (float)wacc[s][r];
+                            cancel = __builtin_fmax(cancel, len2 * wacc[s][r] * wacc[s][r]);
+                        }
                     }
                 }
             }
         }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) cancel = __builtin_fmax(cancel, __shfl_xor(cancel, o));
+        if (lane == 0) cancels[wave >> 3] = cancel;
     } else {
         // the tiles: slot s of the w-th of these wavefronts holds tile CW s + w of the upper triangle, so that what is left is always
         // dealt evenly
@@ -527,6 +420,15 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
             }
         }
     }
+    __syncthreads();
+    const double cancel = __builtin_fmax(cancels[0], cancels[1]);
+    const bool slow = !(cancel < kSlow);
+    if (tid == 0) {
+        if (!(cancel < kIllcond)) atomicOr(flags, DQ_FLAG_ILLCOND_PANEL);
+        *refine = slow ? kDone : (cancel > kRefine ? 1u : 0u);
+    }
+    static_assert(sizeof(keep) >= orthogonalise_lds(CHOL_WAVES, GB) * sizeof(double), "scratch of the slow way");
+    if (slow) orthogonalise_slowly<CHOL_WAVES>(A, lda, rows, cols, U, ldu, &keep[0][0], flags);
 }
 
 // ---- Q = A U^-1 ---------------------------------------------------------------------------------------------------
@@ -608,7 +510,8 @@ __global__ __launch_bounds__(256) void block_solve_kernel(float* A, long lda, in
     __shared__ __attribute__((aligned(16))) float q[SR][SLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r0 = blockIdx.x * SR;
-    const bool again = *refine != 0u;
+    const unsigned mode = *refine;
+    const bool again = mode == 1u;
     const int c4 = 4 * (tid & 63);
 #pragma unroll
     for (int i = 0; i < SR / 4; ++i) {
@@ -619,7 +522,7 @@ __global__ __launch_bounds__(256) void block_solve_kernel(float* A, long lda, in
         if (again) *reinterpret_cast<float4*>(&a[r][c4]) = v;
     }
     __syncthreads();
-    solve_rows<RT>(q, U, ldu, inv, cols, lane, wave);
+    if (mode != kDone) solve_rows<RT>(q, U, ldu, inv, cols, lane, wave);
     if (again) {
         const int c = lane & 15, g = lane >> 4;
         for (int s = 0; s < (cols + 63) / 64; ++s) {          // A - Q U
@@ -661,7 +564,101 @@ __global__ __launch_bounds__(256) void block_solve_kernel(float* A, long lda, in
     }
 }
 
+// ---- after a third projection ---------------------------------------------------------------------------------------
+// 16 columns of U from s0 on <- (I + X) U in place, X (upper triangular) by its entries: from the first 64 rows on, so that nothing is
+// read that is new.
+template <class X>
+__device__ __forceinline__ void upper_times_columns(const X& x, int n, float* U, long ldu, int s0) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4, last = s0 + 16 < n ? s0 + 16 : n, col = s0 + c < n ? s0 + c : n - 1;
+    for (int b = 0; 64 * b < last; ++b) {
+        const int i0 = 64 * b + 16 * wave;
+        f32x4 acc = {};
+#pragma unroll 8
+        for (int k = i0; k < last; k += 4) acc = MFMA32(x(i0 + c, k + g), k + g < n ? U[(long)(k + g) * ldu + col] : 0.f, acc);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (i0 + 4 * g + r <= s0 + c && s0 + c < n) U[(long)(i0 + 4 * g + r) * ldu + s0 + c] += acc[r];
+    }
+}
+
+// The workgroups from `tiles` on: U <- (I + S) U, S from the blocks' third projections.  Those before: E = R^T R - I in fp64, one 64 x 64
+// tile of the upper triangle each.
+__global__ __launch_bounds__(256) void third_pass_kernel(const float* __restrict__ R, long ldr, int n, int tiles, float* __restrict__ E,
+                                                         long lde, const float* __restrict__ S, long lds_, float* U, long ldu,
+                                                         const unsigned* __restrict__ again, unsigned* flags) {
+    if (again[0] == 0u) return;
+    if ((int)blockIdx.x >= tiles) {
+        auto x = [&](int i, int j) -> float {
+            return j < n && i < j / GB * GB && again[j / GB] != 0u ? S[(long)i * lds_ + j] : 0.f;
+        };
+        upper_times_columns(x, n, U, ldu, 16 * ((int)blockIdx.x - tiles));
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int ti, tj;
+    gram_tile(blockIdx.x, (n + 63) / 64, ti, tj);
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32, c = lane & 15, g = lane >> 4;
+    if (ti == tj && wm > wn) return;
+    f64x4 acc[2][2] = {};
+    gram_rows(R, ldr, n, ti, tj, wm, wn, 0, n, c, g, acc);
+    bool large = false;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 64 * ti + wm + 16 * i + 4 * v + g, k = 64 * tj + wn + 16 * j + c;
+                if (r > k || k >= n) continue;
+                const double e = acc[i][j][v] - (r == k ? 1.0 : 0.0);
+                E[(long)r * lde + k] = (float)e;
+                large |= !(__builtin_fabs(e) < 0x1p-10);
+            }
+    if (large) atomicOr(flags, DQ_FLAG_ILLCOND_PANEL);      // R stays off by the square of it
+}
+
+// R <- R (I - X), U <- (I + X) U in place, X the upper triangle of E, half of its diagonal: R^T R = I to |E|^2.  The first workgroups
+// have 16 rows of R each and go through its columns from the last 64 back.
+__global__ __launch_bounds__(256) void correct_kernel(const float* __restrict__ E, long lde, int n, float* R, long ldr, float* U,
+                                                      long ldu, const unsigned* __restrict__ again) {
+    if (again[0] == 0u) return;
+    const int strips = (n + 15) / 16;
+    auto x = [&](int i, int j) -> float {
+        if (i > j || j >= n) return 0.f;
+        const float v = E[(long)i * lde + j];
+        return i < j ? v : 0.5f * v;
+    };
+    if ((int)blockIdx.x >= strips) {
+        upper_times_columns(x, n, U, ldu, 16 * ((int)blockIdx.x - strips));
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4, s0 = 16 * blockIdx.x;
+    const float* row = R + (long)(s0 + c < n ? s0 + c : n - 1) * ldr;
+    for (int b = (n - 1) / 64; b >= 0; --b) {
+        const int j0 = 64 * b + 16 * wave;
+        f32x4 acc = {};
+#pragma unroll 8
+        for (int k = 0; k < j0 + 16; k += 4) acc = MFMA32(k + g < n ? row[k + g] : 0.f, x(k + g, j0 + c), acc);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (s0 + 4 * g + r < n && j0 + c < n) R[(long)(s0 + 4 * g + r) * ldr + j0 + c] -= acc[r];
+    }
+}
+
 }  // namespace
+
+hipError_t launch_third_pass(float* R, long ldr, int n, const float* S, long lds_, float* E, long lde, float* U, long ldu,
+                             const unsigned* again, unsigned* flags, hipStream_t s) {
+    if (n < 1) return hipErrorInvalidValue;
+    const int strips = (n + 15) / 16, nt = (n + 63) / 64, tiles = nt * (nt + 1) / 2, more = U != nullptr ? strips : 0;
+    hipLaunchKernelGGL(third_pass_kernel, dim3(tiles + more), dim3(256), 0, s, R, ldr, n, tiles, E, lde, S, lds_, U, ldu, again, flags);
+    hipLaunchKernelGGL(correct_kernel, dim3(strips + more), dim3(256), 0, s, E, lde, n, R, ldr, U, ldu, again);
+    return hipGetLastError();
+}
 
 // chunks of rows of a Gram product: 64 rows at least, 32 chunks at most
 static int gram64_chunk(int rows) {
@@ -684,18 +681,10 @@ hipError_t launch_gram64(const float* A, long lda, int rows, int cols, double* p
     return hipGetLastError();
 }
 
-hipError_t launch_second_sum(const float* part, int splits, long stride, long ldp, int rows, int cols, float* S, long lds_,
-                             unsigned* again, hipStream_t s) {
-    if (rows < 1 || cols < 1 || cols > GB) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(second_sum_kernel, dim3(rows < 2048 ? rows : 2048), dim3(GB), 0, s, part, splits, stride, ldp, rows, cols, S,
-                       lds_, again);
-    return hipGetLastError();
-}
-
-hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, unsigned* refine, unsigned* flags,
-                         const SecondPass& second, unsigned long long* started, unsigned long long value, hipStream_t s) {
+hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, float* A, long lda, int rows, unsigned* refine,
+                         unsigned* flags, const SecondPass& second, unsigned long long* started, unsigned long long value, hipStream_t s) {
     if (cols < 1 || cols > GB) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(chol64_kernel, dim3(1), dim3(64 * CHOL_WAVES), 0, s, G, cols, U, ldu, inv, refine, flags, second, started,
+    hipLaunchKernelGGL(chol64_kernel, dim3(1), dim3(64 * CHOL_WAVES), 0, s, G, cols, U, ldu, inv, A, lda, rows, refine, flags, second, started,
                        value);
     return hipGetLastError();
 }
