@@ -163,8 +163,8 @@ dq_status dq_device_flags(dq_ctx* ctx, unsigned* host_out);
 /* ---- the hot path ------------------------------------------------------------------- */
 
 /* Sec. 4.3 / the QR step of Alg. 1:  Z (n x n) -> orthogonal R and, optionally, upper-triangular U with
- * Z = R U and diag(U) >= 0, which makes R unique for nonsingular Z.  n <= 128: Alg. 2 as printed, one workgroup a problem.
- * Above: by blocks of 256 columns, Cholesky of their Gram matrices in fp64, twice; blocked Householder QR (Alg. 2 in
+ * Z = R U and diag(U) >= 0, which makes R unique for nonsingular Z.  n <= 128: one workgroup a problem, Cholesky
+ * of the Gram matrix in fp64.  Above: by blocks of 256 columns, Cholesky of their Gram matrices in fp64, twice; blocked Householder QR (Alg. 2 in
  * blocked compact-WY form) followed by sign normalisation where one of its options below is set.
  * Z: in, b x (n x n) fp32.  R: out, fp32.  U_or_null: out, fp32, strictly-lower part written as 0. */
 dq_status dq_qr_orth(dq_ctx* ctx, int b, int n,

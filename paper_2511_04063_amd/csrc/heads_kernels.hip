@@ -1,15 +1,12 @@
 // Batched path for small rotations, n <= 128 (per-head rotations; the "heads" workload has 64 of size 128): every problem
 // of a batch runs in the same launch.
-//   * heads_qr_kernel: R, U = qr(Z) for one latent per workgroup, entirely on chip.  Alg. 2 as printed:
-//     column by column, the reflector is applied to the trailing columns of the matrix and accumulated into the
-//     orthogonal factor in the same step (A <- H A, Q <- Q H); the signs are then fixed so that diag(U) >= 0.
+//   * heads_qr_kernel: R, U = qr(Z) for one latent per workgroup, entirely on chip: Cholesky of the Gram matrix in fp64, twice.
 //   * heads_rlg_kernel: Alg. 1, rotation and loss steps, fused for bf16 activations.  A workgroup streams 64-token tiles of X once;
 //     Y = X R (R as two bf16 planes held in registers), the Whip loss and its gradient (Eq. 4) and the tile's
 //     contribution to G = X^T dY are formed on chip: Y and dY never reach HBM.
 //   * heads_reduce_kernel: sums the per-workgroup partial G and loss.
 //   * heads_backward_kernel: the derivative through the QR and the update, one problem per workgroup, out of LDS.
-#include <type_traits>
-
+#include "dq_chol16.h"
 #include "dq_internal.h"
 #include "dq_wave.h"
 
@@ -20,19 +17,17 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int HN = kHeadDim;     // largest matrix size of this path
+#define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x4f32((a), (b), (c), 0, 0, 0)
 
 __device__ __forceinline__ double wave_total(double v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
     return v;
-}
-
-__device__ __forceinline__ float lane_value(float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
 __device__ __forceinline__ uint32_t to_bf16_rne(float f) {
@@ -43,196 +38,408 @@ __device__ __forceinline__ uint32_t to_bf16_rne(float f) {
 }
 
 // ------------------------------------------------------------------------------------------------ S1 + S2
-// Alg. 2 with the unnormalised reflector vector: for column j, x = A[j:, j], beta = -sign(x_0) ||x||,
-// u = x - beta e_0, H = I - gamma u u^T with gamma = 2 / u^T u  (the same reflection as the paper's normalised v);
-// a column that is already zero below the diagonal gets H = I.
-// 512 threads: four adjacent lanes ("item" i = tid / 4, part h = tid % 4) hold one column of A AND one row of Q in
-// registers, lane part h owning the 4-row groups g with g % 4 == h of both.  Both get x <- x - gamma (u . x) u (the
-// column only if it lies right of j), with ONE read of u from LDS for the two, the partial dot products of the four
-// lanes meeting through DPP.  Columns are dealt to the items round-robin over the wavefronts (item i holds column
-// 8 (i % 16) + i / 16), so that every wavefront keeps live columns to the end.  The owners of column j + 1 publish it in
-// LDS at the end of step j, so a step needs one barrier; every wavefront forms the column norm itself.  Rows are handled
-// in blocks of 16: blocks above the diagonal block are skipped (the block index is a template parameter, so register
-// indices are static and a step runs straight-line code), the diagonal block substitutes u_0 for the raw pivot and
-// zero above it.
-constexpr int QS = 4;                   // lanes per column / row
-constexpr int QB = 16;                  // rows per block = 4 groups, one per lane part
-// NG: 4-row groups held by a thread (of its column and of its row) = blocks of 16 rows carried, 4, 6 or 8: the rest of a
-// smaller matrix is zero (32 problems of order 80: 91 us with all 8 carried, 74 with 6).  Bound: the vector ALU and the
-// chain of dependent operations of a step, half and half; four workgroups per problem, each with all of A and a quarter
-// of Q's rows, took as long as one.
+// R, U of one latent per workgroup, in LDS and registers: G = A^T A, G = U^T U and Q^T = U^-T A^T in fp64 on the matrix cores, which
+// leaves Q^T Q = I + E at 1e-16 times the square of the condition number.  Q once more where that is not yet the identity: the factor I + X
+// with X the upper half of E leaves |E|^2, again where that is no rounding; another factorisation where E is no small number; and
+// column by column where there is no Gram matrix to speak of (condition numbers from 1e8 on).
+// Wavefront 0 factors the 16 x 16 diagonal tiles, the other seven hold the tiles of G's upper triangle (see chol64_kernel, which has
+// more of them).  Q's rows are independent of each other, 16 to a wavefront: their transposes take the factorisation's steps as more columns
+// of G would.  (In fp32 Q cost 6 us, and E, from condition numbers of 100 on, a correction and one more look, 10 to 45 us.)
+// Us: U above the diagonal, below it X^T, its diagonal in dinv.
+// Bound: one compute unit's fp64 matrix cores and the chain of its diagonal tiles.  Column by column before (1 us a column: a chain of
+// barrier, norm, dot product and update) and now: 64 latents of order 128 127 / 69 us, 512 of them 277 / 152, 64 of 112 117 / 52, 64 of 96
+// 89 / 41, 32 of 80 77 / 33, 64 of 64 51 / 22.  Of the 69 us: G 19, the factor 23 (eight diagonal tiles), Q about 10, E 11.
+constexpr int HW = 7;            // wavefronts that hold tiles
+constexpr double kHeadsDone = 4e-14;      // |R^T R - I|_F^2 / n with which R is finished: 2e-7 (column by column it was 3.3 to 4.1e-7)
 
-__device__ __forceinline__ int item_column(int item) { return 8 * (item & 15) + (item >> 4); }
-__device__ __forceinline__ int column_item(int c) { return 16 * (c & 7) + (c >> 3); }
+template <int NT>
+struct HeadsQr {
+    static constexpr int N = 16 * NT, LD = N + 4, TILES = NT * (NT + 1) / 2, SLOTS = (TILES + HW - 1) / HW, NB = (NT + 3) / 4;
+    // U's tiles above the diagonal, the diagonal ones' inverses and the exchange buffers lie where Q is before and after
+    static constexpr int ROW = 0, WINV = ROW + NT * (NT - 1) / 2 * 256, NEXT = WINV + NT * 16 * CLD, DIAG = NEXT + 512,
+                         COPY = DIAG + 512, USED = COPY + 16 * CLD > N * LD / 2 ? COPY + 16 * CLD : N * LD / 2,
+                         SLOW = orthogonalise_lds(HW + 1, N),
+                         POOL = USED > SLOW ? USED : SLOW;
+};
 
-// rows of this thread's k-th group: 4 * (k * QS + h) .. + 3
-template <int JB, int NG>
-__device__ __forceinline__ void publish_from(float* cb, const float (&x)[4 * NG], int h, int j) {
+// acc[t] (16 rows, columns 64 s + 16 t ..) += row[k] M[k][.] over k >= 64 first, M upper triangular with its transpose below Us's diagonal and
+// its diagonal in dinv
+template <int NT>
+__device__ __forceinline__ void heads_times_upper(const float* row, const float* Us, const float* dinv, int first, int s, int c, int g,
+                                                  f32x4 (&acc)[4]) {
+    constexpr int LD = HeadsQr<NT>::LD;
+#pragma unroll 1
+    for (int kb = first; kb < s; ++kb)
+#pragma unroll 4
+        for (int q = 0; q < 16; ++q) {
+            const int k = 64 * kb + 4 * q + g;
+            const float a = row[k];
 #pragma unroll
-    for (int k = JB; k < NG; ++k) {
-        const int i = 4 * (k * QS + h);
-        float4 v = make_float4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
-        if (k == JB) {   // diagonal block: entries above the diagonal are published as zero
-            v.x = i >= j ? v.x : 0.f; v.y = i + 1 >= j ? v.y : 0.f; v.z = i + 2 >= j ? v.z : 0.f; v.w = i + 3 >= j ? v.w : 0.f;
+            for (int t = 0; t < 4; ++t)
+                if (4 * s + t < NT) acc[t] = MFMA16(a, Us[(64 * s + 16 * t + c) * LD + k], acc[t]);
         }
-        *reinterpret_cast<float4*>(cb + i) = v;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int k = 64 * s + 4 * q + g;
+        if (4 * s + q / 4 >= NT) continue;
+        const float a = row[k];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (t >= q / 4 && 4 * s + t < NT) {
+                float m = Us[(64 * s + 16 * t + c) * LD + k];
+                if (t == q / 4) m = 4 * (q & 3) + g < c ? m : (4 * (q & 3) + g == c ? dinv[64 * s + 16 * t + c] : 0.f);
+                acc[t] = MFMA16(a, m, acc[t]);
+            }
     }
 }
 
-// x <- x - gamma (u . x) u for this thread's part of its column (if live) and of its row of Q, for block row JB = j / 16
-// of the pivot; u is the published column with u_0 = uj in place of the raw pivot.  LARGE: gamma times g2 in place of gamma
-template <int JB, int NG, bool LARGE>
-__device__ __forceinline__ void reflect_from(const float* cb, float (&xc)[4 * NG], float (&xq)[4 * NG], bool col_live,
-                                             int h, int j, float uj, float gamma, float g2) {
-    float4 u[NG - JB];
-#pragma unroll
-    for (int k = JB; k < NG; ++k) u[k - JB] = *reinterpret_cast<const float4*>(cb + 4 * (k * QS + h));
-    {   // diagonal block: the pivot entry becomes u_0 (the entries above it were published as zero)
-        const int i = 4 * (JB * QS + h);
-        float4& v = u[0];
-        v.x = i == j ? uj : v.x; v.y = i + 1 == j ? uj : v.y; v.z = i + 2 == j ? uj : v.z; v.w = i + 3 == j ? uj : v.w;
-    }
-    // four independent partial sums per dot product: a lone dependent chain of 32 FMAs would set the pace of the step
-    float c0 = 0.f, c1 = 0.f, c2 = 0.f, c3 = 0.f, q0 = 0.f, q1 = 0.f, q2 = 0.f, q3 = 0.f;
-#pragma unroll
-    for (int k = JB; k < NG; ++k) {
-        const float4 v = u[k - JB];
-        c0 += v.x * xc[4 * k]; c1 += v.y * xc[4 * k + 1]; c2 += v.z * xc[4 * k + 2]; c3 += v.w * xc[4 * k + 3];
-        q0 += v.x * xq[4 * k]; q1 += v.y * xq[4 * k + 1]; q2 += v.z * xq[4 * k + 2]; q3 += v.w * xq[4 * k + 3];
-    }
-    float dc = (c0 + c1) + (c2 + c3), dq = (q0 + q1) + (q2 + q3);
-    dc += lane_xor<1>(dc); dq += lane_xor<1>(dq);
-    dc += lane_xor<2>(dc); dq += lane_xor<2>(dq);
-    const float fc = col_live ? gamma * (LARGE ? g2 * dc : dc) : 0.f;
-    const float fq = gamma * (LARGE ? g2 * dq : dq);
-#pragma unroll
-    for (int k = JB; k < NG; ++k) {
-        const float4 v = u[k - JB];
-        xc[4 * k] -= fc * v.x; xc[4 * k + 1] -= fc * v.y; xc[4 * k + 2] -= fc * v.z; xc[4 * k + 3] -= fc * v.w;
-        xq[4 * k] -= fq * v.x; xq[4 * k + 1] -= fq * v.y; xq[4 * k + 2] -= fq * v.z; xq[4 * k + 3] -= fq * v.w;
-    }
-}
-
-#define DQ_BLOCK_SWITCH(jb, CALL)                                                                  \
-    switch (jb) {                                                                                  \
-        case 0: if constexpr (NG > 0) { CALL(0); } break;                                          \
-        case 1: if constexpr (NG > 1) { CALL(1); } break;                                          \
-        case 2: if constexpr (NG > 2) { CALL(2); } break;                                          \
-        case 3: if constexpr (NG > 3) { CALL(3); } break;                                          \
-        case 4: if constexpr (NG > 4) { CALL(4); } break;                                          \
-        case 5: if constexpr (NG > 5) { CALL(5); } break;                                          \
-        case 6: if constexpr (NG > 6) { CALL(6); } break;                                          \
-        case 7: if constexpr (NG > 7) { CALL(7); } break;                                          \
-        default: break;                                                                            \
-    }
-
-// FULL: n == 128, nothing to guard.
-template <bool FULL, int NG>
-__global__ __launch_bounds__(HN * QS) void heads_qr_kernel(const float* __restrict__ Z, long ldz, long sz,
-                                                           float* __restrict__ R, long ldr, long sr,
-                                                           float* __restrict__ U, long ldu, long su, int n_,
-                                                           unsigned* flags) {
-    const int n = FULL ? HN : n_;
-    __shared__ __attribute__((aligned(16))) float cbuf[2][HN];
-    __shared__ __attribute__((aligned(16))) float sgn[HN];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int item = tid / QS, h = tid % QS;
-    const int col = item_column(item);   // this thread's column of A; its row of Q is `item`
+template <int NT>
+__global__ __launch_bounds__(64 * (HW + 1)) void heads_qr_kernel(const float* __restrict__ Z, long ldz, long sz, float* R, long ldr,
+                                                                 long sr, float* U, long ldu, long su, int n, unsigned* flags) {
+    using H = HeadsQr<NT>;
+    constexpr int N = H::N, LD = H::LD, SLOTS = H::SLOTS;
+    __shared__ __attribute__((aligned(16))) double pool[H::POOL];
+    __shared__ __attribute__((aligned(16))) float Us[N * LD];
+    __shared__ float dinv[N];
+    __shared__ double norm2[N];
+    __shared__ double dev[HW + 1];
+    __shared__ int rows_done;
+    float* const Q = reinterpret_cast<float*>(pool);
+    double *const winv = pool + H::WINV, *const nextbuf = pool + H::NEXT, *const diagbuf = pool + H::DIAG,
+                  *const dcopy = pool + H::COPY;
+    auto tile = [&](int k, int j) { return pool + H::ROW + (k * (2 * NT - k - 1) / 2 + j - k - 1) * 256; };   // (k, j) of U
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c0 = lane & 15, g0 = lane >> 4, w = wave - 1;
+    const int nt = (n + 15) / 16;
     const float* Zp = Z + (long)blockIdx.x * sz;
-    float xc[4 * NG], xq[4 * NG], mydiag = 0.f;
-    // The factorisation.  Columns of norm 2^62 and more: 2 / u . u is no normal fp32 number though the squares are; they are
-    // noticed (returned) and the factorisation is done again with that factor in two, which costs 3 % where it always is.
-    auto factor = [&](auto large) -> bool {
-        constexpr bool LARGE = decltype(large)::value;
-        bool met = false;
-#pragma unroll
-        for (int k = 0; k < NG; ++k)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 4 * (k * QS + h) + e;
-                xc[4 * k + e] = (i < n && col < n) ? Zp[(long)i * ldz + col] : 0.f;
-                xq[4 * k + e] = (i == item) ? 1.f : 0.f;
-            }
-        if (tid < HN) { cbuf[0][tid] = 0.f; cbuf[1][tid] = 0.f; }   // what lies beyond the carried blocks reads as zero
-        __syncthreads();
-        if (col == 0) publish_from<0, NG>(cbuf[0], xc, h, 0);
-        __syncthreads();
-        for (int j = 0; j < n; ++j) {           // (rows and columns from n on are zero and stay zero)
-            const float* cb = cbuf[j & 1];
-            // column norm below the pivot: DPP inside the rows of 16 lanes, then the four row sums through scalar registers
-            const float a0 = cb[lane], a1 = cb[lane + 64];
-            const float alpha = cb[j];
-            float sr_ = (lane > j ? a0 * a0 : 0.f) + (lane + 64 > j ? a1 * a1 : 0.f);
-            sr_ += lane_xor<1>(sr_);
-            sr_ += lane_xor<2>(sr_);
-            sr_ += lane_xor<4>(sr_);
-            sr_ += lane_xor<8>(sr_);
-            const float s = (lane_value(sr_, 0) + lane_value(sr_, 16)) + (lane_value(sr_, 32) + lane_value(sr_, 48));
-            float beta = alpha;   // nothing below the pivot: H = I
-            if (s != 0.f) {
-                // hardware square root (1 ulp): beta only decides how exactly the column is annihilated; 2 / u . u is formed
-                // from the u that is applied, so that H is orthogonal whatever the rounding of beta
-                const float nrm = __builtin_amdgcn_sqrtf(alpha * alpha + s);
-                beta = alpha >= 0.f ? -nrm : nrm;
-                const float uj = alpha - beta;
-                const float uu = fmaf(uj, uj, s);
-                float gamma = 2.f * __builtin_amdgcn_rcpf(uu), g2 = 1.f;
-                if (LARGE) {    // from u at a norm of 1 to 2
-                    const int ex = __builtin_amdgcn_frexp_expf(nrm);
-                    const float us = ldexpf(uj, -ex);
-                    gamma = ldexpf(2.f * __builtin_amdgcn_rcpf(fmaf(us, us, ldexpf(s, -2 * ex))), -ex);
-                    g2 = ldexpf(1.f, -ex);
-                }
-                met = met || !(uu < 0x1p125f);
-#define DQ_CALL(JB) reflect_from<JB, NG, LARGE>(cb, xc, xq, col > j, h, j, uj, gamma, g2)
-                DQ_BLOCK_SWITCH(j / QB, DQ_CALL)
-#undef DQ_CALL
-            }
-            if (col == j) mydiag = beta;
-            if (tid == 0) sgn[j] = beta >= 0.f ? 1.f : -1.f;
-            if (col == j + 1) {
-                float* nb = cbuf[(j + 1) & 1];
-#define DQ_CALL(JB) publish_from<JB, NG>(nb, xc, h, j + 1)
-                DQ_BLOCK_SWITCH((j + 1) / QB, DQ_CALL)
-#undef DQ_CALL
-            }
-            __syncthreads();
+    float* Rp = R + (long)blockIdx.x * sr;
+    float* Up = U != nullptr ? U + (long)blockIdx.x * su : nullptr;
+    auto load = [&](const float* p, long ld) {        // Q <- an n x n matrix, zeros past it
+        for (int e = tid; e < N * N / 4; e += 64 * (HW + 1)) {
+            const int r = e / (N / 4), q = e % (N / 4) * 4;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (r < n && q < n) v = load_quad(p + (long)r * ld + q, n - q);
+            *reinterpret_cast<float4*>(Q + r * LD + q) = v;
         }
-        return met;
     };
-    if (factor(std::false_type{})) factor(std::true_type{});    // (the same for every thread: all see the same columns)
-    if (h == 0 && col < n) {
-        if (!(fabsf(mydiag) <= 3.0e38f)) atomicOr(flags, DQ_FLAG_NONFINITE);
-        else if (mydiag == 0.f) atomicOr(flags, DQ_FLAG_SINGULAR);
+    // tile HW s + w of the upper triangle, row by row, is slot s of the w-th of the seven; 256 i + j
+    int tij[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        int t = HW * s + w, i = 0;
+        while (i < NT && t >= NT - i) { t -= NT - i; ++i; }
+        tij[s] = __builtin_amdgcn_readfirstlane(wave > 0 && i < NT ? 256 * i + i + t : 255);
     }
-    if (U != nullptr) {   // U[i][c] = s_i A[i][c] above the diagonal, |diag| on it
-        float* Up = U + (long)blockIdx.x * su;
+    f64x4 acc[SLOTS];
+    if (tid == 0) rows_done = 0;
+    load(Zp, ldz);
+    bool again = false;
+    for (int step = 0, rows_base = 0; step < 6; ++step) {
+        int c = c0, g = g0;
+        asm volatile("" : "+v"(c), "+v"(g));    // addresses of all phases do not fit the registers across steps
+        __syncthreads();
+        if (step > 0) {
+            // ---- E = Q^T Q - I, in fp32; the tiles dealt as G's
+            f32x4 e[SLOTS];
+            float part = 0.f;
 #pragma unroll
-        for (int k = 0; k < NG; ++k)
+            for (int s = 0; s < SLOTS; ++s) {
+                const int t = opaque(tij[s]), ti = t >> 8, tj = t & 255;
+                e[s] = f32x4{};
+                if (tj < nt) {
+                    const float *pa = Q + g * LD + 16 * ti + c, *pb = Q + g * LD + 16 * tj + c;
+                    f32x4 odd = {};
+#pragma unroll 8
+                    for (int k = 0; k < 4 * nt; k += 2) {
+                        e[s] = MFMA16(pa[4 * k * LD], pb[4 * k * LD], e[s]);
+                        odd = MFMA16(pa[(4 * k + 4) * LD], pb[(4 * k + 4) * LD], odd);
+                    }
+                    e[s] += odd;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 4 * (k * QS + h) + e;
-                if (i < n && col < n) Up[(long)i * ldu + col] = i < col ? sgn[i] * xc[4 * k + e] : (i == col ? fabsf(mydiag) : 0.f);
+                    for (int r = 0; r < 4; ++r) {
+                        if (ti == tj && 4 * g + r == c) e[s][r] = 16 * tj + c < n ? e[s][r] - 1.f : 0.f;
+                        part += (ti == tj ? 1.f : 2.f) * e[s][r] * e[s][r];
+                    }
+                }
             }
+            const double mine = wave_total((double)part);
+            if (lane == 0) dev[wave] = mine;
+            __syncthreads();
+            const double sum = ((dev[0] + dev[1]) + (dev[2] + dev[3])) + ((dev[4] + dev[5]) + (dev[6] + dev[7]));
+            if (sum < kHeadsDone * n) break;
+            if (sum < 1e-3) {
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = opaque(tij[s]), ti = t >> 8, tj = t & 255;
+                    if (tj < nt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int i = 16 * ti + 4 * g + r, j = 16 * tj + c;
+                            if (i < j) Us[j * LD + i] = e[s][r];
+                            if (i == j) dinv[i] = 0.5f * e[s][r];
+                        }
+                }
+                if (tid < N && tid >= 16 * nt) dinv[tid] = 0.f;
+                __syncthreads();
+                if (wave < NT) {                            // Q -= Q X, from the last columns on: what is read is still the old one
+                    float* own = Q + (16 * wave + 4 * g) * LD + c;
+#pragma unroll
+                    for (int b = H::NB - 1; b >= 0; --b) {
+                        f32x4 v[4] = {};
+                        heads_times_upper<NT>(Q + (16 * wave + c) * LD, Us, dinv, 0, b, c, g, v);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if (4 * b + t < NT)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) own[r * LD + 64 * b + 16 * t] -= v[t][r];
+                    }
+                }
+                // U += X U, the tiles of the upper triangle dealt as G's
+                f32x4 xu[SLOTS];
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = opaque(tij[s]), ti = t >> 8, tj = t & 255;
+                    xu[s] = f32x4{};
+                    if (tj < nt) {
+                        const float *px = Us + g * LD + 16 * ti + c, *pu = Us + g * LD + 16 * tj + c;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {       // X's diagonal tile
+                            const int k = 4 * q + g;
+                            const float x = px[(16 * ti + 4 * q) * LD], u = pu[(16 * ti + 4 * q) * LD];
+                            xu[s] = MFMA16(k > c ? x : (k == c ? dinv[16 * ti + c] : 0.f), ti < tj || k <= c ? u : 0.f, xu[s]);
+                        }
+#pragma unroll 1
+                        for (int kk = ti + 1; kk < tj; ++kk)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) xu[s] = MFMA16(px[(16 * kk + 4 * q) * LD], pu[(16 * kk + 4 * q) * LD], xu[s]);
+                        if (ti < tj)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {   // U's
+                                const float u = pu[(16 * tj + 4 * q) * LD];
+                                xu[s] = MFMA16(px[(16 * tj + 4 * q) * LD], 4 * q + g <= c ? u : 0.f, xu[s]);
+                            }
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = opaque(tij[s]), ti = t >> 8, tj = t & 255;
+                    if (tj < nt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int i = 16 * ti + 4 * g + r, j = 16 * tj + c;
+                            if (i <= j) Us[i * LD + j] += xu[s][r];
+                        }
+                }
+                if (sum < 3e-7) break;
+                continue;
+            }
+            if (again) break;
+            again = true;
+            if (!(sum < 1.0)) {            // no factor of that Gram matrix: Z once more, in R's place, the slow way (U in Us)
+                for (int e = tid; e < n * n; e += 64 * (HW + 1)) Rp[(long)(e / n) * ldr + e % n] = Zp[(long)(e / n) * ldz + e % n];
+                if (tid == 0) atomicOr(flags, DQ_FLAG_ILLCOND_PANEL);
+                __syncthreads();
+                orthogonalise_slowly<HW + 1>(Rp, ldr, n, n, Us, LD, pool, flags);
+                load(Rp, ldr);
+                continue;
+            }
+            // Q waits in R, U in U
+            if (wave < NT)
+#pragma unroll 1
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int i = 16 * wave + 4 * g + r, j = 16 * t + c;
+                        if (i < n && j < n) {
+                            Rp[(long)i * ldr + j] = Q[i * LD + j];
+                            if (Up != nullptr && i <= j) Up[(long)i * ldu + j] = Us[i * LD + j];
+                        }
+                    }
+            __threadfence_block();
+        }
+        // ---- G = Q^T Q in fp64, the identity past the last column
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int t = opaque(tij[s]), ti = t >> 8, tj = t & 255;
+            acc[s] = f64x4{};
+            if (tj < nt) {
+                const float *pa = Q + g * LD + 16 * ti + c, *pb = Q + g * LD + 16 * tj + c;
+#pragma unroll 8
+                for (int k = 0; k < 4 * nt; ++k) acc[s] = MFMA64((double)pa[4 * k * LD], (double)pb[4 * k * LD], acc[s]);
+                if (ti == tj)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (4 * r + g == c && 16 * tj + c >= n) acc[s][r] = 1.0;
+            }
+        }
+        // ---- U^T U = G
+        __syncthreads();                       // Q has been read
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int ti = tij[s] >> 8, tj = tij[s] & 255;
+            if (tj >= nt) continue;
+            if (ti == tj)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (4 * r + g == c) norm2[16 * ti + c] = acc[s][r];
+            if (tij[s] == 0) tile_write(dcopy, lane, acc[s]);
+            if (tij[s] == 1) tile_write(nextbuf, lane, acc[s]);
+            if (tij[s] == 257) tile_write(diagbuf, lane, acc[s]);
+        }
+        __syncthreads();
+        if (tid < n) {
+            const double v = norm2[tid];
+            if (!(v < 0x1p1000)) atomicOr(flags, DQ_FLAG_NONFINITE);
+            if (v == 0.0) atomicOr(flags, DQ_FLAG_SINGULAR);
+        }
+        if (wave == 0) {
+            f64x4 dk = tile_read(dcopy, lane);
+            for (int k = 0; k < nt; ++k) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dcopy[(4 * r + g) * CLD + c] = dk[r];
+                __builtin_amdgcn_wave_barrier();
+                double d[16], x[16];
+                int cc = c;
+                asm volatile("" : "+v"(cc));
+#pragma unroll
+                for (int i = 0; i < 16; i += 2) {
+                    const double2 v = *reinterpret_cast<const double2*>(&dcopy[c * CLD + i]);
+                    d[i] = v.x; d[i + 1] = v.y;
+                }
+                const double len2 = norm2[16 * k + c];
+                const double least = __builtin_fmax(len2 * 0x1p-44, 0x1p-600), one = len2 > 0.0 ? 1.0 : 0.0;   // (see chol64_kernel)
+                double mine = 0.0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = i == cc ? one : 0.0;
+                factor_pivots<0>(d, x, cc, least, row_lane<0>(d[0]), mine);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int i = 4 * g + q;
+                    const double xv = pick4(g, x[q], x[4 + q], x[8 + q], x[12 + q]), dv = pick4(g, d[q], d[4 + q], d[8 + q], d[12 + q]);
+                    winv[(k * 16 + i) * CLD + c] = xv;
+                    if (i <= c) Us[(16 * k + i) * LD + 16 * k + c] = (float)dv;
+                }
+                lds_barrier();
+                if (k + 1 < nt) {
+                    const f64x4 next = tile_read(nextbuf + (k & 1) * 256, lane), diag = tile_read(diagbuf + (k & 1) * 256, lane);
+                    const f64x4 u = tile_mul2(inverse_read(winv + k * 16 * CLD, c, g), next);
+                    dk = tile_sub(u, u, diag);
+                }
+            }
+        } else {
+            for (int k = 0; k < nt; ++k) {
+                lds_barrier();
+                const f64x4 ik = inverse_read(winv + k * 16 * CLD, c, g);
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = opaque(tij[s]), tj = t & 255;
+                    if (t >> 8 == k && tj != k && tj < nt) {
+                        acc[s] = tile_mul2(ik, acc[s]);
+                        tile_write(tile(k, tj), lane, acc[s]);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) Us[(16 * k + 4 * r + g) * LD + 16 * tj + c] = (float)acc[s][r];
+                    }
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (lane == 0) __hip_atomic_fetch_add(&rows_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                while (__hip_atomic_load(&rows_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < rows_base + HW * (k + 1)) {}
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int t = opaque(tij[s]), ti = t >> 8, tj = t & 255;
+                    if (ti > k && tj < nt && t != 257 * (k + 1)) {
+                        acc[s] = tile_sub(tile_read(tile(k, ti), lane), tile_read(tile(k, tj), lane), acc[s]);
+                        if (t == 257 * (k + 1) + 1) tile_write(nextbuf + ((k + 1) & 1) * 256, lane, acc[s]);
+                        if (t == 257 * (k + 2)) tile_write(diagbuf + ((k + 1) & 1) * 256, lane, acc[s]);
+                    }
+                }
+            }
+        }
+        rows_base += HW * nt;
+        // ---- Q^T = U^-T A^T in fp64, 16 rows of A a wavefront, as the factorisation forms U's rows
+        f64x4 x[NT];
+        if (wave < nt) {
+            const float* Ap = again ? Rp : Zp;
+            const long lda = again ? ldr : ldz;
+            const int row = 16 * wave + c;
+            const float* pr = Ap + (long)(row < n ? row : 0) * lda;
+            float v[NT][4];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[t][r] = pr[16 * t + 4 * r + g < n ? 16 * t + 4 * r + g : 0];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[t][r] = row < n && 16 * t + 4 * r + g < n ? (double)v[t][r] : 0.0;
+        }
+        __syncthreads();
+        if (wave < nt) {
+#pragma unroll
+            for (int k = 0; k < NT; ++k) {
+                if (NT == 4 && k >= nt) continue;      // (of the other orders NT is the number of tiles)
+                x[k] = tile_mul2(inverse_read(winv + k * 16 * CLD, c, g), x[k]);
+#pragma unroll
+                for (int t = k + 1; t < NT; ++t) {     // (a tile past the last gives what nobody uses)
+                    x[t] = tile_sub(tile_read(tile(k, t), lane), x[k], x[t]);
+                    asm volatile("" ::: "memory");     // the tiles of later steps do not fit the registers
+                }
+            }
+        }
+        // what lies past the last tile
+        if (nt < NT)
+            for (int e = tid; e < N * N; e += 64 * (HW + 1)) {
+                const int r = e / N, q = e % N;
+                if (r >= 16 * nt || q >= 16 * nt) Us[r * LD + q] = 0.f;
+            }
+        __syncthreads();
+        if (wave < NT) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) Q[(16 * wave + c) * LD + 16 * t + 4 * r + g] = wave < nt && t < nt ? (float)x[t][r] : 0.f;
+        }
+        if (again && Up != nullptr) {      // U <- T U with T the second factor
+            f32x4 v[NT];
+            if (wave < NT)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    v[t] = f32x4{};
+#pragma unroll 1
+                    for (int kk = wave; kk <= t; ++kk)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int k = 4 * q + g;
+                            float x = Us[(16 * wave + c) * LD + 16 * kk + k];
+                            if (kk == wave) x = k >= c ? x : 0.f;
+                            const bool in = 16 * kk + k <= 16 * t + c && 16 * t + c < n;
+                            v[t] = MFMA16(x, in ? Up[(long)(16 * kk + k) * ldu + 16 * t + c] : 0.f, v[t]);
+                        }
+                }
+            __syncthreads();
+            if (wave < NT)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int i = 16 * wave + 4 * g + r, j = 16 * t + c;
+                        if (i <= j) Us[i * LD + j] = v[t][r];
+                    }
+        }
     }
-    {                     // R[r][c] = s_c Q[r][c]
-        float* Rp = R + (long)blockIdx.x * sr + (long)item * ldr;
-#pragma unroll
-        for (int k = 0; k < NG; ++k) {
-            const int c = 4 * (k * QS + h);
-            const float4 sg = *reinterpret_cast<const float4*>(sgn + c);
-            const float4 v = make_float4(xq[4 * k] * sg.x, xq[4 * k + 1] * sg.y, xq[4 * k + 2] * sg.z, xq[4 * k + 3] * sg.w);
-            if (item < n && c + 3 < n) {
-                *reinterpret_cast<float4*>(Rp + c) = v;
-            } else if (item < n) {
-                if (c < n) Rp[c] = v.x;
-                if (c + 1 < n) Rp[c + 1] = v.y;
-                if (c + 2 < n) Rp[c + 2] = v.z;
-            }
+    __syncthreads();
+    for (int e = tid; e < N * N / 4; e += 64 * (HW + 1)) {
+        const int r = e / (N / 4), q = e % (N / 4) * 4;
+        if (r >= n || q >= n) continue;
+        store_quad(Rp + (long)r * ldr + q, n - q, *reinterpret_cast<const float4*>(Q + r * LD + q));
+        if (Up != nullptr) {
+            float4 u = *reinterpret_cast<const float4*>(Us + r * LD + q);
+            u.x = q >= r ? u.x : 0.f; u.y = q + 1 >= r ? u.y : 0.f; u.z = q + 2 >= r ? u.z : 0.f; u.w = q + 3 >= r ? u.w : 0.f;
+            store_quad(Up + (long)r * ldu + q, n - q, u);
         }
     }
 }
-#undef DQ_BLOCK_SWITCH
 
 // ------------------------------------------------------------------------------------------------ S3 + S4 + S5
 // JB = number of 32-column blocks of the rotation (n <= 32 JB): a workgroup has JB wavefronts, wavefront w forms the columns
@@ -663,12 +870,13 @@ hipError_t launch_heads_qr(int b, int n, const float* Z, long ldz, long sz, floa
                            long su, unsigned* flags, hipStream_t s) {
     if (b < 1) return hipSuccess;
     if (n < 1 || n > HN) return hipErrorInvalidValue;
-#define DQ_LAUNCH(FULL, NG)                                                                                              \
-    hipLaunchKernelGGL((heads_qr_kernel<FULL, NG>), dim3(b), dim3(HN * QS), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, n, flags)
-    if (n == HN) DQ_LAUNCH(true, 8);
-    else if (n > 96) DQ_LAUNCH(false, 8);
-    else if (n > 64) DQ_LAUNCH(false, 6);
-    else DQ_LAUNCH(false, 4);
+#define DQ_LAUNCH(NT)                                                                                                    \
+    hipLaunchKernelGGL((heads_qr_kernel<NT>), dim3(b), dim3(64 * (HW + 1)), 0, s, Z, ldz, sz, R, ldr, sr, U, ldu, su, n, flags)
+    if (n > 112) DQ_LAUNCH(8);
+    else if (n > 96) DQ_LAUNCH(7);
+    else if (n > 80) DQ_LAUNCH(6);
+    else if (n > 64) DQ_LAUNCH(5);
+    else DQ_LAUNCH(4);
 #undef DQ_LAUNCH
     return hipGetLastError();
 }

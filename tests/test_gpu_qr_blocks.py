@@ -1,4 +1,5 @@
-"""The QR by blocks of 256 columns from fp64 Gram matrices at the edges of its tiles and blocks, against 64 bits."""
+"""The QR from fp64 Gram matrices (small rotations in one workgroup, larger ones by blocks of 256 columns) at the edges of its
+tiles and blocks, against 64 bits."""
 
 import numpy as np
 import pytest
@@ -84,6 +85,32 @@ def _check(Z, R, U):
     res = (R @ U - Z).norm(dim=0) / Z.norm(dim=0)
     assert float(res.max()) < 2e-6
     assert int(torch.count_nonzero(torch.tril(U, -1))) == 0 and bool((U.diagonal() > 0).all())
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [2, 16, 33, 64, 65, 80, 95, 100, 113, 128])
+def test_small_rotations(n, kind):
+    """One workgroup a latent: tiles cut short, 64 x 64 blocks of 1 to 64 columns, a second pass that is not needed, is by a few terms, by
+    another factorisation, and the slow way; several latents in one launch, one alone, without U."""
+    if (n < 41 and kind == "spanned") or (n < 6 and kind == "parallel"):
+        pytest.skip("fewer columns than the kind speaks of")
+    c = B.Context()
+    try:
+        c.ensure_workspace(4, n, 1, B.DQ_F32)
+        ld = -(-n // 4) * 4 + 4
+        Z, R, U, R1 = (torch.full((4, n, ld), 7.0, device="cuda") for _ in range(4))
+        for i, k in enumerate((kind, "gauss", "rotation", kind)):
+            Z[i, :, :n] = _latent(n, k)
+        c.dq_qr_orth(Z[..., :n], R[..., :n], U[..., :n])
+        c.dq_qr_orth(Z[3:, :, :n], R1[3:, :, :n], None)
+        assert torch.equal(R[0], R[3]) and torch.equal(U[0], U[3]) and torch.equal(R1[3], R[3])
+        assert torch.all(R[..., n:] == 7.0) and torch.all(U[..., n:] == 7.0)
+        for i in range(3):
+            _check(Z[i, :, :n], R[i, :, :n], U[i, :, :n])
+        assert c.dq_device_flags() & ~B.DQ_FLAG_ILLCOND_PANEL == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
 
 
 @pytest.mark.parametrize("n", [300, 770])
