@@ -263,8 +263,8 @@ def run_config(cfg_name: str, args):
     raw_ms = dom["ms"] / launches
     avg_ms = max(raw_ms - bracket_ms, 1e-6)
     class_s = avg_ms * launches * 1e-3            # summed kernel time of the class over the K steps
-    # algorithmic work of the class per step (the model's, not what the launches issue: forming R forward issues
-    # 2 n^3 where the model counts 4/3 n^3, the rotation product issues its flops twice for the two planes of R)
+    # algorithmic work of the class per step (the model's, not what the launches issue: the QR's products issue
+    # 4.7 n^3 where the model counts 8/3 n^3, the rotation product issues its flops twice for the two planes of R)
     # The library's default (DQ_OPT_SPLIT_GEMM = 1) moves the full n^3 products of the derivative (R^T G and R M: 3 n^3 of
     # the model's 4 n^3, the triangular solve stays) and all six of the Cayley update from the fp32 to the bf16 matrix
     # cores where planes pay, 4096 and 8192 of the workloads here (six times the flops issued): the model's flops are booked to
@@ -294,7 +294,7 @@ def run_config(cfg_name: str, args):
     traffic, traffic_src = measured_traffic(cfg.name, CLASS_KERNEL.get(names[dominant]))
     roof["traffic"] = traffic
     roof["traffic_unit"] = ("bytes per launch (fetch + write), from " + traffic_src +
-                            " (counter collection serialises the streams: taken on the QR's event route, see that file)"
+                            " (counter collection serialises the streams: the QR's products are ordered by events there, see that file)"
                             ) if traffic_src else None
     roof["kernel"] = CLASS_KERNEL.get(names[dominant], names[dominant])
     roof["algorithmic_work_per_step"] = work
