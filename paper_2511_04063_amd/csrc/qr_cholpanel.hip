@@ -1,5 +1,6 @@
 // Tall panel factorisation spread over many compute units (a communication-avoiding replacement of the
-// one-workgroup Householder panel for tall m x 64 panels of Alg. 2's blocked form):
+// one-workgroup Householder panel for tall m x 64 panels of Alg. 2's blocked form; taken where an option asks for Householder panels,
+// the default QR is by blocks of 256 columns from Gram matrices):
 //
 //   1. CholeskyQR, twice:  G = A^T A = U1^T U1,  Q1 = A U1^-1,  G2 = Q1^T Q1 = U2^T U2,  Q = Q1 U2^-1,
 //      Rf = U2 U1  (A = Q Rf, Q orthonormal to rounding when ||G2 - I|| is small; that is checked).
