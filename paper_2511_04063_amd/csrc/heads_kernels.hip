@@ -39,8 +39,8 @@ __device__ __forceinline__ uint32_t to_bf16_rne(float f) {
 
 // ------------------------------------------------------------------------------------------------ S1 + S2
 // R, U of one latent per workgroup, in LDS and registers: G = A^T A, G = U^T U and Q^T = U^-T A^T in fp64 on the matrix cores, which
-// leaves Q^T Q = I + E at 1e-16 times the square of the condition number.  Q once more where that is not yet the identity: the factor I + X
-// with X the upper half of E leaves |E|^2, again where that is no rounding; another factorisation where E is no small number; and
+// leaves Q^T Q = I + E at 1e-16 times the square of the condition number.  Q once more where that is not yet the identity: by the factor
+// I + X with X the upper half of E where its square is rounding; by another factorisation where it is not; and
 // column by column where there is no Gram matrix to speak of (condition numbers from 1e8 on).
 // Wavefront 0 factors the 16 x 16 diagonal tiles, the other seven hold the tiles of G's upper triangle (see chol64_kernel, which has
 // more of them).  Q's rows are independent of each other, 16 to a wavefront: their transposes take the factorisation's steps as more columns
@@ -51,6 +51,8 @@ __device__ __forceinline__ uint32_t to_bf16_rne(float f) {
 // 89 / 41, 32 of 80 77 / 33, 64 of 64 51 / 22.  Of the 69 us: G 19, the factor 23 (eight diagonal tiles), Q about 10, E 11.
 constexpr int HW = 7;            // wavefronts that hold tiles
 constexpr double kHeadsDone = 4e-14;      // |R^T R - I|_F^2 / n with which R is finished: 2e-7 (column by column it was 3.3 to 4.1e-7)
+// |R^T R - I|_F^2 up to which Q (I - X), (I + X) U is taken: their product lacks X^2 U, at most 1.5e-7 of a column of Z here.
+constexpr double kHeadsNear = 3e-7;
 
 template <int NT>
 struct HeadsQr {
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(64 * (HW + 1)) void heads_qr_kernel(const float* __
     if (tid == 0) rows_done = 0;
     load(Zp, ldz);
     bool again = false;
-    for (int step = 0, rows_base = 0; step < 6; ++step) {
+    for (int step = 0, rows_base = 0;; ++step) {
         int c = c0, g = g0;
         asm volatile("" : "+v"(c), "+v"(g));    // addresses of all phases do not fit the registers across steps
         __syncthreads();
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(64 * (HW + 1)) void heads_qr_kernel(const float* __
             __syncthreads();
             const double sum = ((dev[0] + dev[1]) + (dev[2] + dev[3])) + ((dev[4] + dev[5]) + (dev[6] + dev[7]));
             if (sum < kHeadsDone * n) break;
-            if (sum < 1e-3) {
+            if (sum < kHeadsNear) {
 #pragma unroll
                 for (int s = 0; s < SLOTS; ++s) {
                     const int t = opaque(tij[s]), ti = t >> 8, tj = t & 255;
@@ -231,8 +233,7 @@ __global__ __launch_bounds__(64 * (HW + 1)) void heads_qr_kernel(const float* __
                             if (i <= j) Us[i * LD + j] += xu[s][r];
                         }
                 }
-                if (sum < 3e-7) break;
-                continue;
+                break;
             }
             if (again) break;
             again = true;

@@ -113,6 +113,29 @@ def test_small_rotations(n, kind):
         c.close()
 
 
+@pytest.mark.parametrize("n", [64, 80, 96, 112, 128])
+def test_small_rotated_triangles(n):
+    """Triangles times a rotation, diagonals from 0.4 to 1.4: R of the first factor is off by anything from rounding to all of it, so
+    that some latents lie on either side of each line between finished, corrected, factored again and the slow way."""
+    b = 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    Z = torch.triu(torch.randn(b, n, n, generator=g, device="cuda", dtype=torch.float64))
+    Z.diagonal(dim1=1, dim2=2).abs_().add_(torch.linspace(0.4, 1.4, b, device="cuda", dtype=torch.float64)[:, None])
+    Z = (torch.linalg.qr(torch.randn(b, n, n, generator=g, device="cuda", dtype=torch.float64))[0].contiguous() @ Z.contiguous()).float()
+    c = B.Context()
+    try:
+        c.ensure_workspace(b, n, 1, B.DQ_F32)
+        R, U = torch.empty_like(Z), torch.empty_like(Z)
+        c.dq_qr_orth(Z, R, U)
+        for i in range(b):
+            _check(Z[i], R[i], U[i])
+        assert c.dq_device_flags() & ~B.DQ_FLAG_ILLCOND_PANEL == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
+
+
 @pytest.mark.parametrize("n", [300, 770])
 def test_blocks_under_capture(n):
     """The same launches recorded into a graph, in a context that has met its stream before and in one that has not: every replay, on
