@@ -74,7 +74,7 @@ typedef enum { DQ_OBJ_WHIP = 0, DQ_OBJ_VARIANCE = 1, DQ_OBJ_KURTOSIS = 2, DQ_OBJ
 /* bits of the device status word */
 #define DQ_FLAG_SINGULAR   1u   /* a zero appeared on diag(U): Z is singular (dZ undefined)  */
 #define DQ_FLAG_NONFINITE  2u   /* a NaN or Inf was seen in a pivot or in the loss           */
-#define DQ_FLAG_ILLCOND_PANEL 4u /* informational: columns of one block of the QR cancel against each other by more than 2^14 in
+#define DQ_FLAG_ILLCOND_PANEL 4u /* informational, n > 128: columns of one block of the QR cancel against each other by more than 2^14 in
                                    length (with a Householder option set: a tall 64-column panel was too ill-conditioned for
                                    the many-CU panel route and was factored by the one-workgroup Householder kernel
                                    instead); results are valid.  Also: Z, singular in fp32 (condition number beyond 2^24), has left R

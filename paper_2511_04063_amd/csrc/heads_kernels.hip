@@ -1,6 +1,7 @@
 // Batched path for small rotations, n <= 128 (per-head rotations; the "heads" workload has 64 of size 128): every problem
 // of a batch runs in the same launch.
-//   * heads_qr_kernel: R, U = qr(Z) for one latent per workgroup, entirely on chip: Cholesky of the Gram matrix in fp64, twice.
+//   * heads_qr_kernel: R, U = qr(Z) for one latent per workgroup, entirely on chip: Cholesky of the Gram matrix in fp64, once or
+//     twice, or column by column.
 //   * heads_rlg_kernel: Alg. 1, rotation and loss steps, fused for bf16 activations.  A workgroup streams 64-token tiles of X once;
 //     Y = X R (R as two bf16 planes held in registers), the Whip loss and its gradient (Eq. 4) and the tile's
 //     contribution to G = X^T dY are formed on chip: Y and dY never reach HBM.
@@ -40,29 +41,185 @@ __device__ __forceinline__ uint32_t to_bf16_rne(float f) {
 // ------------------------------------------------------------------------------------------------ S1 + S2
 // R, U of one latent per workgroup, in LDS and registers: G = A^T A, G = U^T U and Q^T = U^-T A^T in fp64 on the matrix cores, which
 // leaves Q^T Q = I + E at 1e-16 times the square of the condition number.  Q once more where that is not yet the identity: by the factor
-// I + X with X the upper half of E where its square is rounding; by another factorisation where it is not; and
-// column by column where there is no Gram matrix to speak of (condition numbers from 1e8 on).
+// I + X with X the upper half of E where its square is rounding; by another factorisation where it is not; and Z column by column
+// (householder_columns) where its Gram matrix has no factor: condition numbers from 1e8 on, columns that vanish or are spanned.
 // Wavefront 0 factors the 16 x 16 diagonal tiles, the other seven hold the tiles of G's upper triangle (see chol64_kernel, which has
 // more of them).  Q's rows are independent of each other, 16 to a wavefront: their transposes take the factorisation's steps as more columns
 // of G would.  (In fp32 Q cost 6 us, and E, from condition numbers of 100 on, a correction and one more look, 10 to 45 us.)
 // Us: U above the diagonal, below it X^T, its diagonal in dinv.
-// Bound: one compute unit's fp64 matrix cores and the chain of its diagonal tiles.  Column by column before (1 us a column: a chain of
-// barrier, norm, dot product and update) and now: 64 latents of order 128 127 / 69 us, 512 of them 277 / 152, 64 of 112 117 / 52, 64 of 96
-// 89 / 41, 32 of 80 77 / 33, 64 of 64 51 / 22.  Of the 69 us: G 19, the factor 23 (eight diagonal tiles), Q about 10, E 11.
+// Bound: one compute unit's fp64 matrix cores and the chain of its diagonal tiles.  Every latent column by column (1 us a column: a
+// chain of barrier, norm, dot product and update) and now: 64 latents of order 128 127 / 65 us, 512 of them 269 / 134, 64 of 112 117 / 50,
+// 64 of 96 89 / 38, 32 of 80 77 / 29, 64 of 64 51 / 20.  Of the 65 us: G 19, the factor 23 (eight diagonal tiles), Q about 10, E 11.
+// One latent of a batch that is factored twice: 140 us at order 128; one that is taken column by column: 198.
 constexpr int HW = 7;            // wavefronts that hold tiles
 constexpr double kHeadsDone = 4e-14;      // |R^T R - I|_F^2 / n with which R is finished: 2e-7 (column by column it was 3.3 to 4.1e-7)
 // |R^T R - I|_F^2 up to which Q (I - X), (I + X) U is taken: their product lacks X^2 U, at most 1.5e-7 of a column of Z here.
 constexpr double kHeadsNear = 3e-7;
+
+// |R^T R - I|_F^2 from which Z is taken column by column: below, no eigenvalue of R^T R is under 0.29, and another factorisation ends it.
+constexpr double kHeadsFar = 0.5;
 
 template <int NT>
 struct HeadsQr {
     static constexpr int N = 16 * NT, LD = N + 4, TILES = NT * (NT + 1) / 2, SLOTS = (TILES + HW - 1) / HW, NB = (NT + 3) / 4;
     // U's tiles above the diagonal, the diagonal ones' inverses and the exchange buffers lie where Q is before and after
     static constexpr int ROW = 0, WINV = ROW + NT * (NT - 1) / 2 * 256, NEXT = WINV + NT * 16 * CLD, DIAG = NEXT + 512,
-                         COPY = DIAG + 512, USED = COPY + 16 * CLD > N * LD / 2 ? COPY + 16 * CLD : N * LD / 2,
-                         SLOW = orthogonalise_lds(HW + 1, N),
-                         POOL = USED > SLOW ? USED : SLOW;
+                         COPY = DIAG + 512, USED = COPY + 16 * CLD;
+    static constexpr int COLUMNS = N * LD;       // floats: householder_columns has its scratch behind Q
+    static constexpr int POOL = USED > (COLUMNS + 4 * HN) / 2 ? USED : (COLUMNS + 4 * HN) / 2;
 };
+
+// Alg. 2 with the unnormalised reflector vector, R and U of any finite Z: for column j, x = A[j:, j], beta = -sign(x_0) ||x||,
+// u = x - beta e_0, H = I - gamma u u^T with gamma = 2 / u^T u  (the same reflection as the paper's normalised v);
+// a column that is already zero below the diagonal gets H = I.  Columns are taken at a length of 1 to 2, by the power of two
+// in norm2 (squared lengths of Z's), and U's get it back.
+// 512 threads: four adjacent lanes ("item" i = tid / 4, part h = tid % 4) hold one column of A AND one row of Q in
+// registers, lane part h owning the 4-row groups g with g % 4 == h of both.  Both get x <- x - gamma (u . x) u (the
+// column only if it lies right of j), with ONE read of u from LDS for the two, the partial dot products of the four
+// lanes meeting through DPP.  Columns are dealt to the items round-robin over the wavefronts (item i holds column
+// 8 (i % 16) + i / 16), so that every wavefront keeps live columns to the end.  The owners of column j + 1 publish it in
+// LDS at the end of step j, so a step needs one barrier; every wavefront forms the column norm itself.  Rows are handled
+// in blocks of 16: blocks above the diagonal block are skipped (the block index is a template parameter, so register
+// indices are static and a step runs straight-line code), the diagonal block substitutes u_0 for the raw pivot and
+// zero above it.
+// Bound: the vector ALU and the chain of dependent operations of a step, half and half, 1 us a column.
+constexpr int QS = 4;                   // lanes per column / row
+constexpr int QB = 16;                  // rows per block = 4 groups, one per lane part
+
+__device__ __forceinline__ float lane_value(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// rows of this thread's k-th group: 4 * (k * QS + h) .. + 3
+template <int JB, int NG>
+__device__ __forceinline__ void publish_from(float* cb, const float (&x)[4 * NG], int h, int j) {
+#pragma unroll
+    for (int k = JB; k < NG; ++k) {
+        const int i = 4 * (k * QS + h);
+        float4 v = make_float4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
+        if (k == JB) {   // diagonal block: entries above the diagonal are published as zero
+            v.x = i >= j ? v.x : 0.f; v.y = i + 1 >= j ? v.y : 0.f; v.z = i + 2 >= j ? v.z : 0.f; v.w = i + 3 >= j ? v.w : 0.f;
+        }
+        *reinterpret_cast<float4*>(cb + i) = v;
+    }
+}
+
+// x <- x - gamma (u . x) u for this thread's part of its column (if live) and of its row of Q, for block row JB = j / 16
+// of the pivot; u is the published column with u_0 = uj in place of the raw pivot
+template <int JB, int NG>
+__device__ __forceinline__ void reflect_from(const float* cb, float (&xc)[4 * NG], float (&xq)[4 * NG], bool col_live,
+                                             int h, int j, float uj, float gamma) {
+    float4 u[NG - JB];
+#pragma unroll
+    for (int k = JB; k < NG; ++k) u[k - JB] = *reinterpret_cast<const float4*>(cb + 4 * (k * QS + h));
+    {   // diagonal block: the pivot entry becomes u_0 (the entries above it were published as zero)
+        const int i = 4 * (JB * QS + h);
+        float4& v = u[0];
+        v.x = i == j ? uj : v.x; v.y = i + 1 == j ? uj : v.y; v.z = i + 2 == j ? uj : v.z; v.w = i + 3 == j ? uj : v.w;
+    }
+    // four independent partial sums per dot product: a lone dependent chain of 32 FMAs would set the pace of the step
+    float c0 = 0.f, c1 = 0.f, c2 = 0.f, c3 = 0.f, q0 = 0.f, q1 = 0.f, q2 = 0.f, q3 = 0.f;
+#pragma unroll
+    for (int k = JB; k < NG; ++k) {
+        const float4 v = u[k - JB];
+        c0 += v.x * xc[4 * k]; c1 += v.y * xc[4 * k + 1]; c2 += v.z * xc[4 * k + 2]; c3 += v.w * xc[4 * k + 3];
+        q0 += v.x * xq[4 * k]; q1 += v.y * xq[4 * k + 1]; q2 += v.z * xq[4 * k + 2]; q3 += v.w * xq[4 * k + 3];
+    }
+    float dc = (c0 + c1) + (c2 + c3), dq = (q0 + q1) + (q2 + q3);
+    dc += lane_xor<1>(dc); dq += lane_xor<1>(dq);
+    dc += lane_xor<2>(dc); dq += lane_xor<2>(dq);
+    const float fc = col_live ? gamma * dc : 0.f, fq = gamma * dq;
+#pragma unroll
+    for (int k = JB; k < NG; ++k) {
+        const float4 v = u[k - JB];
+        xc[4 * k] -= fc * v.x; xc[4 * k + 1] -= fc * v.y; xc[4 * k + 2] -= fc * v.z; xc[4 * k + 3] -= fc * v.w;
+        xq[4 * k] -= fq * v.x; xq[4 * k + 1] -= fq * v.y; xq[4 * k + 2] -= fq * v.z; xq[4 * k + 3] -= fq * v.w;
+    }
+}
+
+#define DQ_BLOCK_SWITCH(jb, CALL)                                                                  \
+    switch (jb) {                                                                                  \
+        case 0: CALL(0); break;                                                                    \
+        case 1: CALL(1); break;                                                                    \
+        case 2: CALL(2); break;                                                                    \
+        case 3: CALL(3); break;                                                                    \
+        case 4: if constexpr (NT > 4) { CALL(4); } break;                                          \
+        case 5: if constexpr (NT > 5) { CALL(5); } break;                                          \
+        case 6: if constexpr (NT > 6) { CALL(6); } break;                                          \
+        case 7: if constexpr (NT > 7) { CALL(7); } break;                                          \
+        default: break;                                                                            \
+    }
+
+// Q <- R, Us <- U (on and above the diagonal; row stride HeadsQr<NT>::LD both)
+template <int NT>
+__device__ __noinline__ void householder_columns(const float* __restrict__ Zp, long ldz, int n, const double* norm2, float* Q, float* Us,
+                                                 unsigned* flags) {
+    using H = HeadsQr<NT>;
+    constexpr int LD = H::LD;
+    static_assert(64 * (HW + 1) == HN * QS, "an item for every column");
+    float *const cbuf0 = Q + H::COLUMNS, *const sgn = cbuf0 + 2 * HN;
+    const int tid = threadIdx.x, lane = tid & 63, item = tid / QS, h = tid % QS;
+    const int col = 8 * (item & 15) + (item >> 4);   // this thread's column of A; its row of Q is `item`
+    const double len2 = col < n ? norm2[col] : 0.0;
+    const int ex = len2 > 0.0 && len2 < 0x1p1000 ? __builtin_amdgcn_frexp_exp(len2) >> 1 : 0;
+    float xc[4 * NT], xq[4 * NT], mydiag = 0.f;
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 4 * (k * QS + h) + e;
+            xc[4 * k + e] = (i < n && col < n) ? ldexpf(Zp[(long)i * ldz + col], -ex) : 0.f;
+            xq[4 * k + e] = (i == item) ? 1.f : 0.f;
+        }
+    __syncthreads();
+    if (tid < 2 * HN) cbuf0[tid] = 0.f;     // what lies beyond the carried blocks reads as zero
+    __syncthreads();
+    if (col == 0) publish_from<0, NT>(cbuf0, xc, h, 0);
+    __syncthreads();
+    for (int j = 0; j < n; ++j) {           // (rows and columns from n on are zero and stay zero)
+        const float* cb = cbuf0 + (j & 1) * HN;
+        // column norm below the pivot: DPP inside the rows of 16 lanes, then the four row sums through scalar registers
+        const float a0 = cb[lane], a1 = cb[lane + 64];
+        const float alpha = cb[j];
+        float sr_ = (lane > j ? a0 * a0 : 0.f) + (lane + 64 > j ? a1 * a1 : 0.f);
+        sr_ += lane_xor<1>(sr_);
+        sr_ += lane_xor<2>(sr_);
+        sr_ += lane_xor<4>(sr_);
+        sr_ += lane_xor<8>(sr_);
+        const float s = (lane_value(sr_, 0) + lane_value(sr_, 16)) + (lane_value(sr_, 32) + lane_value(sr_, 48));
+        float beta = alpha;   // nothing below the pivot: H = I
+        if (s != 0.f) {
+            // hardware square root (1 ulp): beta only decides how exactly the column is annihilated; 2 / u . u is formed
+            // from the u that is applied, so that H is orthogonal whatever the rounding of beta
+            const float nrm = __builtin_amdgcn_sqrtf(alpha * alpha + s);
+            beta = alpha >= 0.f ? -nrm : nrm;
+            const float uj = alpha - beta, gamma = 2.f * __builtin_amdgcn_rcpf(fmaf(uj, uj, s));
+#define DQ_CALL(JB) reflect_from<JB, NT>(cb, xc, xq, col > j, h, j, uj, gamma)
+            DQ_BLOCK_SWITCH(j / QB, DQ_CALL)
+#undef DQ_CALL
+        }
+        if (col == j) mydiag = beta;
+        if (tid == 0) sgn[j] = beta >= 0.f ? 1.f : -1.f;
+        if (col == j + 1) {
+            float* nb = cbuf0 + ((j + 1) & 1) * HN;
+#define DQ_CALL(JB) publish_from<JB, NT>(nb, xc, h, j + 1)
+            DQ_BLOCK_SWITCH((j + 1) / QB, DQ_CALL)
+#undef DQ_CALL
+        }
+        __syncthreads();
+    }
+    if (h == 0 && col < n && mydiag == 0.f) atomicOr(flags, DQ_FLAG_SINGULAR);
+    // U[i][c] = s_i A[i][c] above the diagonal, |diag| on it; R[r][c] = s_c Q[r][c]
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 4 * (k * QS + h) + e;
+            if (i <= col && col < n) Us[i * LD + col] = ldexpf(i < col ? sgn[i] * xc[4 * k + e] : fabsf(mydiag), ex);
+            if (item < n && i < n) Q[item * LD + i] = xq[4 * k + e] * sgn[i];
+        }
+}
+#undef DQ_BLOCK_SWITCH
 
 // acc[t] (16 rows, columns 64 s + 16 t ..) += row[k] M[k][.] over k >= 64 first, M upper triangular with its transpose below Us's diagonal and
 // its diagonal in dinv
@@ -235,16 +392,11 @@ __global__ __launch_bounds__(64 * (HW + 1)) void heads_qr_kernel(const float* __
                 }
                 break;
             }
-            if (again) break;
-            again = true;
-            if (!(sum < 1.0)) {            // no factor of that Gram matrix: Z once more, in R's place, the slow way (U in Us)
-                for (int e = tid; e < n * n; e += 64 * (HW + 1)) Rp[(long)(e / n) * ldr + e % n] = Zp[(long)(e / n) * ldz + e % n];
-                if (tid == 0) atomicOr(flags, DQ_FLAG_ILLCOND_PANEL);
-                __syncthreads();
-                orthogonalise_slowly<HW + 1>(Rp, ldr, n, n, Us, LD, pool, flags);
-                load(Rp, ldr);
-                continue;
+            if (!(sum < kHeadsFar) || again) {     // (again: E was below kHeadsFar and so is one of rounding now; a NaN ends here)
+                householder_columns<NT>(Zp, ldz, n, norm2, Q, Us, flags);
+                break;
             }
+            again = true;
             // Q waits in R, U in U
             if (wave < NT)
 #pragma unroll 1

@@ -29,6 +29,29 @@ def _latent(n, kind):
     elif kind == "decaying":     # condition number 1e7: blocks that the second pass finds ill-conditioned
         Q = torch.linalg.qr(Z)[0]
         Z = (Q * torch.logspace(0, -7, n, device="cuda", dtype=torch.float64)) @ torch.linalg.qr(Z.T.contiguous())[0]
+    # what is singular, exactly or in fp32
+    elif kind == "zero column":
+        Z[:, n // 2 + 1] = 0.0
+    elif kind == "every other zero":
+        Z[:, ::2] = 0.0
+    elif kind == "right half zero":
+        Z[:, n // 2:] = 0.0
+    elif kind == "all zero":
+        Z.zero_()
+    elif kind == "equal columns":
+        Z[:, [n // 3, n - 2, n - 1]] = Z[:, [1]]
+    elif kind == "all equal":
+        Z.fill_(1.0)
+    elif kind == "rank one":
+        Z = Z[:, :1] @ Z[:1, :]
+    elif kind == "half rank":
+        Z = Z[:, :n // 2] @ Z[n // 2:, :][: n // 2]
+    elif kind == "half the rows":      # the right half is spanned by the left one, and what rounding leaves of it is as well
+        Z[n // 2:, :] = 0.0
+    elif kind == "beyond":             # condition number 1e12
+        Z = (torch.linalg.qr(Z)[0] * torch.logspace(0, -12, n, device="cuda", dtype=torch.float64)) @ torch.linalg.qr(Z.T.contiguous())[0]
+    elif kind == "turned triangle":
+        Z = torch.linalg.qr(Z.T.contiguous())[0] @ torch.triu(Z).contiguous()
     ld = -(-n // 4) * 4
     out = torch.full((n, ld), float("nan"), device="cuda")
     out[:, :n] = Z
@@ -40,6 +63,8 @@ def _padded(n):
     return buf, buf[:, :n]
 
 
+SINGULAR = ["zero column", "every other zero", "right half zero", "all zero", "equal columns", "all equal", "rank one", "half rank",
+            "half the rows", "beyond", "turned triangle"]
 KINDS = ["gauss", "rotation", "lengths", "parallel", "spanned", "triangle", "decaying"]
 
 
@@ -78,13 +103,15 @@ def test_blocks_of_256_columns(n, kind):
     _check(Z, *first)
 
 
-def _check(Z, R, U):
+def _check(Z, R, U, singular=False):
     n = Z.shape[0]
     R, U, Z = R.double(), U.double(), Z.double()
     assert float((R.T.contiguous() @ R - torch.eye(n, device="cuda", dtype=torch.float64)).abs().max()) < 1e-6
-    res = (R @ U - Z).norm(dim=0) / Z.norm(dim=0)
+    length = Z.norm(dim=0)
+    res = (R @ U - Z).norm(dim=0) / torch.where(length > 0, length, 1.0)
     assert float(res.max()) < 2e-6
-    assert int(torch.count_nonzero(torch.tril(U, -1))) == 0 and bool((U.diagonal() > 0).all())
+    assert int(torch.count_nonzero(torch.tril(U, -1))) == 0
+    assert bool((U.diagonal() >= 0).all()) if singular else bool((U.diagonal() > 0).all())
 
 
 @pytest.mark.parametrize("kind", KINDS)
@@ -107,7 +134,32 @@ def test_small_rotations(n, kind):
         assert torch.all(R[..., n:] == 7.0) and torch.all(U[..., n:] == 7.0)
         for i in range(3):
             _check(Z[i, :, :n], R[i, :, :n], U[i, :, :n])
-        assert c.dq_device_flags() & ~B.DQ_FLAG_ILLCOND_PANEL == 0
+        assert c.dq_device_flags() == 0
+    finally:
+        torch.cuda.synchronize()
+        c.close()
+
+
+@pytest.mark.parametrize("kind", SINGULAR)
+@pytest.mark.parametrize("n", [3, 17, 64, 70, 96, 101, 128])
+def test_small_singular(n, kind):
+    """R is a rotation and reproduces Z whatever Z's rank, the neighbours in the launch as well; a column that is zero from the
+    start raises DQ_FLAG_SINGULAR, and nothing else is ever raised.  Also scaled far down and up."""
+    c = B.Context()
+    try:
+        c.ensure_workspace(3, n, 1, B.DQ_F32)
+        ld = -(-n // 4) * 4
+        for scale in (1.0, 2.0 ** -90, 2.0 ** 110):
+            Z, R, U = (torch.full((3, n, ld), 7.0, device="cuda") for _ in range(3))
+            for i, k in enumerate(("gauss", kind, "rotation")):
+                Z[i, :, :n] = _latent(n, k) * scale
+            c.dq_qr_orth(Z[..., :n], R[..., :n], U[..., :n])
+            flags = c.dq_device_flags()
+            for i in range(3):
+                _check(Z[i, :, :n] / scale, R[i, :, :n], U[i, :, :n] / scale, singular=i == 1)
+            assert flags & ~B.DQ_FLAG_SINGULAR == 0
+            if "zero" in kind:
+                assert flags == B.DQ_FLAG_SINGULAR
     finally:
         torch.cuda.synchronize()
         c.close()
@@ -130,7 +182,7 @@ def test_small_rotated_triangles(n):
         c.dq_qr_orth(Z, R, U)
         for i in range(b):
             _check(Z[i], R[i], U[i])
-        assert c.dq_device_flags() & ~B.DQ_FLAG_ILLCOND_PANEL == 0
+        assert c.dq_device_flags() == 0
     finally:
         torch.cuda.synchronize()
         c.close()
