@@ -72,13 +72,12 @@ typedef enum { DQ_REDUCE_TOKEN_MEAN = 0, DQ_REDUCE_SUM = 1 } dq_reduce;
 typedef enum { DQ_OBJ_WHIP = 0, DQ_OBJ_VARIANCE = 1, DQ_OBJ_KURTOSIS = 2, DQ_OBJ_QUANT = 3 } dq_objective;
 
 /* bits of the device status word */
-#define DQ_FLAG_SINGULAR   1u   /* a zero appeared on diag(U): Z is singular (dZ undefined)  */
+#define DQ_FLAG_SINGULAR   1u   /* a zero appeared on diag(U): Z is singular.  R is orthogonal and R U = Z, dZ is undefined */
 #define DQ_FLAG_NONFINITE  2u   /* a NaN or Inf was seen in a pivot or in the loss           */
 #define DQ_FLAG_ILLCOND_PANEL 4u /* informational, n > 128: columns of one block of the QR cancel against each other by more than 2^14 in
                                    length (with a Householder option set: a tall 64-column panel was too ill-conditioned for
                                    the many-CU panel route and was factored by the one-workgroup Householder kernel
-                                   instead); results are valid.  Also: Z, singular in fp32 (condition number beyond 2^24), has left R
-                                   orthogonal to no better than 1e-6 */
+                                   instead); results are valid */
 #define DQ_FLAG_BAD_INDEX  8u   /* dq_gather_rows met an index outside [0, T_all): that row was not written  */
 #define DQ_FLAG_SYNC_TIMEOUT 16u /* a device-side wait between the library's streams (DQ_OPT_DEVICE_SYNC) ran into its
                                    time limit: the results of that call are invalid */
@@ -164,7 +163,8 @@ dq_status dq_device_flags(dq_ctx* ctx, unsigned* host_out);
 
 /* Sec. 4.3 / the QR step of Alg. 1:  Z (n x n) -> orthogonal R and, optionally, upper-triangular U with
  * Z = R U and diag(U) >= 0, which makes R unique for nonsingular Z.  n <= 128: one workgroup a problem, Cholesky
- * of the Gram matrix in fp64.  Above: by blocks of 256 columns, Cholesky of their Gram matrices in fp64, twice; blocked Householder QR (Alg. 2 in
+ * of the Gram matrix in fp64, or Householder reflectors where it has no factor.  Above: by blocks of 256 columns, Cholesky of their Gram
+ * matrices in fp64, twice, and 16 columns at a time where they do not hold the columns; blocked Householder QR (Alg. 2 in
  * blocked compact-WY form) followed by sign normalisation where one of its options below is set.
  * Z: in, b x (n x n) fp32.  R: out, fp32.  U_or_null: out, fp32, strictly-lower part written as 0. */
 dq_status dq_qr_orth(dq_ctx* ctx, int b, int n,

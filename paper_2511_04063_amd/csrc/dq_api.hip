@@ -610,17 +610,17 @@ dq_status product_in_parts(dq_ctx* c, hipStream_t s, GemmF32 g, float* part, siz
     return DQ_OK;
 }
 
-// A block's scratch on one stream: its Gram matrix, the inverses of the 64 x 64 diagonal blocks, the words that ask for refinement and
-// for a third projection, and room for partial sums.
+// A block's scratch on one stream: its Gram matrix, the inverses of the 64 x 64 diagonal blocks, the words of the solve, those of
+// launch_finish, and room for partial sums.
 struct GramScratch {
-    double* G; double* dev; float* inv; unsigned* refine; unsigned* again; float* part; size_t part_floats;
-    GramScratch(char* base, size_t bytes, size_t blocks) {
+    double* G; double* dev; float* inv; unsigned* solve; unsigned* words; float* part; size_t part_floats;
+    GramScratch(char* base, size_t bytes, int n) {
         size_t cur = 0;
         G = reinterpret_cast<double*>(base + bump(cur, (size_t)kGramBlock * kGramBlock * 8));
         dev = reinterpret_cast<double*>(base + bump(cur, (size_t)kGramSums * 8));
         inv = reinterpret_cast<float*>(base + bump(cur, (size_t)kGramBlock * 64 * 4));
-        refine = reinterpret_cast<unsigned*>(base + bump(cur, 256));
-        again = reinterpret_cast<unsigned*>(base + bump(cur, (blocks + 1) * 4));
+        solve = reinterpret_cast<unsigned*>(base + bump(cur, 256));
+        words = reinterpret_cast<unsigned*>(base + bump(cur, (size_t)finish_words(n) * 4));
         part = reinterpret_cast<float*>(base + cur);
         part_floats = (bytes - cur) / 4;
     }
@@ -639,9 +639,10 @@ dq_status gram_form(dq_ctx* c, hipStream_t s, const GramScratch& w, int n, int n
 dq_status gram_factor(dq_ctx* c, hipStream_t s, const GramScratch& w, int n, int nc, float* V, long ldv, float* U, long ldu,
                       float* copy, long ldcopy, unsigned long long* started, unsigned long long value,
                       const SecondPass& second = SecondPass()) {
+    if (block_solve_scratch_bytes(n, nc) > w.part_floats * 4) return DQ_ERR_WORKSPACE;
     LaunchScope sc(&c->prof, s, DQ_K_PANEL, (double)n * nc * nc, 0.0);
-    DQ_HIP(launch_chol64(w.G, nc, U, ldu, w.inv, V, ldv, n, w.refine, at<unsigned>(c, 0), second, started, value, s));
-    DQ_HIP(launch_block_solve(V, ldv, n, nc, U, ldu, w.inv, w.refine, copy, ldcopy, s));
+    DQ_HIP(launch_chol64(w.G, nc, U, ldu, w.inv, w.solve, at<unsigned>(c, 0), second, started, value, s));
+    DQ_HIP(launch_block_solve(V, ldv, n, nc, U, ldu, w.inv, w.solve, w.part, copy, ldcopy, at<unsigned>(c, 0), s));
     return DQ_OK;
 }
 
@@ -650,8 +651,7 @@ dq_status gram_factor(dq_ctx* c, hipStream_t s, const GramScratch& w, int n, int
 //   second     the same for the columns behind those
 //   third      Q_J once more against the finished columns of R, S = R_<J^T Q_J, V = Q_J - R_<J S, and against itself,
 //              R_J T_JJ = V; then U's column block, U = T U' with U' what the first pass gave and T = [S; T_JJ]
-// Where V was small or ill-conditioned, R_J is orthogonal to R_<J only to rounding times that: R_J -= R_<J S with S = R_<J^T R_J once
-// more, and at the end U <- (I + S) U and a first-order correction of what S^T S has taken off the columns' orthogonality.
+// Where V was small or ill-conditioned, R_J is orthogonal to R_<J and to itself only to rounding times that: launch_finish, at the end.
 // The first pass leaves Z = Q U' to rounding whatever Q's orthogonality (U' holds what was taken off), and Q^T Q - I at rounding
 // times the condition number; the second brings that to rounding.  Error against 64 bits at n = 700 and 2048, Gaussian
 // latents, latents near a rotation, with columns parallel to 1e-5 and with columns of all lengths: half to a third of
@@ -664,7 +664,7 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
     float* Tm = at<float>(c, L.M);
     const long ld = L.ld;
     const int nb = (n + kGramBlock - 1) / kGramBlock;
-    const GramScratch wA(at<char>(c, L.wpart), L.w2 - L.wpart, nb), wC(at<char>(c, L.qpart), L.qw - L.qpart, nb);
+    const GramScratch wA(at<char>(c, L.wpart), L.w2 - L.wpart, n), wC(at<char>(c, L.qpart), L.qw - L.qpart, n);
     float* farpart = at<float>(c, L.gsplit);
     auto order = [&](hipStream_t after, hipStream_t s, int ev) -> hipError_t {   // s goes on behind what `after` holds now
         hipError_t e = hipEventRecord(c->sync_ev[ev], after);
@@ -702,7 +702,7 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
     auto second_pass = [&](int J) -> dq_status {
         const int c0 = col(J), c1 = col(J + 1), nc = c1 - c0;
         SecondPass second;
-        second.dev = wC.dev; second.again = wC.again; second.block = J;
+        second.dev = wC.dev; second.words = wC.words; second.clear = J == 0 ? finish_words(n) : 0;
         if (J > 0) {
             GemmF32 g;    // S = R_<J^T Q_J
             g.A = R; g.lda = ldr; g.ta = 1;
@@ -729,23 +729,6 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
             g.M = c1; g.N = nc; g.K = c1;
             DQ_TRY(product_in_parts(c, sC, g, wC.part, wC.part_floats));
         }
-        if (J == 0) return DQ_OK;
-        GemmF32 g;    // a third projection: two launches that do nothing otherwise.  S takes the place of the first pass's factor, now spent.
-        g.A = R; g.lda = ldr; g.ta = 1;
-        g.B = R + c0; g.ldb = ldr;
-        g.C = U1 + c0; g.ldc = ld;
-        g.M = c0; g.N = nc; g.K = n;
-        g.only_if = wC.again + J; g.cfg = 3;
-        GemmF32 v;
-        v.A = R; v.lda = ldr;
-        v.B = U1 + c0; v.ldb = ld;
-        v.C = R + c0; v.ldc = ldr;
-        v.M = n; v.N = nc; v.K = c0;
-        v.alpha = -1.f; v.beta = 1.f;
-        v.only_if = wC.again + J; v.cfg = 3;
-        LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
-        DQ_HIP(launch_gemm_f32(g, sC));
-        DQ_HIP(launch_gemm_f32(v, sC));
         return DQ_OK;
     };
     // The products behind a block start when one workgroup has begun to factor the next block's Gram matrix: they have the chip
@@ -784,9 +767,10 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
     }
     if (many) DQ_HIP(order(sA, sC, 0));
     DQ_TRY(second_pass(nb - 1));
-    if (nb > 1) {
+    if (finish_scratch_bytes(n) > wC.part_floats * 4) return DQ_ERR_WORKSPACE;
+    {
         LaunchScope sc(&c->prof, sC, DQ_K_SMALL, 0.0, 0.0);
-        DQ_HIP(launch_third_pass(R, ldr, n, U1, ld, A, ld, U, ldu, wC.again, at<unsigned>(c, 0), sC));
+        DQ_HIP(launch_finish(R, ldr, n, U, ldu, Tm, ld, wC.part, wC.words, at<unsigned>(c, 0), sC));
     }
     if (many) DQ_HIP(order(sC, sA, ev_end));
     return DQ_OK;

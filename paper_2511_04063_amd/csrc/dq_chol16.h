@@ -105,129 +105,5 @@ __device__ __forceinline__ f64x4 tile_sub(f64x4 p, f64x4 q, f64x4 c) {   // c - 
     return c;
 }
 
-// What a block's columns cancel by against each other is taken from U^-1: max over i, j of (|a_j| |U^-1[j][i]|)^2.  From kRefine on
-// A U^-1 gets a step of refinement, from kIllcond on (2^14 in length) the block is reported, from kSlow on (2^18) the Gram matrix
-// does not hold the block any more and orthogonalise_slowly() takes it.
-constexpr double kRefine = 1024.0, kIllcond = 0x1p28, kSlow = 0x1p36;
-
-// Sixteen columns at a time, each lot against the finished columns and itself and all of it twice more: any block of columns that is
-// not singular comes out orthonormal and reproduced to rounding (with twice in all, columns that are rounding noise do not).  A (rows x cols) <- Q, U (cols x cols upper triangle) with A = Q U.
-// lds: orthogonalise_lds(WAVES, cols) doubles.  One workgroup of WAVES wavefronts; for blocks that no other way takes: at 4096 x 256
-// some 3 ms.  Every column's length is positive or *flags gets DQ_FLAG_SINGULAR.
-constexpr int orthogonalise_lds(int waves, int cols) { return waves * 256 + 16 * CLD + 256 + 16 + cols * 8; }
-template <int WAVES>
-__device__ __noinline__ void orthogonalise_slowly(float* A, long lda, int rows, int cols, float* U, long ldu, double* lds,
-                                                  unsigned* flags) {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    double *gpart = lds, *gsum = gpart + WAVES * 256;
-    float *u1 = reinterpret_cast<float*>(gsum + 16 * CLD), *ut = u1 + 256, *rinv = ut + 256, *wl = rinv + 32;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 15, g = lane >> 4;
-    for (int j0 = 0; j0 < cols; j0 += 16) {
-        const int w = cols - j0 < 16 ? cols - j0 : 16;
-        for (int rep = 0; rep < 3; ++rep) {
-            for (int t = wave; t < j0 / 16; t += WAVES) {                 // W = Q^T S
-                const float *pq = A + (long)g * lda + 16 * t + c, *ps = A + (long)g * lda + j0 + (c < w ? c : 0);
-                f4 acc = {};
-#pragma unroll 8
-                for (int k = 0; k < rows; k += 4) {
-                    const bool in = k + g < rows;
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? pq[(long)k * lda] : 0.f, in ? ps[(long)k * lda] : 0.f, acc, 0, 0, 0);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) wl[(16 * t + 4 * g + r) * 16 + c] = c < w ? acc[r] : 0.f;
-            }
-            __syncthreads();
-            for (int e = tid; e < j0 * 16; e += 64 * WAVES) {
-                const int i = e >> 4, q = e & 15;
-                if (q >= w) continue;
-                float* o = U + (long)i * ldu + j0 + q;
-                if (rep == 0) {
-                    *o = wl[e];
-                } else {
-                    float v = 0.f;
-                    for (int p = 0; p <= q; ++p) v += wl[i * 16 + p] * u1[p * 16 + q];
-                    *o += v;
-                }
-            }
-            for (int r = tid; r < rows; r += 64 * WAVES) {                // S -= Q W
-                float* row = A + (long)r * lda;
-                float s[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) s[q] = q < w ? row[j0 + q] : 0.f;
-                for (int i = 0; i < j0; ++i) {
-                    const float a = row[i];
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) s[q] -= a * wl[i * 16 + q];
-                }
-#pragma unroll
-                for (int q = 0; q < 16; ++q)
-                    if (q < w) row[j0 + q] = s[q];
-            }
-            __syncthreads();
-            f64x4 acc = {};                                               // S^T S
-            const float* ps = A + (long)g * lda + j0 + (c < w ? c : 0);
-#pragma unroll 4
-            for (int k = 4 * wave; k < rows; k += 4 * WAVES) {
-                const double v = k + g < rows && c < w ? (double)ps[(long)k * lda] : 0.0;
-                acc = MFMA64(v, v, acc);
-            }
-            tile_write(gpart + wave * 256, lane, acc);
-            __syncthreads();
-            if (tid < 256) {
-                double s = 0.0;
-                for (int z = 0; z < WAVES; ++z) s += gpart[z * 256 + tid];
-                if (tid >> 4 == (tid & 15) && (tid & 15) >= w) s = 1.0;
-                gsum[(tid >> 4) * CLD + (tid & 15)] = s;
-            }
-            __syncthreads();
-            if (wave == 0) {
-                double d[16], x[16], mine = 0.0;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    d[i] = gsum[c * CLD + i];
-                    x[i] = 0.0;
-                }
-                const double len2 = gsum[c * CLD + c];
-                factor_pivots<0>(d, x, c, __builtin_fmax(len2 * 0x1p-44, 0x1p-600), row_lane<0>(d[0]), mine);
-                if (g == 0) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) ut[i * 16 + c] = i <= c && len2 > 0.0 ? (float)d[i] : 0.f;
-                    rinv[c] = len2 > 0.0 ? (float)mine : 0.f;
-                    if (c < w && !(len2 > 0.0)) atomicOr(flags, len2 == 0.0 ? DQ_FLAG_SINGULAR : DQ_FLAG_NONFINITE);
-                }
-            }
-            __syncthreads();
-            for (int r = tid; r < rows; r += 64 * WAVES) {                // S <- S U^-1, by substitution
-                float* row = A + (long)r * lda + j0;
-                float s[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) s[q] = q < w ? row[q] : 0.f;
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    float v = s[q];
-#pragma unroll
-                    for (int i = 0; i < q; ++i) v -= s[i] * ut[i * 16 + q];
-                    s[q] = v * rinv[q];
-                    if (q < w) row[q] = s[q];
-                }
-            }
-            float v = 0.f;
-            if (tid < 256) {
-                const int i = tid >> 4, q = tid & 15;
-                v = ut[tid];
-                if (rep > 0) {
-                    v = 0.f;
-                    for (int p = i; p <= q; ++p) v += ut[i * 16 + p] * u1[p * 16 + q];
-                }
-                if (i < w && q < w && i <= q) U[(long)(j0 + i) * ldu + j0 + q] = v;
-            }
-            __syncthreads();
-            if (tid < 256) u1[tid] = v;          // the product of the factors so far
-        }
-    }
-    __syncthreads();
-}
-
 }  // namespace
 }  // namespace dq

@@ -89,7 +89,6 @@ struct GemmF32 {
     // with x3, for operands whose values are not known to have a split: kGuardWords words of launch_range_scan over them.  Where
     // one is set, the kernel forms the same product on the fp32 matrix cores, with the bits of the tile without x3.
     const unsigned* guard = nullptr;
-    const unsigned* only_if = nullptr;   // 64 x 64 tiles only: a device word; where it is 0 the launch does nothing
     int cfg = -1;          // tile configuration (-1: chosen from the shape; 3: 64 x 64 tiles, K step 32)
     // batch > 1: that many independent products in one launch; problem i reads A + i*batch_a, B + i*batch_b and
     // writes C + i*batch_c (element offsets)
@@ -246,28 +245,31 @@ hipError_t launch_cholqr_fused(float* A, long lda, int m, float* Tout, float* Yp
 constexpr int kGramSums = 160;
 size_t gram64_part_doubles(int rows, int cols);
 // What the second pass has beside that.  dev (kGramSums doubles): U and inv get what launch_chol64 gives where G is the identity up to
-// a first pass's rounding, and dev what tells it so.  again: word J is raised where block J needs a third projection, word 0 where any
-// block does (cleared as the blocks go by; one word more than there are blocks).
-struct SecondPass { double* dev = nullptr; unsigned* again = nullptr; int block = 0; };
+// a first pass's rounding, and dev what tells it so.  words: those of launch_finish; the first `clear` are zeroed (the first block's call).
+struct SecondPass { double* dev = nullptr; unsigned* words = nullptr; int clear = 0; };
 hipError_t launch_gram64(const float* A, long lda, int rows, int cols, double* part, double* G, float* U, long ldu, float* inv,
                          const SecondPass& second, hipStream_t s);
-// U (cols x cols, zeros below the diagonal) with U^T U = G = A^T A (A: rows x cols); inv: the inverses of its 64 x 64 diagonal blocks
-// (row-major, the last one filled up with the identity); *refine: what launch_block_solve has to do.  A block too ill-conditioned for
-// its Gram matrix is orthogonalised here, slowly: A <- Q.  A column that vanishes raises DQ_FLAG_SINGULAR and, in the first pass,
-// DQ_FLAG_ILLCOND_PANEL, which strong cancellation raises as well.
+// U (cols x cols, zeros below the diagonal) with U^T U = G; inv: the inverses of its 64 x 64 diagonal blocks (row-major, the last one
+// filled up with the identity); solve (four words): what launch_block_solve has to do.  A column that vanishes raises DQ_FLAG_SINGULAR
+// and, in the first pass, DQ_FLAG_ILLCOND_PANEL, which strong cancellation raises as well.
 // second: as for launch_gram64.  started (optional): a word that takes `value` as soon
 // as the kernel has its compute unit.
-hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, float* A, long lda, int rows, unsigned* refine,
-                         unsigned* flags, const SecondPass& second, unsigned long long* started, unsigned long long value,
+hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, unsigned* solve, unsigned* flags, const SecondPass& second,
+                         unsigned long long* started, unsigned long long value, hipStream_t s);
+// A (rows x cols) <- A U^-1, and a copy of it to R (may be null).  A block that its Gram matrix does not hold is made orthonormal by itself,
+// U its factor; columns of it that vanish become zero, with their rows of U.
+size_t block_solve_scratch_bytes(int rows, int cols);
+hipError_t launch_block_solve(float* A, long lda, int rows, int cols, float* U, long ldu, const float* inv, unsigned* words, void* scratch,
+                              float* R, long ldr, unsigned* flags, hipStream_t s);
+// Where words[0] is set: the columns of R (n x n) that are not orthogonal to the others to rounding are made so, and U (may be null) keeps
+// its product with R.  A column that is in the span of the others gives way to one that is not, with a zero on U's diagonal and
+// DQ_FLAG_SINGULAR.  T (n x n) and finish_scratch_bytes(n) at `scratch`: scratch.
+// words: [0] the second pass has met a block that is not near the identity; [2..3] workgroups that have arrived at a meeting point so far;
+// from [4] on the largest error of each 16 columns.
+constexpr int finish_words(int n) { return 4 + (n + 15) / 16; }
+size_t finish_scratch_bytes(int n);
+hipError_t launch_finish(float* R, long ldr, int n, float* U, long ldu, float* T, long ldt, void* scratch, unsigned* words, unsigned* flags,
                          hipStream_t s);
-// A (rows x cols) <- A U^-1, and a copy of it to R (may be null)
-hipError_t launch_block_solve(float* A, long lda, int rows, int cols, const float* U, long ldu, const float* inv,
-                              const unsigned* refine, float* R, long ldr, hipStream_t s);
-// Where again[0]: U (may be null) <- (I + S) U, S (strictly upper by blocks, those where again[J] is not set taken as zero) from the third
-// projections, then R and U corrected for E = R^T R - I (n x n, scratch) to first order; entries of E above 2^-10, which only a latent
-// with a condition number beyond 2^24 leaves, raise DQ_FLAG_ILLCOND_PANEL.
-hipError_t launch_third_pass(float* R, long ldr, int n, const float* S, long lds_, float* E, long lde, float* U, long ldu,
-                             const unsigned* again, unsigned* flags, hipStream_t s);
 
 // T (kPanel x kPanel, upper, zero beyond jb) of the compact-WY form from the slice T factors and the split-K
 // partials of V^T [V | C] (gpart[z] at stride, leading dimension ldp: jb Gram columns, then nla columns of V^T C).

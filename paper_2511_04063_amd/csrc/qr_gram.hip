@@ -3,14 +3,14 @@
 // A block A_J is orthogonalised against itself by Cholesky: G = A_J^T A_J in fp64 on the fp64 matrix cores, G = U^T U in one
 // workgroup, Q_J = A_J U^-1 with the inverses of U's 64 x 64 diagonal blocks; then everything right of it loses its part along
 // Q_J.  A second pass orthogonalises Q_J once more, against the finished columns of R and against itself by the same
-// kernels, and where that finds a block ill-conditioned a third projection and a correction at the end follow: R is orthogonal to
-// rounding whenever Z's condition number is below 2^24.
+// kernels.  Where that finds a block ill-conditioned, and where columns have vanished, the columns that are not yet orthogonal are gone
+// through at the end: R is orthogonal to rounding for every finite Z, and reproduces it.
 //   gram64_kernel / gram64_sum_kernel   G of an m x <= 256 block: partial sums of row chunks, then their sum
 //   chol64_kernel                       U and the inverses of its 64 x 64 diagonal blocks
-//   block_solve_kernel                  A U^-1, rows dealt to the whole chip, with a step of refinement where U asks for it
-//   third_pass_kernel / correct_kernel  what the third projections mean for U, and the correction
-// fp64 holds the squares of any fp32 column and resolves condition numbers of a block up to 2^22; a block beyond that is orthogonalised
-// column by column in the Cholesky's workgroup.
+//   block_solve_kernel                  A U^-1, rows dealt to the whole chip
+//   finish_kernel                       what the second pass may have left
+// fp64 holds the squares of any fp32 column and resolves condition numbers of a block up to 2^18 with room to spare; a block beyond that is
+// orthogonalised 16 columns at a time by the workgroups of its solve.
 #include "dq_chol16.h"
 #include "dq_internal.h"
 #include "dq_wave.h"
@@ -23,9 +23,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int GB = kGramBlock;        // columns of a block
 constexpr int GT = GB / 16;           // 16 x 16 tiles across
 static_assert(kGramSums == GB / 64 * (GB / 64 + 1) / 2 * 16, "workgroups of gram64_sum_kernel, 256 entries each");
-constexpr unsigned kDone = 2u;        // *refine
+// What a block's columns cancel by against each other is taken from U^-1: max over i, j of (|a_j| |U^-1[j][i]|)^2.  From kSubstitute on
+// A U^-1 is formed by substitution, from kIllcond on (2^14 in length) the block is reported, from kLots on (2^18), and where a pivot has
+// been raised, its Gram matrix does not hold it any more, and it is made orthonormal 16 columns at a time.
+constexpr double kSubstitute = 1024.0, kIllcond = 0x1p28, kLots = 0x1p36;
+// Columns shorter than 2^-102 count as zeros: the products on split operands do not see all of them, nor is 2^22 / length an fp32 number.
+constexpr double kTiny = 0x1p-204;      // squared
+enum : unsigned { kPlain = 0u, kSubstituted = 1u, kByLots = 2u };        // words[0] of the solve
 // The second pass's G = I + E.  Up to here U = I + X, and from there on its columns may have lost half their length or cancel against
-// each other, and what they have left along R_<J grows as much: once more.
+// each other, and what they have left along R_<J grows as much: finish_kernel looks at them.
 constexpr double kNear = 1e-8, kFar = 0.25;      // |E|_F^2
 #define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_16x16x4f32((a), (b), (c), 0, 0, 0)
 
@@ -186,7 +192,7 @@ struct TileMap {
 __constant__ const TileMap kTiles;
 
 // U: the block's place in the triangular factor (cols x cols, zeros below the diagonal).  inv: GB / 64 row-major 64 x 64 inverses.
-// refine: 1 where A U^-1 needs the step of refinement, kDone where A is Q already (a block that the Gram matrix does not hold), else 0.
+// solve: [0] how A U^-1 is to be formed, [2..3] zeroed for it.
 // second.dev: the sums of gram64_sum_kernel (second pass) or null;
 // where they say that G is I to |E|_F < 1e-4, U and inv are there already.  started (optional) takes `value` when the kernel runs.
 // The slots from `first` on, in order: a jump into code that names each slot's registers.
@@ -228,8 +234,8 @@ __constant__ const TileMap kTiles;
 static_assert(CSLOTS <= 20 && 2 * DEFER == GT / 2, "cases of DQ_SLOTS; the quarter is up to date when its first row is due");
 
 __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* __restrict__ G, int cols, float* __restrict__ U, long ldu,
-                                                     float* __restrict__ inv, float* A, long lda, int rows, unsigned* refine,
-                                                     unsigned* flags, SecondPass second, unsigned long long* started, unsigned long long value) {
+                                                     float* __restrict__ inv, unsigned* solve, unsigned* flags,
+                                                     SecondPass second, unsigned long long* started, unsigned long long value) {
     __shared__ __attribute__((aligned(16))) double rowbuf[GT * 256];   // the step's row of U, tile by tile
     __shared__ __attribute__((aligned(16))) double winv[2][16 * CLD];  // W = U^-T of the step's diagonal tile; of this and the last step
     __shared__ __attribute__((aligned(16))) double udiag[GT][256];     // U's diagonal tiles
@@ -237,17 +243,14 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
     __shared__ __attribute__((aligned(16))) double nextbuf[2][256];    // tiles (k, k + 1) and (k + 1, k + 1) as step k finds them
     __shared__ __attribute__((aligned(16))) double diagbuf[2][256];
     __shared__ __attribute__((aligned(16))) double dcopy[16 * CLD];    // wavefront 0's
-    __shared__ double cancels[2];                                      // of the columns of W that wavefronts 4 and 8 carry
+    __shared__ double cancels[3];                                      // of the columns of W that wavefronts 4 and 8 carry; of raised pivots
     __shared__ int rows_done;                                          // counts them at the end of each step's row
     __shared__ double norm2[GB];                                       // squared column lengths
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int nt = (cols + 15) / 16;
     const double* const dev = second.dev;
-    if (dev != nullptr && tid == 0) {
-        if (second.block == 0) second.again[0] = 0u;
-        second.again[second.block + 1] = 0u;
-    }
+    for (int i = tid; i < second.clear; i += 64 * CHOL_WAVES) second.words[i] = 0u;
     if (started != nullptr && tid == 0) __hip_atomic_store(started, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (dev != nullptr) {
         double s = 0.0;
@@ -255,17 +258,17 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
         if (__builtin_amdgcn_readfirstlane((int)(s < kNear))) {
-            if (tid == 0) *refine = 0u;
+            if (tid == 0) solve[0] = kPlain;
             return;
         }
-        if (!(s < kFar) && second.block > 0 && tid == 0) second.again[0] = second.again[second.block] = 1u;
+        if (!(s < kFar) && tid == 0) second.words[0] = 1u;
     }
     if (tid == 0) rows_done = 0;
     if (tid < GB) {
         const double v = G[tid * (GB + 1)];
         norm2[tid] = v;
         if (!(v < 0x1p1000)) atomicOr(flags, DQ_FLAG_NONFINITE);
-        if (v == 0.0) atomicOr(flags, dev == nullptr ? DQ_FLAG_SINGULAR | DQ_FLAG_ILLCOND_PANEL : DQ_FLAG_SINGULAR);
+        if (v < kTiny) atomicOr(flags, dev == nullptr ? DQ_FLAG_SINGULAR | DQ_FLAG_ILLCOND_PANEL : DQ_FLAG_SINGULAR);
     }
     __syncthreads();
     // Three loops with the same barriers, so that none's registers are live in another.
@@ -274,6 +277,7 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
 #pragma unroll
         for (int r = 0; r < 4; ++r) dk[r] = G[(4 * r + g) * GB + c];
         f64x4 next = {}, diag = {};      // tiles (k, k + 1) and (k + 1, k + 1)
+        double raised = 0.0;
         if (nt > 1) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -294,13 +298,15 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
                 d[i] = v.x; d[i + 1] = v.y;
             }
             const double len2 = norm2[16 * k + c];
-            // what rounding leaves of a column that depends on those before it is kept above 2^-22 of its length; a column of
-            // zeros keeps its pivot's reciprocal finite and its row of the inverse zero
-            const double least = __builtin_fmax(len2 * 0x1p-44, 0x1p-600), one = len2 > 0.0 ? 1.0 : 0.0;
+            // what rounding leaves of a column that depends on those before it is kept above 2^-22 of its length, and the Gram matrix
+            // does not hold the block; a column of zeros gets a pivot that it does not matter beside, and its row of the inverse zero
+            const bool there = len2 >= kTiny;
+            const double least = there ? len2 * 0x1p-44 : 1.0, one = there ? 1.0 : 0.0;
             double mine = 0.0;
 #pragma unroll
             for (int i = 0; i < 16; ++i) x[i] = i == cc ? one : 0.0;
             factor_pivots<0>(d, x, cc, least, row_lane<0>(d[0]), mine);
+            raised = __builtin_fmax(raised, one * (mine * mine * least));      // 1 where the pivot was
             // each row of 16 lanes writes four rows of W and of U's tile
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -321,6 +327,9 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
                 dk = tile_sub(u, u, diag);
             }
         }
+#pragma unroll
+        for (int o = 8; o >= 1; o >>= 1) raised = __builtin_fmax(raised, __shfl_xor(raised, o));
+        if (lane == 0) cancels[2] = raised > 0.9 ? 0x1p100 : 0.0;
     } else if ((wave & 3) == 0) {
         // Columns of W within the 64 x 64 block: 0 and 3 (wavefront 4), 1 and 2 (wavefront 8); slots 0 .. split - 1 are the first's rows
         // from the diagonal down, the others the second's.
@@ -421,22 +430,255 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
         }
     }
     __syncthreads();
-    const double cancel = __builtin_fmax(cancels[0], cancels[1]);
-    const bool slow = !(cancel < kSlow);
+    const double cancel = __builtin_fmax(__builtin_fmax(cancels[0], cancels[1]), cancels[2]);
     if (tid == 0) {
         if (!(cancel < kIllcond)) atomicOr(flags, DQ_FLAG_ILLCOND_PANEL);
-        *refine = slow ? kDone : (cancel > kRefine ? 1u : 0u);
+        solve[0] = !(cancel < kLots) ? kByLots : (cancel > kSubstitute ? kSubstituted : kPlain);
+        solve[2] = solve[3] = 0u;
     }
-    static_assert(sizeof(keep) >= orthogonalise_lds(CHOL_WAVES, GB) * sizeof(double), "scratch of the slow way");
-    if (slow) orthogonalise_slowly<CHOL_WAVES>(A, lda, rows, cols, U, ldu, &keep[0][0], flags);
+}
+
+// ---- columns that a Gram matrix does not hold, 16 at a time -------------------------------------------------------------
+// A lot S goes through turns: W = M_<^T S, S -= M_< W, S^T S = U^T U (its Cholesky factor, in fp64), S <- S U^-1; the last is the one that
+// finds S orthonormal.  Two for a lot of any condition that fp32 can hold, a third where rounding noise was left.  A column that has
+// vanished, or of which at unit length only rounding in the span of the others was left once more, is set to zero, with its row of T: none of
+// what the columns behind it have is along it.
+// The workgroups of one launch do this together and wait for each other at a word in device memory, three times a turn.  They all have
+// a place at the same time: at most 128 of them, two or three to a compute unit, and what runs on other streams ends or, if it is one
+// of these kernels, fits beside them three times over.  The polls are bounded like those between streams.  They share the work by tiles of W
+// (cut along the rows where there are few) and strips of 16 rows; the 16 x 16 numerics are done by all of them alike.
+// Bound: the latency of these steps: a block of 256 columns 0.35 ms at 200 rows, 0.8 at 600, 1.3 at 1536 (by one workgroup, in global
+// memory: 1.2, 4.5 and 13 ms).
+constexpr double kSettled = 1e-2;          // |S^T S - I|_F^2 with which a turn is a lot's last
+constexpr int kTurns = 12;                 // two or three in fact
+constexpr int kLotGroups = 128;            // workgroups, at most
+constexpr int kLotStrips = DQ_MAX_N / 16 / kLotGroups;      // strips of 16 rows that a workgroup has room for
+constexpr int kLotParts = 8;               // parts of W, at most
+constexpr long long kMeetTicks = 5LL * 1000 * 1000 * 100;
+
+struct LotShared {
+    double gsum[16 * CLD], dist[4];
+    float red[4][256], strip[kLotStrips][256], ut[256], u1[256], rinv[16];
+    unsigned gone;
+};
+
+// M (rows x cols): the columns; T: before = after * T; W: kLotParts x cols (a multiple of 16) x 16; gpart: 256 a workgroup.
+struct LotJob {
+    float* M; long ldm; int rows, cols;
+    float* T; long ldt;
+    float* W; double* gpart;
+    int groups;
+};
+size_t lot_scratch_bytes(int cols, int groups) {
+    const size_t lots = (cols + 15) / 16, parts = lots < 32 ? kLotParts : 1;
+    return (size_t)groups * 2048 + parts * lots * 1024;
+}
+
+struct Meeting {                           // what the other workgroups wrote before is there afterwards
+    unsigned long long* arrived; int groups; unsigned* flags;
+    unsigned long long due = 0;
+    __device__ __forceinline__ void operator()() {
+        due += groups;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            (void)__hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            (void)handover_wait(arrived, due, kMeetTicks, flags);
+        }
+        __syncthreads();
+    }
+};
+
+// +1 or -1 by row and column: the bits of both well mixed
+__device__ __forceinline__ float random_sign(unsigned row, unsigned col, unsigned turn) {
+    unsigned h = row * 0x9E3779B1u + col * 0x85EBCA77u + turn * 0xC2B2AE3Du;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        h ^= h >> 15;
+        h *= 0x2C1B3C6Du;
+    }
+    return (h ^ (h >> 16)) & 1u ? 1.f : -1.f;
+}
+
+// The turns of a lot of w columns S against the first 16 * tiles columns of M (no more than there are).  c0 >= 0: S is M's columns from c0 on
+// and T gets its columns; returns those that have vanished.  c0 < 0: such columns become random ones by `seed`, until none is left.
+// *finite: cleared, alike in all workgroups, where S is not.
+__device__ __forceinline__ unsigned turn_lot(const LotJob& b, LotShared& sh, Meeting& meet, float* S, long lds_, int w, int c0, int tiles,
+                                             int seed, bool* finite) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wg = blockIdx.x, nwg = b.groups, rows = b.rows;
+    const int depth = 16 * tiles < b.cols ? 16 * tiles : b.cols;
+    const int groups = (rows + 15) / 16 < nwg ? (rows + 15) / 16 : nwg;
+    int wparts = b.cols > 496 || tiles == 0 ? 1 : nwg / tiles;
+    wparts = wparts < 1 ? 1 : (wparts > kLotParts ? kLotParts : wparts);
+    const int chunk = ((rows + wparts - 1) / wparts + 15) / 16 * 16;
+    const long wstride = (long)((b.cols + 15) / 16) * 256;
+    unsigned fresh = ~0u, empty = 0u;      // columns that no turn has seen, and those that have vanished
+    for (int turn = 0; turn < kTurns; ++turn) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));      // addresses of all phases do not fit the registers across turns
+        const int lane = tid & 63, c = lane & 15, g = lane >> 4, ei = tid >> 4, ej = tid & 15;
+        for (int item = wg; item < tiles * wparts; item += nwg) {         // W
+            const int t = item % tiles, part = item / tiles, qc = 16 * t + c;
+            const int r0 = part * chunk, r1 = r0 + chunk < rows ? r0 + chunk : rows;
+            const float *pq = b.M + (qc < b.cols ? qc : b.cols - 1), *ps = S + (c < w ? c : 0);
+            f32x4 acc = {};
+            int k = r0 + 4 * wave;
+#pragma unroll 8
+            for (; k + 4 <= r1; k += 16) acc = MFMA32(pq[(long)(k + g) * b.ldm], ps[(long)(k + g) * lds_], acc);
+            if (k < r1) {
+                const bool in = k + g < r1;
+                acc = MFMA32(in ? pq[(long)(k + g) * b.ldm] : 0.f, in ? ps[(long)(k + g) * lds_] : 0.f, acc);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sh.red[wave][(4 * g + r) * 16 + c] = acc[r];
+            __syncthreads();
+            b.W[part * wstride + t * 256 + tid] =
+                ej < w && 16 * t + ei < b.cols ? (sh.red[0][tid] + sh.red[1][tid]) + (sh.red[2][tid] + sh.red[3][tid]) : 0.f;
+        }
+        meet();
+        if (c0 >= 0)
+            for (int t = wg; t < tiles; t += nwg) {                       // T's part of it
+                float v = 0.f;
+                for (int p = 0; p < wparts; ++p) v += b.W[p * wstride + t * 256 + tid];
+                __syncthreads();
+                sh.red[0][tid] = v;
+                __syncthreads();
+                if (ej >= w) continue;
+                float* o = b.T + (long)(16 * t + ei) * b.ldt + c0 + ej;
+                if (turn == 0) {
+                    *o = v;
+                } else {
+                    float x = 0.f;
+                    for (int p = 0; p <= ej; ++p) x += sh.red[0][ei * 16 + p] * sh.u1[p * 16 + ej];
+                    *o += x;
+                }
+            }
+        f64x4 gram = {};
+#pragma unroll 1
+        for (int z = 0; z < kLotStrips; ++z) {                            // S -= M W and S^T S, by rows
+            const int r0 = 16 * (wg + z * nwg);
+            if (r0 >= rows) break;
+            const float* row = b.M + (long)(r0 + c < rows ? r0 + c : rows - 1) * b.ldm;
+            f32x4 acc = {};
+            auto take = [&](const float4& a, const float* pw) {
+                acc = MFMA32(a.x, pw[0], acc);
+                acc = MFMA32(a.y, pw[16], acc);
+                acc = MFMA32(a.z, pw[32], acc);
+                acc = MFMA32(a.w, pw[48], acc);
+            };
+            for (int p = 0; p < wparts; ++p) {
+                const float* pw = b.W + p * wstride + 4 * g * 16 + c;
+                int k = 16 * wave;
+#pragma unroll 4
+                for (; k + 16 <= depth; k += 64) take(*reinterpret_cast<const float4*>(row + k + 4 * g), pw + k * 16);
+                if (k < depth)
+                    take(k + 4 * g < depth ? load_quad(row + k + 4 * g, depth - k - 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f), pw + k * 16);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sh.red[wave][(4 * g + r) * 16 + c] = acc[r];
+            __syncthreads();
+            sh.strip[z][tid] = r0 + ei < rows && ej < w ? S[(long)(r0 + ei) * lds_ + ej] - ((sh.red[0][tid] + sh.red[1][tid]) +
+                                                                                           (sh.red[2][tid] + sh.red[3][tid]))
+                                                        : 0.f;
+            __syncthreads();
+            if (wave == 0)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const double v = (double)sh.strip[z][64 * r + lane];
+                    gram = MFMA64(v, v, gram);
+                }
+        }
+        if (wave == 0 && wg < groups) tile_write(b.gpart + (long)wg * 256, lane, gram);
+        meet();
+        double s = 0.0;
+#pragma unroll 8
+        for (int z = 0; z < groups; ++z) s += b.gpart[(long)z * 256 + tid];
+        if (ei == ej && (ej >= w || (empty >> ej & 1u))) s = 1.0;
+        sh.gsum[ei * CLD + ej] = s;
+        __syncthreads();
+        if (wave == 0) {
+            double d[16], x[16], mine = 0.0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                d[i] = sh.gsum[c * CLD + i];
+                x[i] = 0.0;
+            }
+            const double len2 = sh.gsum[c * CLD + c];
+            factor_pivots<0>(d, x, c, __builtin_fmax(len2 * 0x1p-44, 0x1p-600), row_lane<0>(d[0]), mine);
+            // nothing, or, at unit length, nothing but rounding: below 2^-10
+            const bool gone = c < w && (!(len2 >= kTiny) || (!(fresh >> c & 1u) && mine > 0x1p10));
+            const unsigned mask = (unsigned)__ballot(gone) & 0xffffu;
+            if (g == 0) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sh.ut[i * 16 + c] = i <= c && !(mask >> i & 1u) ? (float)d[i] : 0.f;
+                sh.rinv[c] = gone ? 0.f : (float)mine;
+            }
+            if (lane == 0) sh.gone = mask;
+        }
+        // columns of zeros are as they will be, and nothing depends on them
+        const bool zero = sh.gsum[ei * CLD + ei] == 0.0 || sh.gsum[ej * CLD + ej] == 0.0;
+        const double e = s - (ei == ej ? 1.0 : 0.0);
+        double q2 = zero && c0 >= 0 ? 0.0 : e * e;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) q2 += __shfl_xor(q2, o);
+        if (lane == 0) sh.dist[wave] = q2;
+        __syncthreads();
+        const double off = (sh.dist[0] + sh.dist[1]) + (sh.dist[2] + sh.dist[3]);
+        if (!(off < 0x1p1000)) {
+            *finite = false;
+            return empty;
+        }
+        const unsigned gone = sh.gone;
+        if (tid < 16 * kLotStrips) {                                      // S <- S U^-1, by substitution
+            const int r = 16 * (wg + (tid >> 4) * nwg) + (tid & 15);
+            if (r < rows) {
+                const float* s1 = sh.strip[tid >> 4] + (tid & 15) * 16;
+                float q[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    float v = s1[k];
+#pragma unroll
+                    for (int i = 0; i < k; ++i) v -= q[i] * sh.ut[i * 16 + k];
+                    q[k] = v * sh.rinv[k];
+                    asm volatile("" ::: "memory");     // the factor does not fit the registers
+                }
+                if (c0 < 0 && gone != 0u) {
+                    const float unit = __builtin_amdgcn_rsqf((float)rows);
+                    for (int k = 0; k < 16; ++k)
+                        if (gone >> k & 1u) S[(long)r * lds_ + k] = unit * random_sign(r, seed + k, turn);
+                }
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    if (k < w && (c0 >= 0 || !(gone >> k & 1u))) S[(long)r * lds_ + k] = q[k];
+            }
+        }
+        if (c0 >= 0) {
+            float v = sh.ut[tid];                                         // the product of the lot's factors so far
+            if (turn > 0) {
+                v = 0.f;
+                for (int p = ei; p <= ej; ++p) v += sh.ut[ei * 16 + p] * sh.u1[p * 16 + ej];
+            }
+            __syncthreads();
+            sh.u1[tid] = v;
+            if (wg == 0 && ei <= ej && ej < w) b.T[(long)(c0 + ei) * b.ldt + c0 + ej] = v;
+            empty |= gone;
+        }
+        meet();
+        // (off: without columns of zeros)
+        if (off < kSettled && (c0 >= 0 || gone == 0u)) break;
+        fresh = c0 >= 0 ? 0u : gone;
+    }
+    return empty;
 }
 
 // ---- Q = A U^-1 ---------------------------------------------------------------------------------------------------
 // RT times 16 rows a workgroup, by substitution over the 64 columns of each diagonal block: T_s = A_s - sum_i Q_i U_is, Q_s = T_s
-// inv_s.  fp32 matrix instructions; U and the inverses come from L2 in operand layout, 64 rows of them a step ahead.  Where U's
-// columns cancelled by more than 2^5 against each other the products with its inverse lose as much, which one step of refinement,
-// Q += (A - Q U) U^-1, gives back.
+// inv_s.  fp32 matrix instructions; U and the inverses come from L2 in operand layout, 64 rows of them a step ahead.
 // Bound: the chain of ten steps of 64 k, 16 products each per 16 rows, and two barriers a block.
+// Where U's columns cancel by more than 2^5 against each other the products with its inverse lose as much of R U = A.  Substitution
+// column by column loses none whatever U: 16 columns at a time, a thread a row, and products for what is right of them.
 constexpr int SLD = GB + 4;
 
 template <int RT>
@@ -500,18 +742,84 @@ __device__ __forceinline__ void solve_rows(float (*buf)[SLD], const float* __res
     }
 }
 
+// the same by substitution over 16 columns at a time
+template <int RT>
+__device__ __forceinline__ void substitute_rows(float (*buf)[SLD], float* tile, const float* __restrict__ U, long ldu, int cols, int tid) {
+    const int lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4, ei = tid >> 4, ej = tid & 15;
+    for (int l = 0; 16 * l < cols; ++l) {
+        const int j0 = 16 * l;
+        const float u = j0 + ej < cols && ei <= ej ? U[(long)(j0 + ei) * ldu + j0 + ej] : 0.f;
+        tile[tid] = ei < ej ? u : (u > 0.f ? 1.f / u : 0.f);           // (zero: a column that has vanished, or one past the last)
+        float b[GT / 4][4];                  // U right of the tile, 16 columns in four a wavefront
+#pragma unroll
+        for (int t = 0; t < GT / 4; ++t) {
+            const int col = j0 + 16 * (1 + wave + 4 * t) + c;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) b[t][q] = col < cols ? U[(long)(j0 + 4 * q + g) * ldu + col] : 0.f;
+        }
+        __syncthreads();
+        if (tid < 16 * RT) {
+            float* row = buf[tid] + j0;
+            float x[16];
+#pragma unroll
+            for (int k = 0; k < 16; k += 4) *reinterpret_cast<float4*>(x + k) = *reinterpret_cast<const float4*>(row + k);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                x[k] *= tile[k * 17];
+#pragma unroll
+                for (int i = k + 1; i < 16; ++i) x[i] -= x[k] * tile[k * 16 + i];
+            }
+#pragma unroll
+            for (int k = 0; k < 16; k += 4) *reinterpret_cast<float4*>(row + k) = *reinterpret_cast<const float4*>(x + k);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < GT / 4; ++t) {
+            const int c0 = j0 + 16 * (1 + wave + 4 * t);
+            if (c0 >= cols) continue;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                f32x4 acc = {};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc = MFMA32(buf[16 * i + c][j0 + 4 * q + g], b[t][q], acc);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) buf[16 * i + 4 * g + r][c0 + c] -= acc[r];
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // A (rows x cols) <- A U^-1, also written to R where that is given
 template <int RT>
-__global__ __launch_bounds__(256) void block_solve_kernel(float* A, long lda, int rows, int cols, const float* __restrict__ U,
-                                                          long ldu, const float* __restrict__ inv,
-                                                          const unsigned* __restrict__ refine, float* R, long ldr) {
+__global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void block_solve_kernel(float* A, long lda, int rows, int cols, float* U, long ldu,
+                                                          const float* __restrict__ inv, unsigned* words, void* scratch, float* R,
+                                                          long ldr, unsigned* flags) {
     constexpr int SR = 16 * RT;
-    __shared__ __attribute__((aligned(16))) float a[SR][SLD];
     __shared__ __attribute__((aligned(16))) float q[SR][SLD];
+    __shared__ __attribute__((aligned(16))) float tile[256];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r0 = blockIdx.x * SR;
-    const unsigned mode = *refine;
-    const bool again = mode == 1u;
+    const unsigned mode = words[0];
+    if (mode == kByLots) {
+        static_assert(sizeof(LotShared) <= sizeof(q), "room of a workgroup");
+        LotShared& sh = *reinterpret_cast<LotShared*>(&q[0][0]);
+        const int groups = (int)gridDim.x < kLotGroups ? (int)gridDim.x : kLotGroups;
+        if ((int)blockIdx.x >= groups) return;
+        double* const gpart = static_cast<double*>(scratch);
+        const LotJob job{A, lda, rows, cols, U, ldu, reinterpret_cast<float*>(gpart + groups * 256), gpart, groups};
+        Meeting meet{reinterpret_cast<unsigned long long*>(words + 2), groups, flags};
+        bool finite = true;
+        for (int l = 0; 16 * l < cols && finite; ++l)
+            (void)turn_lot(job, sh, meet, A + 16 * l, lda, cols - 16 * l < 16 ? cols - 16 * l : 16, 16 * l, l, 0, &finite);
+        if (R == nullptr) return;
+        for (int r0 = 16 * blockIdx.x; r0 < rows; r0 += 16 * groups)      // (its own strips)
+            for (int e = tid; e < 16 * cols; e += 256) {
+                const int r = r0 + e / cols, k = e % cols;
+                if (r < rows) R[(long)r * ldr + k] = A[(long)r * lda + k];
+            }
+        return;
+    }
     const int c4 = 4 * (tid & 63);
 #pragma unroll
     for (int i = 0; i < SR / 4; ++i) {
@@ -519,144 +827,161 @@ __global__ __launch_bounds__(256) void block_solve_kernel(float* A, long lda, in
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (r0 + r < rows && c4 < cols) v = load_quad(A + (long)(r0 + r) * lda + c4, cols - c4);
         *reinterpret_cast<float4*>(&q[r][c4]) = v;
-        if (again) *reinterpret_cast<float4*>(&a[r][c4]) = v;
     }
     __syncthreads();
-    if (mode != kDone) solve_rows<RT>(q, U, ldu, inv, cols, lane, wave);
-    if (again) {
-        const int c = lane & 15, g = lane >> 4;
-        for (int s = 0; s < (cols + 63) / 64; ++s) {          // A - Q U
-            const int col = 64 * s + 16 * wave + c;
-            const bool in = col < cols;
-            const float* pu = U + (in ? col : cols - 1);
-            f32x4 acc[RT] = {};
-            for (int k = 0; k < 64 * s + 16 * (wave + 1); k += 16) {
-                float b[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int row = k + 4 * u + g;
-                    b[u] = in && row < cols ? pu[(long)row * ldu] : 0.f;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int t = 0; t < RT; ++t) acc[t] = MFMA32(q[16 * t + c][k + 4 * u + g], b[u], acc[t]);
-            }
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) a[16 * t + 4 * g + r][col] -= acc[t][r];
-        }
-        __syncthreads();
-        solve_rows<RT>(a, U, ldu, inv, cols, lane, wave);
-    }
+    if (mode == kSubstituted) substitute_rows<RT>(q, tile, U, ldu, cols, tid);
+    else solve_rows<RT>(q, U, ldu, inv, cols, lane, wave);
 #pragma unroll
     for (int i = 0; i < SR / 4; ++i) {
         const int r = (tid >> 6) + 4 * i;
         if (r0 + r >= rows || c4 >= cols) continue;
-        float4 v = *reinterpret_cast<const float4*>(&q[r][c4]);
-        if (again) {
-            const float4 e = *reinterpret_cast<const float4*>(&a[r][c4]);
-            v.x += e.x; v.y += e.y; v.z += e.z; v.w += e.w;
-        }
+        const float4 v = *reinterpret_cast<const float4*>(&q[r][c4]);
         store_quad(A + (long)(r0 + r) * lda + c4, cols - c4, v);
         if (R != nullptr) store_quad(R + (long)(r0 + r) * ldr + c4, cols - c4, v);
     }
 }
 
-// ---- after a third projection ---------------------------------------------------------------------------------------
-// 16 columns of U from s0 on <- (I + X) U in place, X (upper triangular) by its entries: from the first 64 rows on, so that nothing is
-// read that is new.
-template <class X>
-__device__ __forceinline__ void upper_times_columns(const X& x, int n, float* U, long ldu, int s0) {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c = lane & 15, g = lane >> 4, last = s0 + 16 < n ? s0 + 16 : n, col = s0 + c < n ? s0 + c : n - 1;
-    for (int b = 0; 64 * b < last; ++b) {
-        const int i0 = 64 * b + 16 * wave;
-        f32x4 acc = {};
-#pragma unroll 8
-        for (int k = i0; k < last; k += 4) acc = MFMA32(x(i0 + c, k + g), k + g < n ? U[(long)(k + g) * ldu + col] : 0.f, acc);
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (i0 + 4 * g + r <= s0 + c && s0 + c < n) U[(long)(i0 + 4 * g + r) * ldu + s0 + c] += acc[r];
-    }
-}
+// ---- what the second pass may have left ------------------------------------------------------------------------------
+// E = R^T R - I in fp64; then every lot of 16 columns with an entry of E above kOff, from the left, and U <- T U.  Columns that have
+// vanished become, at the end and 16 at a time, random ones made orthogonal to all others.
+// Where there is nothing to do 2 to 4 us.  One pair of columns parallel to 1e-5 or one column of zeros, which is E, a lot or two and their
+// part of U: 0.27 and 0.5 ms at n = 1536, 0.4 and 3.3 at 4096.  Many lots: 40 us a turn at n = 600, 80 at 1536, 260 at 4096, from when
+// on the products' share of the chip, 128 workgroups, is what bounds them.
+constexpr float kOff = 7e-7f;
+constexpr int kFinishGroups = 1024;        // for E, at most
+__host__ __device__ constexpr int lot_groups_of(int n) { return (n + 15) / 16 < kLotGroups ? (n + 15) / 16 : kLotGroups; }
 
-// The workgroups from `tiles` on: U <- (I + S) U, S from the blocks' third projections.  Those before: E = R^T R - I in fp64, one 64 x 64
-// tile of the upper triangle each.
-__global__ __launch_bounds__(256) void third_pass_kernel(const float* __restrict__ R, long ldr, int n, int tiles, float* __restrict__ E,
-                                                         long lde, const float* __restrict__ S, long lds_, float* U, long ldu,
-                                                         const unsigned* __restrict__ again, unsigned* flags) {
-    if (again[0] == 0u) return;
-    if ((int)blockIdx.x >= tiles) {
-        auto x = [&](int i, int j) -> float {
-            return j < n && i < j / GB * GB && again[j / GB] != 0u ? S[(long)i * lds_ + j] : 0.f;
-        };
-        upper_times_columns(x, n, U, ldu, 16 * ((int)blockIdx.x - tiles));
-        return;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int ti, tj;
-    gram_tile(blockIdx.x, (n + 63) / 64, ti, tj);
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32, c = lane & 15, g = lane >> 4;
-    if (ti == tj && wm > wn) return;
-    f64x4 acc[2][2] = {};
-    gram_rows(R, ldr, n, ti, tj, wm, wn, 0, n, c, g, acc);
-    bool large = false;
+__global__ __launch_bounds__(256, 3) void finish_kernel(float* R, long ldr, int n, float* U, long ldu, float* T, long ldt, double* gpart,
+                                                        float* spare, float* W, unsigned* words, unsigned* flags) {
+    if (words[0] == 0u) return;
+    const int nwg = lot_groups_of(n), all = gridDim.x;      // those beyond have their share of E and go
+    __shared__ LotShared sh;
+    __shared__ unsigned char todo[DQ_MAX_N / 16];
+    __shared__ unsigned short dead[DQ_MAX_N / 16];     // a lot's columns that have vanished
+    __shared__ int late_cols[16], late_n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4, ei = tid >> 4, ej = tid & 15;
+    const int wg = blockIdx.x, lots = (n + 15) / 16;
+    const LotJob job{R, ldr, n, n, T, ldt, W, gpart, nwg};
+    Meeting meet{reinterpret_cast<unsigned long long*>(words + 2), nwg, flags, (unsigned long long)(all - nwg)};
+    // ---- the largest entry of E of every lot
+    {
+        const int nt = (n + 63) / 64, tiles = nt * (nt + 1) / 2, wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+        for (int t = wg; t < tiles; t += all) {
+            int ti, tj;
+            gram_tile(t, nt, ti, tj);
+            if (ti == tj && wm > wn) continue;
+            f64x4 acc[2][2] = {};
+            gram_rows(R, ldr, n, ti, tj, wm, wn, 0, n, c, g, acc);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int j = 0; j < 2; ++j) {
+                const int k = 64 * tj + wn + 16 * j + c;
+                unsigned most = 0u;        // (as bits: a NaN is larger than all)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+                for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = 64 * ti + wm + 16 * i + 4 * v + g, k = 64 * tj + wn + 16 * j + c;
-                if (r > k || k >= n) continue;
-                const double e = acc[i][j][v] - (r == k ? 1.0 : 0.0);
-                E[(long)r * lde + k] = (float)e;
-                large |= !(__builtin_fabs(e) < 0x1p-10);
+                    for (int v = 0; v < 4; ++v) {
+                        const int r = 64 * ti + wm + 16 * i + 4 * v + g;
+                        const unsigned e = __float_as_uint(fabsf((float)(acc[i][j][v] - (r == k ? 1.0 : 0.0))));
+                        if (r <= k && k < n && e > most) most = e;
+                    }
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) {
+                    const unsigned other = (unsigned)__shfl_xor((int)most, o);
+                    most = other > most ? other : most;
+                }
+                const int lot = 4 * tj + wn / 16 + j;
+                if (lane == 0 && lot < lots) (void)atomicMax(words + 4 + lot, most);
             }
-    if (large) atomicOr(flags, DQ_FLAG_ILLCOND_PANEL);      // R stays off by the square of it
-}
-
-// R <- R (I - X), U <- (I + X) U in place, X the upper triangle of E, half of its diagonal: R^T R = I to |E|^2.  The first workgroups
-// have 16 rows of R each and go through its columns from the last 64 back.
-__global__ __launch_bounds__(256) void correct_kernel(const float* __restrict__ E, long lde, int n, float* R, long ldr, float* U,
-                                                      long ldu, const unsigned* __restrict__ again) {
-    if (again[0] == 0u) return;
-    const int strips = (n + 15) / 16;
-    auto x = [&](int i, int j) -> float {
-        if (i > j || j >= n) return 0.f;
-        const float v = E[(long)i * lde + j];
-        return i < j ? v : 0.5f * v;
-    };
-    if ((int)blockIdx.x >= strips) {
-        upper_times_columns(x, n, U, ldu, 16 * ((int)blockIdx.x - strips));
+        }
+    }
+    if (wg >= nwg) {
+        __syncthreads();
+        if (tid == 0) (void)__hip_atomic_fetch_add(meet.arrived, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c = lane & 15, g = lane >> 4, s0 = 16 * blockIdx.x;
-    const float* row = R + (long)(s0 + c < n ? s0 + c : n - 1) * ldr;
-    for (int b = (n - 1) / 64; b >= 0; --b) {
-        const int j0 = 64 * b + 16 * wave;
-        f32x4 acc = {};
-#pragma unroll 8
-        for (int k = 0; k < j0 + 16; k += 4) acc = MFMA32(k + g < n ? row[k + g] : 0.f, x(k + g, j0 + c), acc);
+    meet();
+    for (int l = tid; l < lots; l += 256) {
+        dead[l] = 0;
+        todo[l] = __hip_atomic_load(words + 4 + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > __float_as_uint(kOff);
+    }
+    __syncthreads();
+    // ---- the lots, then, behind them, the columns that have vanished
+    bool finite = true;
+    for (int l = 0;; ++l) {
+        const bool late = l >= lots;
+        int w = n - 16 * l < 16 ? n - 16 * l : 16;
+        if (late) {
+            if (tid == 0) {                // the next 16
+                int m = 0;
+                for (int i = 0; i < lots && m < 16; ++i) {
+                    unsigned left = dead[i];
+                    if (left == 0u) continue;
+                    for (; left != 0u && m < 16; left &= left - 1u) late_cols[m++] = 16 * i + __ffs(left) - 1;
+                    dead[i] = (unsigned short)left;
+                }
+                late_n = m;
+            }
+            __syncthreads();
+            w = late_n;
+            if (w == 0) break;
+            const float unit = __builtin_amdgcn_rsqf((float)n);
+            for (int r0 = 16 * wg; r0 < n; r0 += 16 * nwg)
+                if (r0 + ei < n) spare[(r0 + ei) * 16 + ej] = ej < w ? unit * random_sign(r0 + ei, 16 * l + ej, kTurns) : 0.f;
+            meet();
+        } else if (!todo[l]) {
+            continue;
+        }
+        const unsigned empty = turn_lot(job, sh, meet, late ? spare : R + 16 * l, late ? 16 : ldr, w, late ? -1 : 16 * l, late ? lots : l,
+                                        16 * l, &finite);
+        if (!finite) return;
+        if (late) {
+            for (int r0 = 16 * wg; r0 < n; r0 += 16 * nwg)
+                if (r0 + ei < n && ej < w) R[(long)(r0 + ei) * ldr + late_cols[ej]] = spare[(r0 + ei) * 16 + ej];
+            meet();
+        } else if (tid == 0) {
+            dead[l] = (unsigned short)empty;
+            if (wg == 0 && empty != 0u) atomicOr(flags, DQ_FLAG_SINGULAR);
+        }
         __syncthreads();
+    }
+    if (U == nullptr) return;
+    // ---- U <- T U in place, 16 columns a workgroup, from the first 64 rows on: nothing is read that is new
+    for (int s0 = 16 * wg; s0 < n; s0 += 16 * nwg) {
+        const int last = s0 + 16 < n ? s0 + 16 : n, col = s0 + c < n ? s0 + c : n - 1;
+        for (int b = 0; 64 * b < last; ++b) {
+            const int i0 = 64 * b + 16 * wave;
+            f32x4 acc = {};
+            for (int l = i0 / 16; 16 * l < last; ++l) {
+                if (!todo[l]) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (s0 + 4 * g + r < n && j0 + c < n) R[(long)(s0 + 4 * g + r) * ldr + j0 + c] -= acc[r];
+                for (int q = 0; q < 4; ++q) {
+                    const int i = i0 + c, k = 16 * l + 4 * q + g;
+                    const float x = i <= k && k < n ? T[(long)i * ldt + k] - (i == k ? 1.f : 0.f) : 0.f;
+                    acc = MFMA32(x, k < n ? U[(long)k * ldu + col] : 0.f, acc);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (i0 + 4 * g + r <= s0 + c && s0 + c < n) U[(long)(i0 + 4 * g + r) * ldu + s0 + c] += acc[r];
+        }
     }
 }
 
 }  // namespace
 
-hipError_t launch_third_pass(float* R, long ldr, int n, const float* S, long lds_, float* E, long lde, float* U, long ldu,
-                             const unsigned* again, unsigned* flags, hipStream_t s) {
-    if (n < 1) return hipErrorInvalidValue;
-    const int strips = (n + 15) / 16, nt = (n + 63) / 64, tiles = nt * (nt + 1) / 2, more = U != nullptr ? strips : 0;
-    hipLaunchKernelGGL(third_pass_kernel, dim3(tiles + more), dim3(256), 0, s, R, ldr, n, tiles, E, lde, S, lds_, U, ldu, again, flags);
-    hipLaunchKernelGGL(correct_kernel, dim3(strips + more), dim3(256), 0, s, E, lde, n, R, ldr, U, ldu, again);
+size_t finish_scratch_bytes(int n) { return lot_scratch_bytes(n, lot_groups_of(n)) + (size_t)(n + 15) / 16 * 1024; }
+
+hipError_t launch_finish(float* R, long ldr, int n, float* U, long ldu, float* T, long ldt, void* scratch, unsigned* words, unsigned* flags,
+                         hipStream_t s) {
+    if (n < 1 || n > DQ_MAX_N) return hipErrorInvalidValue;
+    const int nt = (n + 63) / 64, tiles = nt * (nt + 1) / 2, most = tiles < kFinishGroups ? tiles : kFinishGroups;
+    const int groups = lot_groups_of(n);
+    double* gpart = static_cast<double*>(scratch);
+    float* spare = reinterpret_cast<float*>(gpart + groups * 256);
+    hipLaunchKernelGGL(finish_kernel, dim3(most > groups ? most : groups), dim3(256), 0, s, R, ldr, n, U, ldu, T, ldt, gpart, spare,
+                       spare + (size_t)(n + 15) / 16 * 256, words, flags);
     return hipGetLastError();
 }
 
@@ -681,24 +1006,27 @@ hipError_t launch_gram64(const float* A, long lda, int rows, int cols, double* p
     return hipGetLastError();
 }
 
-hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, float* A, long lda, int rows, unsigned* refine,
-                         unsigned* flags, const SecondPass& second, unsigned long long* started, unsigned long long value, hipStream_t s) {
+hipError_t launch_chol64(const double* G, int cols, float* U, long ldu, float* inv, unsigned* solve, unsigned* flags, const SecondPass& second,
+                         unsigned long long* started, unsigned long long value, hipStream_t s) {
     if (cols < 1 || cols > GB) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(chol64_kernel, dim3(1), dim3(64 * CHOL_WAVES), 0, s, G, cols, U, ldu, inv, A, lda, rows, refine, flags, second, started,
+    hipLaunchKernelGGL(chol64_kernel, dim3(1), dim3(64 * CHOL_WAVES), 0, s, G, cols, U, ldu, inv, solve, flags, second, started,
                        value);
     return hipGetLastError();
 }
 
 // 16 rows a workgroup where that fills the chip no more than once
-hipError_t launch_block_solve(float* A, long lda, int rows, int cols, const float* U, long ldu, const float* inv,
-                              const unsigned* refine, float* R, long ldr, hipStream_t s) {
-    if (rows < 1 || cols < 1 || cols > GB) return hipErrorInvalidValue;
+static int solve_groups(int rows) { return rows <= 4096 ? (rows + 15) / 16 : (rows + 31) / 32; }
+size_t block_solve_scratch_bytes(int rows, int cols) { return lot_scratch_bytes(cols, solve_groups(rows) < kLotGroups ? solve_groups(rows) : kLotGroups); }
+
+hipError_t launch_block_solve(float* A, long lda, int rows, int cols, float* U, long ldu, const float* inv, unsigned* words, void* scratch,
+                              float* R, long ldr, unsigned* flags, hipStream_t s) {
+    if (rows < 1 || rows > DQ_MAX_N || cols < 1 || cols > GB) return hipErrorInvalidValue;
     if (rows <= 4096)
-        hipLaunchKernelGGL(block_solve_kernel<1>, dim3((rows + 15) / 16), dim3(256), 0, s, A, lda, rows, cols, U, ldu, inv, refine,
-                           R, ldr);
+        hipLaunchKernelGGL(block_solve_kernel<1>, dim3(solve_groups(rows)), dim3(256), 0, s, A, lda, rows, cols, U, ldu, inv, words, scratch,
+                           R, ldr, flags);
     else
-        hipLaunchKernelGGL(block_solve_kernel<2>, dim3((rows + 31) / 32), dim3(256), 0, s, A, lda, rows, cols, U, ldu, inv, refine,
-                           R, ldr);
+        hipLaunchKernelGGL(block_solve_kernel<2>, dim3(solve_groups(rows)), dim3(256), 0, s, A, lda, rows, cols, U, ldu, inv, words, scratch,
+                           R, ldr, flags);
     return hipGetLastError();
 }
 

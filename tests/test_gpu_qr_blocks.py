@@ -19,7 +19,7 @@ def _latent(n, kind):
         Z = torch.linalg.qr(Z)[0] + 0.3 / np.sqrt(n) * torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64)
     elif kind == "lengths":      # columns of all lengths, 2^-40 to 2^40 among them
         Z *= torch.exp2(torch.linspace(-40, 40, n, device="cuda", dtype=torch.float64)[torch.randperm(n, generator=g, device="cuda")])
-    elif kind == "parallel":     # columns of one block parallel to 1e-5: its factor asks for refinement
+    elif kind == "parallel":     # columns of one block parallel to 1e-5: solved by substitution
         Z[:, n // 2 + 3] = Z[:, n // 2] + 1e-5 * torch.randn(n, generator=g, device="cuda", dtype=torch.float64)
     elif kind == "spanned":      # the last column nearly spanned by the first ones: the second pass has most of it to take off
         Z[:, n - 1] = Z[:, :40] @ torch.randn(40, generator=g, device="cuda", dtype=torch.float64) / 6.0 + 1e-5 * Z[:, n - 1]
@@ -103,6 +103,47 @@ def test_blocks_of_256_columns(n, kind):
     _check(Z, *first)
 
 
+@pytest.mark.parametrize("kind", SINGULAR)
+@pytest.mark.parametrize("n", [129, 200, 256, 257, 300, 513, 770])
+def test_blocks_singular(n, kind):
+    """R is a rotation and reproduces Z whatever Z's rank: columns that are zero, exactly or but for rounding in the span of others,
+    in the same lot of 16, the same block and other ones, in the last, cut lot, all of them.  The same bits with one stream, call after
+    call and without U; a column that is zero from the start raises DQ_FLAG_SINGULAR."""
+    _singular(n, kind)
+
+
+@pytest.mark.parametrize("n,kind", [(1536, "decaying"), (1536, "all equal"), (2064, "half the rows"), (2064, "rank one"), (4112, "zero column"),
+                                    (4112, "parallel"), (4112, "beyond")])
+def test_large_singular(n, kind):
+    """The same where a workgroup of the finish has more than one strip of 16 rows, and of the solve two."""
+    _singular(n, kind)
+
+
+def _singular(n, kind):
+    Z = _latent(n, kind)
+    first = None
+    for single in (0, 0, 1):
+        c = B.Context()
+        try:
+            c.ensure_workspace(1, n, 1, B.DQ_F32)
+            c.dq_set_option(B.DQ_OPT_SINGLE_STREAM, single)
+            (Rb, R), (Ub, U) = _padded(n), _padded(n)
+            R2 = torch.empty_like(Rb)[:, :n]
+            c.dq_qr_orth(Z, R, U)
+            c.dq_qr_orth(Z, R2, None)
+            flags = c.dq_device_flags()
+            assert flags & ~(B.DQ_FLAG_ILLCOND_PANEL | B.DQ_FLAG_SINGULAR) == 0
+            assert flags & B.DQ_FLAG_SINGULAR or "zero" not in kind
+            assert torch.equal(R, R2) and torch.all(Rb[:, n:] == 7.0) and torch.all(Ub[:, n:] == 7.0)
+            if first is None:
+                first = (R.clone(), U.clone())
+            assert torch.equal(R, first[0]) and torch.equal(U, first[1])
+        finally:
+            torch.cuda.synchronize()
+            c.close()
+    _check(Z, *first, singular=True)
+
+
 def _check(Z, R, U, singular=False):
     n = Z.shape[0]
     R, U, Z = R.double(), U.double(), Z.double()
@@ -118,7 +159,7 @@ def _check(Z, R, U, singular=False):
 @pytest.mark.parametrize("n", [2, 16, 33, 64, 65, 80, 95, 100, 113, 128])
 def test_small_rotations(n, kind):
     """One workgroup a latent: tiles cut short, 64 x 64 blocks of 1 to 64 columns, a second pass that is not needed, is by a few terms, by
-    another factorisation, and the slow way; several latents in one launch, one alone, without U."""
+    another factorisation, and column by column; several latents in one launch, one alone, without U."""
     if (n < 41 and kind == "spanned") or (n < 6 and kind == "parallel"):
         pytest.skip("fewer columns than the kind speaks of")
     c = B.Context()
@@ -168,7 +209,7 @@ def test_small_singular(n, kind):
 @pytest.mark.parametrize("n", [64, 80, 96, 112, 128])
 def test_small_rotated_triangles(n):
     """Triangles times a rotation, diagonals from 0.4 to 1.4: R of the first factor is off by anything from rounding to all of it, so
-    that some latents lie on either side of each line between finished, corrected, factored again and the slow way."""
+    that some latents lie on either side of each line between finished, corrected, factored again and taken column by column."""
     b = 64
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
