@@ -73,7 +73,7 @@ typedef enum { DQ_OBJ_WHIP = 0, DQ_OBJ_VARIANCE = 1, DQ_OBJ_KURTOSIS = 2, DQ_OBJ
 
 /* bits of the device status word */
 #define DQ_FLAG_SINGULAR   1u   /* a zero appeared on diag(U): Z is singular.  R is orthogonal and R U = Z, dZ is undefined */
-#define DQ_FLAG_NONFINITE  2u   /* a NaN or Inf was seen in a pivot or in the loss           */
+#define DQ_FLAG_NONFINITE  2u   /* a NaN or Inf was seen in a pivot or in the loss, or a column of Z is too long (dq_qr_orth) */
 #define DQ_FLAG_ILLCOND_PANEL 4u /* informational, n > 128: columns of one block of the QR cancel against each other by more than 2^14 in
                                    length (with a Householder option set: a tall 64-column panel was too ill-conditioned for
                                    the many-CU panel route and was factored by the one-workgroup Householder kernel
@@ -166,6 +166,9 @@ dq_status dq_device_flags(dq_ctx* ctx, unsigned* host_out);
  * of the Gram matrix in fp64, or Householder reflectors where it has no factor.  Above: by blocks of 256 columns, Cholesky of their Gram
  * matrices in fp64, twice, and 16 columns at a time where they do not hold the columns; blocked Householder QR (Alg. 2 in
  * blocked compact-WY form) followed by sign normalisation where one of its options below is set.
+ * Range: for n > 128 columns of Z shorter than 2^-102 count as columns of zeros (DQ_FLAG_SINGULAR), and from a length of 2^120 on
+ * DQ_FLAG_NONFINITE is raised, U may be infinite; for n <= 128 from 2^128 on.  With a Householder option set lengths of 2^-62 to 2^62
+ * are taken; others are not all noticed.
  * Z: in, b x (n x n) fp32.  R: out, fp32.  U_or_null: out, fp32, strictly-lower part written as 0. */
 dq_status dq_qr_orth(dq_ctx* ctx, int b, int n,
                      const float* Z, long ldz, float* R, long ldr,

@@ -260,8 +260,10 @@ void choose_split(int tiles, int K, int kalign, int max_splits, int& splits, int
 
 // An fp32 product: split operands on the bf16 matrix cores where the launcher's 128 x 128 tile applies, unless
 // DQ_OPT_SPLIT_GEMM forbids it.  guard: the words of a scan over the caller's operands that the product's own derive from
-// (GemmF32::guard).  The QR needs none: the squares of a column's entries have to stay inside fp32's range for it to work at all,
-// so a column's norm lies above 2^-63, and what an entry below 2^-110 loses (2^-134) is nothing beside it.
+// (GemmF32::guard).  The QR needs none.  By blocks of 256 columns: it takes columns of length 2^-102 to 2^120 (shorter ones count as
+// zeros, longer ones raise DQ_FLAG_NONFINITE), so that nothing rounds to infinity, and what an entry below 2^-110 loses, 2^-134, is at most
+// 2^-32 of its column.  By Householder reflectors: the squares of a column's entries have to stay inside fp32's range for it to work
+// at all, so a column's norm lies above 2^-63.
 hipError_t product_f32(const dq_ctx* c, GemmF32& g, hipStream_t s, const unsigned* guard = nullptr) {
     g.x3 = c->split_gemm != 0;
     g.guard = guard;

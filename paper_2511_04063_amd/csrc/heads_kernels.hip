@@ -443,7 +443,7 @@ __global__ __launch_bounds__(64 * (HW + 1)) void heads_qr_kernel(const float* __
         __syncthreads();
         if (tid < n) {
             const double v = norm2[tid];
-            if (!(v < 0x1p1000)) atomicOr(flags, DQ_FLAG_NONFINITE);
+            if (!(v < 0x1p256)) atomicOr(flags, DQ_FLAG_NONFINITE);      // or what U has of it may be no fp32 number
             if (v == 0.0) atomicOr(flags, DQ_FLAG_SINGULAR);
         }
         if (wave == 0) {

@@ -9,7 +9,7 @@
 //   chol64_kernel                       U and the inverses of its 64 x 64 diagonal blocks
 //   block_solve_kernel                  A U^-1, rows dealt to the whole chip
 //   finish_kernel                       what the second pass may have left
-// fp64 holds the squares of any fp32 column and resolves condition numbers of a block up to 2^18 with room to spare; a block beyond that is
+// fp64 holds the squares of fp32 columns of 2^-102 to 2^120 and resolves condition numbers of a block up to 2^18 with room to spare; a block beyond that is
 // orthogonalised 16 columns at a time by the workgroups of its solve.
 #include "dq_chol16.h"
 #include "dq_internal.h"
@@ -28,7 +28,8 @@ static_assert(kGramSums == GB / 64 * (GB / 64 + 1) / 2 * 16, "workgroups of gram
 // been raised, its Gram matrix does not hold it any more, and it is made orthonormal 16 columns at a time.
 constexpr double kSubstitute = 1024.0, kIllcond = 0x1p28, kLots = 0x1p36;
 // Columns shorter than 2^-102 count as zeros: the products on split operands do not see all of them, nor is 2^22 / length an fp32 number.
-constexpr double kTiny = 0x1p-204;      // squared
+// From 2^120 on what is formed of them may leave fp32's range.
+constexpr double kTiny = 0x1p-204, kHuge = 0x1p240;      // squared
 enum : unsigned { kPlain = 0u, kSubstituted = 1u, kByLots = 2u };        // words[0] of the solve
 // The second pass's G = I + E.  Up to here U = I + X, and from there on its columns may have lost half their length or cancel against
 // each other, and what they have left along R_<J grows as much: finish_kernel looks at them.
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
     if (tid < GB) {
         const double v = G[tid * (GB + 1)];
         norm2[tid] = v;
-        if (!(v < 0x1p1000)) atomicOr(flags, DQ_FLAG_NONFINITE);
+        if (!(v < kHuge)) atomicOr(flags, DQ_FLAG_NONFINITE);
         if (v < kTiny) atomicOr(flags, dev == nullptr ? DQ_FLAG_SINGULAR | DQ_FLAG_ILLCOND_PANEL : DQ_FLAG_SINGULAR);
     }
     __syncthreads();

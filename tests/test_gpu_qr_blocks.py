@@ -119,6 +119,41 @@ def test_large_singular(n, kind):
     _singular(n, kind)
 
 
+@pytest.mark.parametrize("n", [100, 129, 300, 770])
+def test_lengths_at_the_ends_of_the_range(n):
+    """Columns of all lengths from 2^-101 to 2^118 give R and U as ordinary ones do, without a flag; shorter ones count as zeros and longer
+    ones are reported, alone and among others (n > 128; smaller rotations take any whose U is finite).  What the products on split
+    operands lose of an entry, 2^-134, is some 2^-30 of such a column: no more than the bars of ordinary ones."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    base = torch.linalg.qr(torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64))[0]
+    base = base + 0.3 / np.sqrt(n) * torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64)
+    base = base / base.norm(dim=0)
+    spread = torch.exp2(torch.linspace(-101, 118, n, device="cuda", dtype=torch.float64)[torch.randperm(n, generator=g, device="cuda")])
+    one = torch.ones(n, device="cuda", dtype=torch.float64)
+    short, long = one.clone(), one.clone()
+    short[n // 3], long[n // 3] = 2.0 ** -104, 2.0 ** 121
+    big = n > 128
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 1, B.DQ_F32)
+        for lengths, flags in ((spread, 0), (one * 2.0 ** -101, 0), (one * 2.0 ** 118, 0), (short, B.DQ_FLAG_SINGULAR if big else 0),
+                               (one * 2.0 ** -104, B.DQ_FLAG_SINGULAR if big else 0), (long, B.DQ_FLAG_NONFINITE if big else 0)):
+            _, Z = _padded(n)
+            Z.copy_(base * lengths)
+            R, U = (_padded(n)[1] for _ in range(2))
+            c.dq_qr_orth(Z, R, U)
+            assert c.dq_device_flags() & ~B.DQ_FLAG_ILLCOND_PANEL == flags
+            if flags == B.DQ_FLAG_NONFINITE:
+                continue
+            kept = torch.where(lengths >= 2.0 ** -102, lengths, 0.0) if big else lengths
+            scale = torch.where(kept > 0, 1.0 / lengths, 1.0)      # columns at unit length
+            _check((base * kept).float().double() * scale, R, U.double() * scale, singular=True)
+    finally:
+        torch.cuda.synchronize()
+        c.close()
+
+
 def _singular(n, kind):
     Z = _latent(n, kind)
     first = None
