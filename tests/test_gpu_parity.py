@@ -677,9 +677,10 @@ def test_qr_orth_two_level_blocks(n, rows):
     assert not np.array_equal(out[rows][0], out[0][0])          # the deferred updates did run (another order of sums)
 
 
-@pytest.mark.parametrize("n,two_level_rows", [(4096, -1), (8192, -1), (8192, 0)])
+@pytest.mark.parametrize("n,two_level_rows", [(4096, -1), (8192, -1), (4096, 0), (8192, 0), (8192, 2048)])
 def test_qr_orth_full_size_repeats_its_bits(n, two_level_rows):
-    """The full-size factorisations call after call, each in two fresh contexts: the same bits every time, orthogonal to
+    """The full-size factorisations (-1: the default, blocks of 256 columns from Gram matrices; else Householder panels, with blocking in one
+    level and in two) call after call, each in two fresh contexts: the same bits every time, orthogonal to
     the bar.  The kernels of three streams overlap differently from call to call, so a step whose result depends on which
     wavefront or workgroup gets somewhere first shows up here as a call that differs from the first (one such race, in the
     64 x 64 LU of a panel's small step, did: a few calls in thirty at n = 8192 before it was fixed)."""
@@ -748,10 +749,21 @@ def ctx_householder_only():
     c.close()
 
 
+@pytest.fixture(scope="module")
+def ctx_tall_panels():
+    """A context whose QR goes by Householder panels, tall ones by the many-CU route (an option that speaks of them chooses it)."""
+    c = B.Context()
+    c.dq_set_option(B.DQ_OPT_ACCUM_PANELS, 2)
+    c.ensure_workspace(1, 2100, 64, B.DQ_F32)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
 @pytest.mark.parametrize("n,kind", [(576, "gauss"), (2048, "gauss"), (1100, "near_orthogonal"), (900, "col_scaled")])
-def test_qr_orth_tall_panel_route(ctx, ctx_householder_only, n, kind):
-    """Tall panels (>= 512 rows) are factored by CholeskyQR2 + Householder reconstruction; both routes must meet
-    the same bars against the oracle, and the fast one must not have fallen back on these inputs."""
+def test_qr_orth_tall_panel_route(ctx, ctx_tall_panels, ctx_householder_only, n, kind):
+    """Tall panels (>= 512 rows) are factored by CholeskyQR2 + Householder reconstruction; it, the one-workgroup panels and the default (blocks
+    of 256 columns) must meet the same bars against the oracle, and the first must not have fallen back on these inputs."""
     g = rng(4400 + n)
     Z = g.standard_normal((n, n))
     if kind == "near_orthogonal":
@@ -762,7 +774,7 @@ def test_qr_orth_tall_panel_route(ctx, ctx_householder_only, n, kind):
     Ro, Uo = orc.qr_orth(Z)
     cond = np.linalg.cond(Z.astype(np.float64))
     ctx.ensure_workspace(1, n, 64, B.DQ_F32)
-    for c in (ctx, ctx_householder_only):
+    for c in (ctx, ctx_tall_panels, ctx_householder_only):
         R, U = run_qr(c, Z)
         assert np.abs(R.astype(np.float64).T @ R - np.eye(n)).max() <= 1e-5
         assert np.all(np.tril(U, -1) == 0.0) and np.all(np.diag(U) > 0.0)
@@ -772,9 +784,12 @@ def test_qr_orth_tall_panel_route(ctx, ctx_householder_only, n, kind):
         assert c.dq_device_flags() == 0
 
 
-def test_qr_orth_ill_conditioned_panel_falls_back(ctx):
-    """Two nearly parallel columns inside the first panel: the Gram-matrix route cannot factor it in fp32, the
-    Householder kernel takes over (informational flag), and the result still meets the oracle."""
+@pytest.mark.parametrize("route", ["tall panels", "blocks"])
+def test_qr_orth_ill_conditioned_panel_falls_back(ctx, ctx_tall_panels, route):
+    """Two nearly parallel columns inside the first panel or block.  Panels: the Gram-matrix route cannot factor it in fp32, the
+    Householder kernel takes over; blocks of 256 columns (the default): their Gram matrix in fp64 still holds it, and substitution
+    solves with its factor.  Either says so (informational flag), and the result still meets the oracle."""
+    ctx = ctx_tall_panels if route == "tall panels" else ctx
     n = 640
     g = rng(4500)
     Z = g.standard_normal((n, n))
@@ -791,9 +806,11 @@ def test_qr_orth_ill_conditioned_panel_falls_back(ctx):
     assert rel(R, Ro) < max(1e-4, 2e-7 * cond)
 
 
-def test_qr_orth_ill_conditioned_last_panel_falls_back(ctx):
+@pytest.mark.parametrize("route", ["tall panels", "blocks"])
+def test_qr_orth_ill_conditioned_last_panel_falls_back(ctx, ctx_tall_panels, route):
     """The same inside the last, square 64 x 64 panel (which also takes the Gram-matrix route): nearly parallel
-    columns there make the route hand over to the Householder code in the same kernel."""
+    columns there make the route hand over to the Householder code in the same kernel.  Blocks: the last columns of the only one."""
+    ctx = ctx_tall_panels if route == "tall panels" else ctx
     n = 192
     g = rng(4600)
     Z = g.standard_normal((n, n))
@@ -849,19 +866,20 @@ def test_qr_orth_closed_forms(ctx):
     assert ctx.dq_device_flags() & ~B.DQ_FLAG_ILLCOND_PANEL == 0
 
 
-def test_singular_latent_raises_flag_not_fault(ctx):
-    n = 96
-    Z = rng(4300).standard_normal((n, n)).astype(np.float32)
-    Z[:, 40] = 0.0
-    run_qr(ctx, Z)
-    assert ctx.dq_device_flags() & B.DQ_FLAG_SINGULAR
-    assert ctx.dq_device_flags() == 0          # reading clears the word
-    # the same through a tall panel: the fast route gives up, the Householder kernel reports the zero pivot
-    n = 600
-    Z = rng(4301).standard_normal((n, n)).astype(np.float32)
-    Z[:, 40] = 0.0
-    run_qr(ctx, Z)
-    assert ctx.dq_device_flags() == (B.DQ_FLAG_SINGULAR | B.DQ_FLAG_ILLCOND_PANEL)
+def test_singular_latent_raises_flag_not_fault(ctx, ctx_tall_panels):
+    """A column of zeros: the flag, a rotation that reproduces Z all the same, and a status word that reading clears."""
+    def check(c, seed, n, flags):
+        Z = rng(seed).standard_normal((n, n)).astype(np.float32)
+        Z[:, 40] = 0.0
+        R, U = run_qr(c, Z)
+        assert c.dq_device_flags() == flags and c.dq_device_flags() == 0
+        assert np.abs(R.astype(np.float64).T @ R - np.eye(n)).max() <= 1e-5
+        assert rel(R.astype(np.float64) @ U, Z) < 1e-5 and U[40, 40] == 0.0
+
+    check(ctx, 4300, 96, B.DQ_FLAG_SINGULAR)
+    # by blocks, and through a tall panel: the fast route gives up, the Householder kernel reports the zero pivot
+    for c in (ctx, ctx_tall_panels):
+        check(c, 4301, 600, B.DQ_FLAG_SINGULAR | B.DQ_FLAG_ILLCOND_PANEL)
 
 
 # ----------------------------------------------------------------------------------- rotate + loss + G
