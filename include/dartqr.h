@@ -79,7 +79,7 @@ typedef enum { DQ_OBJ_WHIP = 0, DQ_OBJ_VARIANCE = 1, DQ_OBJ_KURTOSIS = 2, DQ_OBJ
                                    the many-CU panel route and was factored by the one-workgroup Householder kernel
                                    instead); results are valid */
 #define DQ_FLAG_BAD_INDEX  8u   /* dq_gather_rows met an index outside [0, T_all): that row was not written  */
-#define DQ_FLAG_SYNC_TIMEOUT 16u /* a device-side wait between the library's streams (DQ_OPT_DEVICE_SYNC) ran into its
+#define DQ_FLAG_SYNC_TIMEOUT 16u /* a device-side wait between the library's streams (DQ_OPT_DEVICE_SYNC) or workgroups ran into its
                                    time limit: the results of that call are invalid */
 
 /* ---- context and workspace ---------------------------------------------------------- */

@@ -521,9 +521,17 @@ dq_status far_update(dq_ctx* c, hipStream_t s, const Layout& L, float* wpart, fl
 }
 
 // ---------------------------------------------------------------- hand-over between the QR's streams
-// Seven 8-byte words behind the status word, cleared with it: [0] panels factored, [1] trailing updates done,
-// [2] the probe's word, [3] set by a probe wait that gave up, [4..6] the words of the one-launch panels
-// (launch_cholqr_fused).
+// Sixteen 8-byte words behind the status word, cleared with it.  All but kWordStarted hold values that only grow, and what they order
+// depends on that.
+enum {
+    kWordPanel = 0,        // panels factored
+    kWordTrailing = 1,     // trailing updates done
+    kWordProbe = 2,        // the probe's; the one behind it is set by a probe wait that gave up
+    kWordFused = 4,        // four words of the one-launch panels (launch_cholqr_fused)
+    kWordFarNear = 11, kWordFarRest = 12, kWordAccumulated = 13,      // of two-level blocks: seq0 + block + 1 once that is done
+    kWordStarted = 14,     // blocks whose Cholesky has its compute unit: a hint when to start what may run beside it.  A captured graph
+                           // stores the values of its capture again, smaller than what is there; no result may depend on this word
+};
 constexpr long kSyncLimitUs = 5L * 1000 * 1000;   // a hand-over that takes this long is a fault, not a delay
 constexpr long kProbeLimitUs = 2000;
 constexpr int kFusedPanelRows = 8192;   // tallest panel that takes the one-launch route by default
@@ -543,15 +551,15 @@ hipError_t handover_probe(dq_ctx* c, hipStream_t consumer, hipStream_t producer,
     unsigned long long* w = sync_words(c);
     const unsigned long long v = ++c->seq;
     hipError_t e;
-    if ((e = launch_stream_wait(w + 2, v, kProbeLimitUs, nullptr, w + 3, consumer)) != hipSuccess) return e;
-    if ((e = launch_stream_signal(w + 2, v, producer)) != hipSuccess) return e;
+    if ((e = launch_stream_wait(w + kWordProbe, v, kProbeLimitUs, nullptr, w + kWordProbe + 1, consumer)) != hipSuccess) return e;
+    if ((e = launch_stream_signal(w + kWordProbe, v, producer)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(consumer)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(producer)) != hipSuccess) return e;
     unsigned long long gave_up = 1;
-    if ((e = hipMemcpy(&gave_up, w + 3, sizeof(gave_up), hipMemcpyDeviceToHost)) != hipSuccess) return e;
+    if ((e = hipMemcpy(&gave_up, w + kWordProbe + 1, sizeof(gave_up), hipMemcpyDeviceToHost)) != hipSuccess) return e;
     *usable = gave_up == 0;
     if (gave_up != 0) {
-        if ((e = launch_fill_u32(reinterpret_cast<unsigned*>(w + 3), 2, 0u, consumer)) != hipSuccess) return e;
+        if ((e = launch_fill_u32(reinterpret_cast<unsigned*>(w + kWordProbe + 1), 2, 0u, consumer)) != hipSuccess) return e;
         if ((e = hipStreamSynchronize(consumer)) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -740,7 +748,7 @@ dq_status qr_orth_gram(dq_ctx* c, const Layout& L, int n, const float* Z, long l
     // (events do), so that one that runs into its limit costs time only.
     constexpr long kHintUs = 1000;
     const bool hint = many && device_sync_usable(c);
-    unsigned long long* started = hint ? sync_words(c) + 14 : nullptr;
+    unsigned long long* started = hint ? sync_words(c) + kWordStarted : nullptr;
     const unsigned long long seq0 = c->seq;
     c->seq += nb + 1;
     for (int J = 0; J < nb; ++J) {
@@ -802,17 +810,17 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
     unsigned long long* words = sync_words(c);
     const unsigned long long seq0 = c->seq;
     auto panel_done = [&](int p) -> hipError_t {            // on sA: panel p is factored
-        return dsync ? launch_stream_signal(words, seq0 + p + 1, sA) : hipEventRecord(c->sync_ev[2 * p], sA);
+        return dsync ? launch_stream_signal(words + kWordPanel, seq0 + p + 1, sA) : hipEventRecord(c->sync_ev[2 * p], sA);
     };
     auto after_panel = [&](hipStream_t s, int p) -> hipError_t {   // s goes on once panel p is factored
-        return dsync ? launch_stream_wait(words, seq0 + p + 1, kSyncLimitUs, flags, nullptr, s)
+        return dsync ? launch_stream_wait(words + kWordPanel, seq0 + p + 1, kSyncLimitUs, flags, nullptr, s)
                      : hipStreamWaitEvent(s, c->sync_ev[2 * p], 0);
     };
     auto trailing_done = [&](int p) -> hipError_t {         // on sB: the trailing update of panel p has run
-        return dsync ? launch_stream_signal(words + 1, seq0 + p + 1, sB) : hipEventRecord(c->sync_ev[2 * p + 1], sB);
+        return dsync ? launch_stream_signal(words + kWordTrailing, seq0 + p + 1, sB) : hipEventRecord(c->sync_ev[2 * p + 1], sB);
     };
     auto after_trailing = [&](int p) -> hipError_t {        // sA goes on once the trailing update of panel p has run
-        return dsync ? launch_stream_wait(words + 1, seq0 + p + 1, kSyncLimitUs, flags, nullptr, sA)
+        return dsync ? launch_stream_wait(words + kWordTrailing, seq0 + p + 1, kSyncLimitUs, flags, nullptr, sA)
                      : hipStreamWaitEvent(sA, c->sync_ev[2 * p + 1], 0);
     };
     {
@@ -849,9 +857,9 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
     // the only kind that waits for the far-near update)
     if (dsync && !c->single_stream && two_rows > 0 && c->chol_min_m > 0 && c->chol_min_m <= 4 * nb)
         while ((tl_blocks + 2) * ob <= n && n - tl_blocks * ob > two_rows) ++tl_blocks;
-    unsigned long long* wF = words + 11;    // far-near of block b done: seq0 + b + 1
-    unsigned long long* wF2 = words + 12;   // far-rest of block b done
-    unsigned long long* wF3 = words + 13;   // accumulation of block b done
+    unsigned long long* wF = words + kWordFarNear;    // far-near of block b done: seq0 + b + 1
+    unsigned long long* wF2 = words + kWordFarRest;   // far-rest of block b done
+    unsigned long long* wF3 = words + kWordAccumulated;   // accumulation of block b done
     const ReflBufs bufB{at<float>(c, L.wpartB), at<float>(c, L.w2B)};
     float* yring = at<float>(c, L.yring);
     for (int p = 0; p < npanels; ++p) {
@@ -873,7 +881,7 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
         // what the look-ahead columns (and, without the fused look-ahead, the kernels that read them) wait for: the
         // previous trailing update, or, behind a two-level block, that block's far-near update
         const bool after_block = tl_blocks > 0 && jblk == 0 && blk > 0 && blk <= tl_blocks;
-        const unsigned long long* la_word = after_block ? wF : (last_trailing >= 0 ? words + 1 : nullptr);
+        const unsigned long long* la_word = after_block ? wF : (last_trailing >= 0 ? words + kWordTrailing : nullptr);
         const unsigned long long la_value = after_block ? seq0 + blk : seq0 + last_trailing + 1;
         if (tall) {
             // the look-ahead update of the next panel's columns is fused into the last two kernels of the route when
@@ -897,7 +905,7 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
                 c->arrived += (unsigned long long)fused_wgs;
                 c->arrived_rows += (unsigned long long)(fused_wgs - 1);
                 LaunchScope sc(&c->prof, sA, DQ_K_PANEL, 2.0 * m * (double)jb * jb + 4.0 * m * (double)jb * nla, 0.0);
-                DQ_HIP(launch_cholqr_fused(Ap, ld, m, Tp, Yp, vs, at<float>(c, L.cq), tau + k0, tsl, flags, words + 4,
+                DQ_HIP(launch_cholqr_fused(Ap, ld, m, Tp, Yp, vs, at<float>(c, L.cq), tau + k0, tsl, flags, words + kWordFused,
                                            seq0 + p + 1, c->arrived, c->arrived_rows, kSyncLimitUs, sA, &ho));
                 gram_ready = true;
             } else {
