@@ -900,7 +900,7 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
                     ho.wait_word = la_word; ho.wait_value = la_value;
                     ho.limit_us = kSyncLimitUs; ho.flags = flags;
                 }
-                ho.signal_word = words; ho.signal_value = seq0 + p + 1;
+                ho.signal_word = words + kWordPanel; ho.signal_value = seq0 + p + 1;
                 signalled = true;
                 c->arrived += (unsigned long long)fused_wgs;
                 c->arrived_rows += (unsigned long long)(fused_wgs - 1);
@@ -924,7 +924,7 @@ dq_status qr_orth_one(dq_ctx* c, const Layout& L, int n, const float* Z, long ld
                     ho.wait_word = la_word; ho.wait_value = la_value;
                     ho.limit_us = kSyncLimitUs; ho.flags = flags;
                 }
-                ho.signal_word = words; ho.signal_value = seq0 + p + 1;
+                ho.signal_word = words + kWordPanel; ho.signal_value = seq0 + p + 1;
             } else if (last_trailing >= 0) {
                 DQ_HIP(after_trailing(last_trailing));
             }

@@ -11,6 +11,8 @@
 //   finish_kernel                       what the second pass may have left
 // fp64 holds the squares of fp32 columns of 2^-102 to 2^120 and resolves condition numbers of a block up to 2^18 with room to spare; a block beyond that is
 // orthogonalised 16 columns at a time by the workgroups of its solve.
+#include <type_traits>
+
 #include "dq_chol16.h"
 #include "dq_internal.h"
 #include "dq_wave.h"
@@ -448,22 +450,24 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
 // a place at the same time: at most 128 of them, two or three to a compute unit, and what runs on other streams ends or, if it is one
 // of these kernels, fits beside them three times over.  The polls are bounded like those between streams.  They share the work by tiles of W
 // (cut along the rows where there are few) and strips of 16 rows; the 16 x 16 numerics are done by all of them alike.
-// Bound: the latency of these steps: a block of 256 columns 0.35 ms at 200 rows, 0.8 at 600, 1.3 at 1536 (by one workgroup, in global
-// memory: 1.2, 4.5 and 13 ms).
+// Bound: the latency of these steps: a block of 256 columns 0.35 ms at 200 rows, 0.7 at 600, 1.0 at 1536, 2.2 at 4096 (by one workgroup, in
+// global memory: 1.2, 4.5, 13 and 37 ms).
 constexpr double kSettled = 1e-2;          // |S^T S - I|_F^2 with which a turn is a lot's last
 constexpr int kTurns = 12;                 // two or three in fact
 constexpr int kLotGroups = 128;            // workgroups, at most
 constexpr int kLotStrips = DQ_MAX_N / 16 / kLotGroups;      // strips of 16 rows that a workgroup has room for
-constexpr int kLotParts = 8;               // parts of W, at most
+constexpr int kLotParts = 8;               // parts of W along the rows, at most, where it has
+constexpr int kLotTiles = GT - 1;          // no more than these tiles
 constexpr long long kMeetTicks = 5LL * 1000 * 1000 * 100;
 
 struct LotShared {
     double gsum[16 * CLD], dist[4];
     float red[4][256], strip[kLotStrips][256], ut[256], u1[256], rinv[16];
+    float w[kLotTiles][256];
     unsigned gone;
 };
 
-// M (rows x cols): the columns; T: before = after * T; W: kLotParts x cols (a multiple of 16) x 16; gpart: 256 a workgroup.
+// M (rows x cols): the columns; T: before = after * T; W: cols (a multiple of 16) x 16, or kLotParts of that; gpart: 256 a workgroup.
 struct LotJob {
     float* M; long ldm; int rows, cols;
     float* T; long ldt;
@@ -471,8 +475,8 @@ struct LotJob {
     int groups;
 };
 size_t lot_scratch_bytes(int cols, int groups) {
-    const size_t lots = (cols + 15) / 16, parts = lots < 32 ? kLotParts : 1;
-    return (size_t)groups * 2048 + parts * lots * 1024;
+    const size_t lots = (cols + 15) / 16, parts = kLotParts * kLotTiles;      // tiles of W, with all their parts or alone
+    return (size_t)groups * 2048 + (lots > parts ? lots : parts) * 1024;
 }
 
 struct Meeting {                           // what the other workgroups wrote before is there afterwards
@@ -509,92 +513,160 @@ __device__ __forceinline__ unsigned turn_lot(const LotJob& b, LotShared& sh, Mee
     const int wg = blockIdx.x, nwg = b.groups, rows = b.rows;
     const int depth = 16 * tiles < b.cols ? 16 * tiles : b.cols;
     const int groups = (rows + 15) / 16 < nwg ? (rows + 15) / 16 : nwg;
-    int wparts = b.cols > 496 || tiles == 0 ? 1 : nwg / tiles;
+    int wparts = tiles > kLotTiles || tiles == 0 ? 1 : nwg / tiles;
     wparts = wparts < 1 ? 1 : (wparts > kLotParts ? kLotParts : wparts);
     const int chunk = ((rows + wparts - 1) / wparts + 15) / 16 * 16;
-    const long wstride = (long)((b.cols + 15) / 16) * 256;
+    const long wstride = (long)tiles * 256;
     unsigned fresh = ~0u, empty = 0u;      // columns that no turn has seen, and those that have vanished
     for (int turn = 0; turn < kTurns; ++turn) {
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));      // addresses of all phases do not fit the registers across turns
         const int lane = tid & 63, c = lane & 15, g = lane >> 4, ei = tid >> 4, ej = tid & 15;
-        for (int item = wg; item < tiles * wparts; item += nwg) {         // W
-            const int t = item % tiles, part = item / tiles, qc = 16 * t + c;
-            const int r0 = part * chunk, r1 = r0 + chunk < rows ? r0 + chunk : rows;
-            const float *pq = b.M + (qc < b.cols ? qc : b.cols - 1), *ps = S + (c < w ? c : 0);
-            f32x4 acc = {};
+        // W: a tile a workgroup, cut along the rows, or two side by side, whose rows share their cache lines
+        auto project = [&](int t0, int r0, int r1, float* out, auto count) {
+            constexpr int NT = decltype(count)::value;
+            const float *pq[NT], *ps = S + (c < w ? c : 0) + (long)g * lds_;
+            f32x4 acc[NT] = {};
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int qc = 16 * (t0 + i) + c;
+                pq[i] = b.M + (qc < b.cols ? qc : b.cols - 1) + (long)g * b.ldm;
+            }
             int k = r0 + 4 * wave;
 #pragma unroll 8
-            for (; k + 4 <= r1; k += 16) acc = MFMA32(pq[(long)(k + g) * b.ldm], ps[(long)(k + g) * lds_], acc);
+            for (; k + 4 <= r1; k += 16) {
+                const float v = ps[(long)k * lds_];
+#pragma unroll
+                for (int i = 0; i < NT; ++i) acc[i] = MFMA32(pq[i][(long)k * b.ldm], v, acc[i]);
+            }
             if (k < r1) {
                 const bool in = k + g < r1;
-                acc = MFMA32(in ? pq[(long)(k + g) * b.ldm] : 0.f, in ? ps[(long)(k + g) * lds_] : 0.f, acc);
-            }
-            __syncthreads();
+                const float v = in ? ps[(long)k * lds_] : 0.f;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sh.red[wave][(4 * g + r) * 16 + c] = acc[r];
-            __syncthreads();
-            b.W[part * wstride + t * 256 + tid] =
-                ej < w && 16 * t + ei < b.cols ? (sh.red[0][tid] + sh.red[1][tid]) + (sh.red[2][tid] + sh.red[3][tid]) : 0.f;
+                for (int i = 0; i < NT; ++i) acc[i] = MFMA32(in ? pq[i][(long)k * b.ldm] : 0.f, v, acc[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int t = t0 + i;
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sh.red[wave][(4 * g + r) * 16 + c] = acc[i][r];
+                __syncthreads();
+                if (t < tiles)
+                    out[t * 256 + tid] = ej < w && 16 * t + ei < b.cols
+                                             ? (sh.red[0][tid] + sh.red[1][tid]) + (sh.red[2][tid] + sh.red[3][tid]) : 0.f;
+            }
+        };
+        if (wparts > 1) {
+            for (int item = wg; item < tiles * wparts; item += nwg) {
+                const int part = item / tiles, r0 = part * chunk, r1 = r0 + chunk < rows ? r0 + chunk : rows;
+                project(item % tiles, r0, r1, b.W + part * wstride, std::integral_constant<int, 1>());
+            }
+        } else {
+            for (int t = 2 * wg; t < tiles; t += 2 * nwg) project(t, 0, rows, b.W, std::integral_constant<int, 2>());
         }
         meet();
+        if (wparts > 1) {
+            for (int t = 0; t < tiles; ++t) {
+                float v[kLotParts], x = 0.f;
+#pragma unroll
+                for (int p = 0; p < kLotParts; ++p) v[p] = p < wparts ? b.W[p * wstride + t * 256 + tid] : 0.f;
+#pragma unroll
+                for (int p = 0; p < kLotParts; ++p) x += v[p];
+                sh.w[t][tid] = x;
+            }
+            __syncthreads();
+        }
         if (c0 >= 0)
             for (int t = wg; t < tiles; t += nwg) {                       // T's part of it
-                float v = 0.f;
-                for (int p = 0; p < wparts; ++p) v += b.W[p * wstride + t * 256 + tid];
-                __syncthreads();
-                sh.red[0][tid] = v;
-                __syncthreads();
+                float* const part = wparts > 1 ? sh.w[t] : sh.red[0];
+                if (wparts == 1) {
+                    __syncthreads();
+                    part[tid] = b.W[t * 256 + tid];
+                    __syncthreads();
+                }
                 if (ej >= w) continue;
                 float* o = b.T + (long)(16 * t + ei) * b.ldt + c0 + ej;
                 if (turn == 0) {
-                    *o = v;
+                    *o = part[tid];
                 } else {
                     float x = 0.f;
-                    for (int p = 0; p <= ej; ++p) x += sh.red[0][ei * 16 + p] * sh.u1[p * 16 + ej];
+                    for (int p = 0; p <= ej; ++p) x += part[ei * 16 + p] * sh.u1[p * 16 + ej];
                     *o += x;
                 }
             }
-        f64x4 gram = {};
-#pragma unroll 1
-        for (int z = 0; z < kLotStrips; ++z) {                            // S -= M W and S^T S, by rows
-            const int r0 = 16 * (wg + z * nwg);
-            if (r0 >= rows) break;
-            const float* row = b.M + (long)(r0 + c < rows ? r0 + c : rows - 1) * b.ldm;
-            f32x4 acc = {};
-            auto take = [&](const float4& a, const float* pw) {
-                acc = MFMA32(a.x, pw[0], acc);
-                acc = MFMA32(a.y, pw[16], acc);
-                acc = MFMA32(a.z, pw[32], acc);
-                acc = MFMA32(a.w, pw[48], acc);
-            };
-            for (int p = 0; p < wparts; ++p) {
-                const float* pw = b.W + p * wstride + 4 * g * 16 + c;
-                int k = 16 * wave;
-#pragma unroll 4
-                for (; k + 16 <= depth; k += 64) take(*reinterpret_cast<const float4*>(row + k + 4 * g), pw + k * 16);
-                if (k < depth)
-                    take(k + 4 * g < depth ? load_quad(row + k + 4 * g, depth - k - 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f), pw + k * 16);
-            }
-            __syncthreads();
+        // S -= M W and S^T S, by rows
+        auto strips = [&](const float* W, auto count) {
+            constexpr int NZ = decltype(count)::value;
+            const float* row[NZ];
+            f32x4 acc[NZ] = {};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sh.red[wave][(4 * g + r) * 16 + c] = acc[r];
-            __syncthreads();
-            sh.strip[z][tid] = r0 + ei < rows && ej < w ? S[(long)(r0 + ei) * lds_ + ej] - ((sh.red[0][tid] + sh.red[1][tid]) +
-                                                                                           (sh.red[2][tid] + sh.red[3][tid]))
-                                                        : 0.f;
-            __syncthreads();
-            if (wave == 0)
+            for (int z = 0; z < NZ; ++z) {
+                const int r = 16 * (wg + z * nwg) + c;
+                row[z] = b.M + (long)(r < rows ? r : rows - 1) * b.ldm + 4 * g;
+            }
+            auto take = [&](const float4 (&a)[NZ], const float* pw) {
+                const float w0 = pw[0], w1 = pw[16], w2 = pw[32], w3 = pw[48];
+#pragma unroll
+                for (int z = 0; z < NZ; ++z) {
+                    acc[z] = MFMA32(a[z].x, w0, acc[z]);
+                    acc[z] = MFMA32(a[z].y, w1, acc[z]);
+                    acc[z] = MFMA32(a[z].z, w2, acc[z]);
+                    acc[z] = MFMA32(a[z].w, w3, acc[z]);
+                }
+            };
+            const float* pw = W + 4 * g * 16 + c;
+            int k = 16 * wave;
+#pragma unroll 4
+            for (; k + 16 <= depth; k += 64) {
+                float4 a[NZ];
+#pragma unroll
+                for (int z = 0; z < NZ; ++z) a[z] = *reinterpret_cast<const float4*>(row[z] + k);
+                take(a, pw + k * 16);
+            }
+            if (k < depth) {
+                float4 a[NZ];
+#pragma unroll
+                for (int z = 0; z < NZ; ++z)
+                    a[z] = k + 4 * g < depth ? load_quad(row[z] + k, depth - k - 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f);
+                take(a, pw + k * 16);
+            }
+#pragma unroll
+            for (int z = 0; z < NZ; ++z) {
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sh.red[wave][(4 * g + r) * 16 + c] = acc[z][r];
+                __syncthreads();
+                const int r = 16 * (wg + z * nwg) + ei;
+                sh.strip[z][tid] = r < rows && ej < w ? S[(long)r * lds_ + ej] - ((sh.red[0][tid] + sh.red[1][tid]) +
+                                                                                 (sh.red[2][tid] + sh.red[3][tid]))
+                                                      : 0.f;
+            }
+        };
+        const int mine = (rows - 16 * wg + 16 * nwg - 1) / (16 * nwg);    // strips of this workgroup
+        if (wparts > 1) {
+            if (rows <= 16 * nwg) strips(&sh.w[0][0], std::integral_constant<int, 1>());
+            else strips(&sh.w[0][0], std::integral_constant<int, kLotStrips>());
+        } else if (rows <= 16 * nwg) {
+            strips(b.W, std::integral_constant<int, 1>());
+        } else if (rows <= 32 * nwg) {
+            strips(b.W, std::integral_constant<int, 2>());
+        } else {
+            strips(b.W, std::integral_constant<int, kLotStrips>());
+        }
+        __syncthreads();
+        f64x4 gram = {};
+        if (wave == 0)
+            for (int z = 0; z < mine; ++z)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const double v = (double)sh.strip[z][64 * r + lane];
                     gram = MFMA64(v, v, gram);
                 }
-        }
         if (wave == 0 && wg < groups) tile_write(b.gpart + (long)wg * 256, lane, gram);
         meet();
         double s = 0.0;
-#pragma unroll 8
+#pragma unroll 32
         for (int z = 0; z < groups; ++z) s += b.gpart[(long)z * 256 + tid];
         if (ei == ej && (ej >= w || (empty >> ej & 1u))) s = 1.0;
         sh.gsum[ei * CLD + ej] = s;
@@ -797,14 +869,15 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void block_solve_kernel(float
                                                           const float* __restrict__ inv, unsigned* words, void* scratch, float* R,
                                                           long ldr, unsigned* flags) {
     constexpr int SR = 16 * RT;
-    __shared__ __attribute__((aligned(16))) float q[SR][SLD];
+    constexpr size_t ROWS = sizeof(float) * SR * SLD, ROOM = ROWS > sizeof(LotShared) ? ROWS : sizeof(LotShared);
+    __shared__ __attribute__((aligned(16))) char room[ROOM];
     __shared__ __attribute__((aligned(16))) float tile[256];
+    float (*const q)[SLD] = reinterpret_cast<float (*)[SLD]>(room);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r0 = blockIdx.x * SR;
     const unsigned mode = words[0];
     if (mode == kByLots) {
-        static_assert(sizeof(LotShared) <= sizeof(q), "room of a workgroup");
-        LotShared& sh = *reinterpret_cast<LotShared*>(&q[0][0]);
+        LotShared& sh = *reinterpret_cast<LotShared*>(room);
         const int groups = (int)gridDim.x < kLotGroups ? (int)gridDim.x : kLotGroups;
         if ((int)blockIdx.x >= groups) return;
         double* const gpart = static_cast<double*>(scratch);
@@ -843,20 +916,23 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void block_solve_kernel(float
 }
 
 // ---- what the second pass may have left ------------------------------------------------------------------------------
-// E = R^T R - I in fp64; then every lot of 16 columns with an entry of E above kOff, from the left, and U <- T U.  Columns that have
+// E = R^T R - I; then every lot of 16 columns with an entry of E above kOff, from the left, and U <- T U.  Columns that have
 // vanished become, at the end and 16 at a time, random ones made orthogonal to all others.
 // Where there is nothing to do 2 to 4 us.  One pair of columns parallel to 1e-5 or one column of zeros, which is E, a lot or two and their
-// part of U: 0.27 and 0.5 ms at n = 1536, 0.4 and 3.3 at 4096.  Many lots: 40 us a turn at n = 600, 80 at 1536, 260 at 4096, from when
-// on the products' share of the chip, 128 workgroups, is what bounds them.
+// part of U: 0.22 and 0.47 ms at n = 1536, 0.4 and 2.2 at 4096; at 8192 12 ms, 10 of them E at 55 TFLOP/s.  Many lots: 40 us a turn at n =
+// 600, 75 at 1536, 170 at 4096, from when on what 128 workgroups have under way is what bounds them.
 constexpr float kOff = 7e-7f;
-constexpr int kFinishGroups = 1024;        // for E, at most
+constexpr int kFinishGroups = 768;         // for E, at most: as many as there is room for at a time
 __host__ __device__ constexpr int lot_groups_of(int n) { return (n + 15) / 16 < kLotGroups ? (n + 15) / 16 : kLotGroups; }
 
 __global__ __launch_bounds__(256, 3) void finish_kernel(float* R, long ldr, int n, float* U, long ldu, float* T, long ldt, double* gpart,
                                                         float* spare, float* W, unsigned* words, unsigned* flags) {
     if (words[0] == 0u) return;
     const int nwg = lot_groups_of(n), all = gridDim.x;      // those beyond have their share of E and go
-    __shared__ LotShared sh;
+    constexpr int ELD = 72;                // rows of 64 two apart: 16 banks on, four rows side by side
+    constexpr size_t TILES = sizeof(float) * 32 * 2 * ELD, ROOM = TILES > sizeof(LotShared) ? TILES : sizeof(LotShared);
+    __shared__ __attribute__((aligned(16))) char room[ROOM];      // of E's tiles, then of the lots
+    LotShared& sh = *reinterpret_cast<LotShared*>(room);
     __shared__ unsigned char todo[DQ_MAX_N / 16];
     __shared__ unsigned short dead[DQ_MAX_N / 16];     // a lot's columns that have vanished
     __shared__ int late_cols[16], late_n;
@@ -867,13 +943,53 @@ __global__ __launch_bounds__(256, 3) void finish_kernel(float* R, long ldr, int 
     Meeting meet{reinterpret_cast<unsigned long long*>(words + 2), nwg, flags, (unsigned long long)(all - nwg)};
     // ---- the largest entry of E of every lot
     {
+        // a tile of 64 x 64 a workgroup, 32 rows of R at a time through LDS, the next 32 on their way meanwhile
         const int nt = (n + 63) / 64, tiles = nt * (nt + 1) / 2, wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+        float (*const rows)[2][ELD] = reinterpret_cast<float (*)[2][ELD]>(room);
         for (int t = wg; t < tiles; t += all) {
             int ti, tj;
             gram_tile(t, nt, ti, tj);
+            float4 next[4];                // row tid / 16 + 16 i of the left and the right columns 4 (tid % 16) ..
+            auto fetch = [&](int r0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = r0 + ei + 16 * (i >> 1), k = 64 * (i & 1 ? tj : ti) + 4 * ej;
+                    next[i] = r < n && k < n ? load_quad(R + (long)r * ldr + k, n - k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+            };
+            double acc[2][2][4] = {};      // fp32 sums of 64 rows, summed in fp64
+            f32x4 part[2][2] = {};
+            fetch(0);
+            for (int r0 = 0; r0 < n; r0 += 32) {
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(&rows[ei + 16 * (i >> 1)][i & 1][4 * ej]) = next[i];
+                __syncthreads();
+                if (r0 + 32 < n) fetch(r0 + 32);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    float fa[2], fb[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        fa[i] = rows[4 * q + g][0][wm + 16 * i + c];
+                        fb[i] = rows[4 * q + g][1][wn + 16 * i + c];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) part[i][j] = MFMA32(fa[i], fb[j], part[i][j]);
+                }
+                if ((r0 & 32) == 0 && r0 + 32 < n) continue;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[i][j][v] += (double)part[i][j][v];
+                        part[i][j] = f32x4{};
+                    }
+            }
             if (ti == tj && wm > wn) continue;
-            f64x4 acc[2][2] = {};
-            gram_rows(R, ldr, n, ti, tj, wm, wn, 0, n, c, g, acc);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int k = 64 * tj + wn + 16 * j + c;
@@ -882,7 +998,7 @@ __global__ __launch_bounds__(256, 3) void finish_kernel(float* R, long ldr, int 
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int r = 64 * ti + wm + 16 * i + 4 * v + g;
+                        const int r = 64 * ti + wm + 16 * i + 4 * g + v;
                         const unsigned e = __float_as_uint(fabsf((float)(acc[i][j][v] - (r == k ? 1.0 : 0.0))));
                         if (r <= k && k < n && e > most) most = e;
                     }
