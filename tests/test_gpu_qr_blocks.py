@@ -264,11 +264,15 @@ def test_small_rotated_triangles(n):
         c.close()
 
 
+@pytest.mark.parametrize("kinds", [("gauss", "rotation", "lengths", "gauss"),
+                                   ("gauss", "zero column", "turned triangle", "rotation", "half the rows", "turned triangle")],
+                         ids=["ordinary", "singular"])
 @pytest.mark.parametrize("n", [300, 770])
-def test_blocks_under_capture(n):
+def test_blocks_under_capture(n, kinds):
     """The same launches recorded into a graph, in a context that has met its stream before and in one that has not: every replay, on
-    other latents and with eager calls in between, gives the eager call's bits."""
-    latents = [_latent(n, k) for k in ("gauss", "rotation", "lengths", "gauss")]
+    other latents and with eager calls in between, gives the eager call's bits.  Also where what is done differs from replay to replay: by
+    blocks, 16 columns at a time, with a finish."""
+    latents = [_latent(n, k) for k in kinds]
     for met in (True, False):
         s = torch.cuda.Stream()
         with torch.cuda.stream(s):
@@ -290,8 +294,42 @@ def test_blocks_under_capture(n):
                     e.dq_qr_orth(Zi, Re, Ue)
                     s.synchronize()
                     assert torch.equal(R, Re) and torch.equal(U, Ue)
-                assert c.dq_device_flags() == 0
+                flags = c.dq_device_flags()
+                assert flags == (B.DQ_FLAG_SINGULAR | B.DQ_FLAG_ILLCOND_PANEL if "zero column" in kinds else 0)
             finally:
                 s.synchronize()
                 c.close()
                 e.close()
+
+
+@pytest.mark.parametrize("n", [300, 1100])
+def test_singular_latents_on_several_streams(n):
+    """Four contexts on streams of their own factor latents whose workgroups wait for each other, all at the same time: the bits that
+    each gives alone, and no wait that ran into its limit."""
+    kinds = ("turned triangle", "zero column", "half rank", "beyond")
+    latents = [_latent(n, k) for k in kinds]
+    streams = [torch.cuda.Stream() for _ in kinds]
+    contexts, want, got = [], [], []
+    try:
+        for Z, s in zip(latents, streams):
+            with torch.cuda.stream(s):
+                c = B.Context(s)
+                c.ensure_workspace(1, n, 1, B.DQ_F32)
+                contexts.append(c)
+                R, U = _padded(n)[1], _padded(n)[1]
+                c.dq_qr_orth(Z, R, U)
+                got.append((_padded(n)[1], _padded(n)[1]))
+            torch.cuda.synchronize()
+            want.append((R, U))
+        for _ in range(3):
+            for Z, s, c, (R, U) in zip(latents, streams, contexts, got):
+                with torch.cuda.stream(s):
+                    c.dq_qr_orth(Z, R, U)
+        torch.cuda.synchronize()
+        for c, (R, U), (Rw, Uw) in zip(contexts, got, want):
+            assert c.dq_device_flags() & B.DQ_FLAG_SYNC_TIMEOUT == 0
+            assert torch.equal(R, Rw) and torch.equal(U, Uw)
+    finally:
+        torch.cuda.synchronize()
+        for c in contexts:
+            c.close()
