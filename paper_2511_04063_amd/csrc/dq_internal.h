@@ -172,6 +172,12 @@ struct HandOver {
 __device__ __forceinline__ void handover_signal(unsigned long long* word, unsigned long long value) {
     __hip_atomic_store(word, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
+// The barrier of a workgroup in front of a signal or an arrival by one of its threads: __syncthreads() orders its wavefronts' stores
+// to global memory only among themselves (it has no wait on vmcnt), and that thread's release waits for its own wavefront's.
+__device__ __forceinline__ void store_barrier() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
 // returns false if it gave up; one thread calls it
 __device__ __forceinline__ bool handover_wait(const unsigned long long* word, unsigned long long value, long long limit_ticks,
                                               unsigned* flags) {

@@ -83,7 +83,7 @@ __device__ __forceinline__ int wave_reduce_multi(float (&v)[NV], int lane) {
 }
 
 // Workgroup barrier that orders LDS traffic only: it waits for this wavefront's outstanding LDS operations
-// (lgkmcnt) but not for its global stores (vmcnt), which __syncthreads() would also drain.  The panel kernel
+// (lgkmcnt) but not for its global stores (vmcnt).  The panel kernel
 // exchanges data between threads through LDS alone; global memory is only re-read by the thread that wrote it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 

@@ -688,7 +688,7 @@ __global__ __launch_bounds__(NT) void la_update_chol_kernel(float* A, long lda, 
             U1[e] = Gs[(e >> 6) * LS + (e & 63)];
             U1inv[e] = Ws[(e >> 6) * LS + (e & 63)];
         }
-        __syncthreads();                       // every thread's part of U1^-1 is written: the other workgroups may use it
+        store_barrier();                       // every thread's part of U1^-1 is written: the other workgroups may use it
         if (tid == 0) handover_signal(ready, 1ull);
         return;
     }
@@ -1172,7 +1172,7 @@ __global__ __launch_bounds__(NSUM) void panel_fused_kernel(const float* part, in
             U1[e] = Gs[(e >> 6) * LS + (e & 63)];
             U1inv[e] = Wx[(e >> 6) * LS + (e & 63)];
         }
-        __syncthreads();
+        store_barrier();
         if (tid == 0) handover_signal(ps.ready2, ps.epoch);
         return;
     }
@@ -1180,8 +1180,9 @@ __global__ __launch_bounds__(NSUM) void panel_fused_kernel(const float* part, in
     if (b == 0) {
         // ---- the panel's small step, then the top 64 rows
         hr_finish_body(part, nparts, q1, U1, A, lda, m, Tout, Yp, Mm, Mm2, tau, tslices, fb, status, pool, sg, redw);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (of the wavefronts that end here too)
         if (tid >= NTHR) return;
-        __syncthreads();
+        store_barrier();
         if (tid == 0) handover_signal(ps.ready1, ps.epoch);
         if (ho.wait_word != nullptr) {      // the look-ahead columns must have received the previous trailing update
             if (tid == 0) (void)handover_wait(ho.wait_word, ho.wait_value, (long long)ho.limit_us * 100, ho.flags);
@@ -1200,7 +1201,7 @@ __global__ __launch_bounds__(NSUM) void panel_fused_kernel(const float* part, in
         }
         store_partial(wpart, acc, qi, qj, lrow, lk);
         store_partial(gearly, accg, qi, qj, lrow, lk);
-        __syncthreads();
+        store_barrier();
         if (tid == 0) (void)__hip_atomic_fetch_add(ps.count, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         // the reflectors as stored, unit lower triangular, for the update of the top rows
         load_tile(A, lda, 0, B64, Xs, tid);
@@ -1237,7 +1238,7 @@ __global__ __launch_bounds__(NSUM) void panel_fused_kernel(const float* part, in
     f32x16 accg = zero16();
     gram_tile(Cs, accg, qi, qj, lrow, lk);          // C_rows^T C_rows of the columns BEFORE the update
     store_partial(gearly + (long)b * B64 * B64, accg, qi, qj, lrow, lk);
-    __syncthreads();
+    store_barrier();
     if (tid == 0) (void)__hip_atomic_fetch_add(ps.rows, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     panel_wait(ps.ready1, ps.epoch, ps, status, tid);
     const bool fell_back = *fb != 0u;
@@ -1271,7 +1272,7 @@ __global__ __launch_bounds__(NSUM) void panel_fused_kernel(const float* part, in
         proj_tile(Xs, Cs, acc, qi, qj, lrow, lk);
         store_partial(wpart + (long)b * B64 * B64, acc, qi, qj, lrow, lk);
     }
-    __syncthreads();                                // every wavefront is done with Yp in Xs; all partials are stored
+    store_barrier();                                // every wavefront is done with Yp in Xs; all partials are stored
     if (tid == 0) (void)__hip_atomic_fetch_add(ps.count, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     if (!fell_back) {
 #pragma unroll

@@ -484,7 +484,7 @@ struct Meeting {                           // what the other workgroups wrote be
     unsigned long long due = 0;
     __device__ __forceinline__ void operator()() {
         due += groups;
-        __syncthreads();
+        store_barrier();
         if (threadIdx.x == 0) {
             (void)__hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             (void)handover_wait(arrived, due, kMeetTicks, flags);
@@ -1013,7 +1013,7 @@ __global__ __launch_bounds__(256, 3) void finish_kernel(float* R, long ldr, int 
         }
     }
     if (wg >= nwg) {
-        __syncthreads();
+        store_barrier();
         if (tid == 0) (void)__hip_atomic_fetch_add(meet.arrived, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }

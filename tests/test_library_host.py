@@ -4,10 +4,12 @@ include/dartqr.h declares, and its argument checks refuse bad calls before anyth
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
 from paper_2511_04063_amd import binding as B
+from paper_2511_04063_amd.build import HIPCC_FLAGS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -97,3 +99,28 @@ def test_workspace_of_small_batches():
     assert many - one <= 1024 * (4 * 1024 + 16 * (4096 + 8))
     assert B.workspace_bytes(100000, 16, 512, B.DQ_BF16) == many
     assert B.workspace_bytes(64, 128, 16384, B.DQ_BF16) - B.workspace_bytes(1, 128, 16384, B.DQ_BF16) <= 63 * 15 * 65536 + 63 * 64
+
+
+def test_stores_have_arrived_before_a_signal(tmp_path):
+    """Workgroups hand data to each other by a word that one thread sets behind a barrier.  Every wavefront has to wait for its own stores
+    in front of that barrier: the thread's release waits for its own wavefront's only."""
+    csrc = os.path.join(ROOT, "paper_2511_04063_amd", "csrc")
+    arrivals = 0
+    for name in ("qr_gram.hip", "qr_cholpanel.hip"):
+        lines = open(os.path.join(csrc, name)).read().splitlines()
+        for i, line in enumerate(lines):
+            if re.search(r"fetch_add\(.*__ATOMIC_RELEASE|handover_signal\((ready|ps\.)", line):
+                arrivals += 1
+                assert any("store_barrier();" in before for before in lines[i - 2:i]), f"{name}:{i + 1}"
+    assert arrivals == 8
+    src, out = tmp_path / "k.hip", tmp_path / "k.s"
+    src.write_text('#include "dq_internal.h"\n'
+                   "__global__ void k(float* a, unsigned long long* word) {\n"
+                   "    a[threadIdx.x] = 1.f;\n"
+                   "    dq::store_barrier();\n"
+                   "    if (threadIdx.x == 0) dq::handover_signal(word, 1ull);\n"
+                   "}\n")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *HIPCC_FLAGS, "--cuda-device-only", "-S", "-w", "-I", csrc,
+                    "-I", os.path.join(ROOT, "include"), str(src), "-o", str(out)], check=True, capture_output=True)
+    code = [w for w in re.findall(r"global_store_dword\b|s_waitcnt vmcnt\(0\)|s_barrier|global_store_dwordx2|buffer_wbl2", out.read_text())]
+    assert code[:5] == ["global_store_dword", "s_waitcnt vmcnt(0)", "s_barrier", "buffer_wbl2", "s_waitcnt vmcnt(0)"]
