@@ -333,3 +333,29 @@ def test_singular_latents_on_several_streams(n):
         torch.cuda.synchronize()
         for c in contexts:
             c.close()
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n", [100, 300, 1100])
+def test_latents_that_are_not_finite(n, value):
+    """One such entry is reported and nothing else is, wherever it lies, also where columns are zero or parallel and workgroups wait for
+    each other; the context's next latent is factored as ever."""
+    c = B.Context()
+    try:
+        c.ensure_workspace(1, n, 1, B.DQ_F32)
+        good = _latent(n, "gauss")
+        for kind in ("gauss", "parallel", "zero column"):
+            for row, col in ((0, 0), (n // 2, n // 2), (n - 1, n - 1)):
+                Z = _latent(n, kind)
+                Z[row, col] = value
+                R, U = (_padded(n)[1] for _ in range(2))
+                c.dq_qr_orth(Z, R, U)
+                flags = c.dq_device_flags()
+                assert flags & B.DQ_FLAG_NONFINITE
+                assert flags & ~(B.DQ_FLAG_NONFINITE | B.DQ_FLAG_SINGULAR | B.DQ_FLAG_ILLCOND_PANEL) == 0
+        c.dq_qr_orth(good, R, U)
+        assert c.dq_device_flags() == 0
+        _check(good, R, U)
+    finally:
+        torch.cuda.synchronize()
+        c.close()
