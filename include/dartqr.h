@@ -25,7 +25,7 @@
  *  - Errors: arguments are checked on the host before anything is enqueued; a non-DQ_OK
  *    return means nothing was launched and no output was touched.  Numerical trouble
  *    (singular Z, non-finite values) sets bits in a device status word (dq_device_flags);
- *    outputs are then unspecified but every kernel still terminates normally.
+ *    outputs are then unspecified, unless the bit says more, but every kernel still terminates normally.
  *  - One context per stream; a context is not re-entrant.  Calls on one context are
  *    serialised by its stream and share its workspace.
  */
@@ -169,6 +169,8 @@ dq_status dq_device_flags(dq_ctx* ctx, unsigned* host_out);
  * Range: for n > 128 columns of Z shorter than 2^-102 count as columns of zeros (DQ_FLAG_SINGULAR), and from a length of 2^120 on
  * DQ_FLAG_NONFINITE is raised, U may be infinite; for n <= 128 from 2^128 on.  With a Householder option set lengths of 2^-62 to 2^62
  * are taken; others are not all noticed.
+ * An ill-conditioned Z of n > 128 is factored by up to 128 workgroups that wait for each other: the context's stream needs 64
+ * compute units (a stream with a narrower mask meets DQ_FLAG_SYNC_TIMEOUT after 5 s); ordinary ones need no particular number.
  * Z: in, b x (n x n) fp32.  R: out, fp32.  U_or_null: out, fp32, strictly-lower part written as 0. */
 dq_status dq_qr_orth(dq_ctx* ctx, int b, int n,
                      const float* Z, long ldz, float* R, long ldr,

@@ -447,7 +447,7 @@ __global__ __launch_bounds__(64 * CHOL_WAVES) void chol64_kernel(const double* _
 // vanished, or of which at unit length only rounding in the span of the others was left once more, is set to zero, with its row of T: none of
 // what the columns behind it have is along it.
 // The workgroups of one launch do this together and wait for each other at a word in device memory, three times a turn.  They all have
-// a place at the same time: at most 128 of them, two or three to a compute unit, and what runs on other streams ends or, if it is one
+// a place at the same time: at most 128 of them, two or three to a compute unit (64 units at least), and what runs on other streams ends or, if it is one
 // of these kernels, fits beside them three times over.  The polls are bounded like those between streams.  They share the work by tiles of W
 // (cut along the rows where there are few) and strips of 16 rows; the 16 x 16 numerics are done by all of them alike.
 // Bound: the latency of these steps: a block of 256 columns 0.35 ms at 200 rows, 0.7 at 600, 1.0 at 1536, 2.2 at 4096 (by one workgroup, in
